@@ -1,0 +1,211 @@
+"""The workloads on which the expert module's speed is measured.
+
+A case is one call of the library on one batch, the way a serving or batch-inference program makes
+it: weights packed and pointer tables built once at start-up, buffers owned by the caller, then one
+call per layer and batch.  The shapes are the layer shapes of workloads/configs.py (two Mixtral-like
+with 8 wide experts, two DeepSeek-like with many narrow experts and shared experts, one tiny), at
+the batch sizes of the paper's two phases: decode (from one token, 75 tokens per expert in its
+Table 1) and prefill (thousands of tokens per expert).
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+from paper_2503_09716_amd import Moe, make_shape
+
+# H, F, E, k, shared experts, renormalised weights, gate bias (None, "normal" or "zipf")
+SHAPES = {
+    "tiny": (512, 1024, 8, 2, 0, True, None),
+    "8x7b": (4096, 14336, 8, 2, 0, True, None),
+    "8x22b": (6144, 16384, 8, 2, 0, True, "normal"),
+    "lite": (2048, 1408, 64, 6, 2, False, None),
+    "v2": (5120, 1536, 160, 6, 2, False, "zipf"),
+}
+
+
+def _case(shape, T, call="layer", **options):
+    H, F, E, k, shared, renorm, bias = SHAPES[shape]
+    case = {"call": call, "T": T, "H": H, "F": F, "E": E, "k": k, "shared": shared, "renorm": renorm,
+            "bias": bias or "none", "pack_gate": True, "out_fp32": False}
+    case.update(options)
+    return case
+
+
+def listed():
+    cases = [
+        # A small layer in a latency-bound loop that may not allocate: the built-in workspace.
+        ("tiny_static", _case("tiny", 256, call="static")),
+        # Interactive decode of one sequence: eight experts' weights are read for one row each.
+        ("lite_decode_1", _case("lite", 1)),
+        # Decode of a small batch: every expert active with a few rows, bound by reading all weights.
+        ("8x7b_decode_32", _case("8x7b", 32)),
+        # The decode row of Table 1: 75 tokens per expert on average, skewed, 160 experts.
+        ("v2_decode_2000", _case("v2", 2000)),
+        # A few hundred tokens per expert, odd count: short prompts, or the last pass of a batch; the
+        # gate matrix is handed over as the model file holds it.
+        ("8x7b_odd_1511", _case("8x7b", 1511, pack_gate=False)),
+        # The staged calls of a program that looks at the routing between them (explicit row
+        # gather, fp32 expert outputs, fp32 result).
+        ("lite_staged_3001", _case("lite", 3001, call="staged", out_fp32=True)),
+        # A batch run in passes because its intermediates must fit beside a KV cache.
+        ("8x7b_chunked_5003", _case("8x7b", 5003, call="chunked", per_pass=2048)),
+        # Prefill: the large accumulated batches module-based batching is for.
+        ("8x7b_prefill_4096", _case("8x7b", 4096)),
+        ("8x22b_prefill_16384", _case("8x22b", 16384)),
+        ("lite_prefill_16384", _case("lite", 16384)),
+        ("v2_prefill_32768", _case("v2", 32768)),
+        # Expert weights in pinned host memory, fetched in groups of eight experts while earlier
+        # groups are computed (bound by the host link).
+        ("lite_streamed_4096", _case("lite", 4096, call="streamed", group=8, slots=2)),
+    ]
+    return [dict(c, name=n) for n, c in cases]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case: a shape family, a batch size spread over the logarithm of its range, the options at random."""
+    kind = rng.choice(["tiny", "8x7b", "8x7b", "8x22b", "lite", "lite", "v2", "v2", "generic", "streamed"])
+    pack_gate = rng.random() < 0.7
+    if kind == "tiny":
+        case = _case("tiny", _log_int(rng, 1, 256), call="static", pack_gate=pack_gate)
+        case.update(H=64 * rng.randint(4, 16), F=64 * rng.randint(2, 32), E=rng.randint(4, 8), k=rng.randint(1, 4),
+                    renorm=rng.random() < 0.5)
+        return case
+    if kind == "streamed":
+        return _case("lite", _log_int(rng, 16, 4096), call="streamed", group=rng.choice([4, 8, 16]),
+                     slots=rng.randint(2, 3), pack_gate=pack_gate)
+    if kind == "generic":
+        # neither a model's shape nor a tuned one: any multiple of 64, any expert count
+        case = _case("lite", _log_int(rng, 16, 8192), pack_gate=pack_gate, out_fp32=rng.random() < 0.3)
+        E = rng.randint(4, 128)
+        case.update(H=64 * rng.randint(8, 64), F=64 * rng.randint(8, 48), E=E, k=rng.randint(1, min(8, E)),
+                    shared=rng.randint(0, 2), renorm=rng.random() < 0.5,
+                    bias=rng.choice(["none", "normal", "zipf"]), call=rng.choice(["layer", "staged"]))
+        return case
+    top = {"8x7b": 16384, "8x22b": 16384, "lite": 16384, "v2": 32768}[kind]
+    T = _log_int(rng, 1, top)
+    call = rng.choice(["layer", "layer", "layer", "staged", "chunked"])
+    case = _case(kind, T, call=call, pack_gate=pack_gate, out_fp32=rng.random() < 0.3)
+    if call == "chunked":
+        case["per_pass"] = max(1, min(T, _log_int(rng, max(1, T // 4), T)))
+    return case
+
+
+def _gate_bias(kind, E, rng):
+    if kind == "normal":
+        return rng.standard_normal(E).astype(np.float32)
+    if kind == "zipf":     # log of a Zipf(1.1) law over a random ranking of the experts
+        return (-1.1 * np.log(rng.permutation(E) + 1.0)).astype(np.float32)
+    return None
+
+
+class _State:
+    """What a program holds between calls: context, weights, tables, buffers."""
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+
+    def normal(rows, cols, std):
+        return torch.empty((rows, cols), dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+
+    T, H, F, E, k, shared = (case[n] for n in ("T", "H", "F", "E", "k", "shared"))
+    s = _State()
+    s.case = case
+    s.moe = moe = Moe(0)
+    s.shape = make_shape(T, H, F, E, k, shared, case["renorm"])
+    s.x = normal(T, H, 1.0)
+    wg = normal(H, E, 0.02)
+    s.wg = moe.pack_gate(s.shape, wg) if case["pack_gate"] else wg
+    moe.set_option("gate_packed", 1 if case["pack_gate"] else 0)
+    moe.set_option("out_fp32", 1 if case["out_fp32"] else 0)
+    bias = _gate_bias(case["bias"], E, np.random.default_rng(seed))
+    s.bias = None if bias is None else torch.from_numpy(bias).cuda()
+    n = E + shared
+    if case["call"] == "streamed":
+        host = torch.empty(3 * n * H * F, dtype=torch.bfloat16, pin_memory=True)
+        parts = list(host.split(H * F))
+        for e in range(n):
+            for i, (rows, cols) in enumerate(((H, F), (H, F), (F, H))):
+                parts[3 * e + i].copy_(moe.pack_weight(normal(rows, cols, 0.02)))
+        s.w1, s.w3, s.w2 = parts[0::3], parts[1::3], parts[2::3]
+        slot_bytes = max(case["group"], shared) * 3 * H * F * 2
+        s.slots = torch.empty(case["slots"] * slot_bytes, dtype=torch.uint8, device="cuda")
+    else:
+        s.w1 = [moe.pack_weight(normal(H, F, 0.02)) for _ in range(n)]
+        s.w3 = [moe.pack_weight(normal(H, F, 0.02)) for _ in range(n)]
+        s.w2 = [moe.pack_weight(normal(F, H, 0.02)) for _ in range(n)]
+        s.tables = moe.tables(s.w1, s.w3, s.w2)
+    per_call = case.get("per_pass", T)
+    s.workspace = moe.new_workspace(make_shape(per_call, H, F, E, k, shared, case["renorm"]))
+    s.out = torch.empty((T, H), dtype=torch.float32 if case["out_fp32"] else torch.bfloat16, device="cuda")
+    if case["call"] == "staged":
+        i32 = dict(dtype=torch.int32, device="cuda")
+        s.topk_idx = torch.empty((T, k), **i32)
+        s.topk_w = torch.empty((T, k), dtype=torch.float32, device="cuda")
+        s.logits = torch.empty((T, E), dtype=torch.float32, device="cuda")
+        s.offsets = torch.empty(E + 1, **i32)
+        s.perm, s.inv_perm, s.row_token = (torch.empty(T * k, **i32) for _ in range(3))
+        s.x_perm = torch.empty((T * k, H), dtype=torch.bfloat16, device="cuda")
+        s.h = moe.new_h_scratch(s.shape)
+        s.y_perm = torch.empty((T * k, H), dtype=torch.float32, device="cuda")
+        s.y_shared = torch.empty((T, H), dtype=torch.float32, device="cuda") if shared else None
+    torch.cuda.synchronize()
+    return s
+
+
+def run(s):
+    moe, case = s.moe, s.case
+    call = case["call"]
+    if call == "layer":
+        moe.layer(s.shape, s.x, s.wg, s.bias, s.w1, s.w3, s.w2, s.out, s.workspace, tables=s.tables)
+    elif call == "static":
+        moe.layer_static(s.shape, s.x, s.wg, s.bias, s.w1, s.w3, s.w2, s.out, tables=s.tables)
+    elif call == "chunked":
+        moe.layer_chunked(s.shape, s.x, s.wg, s.bias, s.w1, s.w3, s.w2, case["per_pass"], s.out, s.workspace,
+                          tables=s.tables)
+    elif call == "streamed":
+        moe.layer_streamed(s.shape, s.x, s.wg, s.bias, s.w1, s.w3, s.w2, s.slots, case["slots"], case["group"], s.out,
+                           s.workspace)
+    else:
+        moe.route(s.shape, s.x, s.wg, s.bias, s.topk_idx, s.topk_w, s.logits, s.workspace)
+        moe.permute(s.shape, s.x, s.topk_idx, s.x_perm, s.offsets, s.perm, s.inv_perm, s.row_token, s.workspace)
+        moe.grouped_ffn(s.shape, s.x_perm, None, s.x, s.offsets, s.w1, s.w3, s.w2, s.h, s.y_perm, s.y_shared,
+                        s.workspace)
+        moe.combine(s.shape, s.y_perm, s.inv_perm, s.topk_w, s.y_shared, s.out)
+        return {"out": s.out, "topk_idx": s.topk_idx, "topk_w": s.topk_w, "logits": s.logits, "offsets": s.offsets}
+    return s.out
+
+
+def work(case):
+    """x, the gate matrix and the weights of the experts that receive rows (their expected number) read
+    once, the output (and what a staged program asked for) written once; multiply-adds of real rows."""
+    T, H, F, E, k, shared = (case[n] for n in ("T", "H", "F", "E", "k", "shared"))
+    # expected number of experts with at least one row: near-uniform picks, or by the Zipf law's shares
+    share = np.full(E, 1.0 / E)
+    if case["bias"] == "zipf":
+        share = np.arange(1, E + 1) ** -1.1
+        share /= share.sum()
+    active = float((1.0 - (1.0 - np.minimum(k * share, 1.0)) ** T).sum())
+    nbytes = 2 * T * H + 2 * H * E + (4 if case["out_fp32"] else 2) * T * H + (active + shared) * 3 * H * F * 2
+    if case["call"] == "staged":
+        nbytes += T * k * (2 * H + 4 * H + 4 * 5) + (4 * T * H if shared else 0) + 4 * T * E + 4 * (E + 1)
+    flops = 6 * T * (k + shared) * H * F + 2 * T * H * E
+    return {"bytes": int(nbytes), "flops": int(flops)}
+
+
+def tolerance(case):
+    """h (and the output, unless fp32) are rounded to bf16; sums are fp32.  Against the layer in 64 bits
+    without those roundings the output measures 2.35e-3 (bf16) and 1.66e-3 (fp32) on the tiny, the
+    lite and the 8x7b shape alike; about four times that is stated."""
+    tol = {"rel": 1e-2}
+    if case["call"] == "staged":
+        # a near-tie of two experts' logits may be decided either way; a row's routing then differs
+        tol["differ"] = 1e-3
+    return tol
