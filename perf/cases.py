@@ -109,12 +109,18 @@ class _State:
     """What a program holds between calls: context, weights, tables, buffers."""
 
 
-def prepare(case, seed):
+def _draws(seed):
+    """Source of the bf16 matrices of a seed; prepare and exact draw in the same order."""
     gen = torch.Generator(device="cuda").manual_seed(seed)
 
     def normal(rows, cols, std):
         return torch.empty((rows, cols), dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
 
+    return normal
+
+
+def prepare(case, seed):
+    normal = _draws(seed)
     T, H, F, E, k, shared = (case[n] for n in ("T", "H", "F", "E", "k", "shared"))
     s = _State()
     s.case = case
@@ -181,6 +187,43 @@ def run(s):
         moe.combine(s.shape, s.y_perm, s.inv_perm, s.topk_w, s.y_shared, s.out)
         return {"out": s.out, "topk_idx": s.topk_idx, "topk_w": s.topk_w, "logits": s.logits, "offsets": s.offsets}
     return s.out
+
+
+def exact(case, seed):
+    """The layer in 64 bits: linear gate, softmax, top-k, SwiGLU experts, weighted sum, shared experts."""
+    normal = _draws(seed)
+    T, H, F, E, k, shared = (case[n] for n in ("T", "H", "F", "E", "k", "shared"))
+    x = normal(T, H, 1.0).double()
+    logits = x @ normal(H, E, 0.02).double()
+    bias = _gate_bias(case["bias"], E, np.random.default_rng(seed))
+    if bias is not None:
+        logits += torch.from_numpy(bias).cuda().double()
+    topk_idx = logits.topk(k, dim=1).indices
+    topk_w = torch.softmax(logits, dim=1).gather(1, topk_idx)
+    if case["renorm"]:
+        topk_w = topk_w / topk_w.sum(dim=1, keepdim=True)
+    n = E + shared
+    if case["call"] == "streamed":     # drawn expert by expert
+        w1, w3, w2 = zip(*((normal(H, F, 0.02), normal(H, F, 0.02), normal(F, H, 0.02)) for _ in range(n)))
+    else:
+        w1, w3 = ([normal(H, F, 0.02) for _ in range(n)] for _ in range(2))
+        w2 = [normal(F, H, 0.02) for _ in range(n)]
+    out = torch.zeros((T, H), dtype=torch.float64, device="cuda")
+    for e in range(n):
+        if e < E:
+            token, rank = (topk_idx == e).nonzero(as_tuple=True)
+            if token.numel() == 0:
+                continue
+            rows, weight = x[token], topk_w[token, rank, None]
+        else:
+            token, rows, weight = slice(None), x, 1.0
+        h = torch.nn.functional.silu(rows @ w1[e].double()) * (rows @ w3[e].double())
+        out[token] += weight * (h @ w2[e].double())    # a token picks an expert once
+    if case["call"] == "staged":
+        offsets = torch.zeros(E + 1, dtype=torch.int32, device="cuda")
+        offsets[1:] = torch.bincount(topk_idx.flatten(), minlength=E).cumsum(0)
+        return {"out": out, "topk_idx": topk_idx.int(), "topk_w": topk_w, "logits": logits, "offsets": offsets}
+    return out
 
 
 def work(case):
