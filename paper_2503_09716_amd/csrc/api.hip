@@ -293,7 +293,6 @@ moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     a.n_tiles = (rg.ep + 255) / 256;
     a.max_mtiles = rg.splits * ((s.T + rg.tm - 1) / rg.tm);
     a.group_m = 8;
-    a.xcd_remap = 0;
     a.small_tiles = 1;
     a.out_fp32 = 3;
     a.lda_bytes = s.H * 2;
@@ -311,23 +310,12 @@ moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     return MOE_OK;
 }
 
-// Rows per m-tile for one GEMM.  Tiles of 256 rows are the efficient shape (measured: the
-// 128-row shape runs at ~0.75 of their rate); 128 rows only win when a launch has so few
-// 256-row tiles that most CUs would idle in its last round.
-double expected_tiles(const moe_shape& s, int tm, int n_tiles, int nseg) {
-    return ((double)s.T * s.top_k / tm + 0.5 * s.E + (double)nseg * ((s.T + tm - 1) / tm)) * n_tiles;
-}
-
-int pick_tile_rows(const moe_shape& s, int n_tiles, int nseg) {
-    double best = 0;
-    int best_tm = 256;
-    for (int tm : {256, 128}) {
-        const double tiles = expected_tiles(s, tm, n_tiles, nseg);
-        const double rounds = (double)(int64_t)((tiles + 255) / 256);
-        const double cost = rounds * tm * (tm == 128 ? 1.35 : 1.0);
-        if (best == 0 || cost < best) { best = cost; best_tm = tm; }
-    }
-    return best_tm;
+// Whether the plan kernel may choose tiles lower than 256 rows for a launch: only where that can
+// fill idle CUs, in launches of at most four rounds of 256-row tiles on average (with more rounds
+// the tallest tiles win: 128-row tiles run at about 0.75 of their rate).
+int may_choose_rows(const moe_shape& s, int n_tiles, int nseg) {
+    const double tiles = ((double)s.T * s.top_k / 256 + 0.5 * s.E + (double)nseg * ((s.T + 255) / 256)) * n_tiles;
+    return tiles <= 4 * 256.0;
 }
 
 // m-tiles swept together before moving along n.  Tiles of one expert share W panels, so runs
@@ -361,8 +349,9 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     TileDesc* descs_down = (TileDesc*)(ws + L.descs_down);
     const size_t Rpad = ((size_t)s.T * s.top_k + 15) & ~(size_t)15;   // shared experts' rows of h start block-aligned
     const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;
-    int tm_up = c->gemm.tile_rows_up ? c->gemm.tile_rows_up : pick_tile_rows(s, nt_up, s.num_shared);
-    int tm_down = c->gemm.tile_rows_down ? c->gemm.tile_rows_down : pick_tile_rows(s, nt_down, s.num_shared ? 1 : 0);
+    int tm_up = c->gemm.tile_rows_up ? c->gemm.tile_rows_up : 256;
+    int tm_down = c->gemm.tile_rows_down ? c->gemm.tile_rows_down : 256;
+    const int choose_up = !c->gemm.tile_rows_up && may_choose_rows(s, nt_up, s.num_shared);
     // tiles above 256 rows exist for the 4-wave, 1-wave-row kernel only
     const bool tall_kernel = c->gemm.waves == 4 && c->gemm.wave_rows == 1;
     // Gate/up GEMM: 320-row tiles move 10 % fewer bytes per FLOP from L2 to LDS (the chip is
@@ -370,7 +359,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     // that GEMM; not when an expert is only about four tiles (C2: 1024 rows = 3 tiles + a tail
     // that needs a pass of its own, +10 %).  In the down GEMM the 320-row variant measures within
     // 1 % of the 256-row one either way, so it keeps 256.
-    if (!c->gemm.tile_rows_up && tall_kernel && tm_up == 256 && (double)s.T * s.top_k / s.E >= 1200.0) tm_up = 320;
+    if (!c->gemm.tile_rows_up && tall_kernel && !choose_up && (double)s.T * s.top_k / s.E >= 1200.0) tm_up = 320;
     if (!tall_kernel && tm_up > 256) tm_up = 256;
     if (!tall_kernel && tm_down > 256) tm_down = 256;
     // Short tail tiles go last by default: the other tiles of a launch then all take the same
@@ -384,6 +373,9 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     // spares the launch of the reduction: tiny matrices (a launch costs more than it can save).
     int dsp = (tl_down && c->gemm.small_tiles && c->gemm.down_tail_splits != 0) ? down_tail_splits(s) : 1;
     if (c->gemm.down_tail_splits == 1 && (int64_t)s.F * s.H < ((int64_t)1 << 21)) dsp = 1;
+    // Forced pieces: which rows are cut must not depend on what else a pass covers, so the heights are fixed.
+    const int choose_down = !c->gemm.tile_rows_down && may_choose_rows(s, nt_down, s.num_shared ? 1 : 0) &&
+                            !(dsp > 1 && c->gemm.down_tail_splits == 2);
     // "many rounds" for the plan's rule: eight rounds of 256 tiles (at two to three rounds pieces
     // measured +6 %, at four to five +-0, at thirteen -2 %)
     const int split_rule_tiles = c->gemm.down_tail_splits == 2 ? 0 : (2048 + nt_down - 1) / nt_down;
@@ -397,15 +389,15 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
         const double per_expert = (double)s.T * s.top_k / ((double)s.E * 256);
         int tall = c->gemm.tall_tiles >= 0 ? c->gemm.tall_tiles : (per_expert <= 8.0 ? 2 : 1);
         if (!tall_kernel) tall = 0;
-        HIP_TRY(c, launch_ffn_plan(s, offsets, tm_up, tm_down, tl_up, tl_down, c->gemm.small_tiles != 0, ps.e_lo, ps.e_hi,
-                                   ps.shared_on, dsp, 4, split_rule_tiles, tall, tall, split_tails, plan, descs_up,
-                                   descs_down, st));
+        const PlanArgs pa{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
+                          nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, ps.e_lo, ps.e_hi, ps.shared_on,
+                          dsp, 4, split_rule_tiles, tall, tall, split_tails, plan, descs_up, descs_down};
+        HIP_TRY(c, launch_ffn_plan(pa, st));
     }
     GemmArgs a;
     memset(&a, 0, sizeof(a));
     a.plan = plan;
     a.T = s.T;
-    a.xcd_remap = c->gemm.xcd_remap;
     a.small_tiles = c->gemm.small_tiles;
     a.out_fp32 = 0;
     a.t_pad = (s.T + 15) & ~15;
@@ -413,7 +405,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     // GEMM 1: [rows, H] x W1p/W3p [F, H] -> h [rows, F]
     a.descs = descs_up;
     a.group_m = pick_group_m(c, s, tm_up);
-    a.max_mtiles = ps.mtiles_up > 0 ? ps.mtiles_up : (int)max_mtiles(s, tm_up);
+    a.max_mtiles = ps.mtiles_up > 0 ? ps.mtiles_up : (int)max_mtiles(s, choose_up ? 128 : tm_up);
     a.a_routed = (const char*)(x_perm_tiled ? x_perm_tiled : (row_token ? x : x_perm));
     a.a_shared = (const char*)x;
     a.row_token = x_perm_tiled ? nullptr : row_token;
@@ -437,7 +429,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     // GEMM 2: h [rows, F] x W2p [H, F] -> y [rows, H]
     a.descs = descs_down;
     a.group_m = pick_group_m(c, s, tm_down);
-    a.max_mtiles = (ps.mtiles_down > 0 ? ps.mtiles_down : (int)max_mtiles(s, tm_down)) + s.E * (dsp - 1);
+    a.max_mtiles = (ps.mtiles_down > 0 ? ps.mtiles_down : (int)max_mtiles(s, choose_down ? 128 : tm_down)) + s.E * (dsp - 1);
     a.a_routed = (const char*)h;
     a.a_shared = (const char*)h + Rpad * s.F * 2;
     a.row_token = nullptr;

@@ -34,7 +34,9 @@ struct PlanHeader {
     int32_t n_run_up;   // the first n_run_* entries of each list are in group order; short tail tiles moved
     int32_t n_run_down; // to the end of the list (if any) follow them
     int32_t n_split_tails;  // down GEMM: short tails whose K range is cut into pieces (0 if that is off)
-    int32_t pad[3];
+    int32_t xcd_run_up;    // tiles per XCD run (tile_order); 0 = the hardware's own order
+    int32_t xcd_run_down;
+    int32_t pad[1];
 };
 
 // Rows of y_perm that the K-split pieces of one short tail add up to.
@@ -59,7 +61,6 @@ struct GemmArgs {
     int32_t n_tiles;           // tiles along N
     int32_t max_mtiles;        // grid = max_mtiles * n_tiles
     int32_t group_m;
-    int32_t xcd_remap;
     int32_t small_tiles;       // 1: a short tail tile runs the 128/64/32-row variant
     int32_t out_fp32;          // GEMM2: output stored as fp32 (else bf16): bit 0 routed tiles, bit 1 shared tiles (GEMM1 always stores bf16)
     int32_t lda_bytes;         // row stride of a row-major A operand
@@ -75,6 +76,20 @@ struct GemmArgs {
     const char* w_uniform;
     uint32_t w_uniform_stride;
     int32_t uniform_tm, uniform_per, uniform_splits;
+};
+
+struct PlanArgs {
+    const int32_t* offsets;
+    int32_t T, t_pad, E, Ns;
+    int32_t tm_up, tm_down;             // height cap of the m-tiles: 128 .. 320, a multiple of 32
+    int32_t choose_up, choose_down;     // 1: a lower cap (down to 128) may be chosen from the row counts
+    int32_t nt_up, nt_down;             // tiles along N
+    int32_t tails_last_up, tails_last_down, small_tiles, xcd_remap;
+    int32_t e_lo, e_hi, shared_on;      // the lists cover routed experts [e_lo, e_hi) and, if shared_on, the shared experts
+    int32_t down_splits, split_max_blocks, split_rule_tiles, tall_up, tall_down;
+    SplitTail* split_tails;
+    PlanHeader* plan;
+    TileDesc *descs_up, *descs_down;
 };
 
 struct GemmConfig {
@@ -128,11 +143,7 @@ hipError_t launch_zero_offsets(int E, int32_t* offsets, hipStream_t st);
 hipError_t launch_permute_gather_tiled(const moe_shape& s, const void* x, const int32_t* row_token, void* x_tiled,
                                        hipStream_t st);
 
-// the lists cover routed experts [e_lo, e_hi) and, if shared_on, the shared experts
-hipError_t launch_ffn_plan(const moe_shape& s, const int32_t* offsets, int tm_up, int tm_down, bool tails_last_up,
-                           bool tails_last_down, bool small_tiles, int e_lo, int e_hi, bool shared_on,
-                           int down_tail_splits, int split_max_blocks, int split_rule_tiles, int tall_up, int tall_down,
-                           SplitTail* split_tails, PlanHeader* plan, TileDesc* descs_up, TileDesc* descs_down, hipStream_t st);
+hipError_t launch_ffn_plan(const PlanArgs& a, hipStream_t st);
 // y_perm rows of the split tails = sum over pieces of the fp32 partials, in y_perm's dtype
 hipError_t launch_split_tail_reduce(const moe_shape& s, const PlanHeader* plan, const SplitTail* tails, const float* partial,
                                     int splits, void* y_perm, bool y_fp32, hipStream_t st);

@@ -15,7 +15,7 @@
 // unless a tiled copy exists.
 //
 // Tile routine (one workgroup = NW wavefronts in a WM x WN grid):
-//   * macro tile: BM rows of X (320/288/256/128/64/32) x 256 rows of W (GEMM 1: 128 gate + 128
+//   * macro tile: BM rows of X (32, 64, ... 320) x 256 rows of W (GEMM 1: 128 gate + 128
 //     up rows, so the SiLU-gate product is formed in registers); K advances in sub-tiles of 32.
 //     The 288- and 320-row tiles (4 waves side by side only) keep the accumulators of their last
 //     2-4 X blocks in VGPRs, the 256 AGPRs being full; they serve as the standard tile of GEMM 1
@@ -42,7 +42,7 @@
 //     one or two LDS reads, at most one global load} fenced by scheduling barriers, so the
 //     matrix pipe always has independent work queued.
 //   * ragged tails: rows past the end of a group are clamped on load and masked on store;
-//     short tails use the 128/64/32-row variants so padded MFMA work stays small.
+//     a tile runs the lowest variant that holds its rows, so padded MFMA work stays small.
 //
 // Work distribution: a device-built list of m-tiles (ffn_plan) x n-tiles; workgroup ids are
 // remapped so each XCD (ids are dealt round-robin over the 8 XCDs) receives runs of 32
@@ -58,7 +58,7 @@ namespace {
 constexpr int BK = 32;              // K elements per LDS stage
 constexpr int ROWB = BK * 2;        // bytes per LDS row
 constexpr int WROWS = 256;          // W rows per macro tile
-constexpr int NS = 4;               // LDS ring depth
+constexpr int NS = 4;               // LDS ring depth (deeper rings for the low tiles, up to 8 stages, measured the same)
 constexpr int MAX_ROWS = 320;       // tallest macro tile: a full 256-row tile that also takes a short tail of its group
 constexpr int MAX_STAGE = (MAX_ROWS + WROWS) * ROWB;     // 36 KiB
 constexpr int MAX_LDS = NS * MAX_STAGE;
@@ -476,13 +476,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
 }
 
 // Workgroup id -> position in the tile order.  Hardware deals consecutive workgroup ids to the
-// 8 XCDs in turn; inside each run of 256 ids, XCD x is given tiles [32x, 32x+32).
-__device__ __forceinline__ int tile_order(const int wg, const int total, const int remap) {
-    if (!remap) return wg;
-    const int full = total & ~255;
-    if (wg >= full) return wg;
-    const int q = wg >> 8, r = wg & 255;
-    return (q << 8) + ((r & 7) << 5) + (r >> 3);
+// 8 XCDs in turn; inside each stretch of 8 * run ids, XCD x is given tiles [run * x, run * (x + 1)).
+// Only whole rounds of 256 tiles are dealt in runs of 32, and whole stretches in shorter ones.
+__device__ __forceinline__ int tile_order(const int wg, const int total, const int run) {
+    if (!run) return wg;
+    const int span = run * 8;   // 64 or 256
+    if (wg >= (total & ~(span - 1))) return wg;
+    const int r = wg & (span - 1);
+    return (wg - r) + (r & 7) * run + (r >> 3);
 }
 
 // Tile picked by this workgroup (false: nothing to do).  The first n_run entries of the m-tile
@@ -515,7 +516,7 @@ __device__ __forceinline__ bool pick_tile(const GemmArgs& p, const bool gated, T
     // idle: a launch of 128 tiles measured 251 us on four XCDs against 210 us on eight, the
     // second of two rounds 6 % more; over the Mixtral-shaped layer from 1024 to 8192 tokens the
     // gate/up GEMM is 0.7-2.6 % faster this way, the named workloads are unchanged.
-    const int L = tile_order(blockIdx.x, count * p.n_tiles, p.xcd_remap);
+    const int L = tile_order(blockIdx.x, count * p.n_tiles, gated ? p.plan->xcd_run_up : p.plan->xcd_run_down);
     const int run_positions = n_run * p.n_tiles;
     int mt;
     if (L < run_positions) {
@@ -552,8 +553,12 @@ __global__ __launch_bounds__(256, 1) void ffn_gemm_kernel(const GemmArgs p) {
     } else {
         if (blocks > 9) gemm_tile<4, 1, 10, GATED>(p, d, n_tile, lds);
         else if (blocks > 8) gemm_tile<4, 1, 9, GATED>(p, d, n_tile, lds);
-        else if (blocks > 4) gemm_tile<4, 1, 8, GATED>(p, d, n_tile, lds);
-        else if (blocks > 2) gemm_tile<4, 1, 4, GATED>(p, d, n_tile, lds);
+        else if (blocks > 7) gemm_tile<4, 1, 8, GATED>(p, d, n_tile, lds);
+        else if (blocks > 6) gemm_tile<4, 1, 7, GATED>(p, d, n_tile, lds);
+        else if (blocks > 5) gemm_tile<4, 1, 6, GATED>(p, d, n_tile, lds);
+        else if (blocks > 4) gemm_tile<4, 1, 5, GATED>(p, d, n_tile, lds);
+        else if (blocks > 3) gemm_tile<4, 1, 4, GATED>(p, d, n_tile, lds);
+        else if (blocks > 2) gemm_tile<4, 1, 3, GATED>(p, d, n_tile, lds);
         else if (blocks > 1) gemm_tile<4, 1, 2, GATED>(p, d, n_tile, lds);
         else gemm_tile<4, 1, 1, GATED>(p, d, n_tile, lds);
     }
@@ -603,10 +608,83 @@ __device__ __forceinline__ void block_scan3(int& a, int& b, int& c, int (&tot)[3
     c = oc + ic - c;
 }
 
-// Builds the two m-tile lists (gate/up GEMM with tiles of tm_up rows, down GEMM with tm_down rows)
+// How the rows of one group are cut into m-tiles for a tile height cap `tm`: tiles of `h` rows and a
+// last one with the rest.  A group of two or three tiles is cut evenly, in steps of 32 rows: its
+// tiles then run side by side, share the W panels they stream and finish together, where a short
+// tail moved to the end of the list read them a second time (8x7B, 1511 tokens = 378 rows per
+// expert: gate/up GEMM 740 -> 600 us, down 351 -> 300).  A longer one is cut into full tiles and
+// a tail.  A tail of at most 64 rows next to full 256-row tiles joins the last of them.
+struct GroupCut {
+    int h, nfull, tail, joined;
+    bool even;
+};
+__device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, const bool tall) {
+    GroupCut c;
+    c.h = tm;
+    c.nfull = rows / tm;
+    c.tail = rows - c.nfull * tm;
+    c.joined = tall && tm == 256 && c.nfull > 0 && c.tail <= MAX_ROWS - 256 ? c.tail : 0;
+    c.tail -= c.joined;
+    c.even = c.tail > 0 && (c.nfull == 1 || c.nfull == 2);
+    if (c.even) {
+        const int m = c.nfull + 1;
+        c.h = ((rows + m - 1) / m + 31) & ~31;   // (m - 1) * h < rows: rows > tm * (m - 1) >= 128 * (m - 1)
+        c.nfull = rows / c.h;
+        c.tail = rows - c.nfull * c.h;
+    }
+    return c;
+}
+
+// Height cap of a list's tiles, chosen from the call's real row counts (launches of a few rounds
+// of tiles only; with more the tallest is best).  What a tile costs per K sub-tile, in rows of
+// matrix work (1.3 ns), is its height plus a constant for what it loads: 290 while at most half
+// of the CUs are busy (a CU fills its LDS at about 44 GB/s), more when all of them are and share
+// the memory's bandwidth: 520 for a tile that streams its W panel alone, 340 next to another
+// tile of its group.  (Uniform groups on the 8x7B layer: 0.72 us at 32 rows, 0.81 at 128, 1.01 at
+// 256, 1.14 at 320 with 1792 tiles; 0.42, 0.52 and 0.68 at 32, 128 and 256 rows with 128 tiles;
+// 0.74 at 192 and 0.83 at 256 rows, two tiles to a panel.)  A launch costs its whole rounds of
+// 256 tiles times the mean tile, and no less than its longest tile.  With caps below 256 an
+// expert of 250 rows is two tiles of 128: the down GEMM of eight such experts fills the chip
+// with one round of 256 tiles instead of half a round of 256-row ones (8x7B, 1000 tokens:
+// 310 -> 268 us).
+constexpr int PLAN_CAPS = 5;
+__device__ constexpr int plan_cap(const int c) { return 256 - 32 * c; }
+
+template <int TM>
+__device__ __forceinline__ float list_cost(const int* rows, const int ngroups, const int nseg0, const bool tall,
+                                           const int n_tiles, const int lane) {
+    // n: tiles; alone: tiles that are their group's only one; sum: rows; longest: highest tile (shared experts
+    // of the down GEMM walk nseg0 segments)
+    // (n and alone share a word: a launch with a choice has at most a few thousand m-tiles)
+    int n_alone = 0, sum = 0, longest = 0;
+    for (int g = lane; g < ngroups; g += 64) {
+        const int r = rows[g];
+        if (r == 0) continue;
+        const GroupCut c = cut_group(r, TM, tall);
+        const int m = c.nfull + (c.tail > 0);
+        const int seg = g == 0 ? nseg0 : 1;
+        n_alone += m + (m == 1 ? 1 << 16 : 0);
+        sum += ((r + 31) & ~31) + (seg - 1) * (r + 290 * m);
+        longest = max(longest, (290 + (((m > 1 ? c.h : r) + 31) & ~31)) * seg);
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        n_alone += __shfl_xor(n_alone, d, 64);
+        sum += __shfl_xor(sum, d, 64);
+        longest = max(longest, __shfl_xor(longest, d, 64));
+    }
+    const int n = n_alone & 0xffff, alone = n_alone >> 16;
+    if (n == 0) return 0.f;
+    const int tiles = n * n_tiles;
+    const float busy = fminf(fmaxf((float)(tiles - 128) / 128.f, 0.f), 1.f);
+    const float mean = ((float)sum + 290.f * n + busy * (50.f * (n - alone) + 230.f * alone)) / (float)n;
+    return fmaxf((float)((tiles + 255) / 256) * mean, (float)longest);
+}
+
+// Builds the two m-tile lists (gate/up GEMM with tiles of up to tm_up rows, down GEMM with tm_down)
 // from expert_offsets.  Group order: shared expert 0, routed experts, shared experts 1.. (the down
 // GEMM takes the first two parts only: shared experts are concatenated along K there).
-// A group of n rows gives floor(n/tm) full tiles and at most one tail tile.  A tail higher than
+// cut_group says how a group's rows become tiles.  A tail higher than
 // half a tile runs the full-height variant and always stays with its group; a short tail runs
 // a short variant.  tails_last = 0: the short tail, too, directly follows its group's tiles,
 // which keeps the load-bound short tiles mixed with the compute-bound full ones (better when
@@ -614,41 +692,64 @@ __device__ __forceinline__ void block_scan3(int& a, int& b, int& c, int (&tot)[3
 // sorted by falling height, ties in group order, so a launch with few rounds ends on its
 // smallest work items and its other tiles all take the same time (CUs that share operand
 // panels in L2 stay in step).  n_run_* = number of entries listed in group order.
-__global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict__ offsets, int T, int t_pad, int E, int Ns,
-                                                       int tm_up, int tm_down, int tails_last_up, int tails_last_down,
-                                                       int small_tiles, int e_lo, int e_hi, int shared_on, int down_splits,
-                                                       int split_max_blocks, int split_rule_tiles, int tall_up, int tall_down,
-                                                       SplitTail* __restrict__ split_tails, PlanHeader* __restrict__ plan,
-                                                       TileDesc* __restrict__ descs_up, TileDesc* __restrict__ descs_down) {
+__global__ __launch_bounds__(256) void ffn_plan_kernel(const PlanArgs p) {
     __shared__ int wsum[4][3];
+    __shared__ int group_rows[256];
+    __shared__ float cap_cost[2][PLAN_CAPS];
     const int tid = threadIdx.x;
+    const int E = p.E, Ns = p.Ns;
     // group order: g = 0 -> shared 0 (if any), then routed 0..E-1, then shared 1..Ns-1
     const int ngroups = E + Ns;
     int row_begin = 0, rows = 0, group = 0, srow = -1;
     if (tid < ngroups) {
         int pos = tid;
-        if (Ns > 0 && pos == 0) { group = E; rows = T; row_begin = 0; srow = 0; }
+        if (Ns > 0 && pos == 0) { group = E; rows = p.T; row_begin = 0; srow = 0; }
         else {
             if (Ns > 0) pos -= 1;
-            if (pos < E) { group = pos; row_begin = offsets[pos]; rows = offsets[pos + 1] - row_begin; srow = -1; }
-            else { const int s = pos - E + 1; group = E + s; rows = T; row_begin = 0; srow = s * t_pad; }
+            if (pos < E) { group = pos; row_begin = p.offsets[pos]; rows = p.offsets[pos + 1] - row_begin; srow = -1; }
+            else { const int s = pos - E + 1; group = E + s; rows = p.T; row_begin = 0; srow = s * p.t_pad; }
         }
         // a streamed pass covers routed experts [e_lo, e_hi) and, if shared_on, the shared experts
-        if (group < E ? (group < e_lo || group >= e_hi) : !shared_on) rows = 0;
+        if (group < E ? (group < p.e_lo || group >= p.e_hi) : !p.shared_on) rows = 0;
+    }
+    int tm_of[2] = {p.tm_up, p.tm_down};
+    // groups of at most 128 rows are one tile under every cap
+    if ((p.choose_up || p.choose_down) && __syncthreads_or(rows > 128)) {
+        group_rows[tid] = rows;
+        __syncthreads();
+        const int wave = tid >> 6, lane = tid & 63;
+        for (int w = wave; w < 2 * PLAN_CAPS; w += 4) {   // wave-uniform
+            const int which = w / PLAN_CAPS, c = w % PLAN_CAPS;
+            if (!(which == 0 ? p.choose_up : p.choose_down)) continue;
+            const int groups = which == 0 ? ngroups : (Ns > 0 ? E + 1 : E);
+            const int nseg0 = which == 1 && Ns > 1 ? Ns : 1, nt = which == 0 ? p.nt_up : p.nt_down;
+            const bool tall = (which == 0 ? p.tall_up : p.tall_down) != 0;
+            float cost;
+            if (c == 0) cost = list_cost<plan_cap(0)>(group_rows, groups, nseg0, tall, nt, lane);
+            else if (c == 1) cost = list_cost<plan_cap(1)>(group_rows, groups, nseg0, tall, nt, lane);
+            else if (c == 2) cost = list_cost<plan_cap(2)>(group_rows, groups, nseg0, tall, nt, lane);
+            else if (c == 3) cost = list_cost<plan_cap(3)>(group_rows, groups, nseg0, tall, nt, lane);
+            else cost = list_cost<plan_cap(4)>(group_rows, groups, nseg0, tall, nt, lane);
+            if (lane == 0) cap_cost[which][c] = cost;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int which = 0; which < 2; ++which) {
+            if (!(which == 0 ? p.choose_up : p.choose_down)) continue;
+            float best = cap_cost[which][0] * 0.97f;   // the tallest unless another is clearly cheaper
+            for (int c = 1; c < PLAN_CAPS; ++c)
+                if (cap_cost[which][c] < best) { best = cap_cost[which][c]; tm_of[which] = plan_cap(c); }
+        }
     }
     for (int which = 0; which < 2; ++which) {
-        const int tm = which == 0 ? tm_up : tm_down;
-        TileDesc* descs = which == 0 ? descs_up : descs_down;
+        const int tm = tm_of[which];
+        TileDesc* descs = which == 0 ? p.descs_up : p.descs_down;
+        const int tall = which == 0 ? p.tall_up : p.tall_down;
         const int last = which == 0 ? ngroups - 1 : (Ns > 0 ? E : E - 1);  // last group of this list
         const bool mine = tid <= last;
-        const bool tails_last = (which == 0 ? tails_last_up : tails_last_down) != 0;
-        const int nfull = mine ? rows / tm : 0;
-        int tail = mine ? rows - nfull * tm : 0;
-        // Tall tiles: a tail of at most 64 rows joins the group's last full 256-row tile (288 or
-        // 320 rows, 12-25 % more time for that tile) instead of costing a pass of its own over
-        // the group's weights.
-        const int joined = ((which == 0 ? tall_up : tall_down) && tm == 256 && nfull > 0 && tail <= MAX_ROWS - 256) ? tail : 0;
-        tail -= joined;
+        const bool tails_last = (which == 0 ? p.tails_last_up : p.tails_last_down) != 0;
+        const GroupCut cut = cut_group(mine ? rows : 0, tm, tall != 0);
+        const int nfull = cut.nfull, tail = cut.tail, joined = cut.joined, h = cut.h;
         const int blocks = (tail + 31) >> 5;   // 32-row blocks of the tail tile, 0 = none
         // A tail higher than half a tile runs the full-height variant and takes as long as a full
         // tile, so it stays with its group (keeps the group's W panels shared and the CUs in
@@ -656,14 +757,14 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict
         // (A shared expert's tail is not moved in a down list with K pieces: the pieces' partial
         // sums are reduced into y_perm, while shared rows belong to y_shared.)
         // (at most 128 rows: the K pieces' partial buffers hold SPLIT_TAIL_ROWS rows)
-        const bool moved = tails_last && blocks > 0 && small_tiles && blocks * 64 <= min(tm, 2 * SPLIT_TAIL_ROWS) &&
-                           !(which == 1 && down_splits > 1 && group >= E);
+        const bool moved = tails_last && blocks > 0 && !cut.even && p.small_tiles && blocks * 64 <= min(tm, 2 * SPLIT_TAIL_ROWS) &&
+                           !(which == 1 && p.down_splits > 1 && group >= E);
         // tall_* = 2: the tall tile keeps its place in the group (it shares the W panels its
         // neighbours stream, which is the point when a group is only a few tiles).  tall_* = 1 and
         // tails_last: a tall tile takes longer than its neighbours and in a long launch puts the
         // CUs it runs on out of step for the rest of it, so it leaves the group order too: tall
         // tiles come first after the run region, one entry each, never cut along K.
-        const bool tall_moved = tails_last && joined > 0 && (which == 0 ? tall_up : tall_down) == 1;
+        const bool tall_moved = tails_last && joined > 0 && tall == 1;
         const int nrun = nfull - (tall_moved ? 1 : 0) + (blocks > 0 && !moved);   // tiles listed in group order
         // Positions by prefix sums over the groups (at most 256, one per thread): tiles listed in
         // group order; tall tiles moved behind them; moved short tails, counted per height in
@@ -677,8 +778,8 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict
         const int cnt[5] = {0, (tot[1] >> 10) & 1023, (tot[1] >> 20) & 1023, tot[2] & 1023, (tot[2] >> 10) & 1023};
         const int pre[5] = {0, (k2 >> 10) & 1023, (k2 >> 20) & 1023, k3 & 1023, (k3 >> 10) & 1023};
         const int tails = cnt[1] + cnt[2] + cnt[3] + cnt[4];
-        // Down list with K pieces: only the moved tails of at most split_max_blocks 32-row blocks are
-        // cut (down_splits list entries each); the higher ones, which come first, stay whole.
+        // Down list with K pieces: only the moved tails of at most p.split_max_blocks 32-row blocks are
+        // cut (p.down_splits list entries each); the higher ones, which come first, stay whole.
         // Whether to cut at all is decided here, where the tile counts are known.  Pieces make a
         // launch faster in two cases only (measured on the Mixtral-shaped layer from 64 to 16384
         // tokens): when EVERY tile of the launch is a short tail (a few tokens per expert: the
@@ -686,22 +787,27 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict
         // many rounds of tiles long (the tails at its end then finish sooner: -2 % on the
         // 16384-token, skewed workload).  In between, a launch of one to three rounds is as long
         // as its full tiles whatever happens to the tails, and pieces only add a round and
-        // traffic (+6 ... +50 % measured).  split_rule_tiles: that many m-tiles or more count as
+        // traffic (+6 ... +50 % measured).  p.split_rule_tiles: that many m-tiles or more count as
         // "many rounds"; 0: always cut.
         int n_whole = tails;
-        bool cutting = which == 1 && down_splits > 1;
+        bool cutting = which == 1 && p.down_splits > 1;
         if (cutting) {
             n_whole = 0;
-            for (int b = split_max_blocks + 1; b <= 4; ++b) n_whole += cnt[b];
+            for (int b = p.split_max_blocks + 1; b <= 4; ++b) n_whole += cnt[b];
             const int others = n_run_s + n_tall_s + n_whole;
-            cutting = split_rule_tiles == 0 || others == 0 || others + tails - n_whole >= split_rule_tiles;
+            cutting = p.split_rule_tiles == 0 || others == 0 || others + tails - n_whole >= p.split_rule_tiles;
             if (!cutting) n_whole = tails;
         }
         const int n_cut = tails - n_whole;
         if (tid == 0) {
-            const int total = n_run_s + n_tall_s + n_whole + n_cut * (cutting ? down_splits : 1);
-            if (which == 0) { plan->n_gate_up = total; plan->n_run_up = n_run_s; }
-            else { plan->n_down = total; plan->n_run_down = n_run_s; plan->n_split_tails = n_cut; }
+            const int total = n_run_s + n_tall_s + n_whole + n_cut * (cutting ? p.down_splits : 1);
+            // Tiles per XCD run (tile_order): 32, or 8 in a launch of a few rounds next to shared experts.
+            // Theirs are the first and longest tiles of the list; in runs of 32 a few rounds of them
+            // land on two or three XCDs, which then finish last (two shared experts next to 64 routed
+            // ones, down GEMM: 1000 tokens 129 -> 95 us, 3001 tokens 174 -> 149 us).
+            const int run = !p.xcd_remap ? 0 : (Ns > 0 && total * (which == 0 ? p.nt_up : p.nt_down) <= 10 * 256 ? 8 : 32);
+            if (which == 0) { p.plan->n_gate_up = total; p.plan->n_run_up = n_run_s; p.plan->xcd_run_up = run; }
+            else { p.plan->n_down = total; p.plan->n_run_down = n_run_s; p.plan->n_split_tails = n_cut; p.plan->xcd_run_down = run; }
         }
         if (mine) {
             TileDesc d;
@@ -711,32 +817,32 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict
             for (int i = 0; i < nrun; ++i) {
                 // entry nlisted (if any) is a tail that stays with its group; it starts after all full tiles
                 const int at = i < nlisted ? i : nfull;
-                d.row0 = row_begin + at * tm;
-                d.nrows = min(tm, rows - at * tm) + ((at == nfull - 1 && !tall_moved) ? joined : 0);
+                d.row0 = row_begin + at * h;
+                d.nrows = min(h, rows - at * h) + ((at == nfull - 1 && !tall_moved) ? joined : 0);
                 descs[base + i] = d;
             }
             if (tall_moved) {
                 const int before = k2 & 1023;   // tall tiles of the groups before this one
-                d.row0 = row_begin + (nfull - 1) * tm;
-                d.nrows = tm + joined;
+                d.row0 = row_begin + (nfull - 1) * h;
+                d.nrows = h + joined;
                 descs[n_run_s + before] = d;
             }
             if (moved) {
                 // tails that come before this one: the higher ones, and those as high of earlier groups
                 int rank = pre[blocks];
                 for (int b = blocks + 1; b <= 4; ++b) rank += cnt[b];
-                d.row0 = row_begin + nfull * tm;
+                d.row0 = row_begin + nfull * h;
                 d.nrows = tail;
                 const int tbase = n_run_s + n_tall_s;
-                if (cutting && blocks <= split_max_blocks) {
+                if (cutting && blocks <= p.split_max_blocks) {
                     // one entry per K piece; the pieces' partial sums are added up after the launch
                     const int q = rank - n_whole;   // falling height: the whole ones rank first
-                    for (int sp = 0; sp < down_splits; ++sp) {
-                        d.srow = -2 - (q * down_splits + sp);
-                        descs[tbase + n_whole + q * down_splits + sp] = d;
+                    for (int sp = 0; sp < p.down_splits; ++sp) {
+                        d.srow = -2 - (q * p.down_splits + sp);
+                        descs[tbase + n_whole + q * p.down_splits + sp] = d;
                     }
-                    split_tails[q].row0 = d.row0;
-                    split_tails[q].nrows = tail;
+                    p.split_tails[q].row0 = d.row0;
+                    p.split_tails[q].nrows = tail;
                 } else {
                     descs[tbase + rank] = d;
                 }
@@ -801,14 +907,8 @@ hipError_t ffn_gemm_init() {
     return hipSuccess;
 }
 
-hipError_t launch_ffn_plan(const moe_shape& s, const int32_t* offsets, int tm_up, int tm_down, bool tails_last_up,
-                           bool tails_last_down, bool small_tiles, int e_lo, int e_hi, bool shared_on,
-                           int down_tail_splits, int split_max_blocks, int split_rule_tiles, int tall_up, int tall_down,
-                           SplitTail* split_tails, PlanHeader* plan, TileDesc* descs_up, TileDesc* descs_down, hipStream_t st) {
-    hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(256), 0, st, offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down,
-                       tails_last_up ? 1 : 0, tails_last_down ? 1 : 0, small_tiles ? 1 : 0, e_lo, e_hi, shared_on ? 1 : 0,
-                       tails_last_down ? down_tail_splits : 1, split_max_blocks, split_rule_tiles, tall_up, tall_down, split_tails, plan, descs_up,
-                       descs_down);
+hipError_t launch_ffn_plan(const PlanArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

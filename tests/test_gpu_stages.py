@@ -324,6 +324,39 @@ def test_grouped_ffn_every_tail_class(moe, F, num_shared, tall):
         say(P.assert_output(ysh.float().cpu().numpy(), ref_s, "y_shared"))
 
 
+# Rows per expert around the edges of evenly cut groups: each tile height from 32 to 320 rows occurs, as one of
+# two or three tiles and alone, full and with one row more or less than a multiple of 32.
+EVEN_COUNTS = [65, 96, 97, 129, 160, 161, 192, 193, 224, 225, 250, 256, 288, 321, 378, 384, 385, 448, 449, 511, 513, 577, 641, 767]
+
+
+@pytest.mark.parametrize("tile_rows,num_shared", [(0, 0), (0, 2), (128, 0), (256, 1), (320, 0)])
+def test_grouped_ffn_evenly_cut_groups(moe, tile_rows, num_shared):
+    """tile_rows 0: the plan chooses the cap itself (narrow matrices: the lowest); every row against the oracle."""
+    counts = np.array(EVEN_COUNTS)
+    E, T = len(counts), int(counts.sum())
+    cfg = scaled_config("C4", T=T, H=128, F=128, E=E, top_k=1, num_shared=num_shared)
+    idx_h = np.repeat(np.arange(E, dtype=np.int32), counts)
+    idx_h = idx_h[np.random.default_rng(6).permutation(T)].reshape(T, 1)
+    say("even cuts", cfg, "tile rows", tile_rows)
+    moe.set_option("gemm_tile_rows_up", tile_rows)
+    moe.set_option("gemm_tile_rows_down", tile_rows)
+    try:
+        y, ysh, perm, off, li = run_ffn_stage(moe, cfg, idx_h, wave_rows=1)
+    finally:
+        moe.set_option("gemm_tile_rows_up", 0)
+        moe.set_option("gemm_tile_rows_down", 0)
+    u = torch_bf16_to_u16
+    hw1 = [u(t) for t in li.w1]; hw3 = [u(t) for t in li.w3]; hw2 = [u(t) for t in li.w2]
+    hx = u(li.x)
+    ref = orc.expert_rows(hx[perm], np.repeat(np.arange(E, dtype=np.int32), counts), hw1, hw3, hw2)
+    say(P.assert_output(y.float().cpu().numpy(), ref, "y_perm"))
+    if num_shared:
+        ref_s = np.zeros((T, cfg.H), np.float32)
+        for sh in range(num_shared):
+            ref_s += orc.expert_rows(hx, np.full(T, E + sh, np.int32), hw1, hw3, hw2)
+        say(P.assert_output(ysh.float().cpu().numpy(), ref_s, "y_shared"))
+
+
 def test_grouped_ffn_bf16_y(moe):
     """Option y_fp32 = 0: y in bf16 is the RNE rounding of the fp32 y, bit for bit."""
     cfg = scaled_config("C4", T=300, H=256, F=192, E=16, top_k=4)
