@@ -328,6 +328,41 @@ int pick_group_m(const moe_ctx* c, const moe_shape& s, int tm) {
     return g < 4 ? 4 : (g > 8 ? 8 : g);
 }
 
+// Which of the two GEMMs of a small batch run one wavefront per 16 or 32 output columns (ffn_small.hip).
+// Measured with cold weights against the tile routine, us (tile -> small):
+//   gate/up  64 experts top-6 + 2 shared, F = 1408: 1 token 29 -> 22, 4: 57 -> 54, 16: 111 -> 108, 32: 124 -> 132;
+//            8 experts top-2, F = 14336: 1: 92 -> 90, 8: 312 -> 295, 32: 335 -> 337;
+//            160 experts top-6 + 2 shared, F = 1536: 1: 77 -> 52, 32: 309 -> 317;
+//            8 experts top-2, H = 512, F = 1024: 16: 12.1 -> 9.2, 128: 13.1 -> 12.3, 256: 14.6 -> 15.3
+//   down     the same: 1: 37 -> 15, 4: 44 -> 28, 16: 62 -> 52, 32: 81 -> 68, 64: 85 -> 76;
+//            1: 66 -> 47, 8: 158 -> 145, 32: 177 -> 166, 64: 181 -> 175 (32 columns), 128: 186 -> 310;
+//            1: 43 -> 30, 32: 160 -> 161;  16: 16.2 -> 8.4, 128: 17.0 -> 11.2, 256: 17.9 -> 12.3
+// So: the down GEMM up to 64 tokens, the gate/up GEMM up to 16 (every group one block of 16 rows; X is
+// re-read by every wave, which costs more than the idle CUs from then on), and both somewhat further
+// when the tile routine would have tiles for a quarter of the CUs at most.
+constexpr int SMALL_TILE_ROWS = 128;
+struct SmallRule {
+    bool up, down;
+    int down_cols;     // 16-column blocks per wave of the down GEMM
+    int halves;        // 64-row units per m-tile
+    int mtiles_up, mtiles_down;   // m-tiles of SMALL_TILE_ROWS rows at most (also if a token picks an expert twice)
+};
+SmallRule small_rule(const moe_ctx* c, const moe_shape& s) {
+    SmallRule r;
+    const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;   // tiles of the tile routine along N
+    const int64_t pairs = (int64_t)s.T * s.top_k;
+    const int groups = (int)(pairs < s.E ? pairs : s.E);   // routed groups with rows, at most
+    const bool allowed = c->gemm.small_tiles && !c->gemm.tile_rows_up && !c->gemm.tile_rows_down && c->gemm.down_tail_splits != 2;
+    r.up = allowed && (s.T <= 16 || (s.T <= 128 && (groups + s.num_shared) * nt_up <= 64));
+    r.down = allowed && (s.T <= 64 || (s.T <= 256 && (groups + (s.num_shared > 0)) * nt_down <= 64));
+    r.down_cols = s.T <= 32 ? 1 : 2;
+    r.halves = s.T <= 64 ? 1 : 2;
+    const int routed = groups + (int)(pairs / SMALL_TILE_ROWS), per_shared = (s.T + SMALL_TILE_ROWS - 1) / SMALL_TILE_ROWS;
+    r.mtiles_up = routed + s.num_shared * per_shared;
+    r.mtiles_down = routed + (s.num_shared > 0) * per_shared;
+    return r;
+}
+
 // Which groups one pass of the two GEMMs covers (streamed weights run several passes), and how
 // many m-tiles it can have at most (0 = the bound for any routing).
 struct FfnPass {
@@ -349,9 +384,11 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     TileDesc* descs_down = (TileDesc*)(ws + L.descs_down);
     const size_t Rpad = ((size_t)s.T * s.top_k + 15) & ~(size_t)15;   // shared experts' rows of h start block-aligned
     const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;
-    int tm_up = c->gemm.tile_rows_up ? c->gemm.tile_rows_up : 256;
+    // Up to 256 tokens a group of 129 to 256 rows (most often a shared expert) is two tiles: as one it would
+    // be the longest tile of a short launch (64 experts + 2 shared, 200 tokens: gate/up 137 -> 130 us).
+    int tm_up = c->gemm.tile_rows_up ? c->gemm.tile_rows_up : (s.T <= 256 ? 128 : 256);
     int tm_down = c->gemm.tile_rows_down ? c->gemm.tile_rows_down : 256;
-    const int choose_up = !c->gemm.tile_rows_up && may_choose_rows(s, nt_up, s.num_shared);
+    int choose_up = tm_up == 256 && !c->gemm.tile_rows_up && may_choose_rows(s, nt_up, s.num_shared);
     // tiles above 256 rows exist for the 4-wave, 1-wave-row kernel only
     const bool tall_kernel = c->gemm.waves == 4 && c->gemm.wave_rows == 1;
     // Gate/up GEMM: 320-row tiles move 10 % fewer bytes per FLOP from L2 to LDS (the chip is
@@ -368,13 +405,18 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     // its smallest work items.
     const bool tl_up = c->gemm.tails_last != 0;
     const bool tl_down = c->gemm.tails_last != 0;
+    // Small batches: one wavefront per 16 or 32 columns instead of a workgroup per 256 (ffn_small.hip)
+    const SmallRule sm = small_rule(c, s);
+    if (sm.up) { tm_up = SMALL_TILE_ROWS; choose_up = 0; }
+    if (sm.down) tm_down = SMALL_TILE_ROWS;
     // K pieces for short tails of the down GEMM: the device-side plan decides from the real tile
     // counts whether to cut (ffn_plan_kernel); here only what the shape alone rules out, which
     // spares the launch of the reduction: tiny matrices (a launch costs more than it can save).
-    int dsp = (tl_down && c->gemm.small_tiles && c->gemm.down_tail_splits != 0) ? down_tail_splits(s) : 1;
+    int dsp = (!sm.down && tl_down && c->gemm.small_tiles && c->gemm.down_tail_splits != 0) ? down_tail_splits(s) : 1;
     if (c->gemm.down_tail_splits == 1 && (int64_t)s.F * s.H < ((int64_t)1 << 21)) dsp = 1;
+    if (s.T <= 256 && dsp == 1 && !c->gemm.tile_rows_down) tm_down = 128;   // as above; not where short tails may be cut along K
     // Forced pieces: which rows are cut must not depend on what else a pass covers, so the heights are fixed.
-    const int choose_down = !c->gemm.tile_rows_down && may_choose_rows(s, nt_down, s.num_shared ? 1 : 0) &&
+    const int choose_down = tm_down == 256 && !c->gemm.tile_rows_down && may_choose_rows(s, nt_down, s.num_shared ? 1 : 0) &&
                             !(dsp > 1 && c->gemm.down_tail_splits == 2);
     // "many rounds" for the plan's rule: eight rounds of 256 tiles (at two to three rounds pieces
     // measured +6 %, at four to five +-0, at thirteen -2 %)
@@ -405,7 +447,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     // GEMM 1: [rows, H] x W1p/W3p [F, H] -> h [rows, F]
     a.descs = descs_up;
     a.group_m = pick_group_m(c, s, tm_up);
-    a.max_mtiles = ps.mtiles_up > 0 ? ps.mtiles_up : (int)max_mtiles(s, choose_up ? 128 : tm_up);
+    a.max_mtiles = ps.mtiles_up > 0 ? ps.mtiles_up : (sm.up ? sm.mtiles_up : (int)max_mtiles(s, choose_up ? 128 : tm_up));
     a.a_routed = (const char*)(x_perm_tiled ? x_perm_tiled : (row_token ? x : x_perm));
     a.a_shared = (const char*)x;
     a.row_token = x_perm_tiled ? nullptr : row_token;
@@ -424,12 +466,19 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     a.n_tiles = nt_up;
     {
         StageTimer tm(c, st, MOE_STAGE_FFN_GATE_UP);
-        HIP_TRY(c, launch_ffn_gemm(true, a, c->gemm, st));
+        if (sm.up) {
+            a.n_tiles = s.F / 32;
+            HIP_TRY(c, launch_ffn_small(true, a, 2, sm.halves, st));
+        } else {
+            HIP_TRY(c, launch_ffn_gemm(true, a, c->gemm, st));
+        }
     }
     // GEMM 2: h [rows, F] x W2p [H, F] -> y [rows, H]
     a.descs = descs_down;
     a.group_m = pick_group_m(c, s, tm_down);
-    a.max_mtiles = (ps.mtiles_down > 0 ? ps.mtiles_down : (int)max_mtiles(s, choose_down ? 128 : tm_down)) + s.E * (dsp - 1);
+    a.max_mtiles = (ps.mtiles_down > 0 ? ps.mtiles_down
+                                       : (sm.down ? sm.mtiles_down : (int)max_mtiles(s, choose_down ? 128 : tm_down))) +
+                   s.E * (dsp - 1);
     a.a_routed = (const char*)h;
     a.a_shared = (const char*)h + Rpad * s.F * 2;
     a.row_token = nullptr;
@@ -450,7 +499,12 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     a.n_tiles = nt_down;
     {
         StageTimer tm(c, st, MOE_STAGE_FFN_DOWN);
-        HIP_TRY(c, launch_ffn_gemm(false, a, c->gemm, st));
+        if (sm.down) {
+            a.n_tiles = s.H / (16 * sm.down_cols);
+            HIP_TRY(c, launch_ffn_small(false, a, sm.down_cols, sm.halves, st));
+        } else {
+            HIP_TRY(c, launch_ffn_gemm(false, a, c->gemm, st));
+        }
         if (dsp > 1)
             HIP_TRY(c, launch_split_tail_reduce(s, plan, split_tails, (const float*)(ws + L.split_partial), dsp, y_perm, y_fp32, st));
     }
@@ -491,8 +545,10 @@ moe_status run_front(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     // The gather is either fused into GEMM 1's loads (row-major x, 64-byte pieces from 16 distant
     // rows per load) or done once into a tiled x_perm (one extra pass over T*k*H*2 bytes, after
     // which GEMM 1 loads whole 1 KiB blocks).  The extra pass pays off when each x row is re-read
-    // by many n-tiles, i.e. for wide experts.
-    const bool tiled = c->gemm.x_tiled == 1 || (c->gemm.x_tiled < 0 && s.F >= 4096);
+    // by many n-tiles, i.e. for wide experts, and there are enough rows for the loads of x to matter (8x7B,
+    // gather + gate/up GEMM, tiled against fused: 347 / 341 us at 16 rows per expert, 366 / 362 at 64,
+    // 410 / 440 at 175).
+    const bool tiled = c->gemm.x_tiled == 1 || (c->gemm.x_tiled < 0 && s.F >= 4096 && (int64_t)s.T * s.top_k > 64 * (int64_t)s.E);
     f->x_tiled = nullptr;
     if (tiled) {
         StageTimer tm(c, hs, MOE_STAGE_PERMUTE_GATHER);

@@ -713,8 +713,9 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const PlanArgs p) {
         if (group < E ? (group < p.e_lo || group >= p.e_hi) : !p.shared_on) rows = 0;
     }
     int tm_of[2] = {p.tm_up, p.tm_down};
-    // groups of at most 128 rows are one tile under every cap
-    if ((p.choose_up || p.choose_down) && __syncthreads_or(rows > 128)) {
+    // routed groups of at most 128 rows are one tile under every cap, and the shared experts by themselves are
+    // not worth the 5 us that the choice takes
+    if ((p.choose_up || p.choose_down) && __syncthreads_or(group < E && rows > 128)) {
         group_rows[tid] = rows;
         __syncthreads();
         const int wave = tid >> 6, lane = tid & 63;

@@ -584,3 +584,33 @@ def test_accumulate_then_chunked_layer(moe):
     finally:
         moe.set_option("out_fp32", 0)
         moe.set_option("down_tail_splits", 1)
+
+
+SMALL_CASES = [   # T, H, F, E, k, shared: edges of 16 / 32 / 64 rows, K shorter than, equal to and past a wave's ring of sub-tiles
+    (1, 64, 64, 1, 1, 0), (1, 2048, 1408, 64, 6, 2), (2, 512, 1024, 8, 2, 0), (15, 576, 320, 5, 4, 1), (16, 512, 512, 4, 4, 2),
+    (17, 320, 832, 6, 3, 3), (32, 256, 448, 20, 6, 2), (33, 448, 256, 4, 2, 1), (63, 128, 192, 3, 3, 0), (64, 1024, 576, 40, 8, 2),
+    (65, 512, 384, 4, 2, 1), (128, 512, 1024, 8, 2, 0), (129, 256, 512, 4, 4, 0), (200, 384, 256, 3, 1, 2), (256, 512, 1024, 8, 2, 0),
+]
+
+
+@pytest.mark.parametrize("T,H,F,E,k,shared", SMALL_CASES)
+@pytest.mark.parametrize("y_fp32", [0, 1])
+def test_layer_small_batches_give_the_tile_routine_s_bits(moe, T, H, F, E, k, shared, y_fp32):
+    """Small batches run one wavefront per 16 or 32 columns (option small_tiles = 0 keeps them on the tile routine): every
+    output element is the same chain of additions, so both give the same bits; and the result is the oracle's."""
+    cfg = scaled_config("C4", T=T, H=H, F=F, E=E, top_k=k, num_shared=shared)
+    say("small", cfg, "y fp32", y_fp32)
+    gl = P.GpuLayer(moe, make_layer_inputs(cfg, device="cuda"))
+    moe.set_option("layer_y_fp32", y_fp32)
+    moe.set_option("down_tail_splits", 0)
+    try:
+        out, out16 = gl.run_layer_both()
+        moe.set_option("small_tiles", 0)
+        ref, ref16 = gl.run_layer_both()
+    finally:
+        moe.set_option("small_tiles", 1)
+        moe.set_option("layer_y_fp32", -1)
+        moe.set_option("down_tail_splits", 1)
+    assert torch.equal(out, ref) and torch.equal(out16, ref16)
+    if y_fp32 and F >= 128:
+        say(json.dumps(P.check_layer_against_oracle(gl, out, out16=out16)["output"]))
