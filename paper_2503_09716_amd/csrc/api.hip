@@ -370,19 +370,18 @@ struct FfnPass {
     bool shared_on;
     int mtiles_up, mtiles_down;
 };
+FfnPass whole_layer(const moe_shape& s) { return FfnPass{0, s.E, true, 0, 0}; }
 
-// x_perm_tiled: when non-null, the routed rows of GEMM 1 are read from it (tiled layout) and
-// x_perm / row_token are not used for them.
-moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int32_t* row_token, const void* x,
-                   const void* x_perm_tiled, const int32_t* offsets, void** tab, char* ws, void* h, void* y_perm,
-                   void* y_shared, bool y_fp32, bool shared_fp32, hipStream_t st, const FfnPass* pass = nullptr) {
-    const FfnPass all{0, s.E, true, 0, 0};
-    const FfnPass& ps = pass ? *pass : all;
+// What both GEMMs of one call (or one streamed pass) run with, fixed on the host from the shape.
+struct FfnSetup {
+    PlanArgs plan;
+    SmallRule sm;
+    int mtiles_up, mtiles_down;   // m-tiles each list can have at most
+    int group_m_up, group_m_down;
+};
+
+FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets, char* ws, const FfnPass& ps) {
     const Layout L = make_layout(s);
-    PlanHeader* plan = (PlanHeader*)(ws + L.plan);
-    TileDesc* descs_up = (TileDesc*)(ws + L.descs_up);
-    TileDesc* descs_down = (TileDesc*)(ws + L.descs_down);
-    const size_t Rpad = ((size_t)s.T * s.top_k + 15) & ~(size_t)15;   // shared experts' rows of h start block-aligned
     const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;
     // Up to 256 tokens a group of 129 to 256 rows (most often a shared expert) is two tiles: as one it would
     // be the longest tile of a short launch (64 experts + 2 shared, 200 tokens: gate/up 137 -> 130 us).
@@ -421,33 +420,52 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
     // "many rounds" for the plan's rule: eight rounds of 256 tiles (at two to three rounds pieces
     // measured +6 %, at four to five +-0, at thirteen -2 %)
     const int split_rule_tiles = c->gemm.down_tail_splits == 2 ? 0 : (2048 + nt_down - 1) / nt_down;
-    SplitTail* split_tails = (SplitTail*)(ws + L.split_tails);
-    {
+    // In place when a group is at most one run of m-tiles (the tall tile then shares its
+    // group's W panels in L2: C2 step -4 %, against -0.5 % after the run region); after the run
+    // region for longer groups (C3: in place +5 %, after -0.7 %).
+    const double per_expert = (double)s.T * s.top_k / ((double)s.E * 256);
+    int tall = c->gemm.tall_tiles >= 0 ? c->gemm.tall_tiles : (per_expert <= 8.0 ? 2 : 1);
+    if (!tall_kernel) tall = 0;
+    FfnSetup f;
+    f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
+                      nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, ps.e_lo, ps.e_hi, ps.shared_on,
+                      dsp, 4, split_rule_tiles, tall, tall, (SplitTail*)(ws + L.split_tails), (PlanHeader*)(ws + L.plan),
+                      (TileDesc*)(ws + L.descs_up), (TileDesc*)(ws + L.descs_down)};
+    f.sm = sm;
+    f.mtiles_up = ps.mtiles_up > 0 ? ps.mtiles_up : (sm.up ? sm.mtiles_up : (int)max_mtiles(s, choose_up ? 128 : tm_up));
+    f.mtiles_down = (ps.mtiles_down > 0 ? ps.mtiles_down : (sm.down ? sm.mtiles_down : (int)max_mtiles(s, choose_down ? 128 : tm_down))) +
+                    s.E * (dsp - 1);
+    if (s.num_shared > 0 && s.T <= SHARED_LOW_TOKENS) f.mtiles_down += (s.T + 127) / 128;
+    f.group_m_up = pick_group_m(c, s, tm_up);
+    f.group_m_down = pick_group_m(c, s, tm_down);
+    return f;
+}
+
+// x_perm_tiled: when non-null, the routed rows of GEMM 1 are read from it (tiled layout) and
+// x_perm / row_token are not used for them.  planned: the m-tile lists are there already.
+moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool planned, const void* x_perm, const int32_t* row_token,
+                   const void* x, const void* x_perm_tiled, void** tab, char* ws, void* h, void* y_perm, void* y_shared,
+                   bool y_fp32, bool shared_fp32, hipStream_t st) {
+    const Layout L = make_layout(s);
+    const SmallRule& sm = f.sm;
+    const int nt_up = f.plan.nt_up, nt_down = f.plan.nt_down, dsp = f.plan.down_splits;
+    const size_t Rpad = ((size_t)s.T * s.top_k + 15) & ~(size_t)15;   // shared experts' rows of h start block-aligned
+    if (!planned) {
         StageTimer tm(c, st, MOE_STAGE_PLAN);
-        // tall tiles exist for the 4-wave, 1-wave-row kernel only
-        // In place when a group is at most one run of m-tiles (the tall tile then shares its
-        // group's W panels in L2: C2 step -4 %, against -0.5 % after the run region); after the run
-        // region for longer groups (C3: in place +5 %, after -0.7 %).
-        const double per_expert = (double)s.T * s.top_k / ((double)s.E * 256);
-        int tall = c->gemm.tall_tiles >= 0 ? c->gemm.tall_tiles : (per_expert <= 8.0 ? 2 : 1);
-        if (!tall_kernel) tall = 0;
-        const PlanArgs pa{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
-                          nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, ps.e_lo, ps.e_hi, ps.shared_on,
-                          dsp, 4, split_rule_tiles, tall, tall, split_tails, plan, descs_up, descs_down};
-        HIP_TRY(c, launch_ffn_plan(pa, st));
+        HIP_TRY(c, launch_ffn_plan(f.plan, st));
     }
     GemmArgs a;
     memset(&a, 0, sizeof(a));
-    a.plan = plan;
+    a.plan = f.plan.plan;
     a.T = s.T;
     a.small_tiles = c->gemm.small_tiles;
     a.out_fp32 = 0;
     a.t_pad = (s.T + 15) & ~15;
     a.split_rows = 0;
     // GEMM 1: [rows, H] x W1p/W3p [F, H] -> h [rows, F]
-    a.descs = descs_up;
-    a.group_m = pick_group_m(c, s, tm_up);
-    a.max_mtiles = ps.mtiles_up > 0 ? ps.mtiles_up : (sm.up ? sm.mtiles_up : (int)max_mtiles(s, choose_up ? 128 : tm_up));
+    a.descs = f.plan.descs_up;
+    a.group_m = f.group_m_up;
+    a.max_mtiles = f.mtiles_up;
     a.a_routed = (const char*)(x_perm_tiled ? x_perm_tiled : (row_token ? x : x_perm));
     a.a_shared = (const char*)x;
     a.row_token = x_perm_tiled ? nullptr : row_token;
@@ -474,11 +492,9 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
         }
     }
     // GEMM 2: h [rows, F] x W2p [H, F] -> y [rows, H]
-    a.descs = descs_down;
-    a.group_m = pick_group_m(c, s, tm_down);
-    a.max_mtiles = (ps.mtiles_down > 0 ? ps.mtiles_down
-                                       : (sm.down ? sm.mtiles_down : (int)max_mtiles(s, choose_down ? 128 : tm_down))) +
-                   s.E * (dsp - 1);
+    a.descs = f.plan.descs_down;
+    a.group_m = f.group_m_down;
+    a.max_mtiles = f.mtiles_down;
     a.a_routed = (const char*)h;
     a.a_shared = (const char*)h + Rpad * s.F * 2;
     a.row_token = nullptr;
@@ -506,7 +522,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const void* x_perm, const int
             HIP_TRY(c, launch_ffn_gemm(false, a, c->gemm, st));
         }
         if (dsp > 1)
-            HIP_TRY(c, launch_split_tail_reduce(s, plan, split_tails, (const float*)(ws + L.split_partial), dsp, y_perm, y_fp32, st));
+            HIP_TRY(c, launch_split_tail_reduce(s, f.plan.plan, f.plan.split_tails, (const float*)(ws + L.split_partial), dsp, y_perm, y_fp32, st));
     }
     return MOE_OK;
 }
@@ -519,10 +535,11 @@ struct LayerFront {
     const void* x_tiled;   // nullptr: the gather is fused into GEMM 1's loads
     void *h, *y_perm, *y_shared;
     bool y32;              // dtype of y_perm
+    bool planned;          // the m-tile lists were built next to the permutation
 };
 
 moe_status run_front(moe_ctx* c, const moe_shape& s, const void* x, const void* wg, const float* bias, char* w8,
-                     hipStream_t hs, LayerFront* f) {
+                     hipStream_t hs, const PlanArgs* plan, LayerFront* f) {
     const Layout L = make_layout(s);
     f->topk_idx = (int32_t*)(w8 + L.topk_idx);
     f->topk_w = (float*)(w8 + L.topk_w);
@@ -540,7 +557,7 @@ moe_status run_front(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     {
         StageTimer tm(c, hs, MOE_STAGE_PERMUTE_INDEX);
         HIP_TRY(c, launch_permute_index(s, f->topk_idx, (int32_t*)(w8 + L.chunk_counts), f->offsets, f->perm, f->inv_perm,
-                                        f->row_token, hs));
+                                        f->row_token, plan, &f->planned, hs));
     }
     // The gather is either fused into GEMM 1's loads (row-major x, 64-byte pieces from 16 distant
     // rows per load) or done once into a tiled x_perm (one extra pass over T*k*H*2 bytes, after
@@ -574,9 +591,11 @@ moe_status layer_with_workspace(moe_ctx* c, const moe_shape* s, const void* x, c
                                 char* ws, hipStream_t hs) {
     void** tab = nullptr;
     if (moe_status st = weight_table(c, s->E + s->num_shared, w1p, w3p, w2p, hs, &tab)) return st;
+    const FfnSetup fs = ffn_setup(c, *s, (const int32_t*)(ws + make_layout(*s).offsets), ws, whole_layer(*s));
     LayerFront f;
-    if (moe_status st = run_front(c, *s, x, wg, bias, ws, hs, &f)) return st;
-    if (moe_status st = run_ffn(c, *s, nullptr, f.row_token, x, f.x_tiled, f.offsets, tab, ws, f.h, f.y_perm,
+    // While stages are timed the lists are built by a launch of their own, so that it can be told from the permutation.
+    if (moe_status st = run_front(c, *s, x, wg, bias, ws, hs, c->prof ? nullptr : &fs.plan, &f)) return st;
+    if (moe_status st = run_ffn(c, *s, fs, f.planned, nullptr, f.row_token, x, f.x_tiled, tab, ws, f.h, f.y_perm,
                                 f.y_shared, f.y32, true, hs))
         return st;
     {
@@ -723,7 +742,7 @@ moe_status moe_permute(moe_ctx* c, const moe_shape* s, const void* x, const int3
     {
         StageTimer tm(c, hs, MOE_STAGE_PERMUTE_INDEX);
         HIP_TRY(c, launch_permute_index(*s, idx, (int32_t*)((char*)ws + L.chunk_counts), offsets, perm, inv_perm,
-                                        row_token, hs));
+                                        row_token, nullptr, nullptr, hs));
     }
     if (x_perm) {
         StageTimer tm(c, hs, MOE_STAGE_PERMUTE_GATHER);
@@ -746,8 +765,8 @@ moe_status moe_grouped_ffn(moe_ctx* c, const moe_shape* s, const void* x_perm, c
     hipStream_t hs = (hipStream_t)stream;
     void** tab = nullptr;
     if (moe_status st = weight_table(c, s->E + s->num_shared, w1p, w3p, w2p, hs, &tab)) return st;
-    return run_ffn(c, *s, x_perm, row_token, x, nullptr, offsets, tab, (char*)ws, h, y_perm, y_shared, c->y_fp32,
-                   c->y_fp32, hs);
+    return run_ffn(c, *s, ffn_setup(c, *s, offsets, (char*)ws, whole_layer(*s)), false, x_perm, row_token, x, nullptr, tab,
+                   (char*)ws, h, y_perm, y_shared, c->y_fp32, c->y_fp32, hs);
 }
 
 moe_status moe_combine(moe_ctx* c, const moe_shape* s, const void* y_perm, const int32_t* inv_perm, const float* w,
@@ -838,7 +857,7 @@ moe_status moe_layer_streamed(moe_ctx* c, const moe_shape* s, const void* x, con
         if (!hw1[e] || !hw3[e] || !hw2[e]) return fail(c, MOE_E_ARG, "layer_streamed: host weight pointer %d is NULL", e);
     hipStream_t hs = (hipStream_t)stream;
     LayerFront f;
-    if (moe_status st = run_front(c, *s, x, wg, bias, (char*)ws, hs, &f)) return st;
+    if (moe_status st = run_front(c, *s, x, wg, bias, (char*)ws, hs, nullptr, &f)) return st;
     // the per-expert row counts decide what is fetched: one synchronising read-back
     HIP_TRY(c, hipMemcpyAsync(c->h_offsets, f.offsets, (size_t)(E + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, hs));
     HIP_TRY(c, hipStreamSynchronize(hs));
@@ -890,8 +909,8 @@ moe_status moe_layer_streamed(moe_ctx* c, const moe_shape* s, const void* x, con
         void** tab = nullptr;
         if (moe_status st = weight_table(c, E + Ns, t1.data(), t3.data(), t2.data(), hs, &tab)) return st;
         const FfnPass pass{G.shared ? 0 : G.lo, G.shared ? 0 : G.hi, G.shared, mt, G.shared ? (s->T + 127) / 128 : mt};
-        if (moe_status st = run_ffn(c, *s, nullptr, f.row_token, x, f.x_tiled, f.offsets, tab, (char*)ws, f.h, f.y_perm,
-                                    f.y_shared, f.y32, true, hs, &pass))
+        if (moe_status st = run_ffn(c, *s, ffn_setup(c, *s, f.offsets, (char*)ws, pass), false, nullptr, f.row_token, x, f.x_tiled,
+                                    tab, (char*)ws, f.h, f.y_perm, f.y_shared, f.y32, true, hs))
             return st;
         HIP_TRY(c, hipEventRecord(c->slot_free[slot], hs));
         ++c->stream_groups;

@@ -78,6 +78,7 @@ struct GemmArgs {
     int32_t uniform_tm, uniform_per, uniform_splits;
 };
 
+constexpr int SHARED_LOW_TOKENS = 1024;   // up to here the shared experts' tiles of the down GEMM are at most 128 rows
 struct PlanArgs {
     const int32_t* offsets;
     int32_t T, t_pad, E, Ns;
@@ -134,8 +135,11 @@ __host__ __device__ constexpr int block_swizzle(const int r) { return (0 - (r >>
 
 constexpr int PERMUTE_CHUNK_TOKENS = 256;
 inline int permute_chunks(const moe_shape& s) { return (s.T + PERMUTE_CHUNK_TOKENS - 1) / PERMUTE_CHUNK_TOKENS; }
+// plan: when non-null, the m-tile lists are built by one more workgroup of the last launch, and *planned
+// says whether they were (not in the form with three launches)
 hipError_t launch_permute_index(const moe_shape& s, const int32_t* idx, int32_t* chunk_counts, int32_t* offsets,
-                                int32_t* perm, int32_t* inv_perm, int32_t* row_token, hipStream_t st);
+                                int32_t* perm, int32_t* inv_perm, int32_t* row_token, const PlanArgs* plan, bool* planned,
+                                hipStream_t st);
 hipError_t launch_permute_gather(const moe_shape& s, const void* x, const int32_t* perm, void* x_perm,
                                  hipStream_t st);
 hipError_t launch_zero_offsets(int E, int32_t* offsets, hipStream_t st);

@@ -15,6 +15,7 @@
 // usual sizes (count; scan + place), three when the table of histograms is too large for every
 // workgroup to add up.
 #include "common.h"
+#include "plan.h"
 
 namespace moe {
 namespace {
@@ -119,19 +120,10 @@ __global__ __launch_bounds__(64) void permute_place_kernel(const int32_t* __rest
     }
 }
 
-// Common tail of the two kernels below.  Thread e < E comes in with its expert's pair count over
-// all chunks (total) and over the chunks before this workgroup's (before); mask[][] is zero.
-// Exclusive prefix sum of the totals over the experts (-> expert_offsets, written by chunk 0, and
-// this chunk's cursors), then the placement of the chunk: wavefront w takes tokens 64w .. 64w+63,
-// the lane masks of all four wavefronts give a pair its rank.
-__device__ __forceinline__ void scan_and_place_chunk(const int32_t* __restrict__ idx, const int T, const int k, const int E,
-                                                     const int total, const int before,
-                                                     unsigned long long (&mask)[4][MAX_E], int (&cur)[MAX_E],
-                                                     int (&wave_sum)[4], int32_t* __restrict__ offsets,
-                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
-                                                     int32_t* __restrict__ row_token) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, chunk = blockIdx.x;
-    int incl = total;
+// Exclusive prefix sum of one value per thread over the 256 threads of a workgroup.
+__device__ __forceinline__ int block_exclusive(const int v, int (&wave_sum)[4]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int incl = v;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const int t = __shfl_up(incl, d, 64);
@@ -143,7 +135,35 @@ __device__ __forceinline__ void scan_and_place_chunk(const int32_t* __restrict__
 #pragma unroll
     for (int w = 0; w < 4; ++w)
         if (w < wave) base += wave_sum[w];
-    const int excl = base + incl - total;
+    return base + incl - v;
+}
+
+// The work of one extra workgroup of the two kernels below: the m-tile lists of the grouped GEMMs,
+// which need nothing but the experts' totals, next to the placement instead of in a launch of their
+// own after it (4 us of every small batch).
+__device__ __forceinline__ void plan_from_totals(const PlanArgs& plan, const int E, const int total, int (&offs)[MAX_E + 1],
+                                                 int (&wave_sum)[4]) {
+    const int tid = threadIdx.x;
+    const int excl = block_exclusive(total, wave_sum);
+    if (tid < E) offs[tid] = excl;
+    if (tid == E - 1) offs[E] = excl + total;
+    __syncthreads();
+    plan_lists(plan, (const int*)offs);
+}
+
+// Common tail of the two kernels below.  Thread e < E comes in with its expert's pair count over
+// all chunks (total) and over the chunks before this workgroup's (before); mask[][] is zero.
+// Exclusive prefix sum of the totals over the experts (-> expert_offsets, written by chunk 0, and
+// this chunk's cursors), then the placement of the chunk: wavefront w takes tokens 64w .. 64w+63,
+// the lane masks of all four wavefronts give a pair its rank.
+__device__ __forceinline__ void scan_and_place_chunk(const int32_t* __restrict__ idx, const int T, const int k, const int E,
+                                                     const int total, const int before,
+                                                     unsigned long long (&mask)[4][MAX_E], int (&cur)[MAX_E + 1],
+                                                     int (&wave_sum)[4], int32_t* __restrict__ offsets,
+                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
+                                                     int32_t* __restrict__ row_token) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, chunk = blockIdx.x;
+    const int excl = block_exclusive(total, wave_sum);
     if (tid < E) {
         cur[tid] = excl + before;
         if (chunk == 0) offsets[tid] = excl;
@@ -185,10 +205,11 @@ static_assert(PERMUTE_CHUNK_TOKENS == 256, "the fused kernel gives each of its 4
 
 __global__ __launch_bounds__(256) void permute_index_fused_kernel(const int32_t* __restrict__ idx, int T, int k, int E,
                                                                   int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
-                                                                  int32_t* __restrict__ inv_perm, int32_t* __restrict__ row_token) {
+                                                                  int32_t* __restrict__ inv_perm, int32_t* __restrict__ row_token,
+                                                                  int nchunks, const PlanArgs plan) {
     __shared__ int hist[4][2][MAX_E];              // [wave][0: all chunks, 1: chunks before mine][expert]
     __shared__ unsigned long long mask[4][MAX_E];  // [wave][expert]: lanes of that wave that picked the expert
-    __shared__ int cur[MAX_E];
+    __shared__ int cur[MAX_E + 1];
     __shared__ int wave_sum[4];
     const int tid = threadIdx.x, wave = tid >> 6, chunk = blockIdx.x;
     for (int i = tid; i < 4 * 2 * MAX_E; i += 256) (&hist[0][0][0])[i] = 0;
@@ -209,6 +230,10 @@ __global__ __launch_bounds__(256) void permute_index_fused_kernel(const int32_t*
 #pragma unroll
         for (int w = 0; w < 4; ++w) { total += hist[w][0][tid]; before += hist[w][1][tid]; }
     }
+    if (chunk == nchunks) {   // the extra workgroup
+        plan_from_totals(plan, E, total, cur, wave_sum);
+        return;
+    }
     scan_and_place_chunk(idx, T, k, E, total, before, mask, cur, wave_sum, offsets, perm, inv_perm, row_token);
 }
 
@@ -223,10 +248,11 @@ constexpr int PLACE_SCAN_MAX_COUNTS = 1 << 14;
 __global__ __launch_bounds__(256) void permute_place_scan_kernel(const int32_t* __restrict__ idx, int T, int k, int E, int ep2,
                                                                  const int32_t* __restrict__ chunk_counts, int nchunks,
                                                                  int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
-                                                                 int32_t* __restrict__ inv_perm, int32_t* __restrict__ row_token) {
+                                                                 int32_t* __restrict__ inv_perm, int32_t* __restrict__ row_token,
+                                                                 const PlanArgs plan) {
     __shared__ int sum[2][MAX_E];                  // [0: all chunks, 1: chunks before mine][expert]
     __shared__ unsigned long long mask[4][MAX_E];
-    __shared__ int cur[MAX_E];
+    __shared__ int cur[MAX_E + 1];
     __shared__ int wave_sum[4];
     const int tid = threadIdx.x, chunk = blockIdx.x;
     for (int i = tid; i < 2 * MAX_E; i += 256) (&sum[0][0])[i] = 0;
@@ -245,6 +271,10 @@ __global__ __launch_bounds__(256) void permute_place_scan_kernel(const int32_t* 
     }
     __syncthreads();
     const int total = tid < E ? sum[0][tid] : 0, before = tid < E ? sum[1][tid] : 0;
+    if (chunk == nchunks) {   // the extra workgroup
+        plan_from_totals(plan, E, total, cur, wave_sum);
+        return;
+    }
     scan_and_place_chunk(idx, T, k, E, total, before, mask, cur, wave_sum, offsets, perm, inv_perm, row_token);
 }
 
@@ -296,21 +326,26 @@ hipError_t launch_permute_gather_tiled(const moe_shape& s, const void* x, const 
 }
 
 hipError_t launch_permute_index(const moe_shape& s, const int32_t* idx, int32_t* chunk_counts, int32_t* offsets,
-                                int32_t* perm, int32_t* inv_perm, int32_t* row_token, hipStream_t st) {
+                                int32_t* perm, int32_t* inv_perm, int32_t* row_token, const PlanArgs* plan, bool* planned,
+                                hipStream_t st) {
     const int nchunks = permute_chunks(s);
+    const PlanArgs pa = plan ? *plan : PlanArgs{};
+    const dim3 grid(nchunks + (plan ? 1 : 0)), block(256);
+    if (planned) *planned = plan != nullptr;
     if ((int64_t)s.T * s.top_k <= FUSED_MAX_PAIRS) {
-        hipLaunchKernelGGL(permute_index_fused_kernel, dim3(nchunks), dim3(256), 0, st, idx, s.T, s.top_k, s.E, offsets, perm,
-                           inv_perm, row_token);
+        hipLaunchKernelGGL(permute_index_fused_kernel, grid, block, 0, st, idx, s.T, s.top_k, s.E, offsets, perm, inv_perm,
+                           row_token, nchunks, pa);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(permute_count_kernel, dim3(nchunks), dim3(256), 0, st, idx, s.T, s.top_k, s.E, chunk_counts);
     if ((int64_t)nchunks * s.E <= PLACE_SCAN_MAX_COUNTS) {
         int ep2 = 1;
         while (ep2 < s.E) ep2 <<= 1;
-        hipLaunchKernelGGL(permute_place_scan_kernel, dim3(nchunks), dim3(256), 0, st, idx, s.T, s.top_k, s.E, ep2,
-                           (const int32_t*)chunk_counts, nchunks, offsets, perm, inv_perm, row_token);
+        hipLaunchKernelGGL(permute_place_scan_kernel, grid, block, 0, st, idx, s.T, s.top_k, s.E, ep2,
+                           (const int32_t*)chunk_counts, nchunks, offsets, perm, inv_perm, row_token, pa);
         return hipGetLastError();
     }
+    if (planned) *planned = false;
     hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(256), 0, st, chunk_counts, nchunks, s.E, offsets);
     hipLaunchKernelGGL(permute_place_kernel, dim3(nchunks), dim3(64), 0, st, idx, s.T, s.top_k, s.E,
                        (const int32_t*)chunk_counts, (const int32_t*)offsets, perm, inv_perm, row_token);

@@ -1,0 +1,287 @@
+// The m-tile lists of the two grouped GEMMs, built on the device from expert_offsets.
+#pragma once
+#include "common.h"
+
+namespace moe {
+namespace {
+
+constexpr int PLAN_MAX_ROWS = 320;   // tallest m-tile: a full 256-row tile that also takes a short tail of its group
+
+// Exclusive prefix sums of three per-thread counters over the 256 threads of a workgroup, and
+// their totals (every thread gets them): a wave-level scan, then the four wave sums through LDS.
+__device__ __forceinline__ void block_scan3(int& a, int& b, int& c, int (&tot)[3], int (*wsum)[3], const int tid) {
+    const int lane = tid & 63, w = tid >> 6;
+    int ia = a, ib = b, ic = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int ta = __shfl_up(ia, d, 64), tb = __shfl_up(ib, d, 64), tc = __shfl_up(ic, d, 64);
+        if (lane >= d) { ia += ta; ib += tb; ic += tc; }
+    }
+    if (lane == 63) { wsum[w][0] = ia; wsum[w][1] = ib; wsum[w][2] = ic; }
+    __syncthreads();
+    int oa = 0, ob = 0, oc = 0;
+    tot[0] = tot[1] = tot[2] = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (i < w) { oa += wsum[i][0]; ob += wsum[i][1]; oc += wsum[i][2]; }
+        tot[0] += wsum[i][0]; tot[1] += wsum[i][1]; tot[2] += wsum[i][2];
+    }
+    __syncthreads();   // wsum may be written again
+    a = oa + ia - a;
+    b = ob + ib - b;
+    c = oc + ic - c;
+}
+
+// How the rows of one group are cut into m-tiles for a tile height cap `tm`: tiles of `h` rows and a
+// last one with the rest.  A group of two or three tiles is cut evenly, in steps of 32 rows: its
+// tiles then run side by side, share the W panels they stream and finish together, where a short
+// tail moved to the end of the list read them a second time (8x7B, 1511 tokens = 378 rows per
+// expert: gate/up GEMM 740 -> 600 us, down 351 -> 300).  A longer one is cut into full tiles and
+// a tail.  A tail of at most 64 rows next to full 256-row tiles joins the last of them.
+struct GroupCut {
+    int h, nfull, tail, joined;
+    bool even;
+};
+__device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, const bool tall, const bool even = true) {
+    GroupCut c;
+    c.h = tm;
+    c.nfull = rows / tm;
+    c.tail = rows - c.nfull * tm;
+    c.joined = tall && tm == 256 && c.nfull > 0 && c.tail <= PLAN_MAX_ROWS - 256 ? c.tail : 0;
+    c.tail -= c.joined;
+    c.even = even && c.tail > 0 && (c.nfull == 1 || c.nfull == 2);
+    if (c.even) {
+        const int m = c.nfull + 1;
+        c.h = ((rows + m - 1) / m + 31) & ~31;   // (m - 1) * h < rows: rows > tm * (m - 1) >= 128 * (m - 1)
+        c.nfull = rows / c.h;
+        c.tail = rows - c.nfull * c.h;
+    }
+    return c;
+}
+
+// Height cap of a list's tiles, chosen from the call's real row counts (launches of a few rounds
+// of tiles only; with more the tallest is best).  What a tile costs per K sub-tile, in rows of
+// matrix work (1.3 ns), is its height plus a constant for what it loads: 290 while at most half
+// of the CUs are busy (a CU fills its LDS at about 44 GB/s), more when all of them are and share
+// the memory's bandwidth: 520 for a tile that streams its W panel alone, 340 next to another
+// tile of its group.  (Uniform groups on the 8x7B layer: 0.72 us at 32 rows, 0.81 at 128, 1.01 at
+// 256, 1.14 at 320 with 1792 tiles; 0.42, 0.52 and 0.68 at 32, 128 and 256 rows with 128 tiles;
+// 0.74 at 192 and 0.83 at 256 rows, two tiles to a panel.)  A launch costs its whole rounds of
+// 256 tiles times the mean tile, and no less than its longest tile.  With caps below 256 an
+// expert of 250 rows is two tiles of 128: the down GEMM of eight such experts fills the chip
+// with one round of 256 tiles instead of half a round of 256-row ones (8x7B, 1000 tokens:
+// 310 -> 268 us).
+constexpr int PLAN_CAPS = 5;
+__device__ constexpr int plan_cap(const int c) { return 256 - 32 * c; }
+
+template <int TM>
+__device__ __forceinline__ float list_cost(const int* rows, const int ngroups, const int nseg0, const bool tall,
+                                           const int n_tiles, const int lane) {
+    // n: tiles; alone: tiles that are their group's only one; sum: rows; longest: highest tile (shared experts
+    // of the down GEMM walk nseg0 segments)
+    // (n and alone share a word: a launch with a choice has at most a few thousand m-tiles)
+    int n_alone = 0, sum = 0, longest = 0;
+    for (int g = lane; g < ngroups; g += 64) {
+        const int r = rows[g];
+        if (r == 0) continue;
+        const GroupCut c = cut_group(r, TM, tall);
+        const int m = c.nfull + (c.tail > 0);
+        const int seg = g == 0 ? nseg0 : 1;
+        n_alone += m + (m == 1 ? 1 << 16 : 0);
+        sum += ((r + 31) & ~31) + (seg - 1) * (r + 290 * m);
+        longest = max(longest, (290 + (((m > 1 ? c.h : r) + 31) & ~31)) * seg);
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        n_alone += __shfl_xor(n_alone, d, 64);
+        sum += __shfl_xor(sum, d, 64);
+        longest = max(longest, __shfl_xor(longest, d, 64));
+    }
+    const int n = n_alone & 0xffff, alone = n_alone >> 16;
+    if (n == 0) return 0.f;
+    const int tiles = n * n_tiles;
+    const float busy = fminf(fmaxf((float)(tiles - 128) / 128.f, 0.f), 1.f);
+    const float mean = ((float)sum + 290.f * n + busy * (50.f * (n - alone) + 230.f * alone)) / (float)n;
+    return fmaxf((float)((tiles + 255) / 256) * mean, (float)longest);
+}
+
+// Builds the two m-tile lists (gate/up GEMM with tiles of up to tm_up rows, down GEMM with tm_down)
+// from expert_offsets.  Group order: shared expert 0, routed experts, shared experts 1.. (the down
+// GEMM takes the first two parts only: shared experts are concatenated along K there).
+// cut_group says how a group's rows become tiles.  A tail higher than
+// half a tile runs the full-height variant and always stays with its group; a short tail runs
+// a short variant.  tails_last = 0: the short tail, too, directly follows its group's tiles,
+// which keeps the load-bound short tiles mixed with the compute-bound full ones (better when
+// a launch has many rounds of tiles).  tails_last = 1: the short tails follow all other tiles,
+// sorted by falling height, ties in group order, so a launch with few rounds ends on its
+// smallest work items and its other tiles all take the same time (CUs that share operand
+// panels in L2 stay in step).  n_run_* = number of entries listed in group order.
+// One workgroup of 256 threads; `offsets`: E + 1 prefix sums in global memory or LDS.
+template <class Offsets>
+__device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offsets) {
+    __shared__ int wsum[4][3];
+    __shared__ int group_rows[256];
+    __shared__ float cap_cost[2][PLAN_CAPS];
+    const int tid = threadIdx.x;
+    const int E = p.E, Ns = p.Ns;
+    // group order: g = 0 -> shared 0 (if any), then routed 0..E-1, then shared 1..Ns-1
+    const int ngroups = E + Ns;
+    int row_begin = 0, rows = 0, group = 0, srow = -1;
+    if (tid < ngroups) {
+        int pos = tid;
+        if (Ns > 0 && pos == 0) { group = E; rows = p.T; row_begin = 0; srow = 0; }
+        else {
+            if (Ns > 0) pos -= 1;
+            if (pos < E) { group = pos; row_begin = offsets[pos]; rows = offsets[pos + 1] - row_begin; srow = -1; }
+            else { const int s = pos - E + 1; group = E + s; rows = p.T; row_begin = 0; srow = s * p.t_pad; }
+        }
+        // a streamed pass covers routed experts [e_lo, e_hi) and, if shared_on, the shared experts
+        if (group < E ? (group < p.e_lo || group >= p.e_hi) : !p.shared_on) rows = 0;
+    }
+    int tm_of[2] = {p.tm_up, p.tm_down};
+    // routed groups of at most 128 rows are one tile under every cap, and the shared experts by themselves are
+    // not worth the 5 us that the choice takes
+    if ((p.choose_up || p.choose_down) && __syncthreads_or(group < E && rows > 128)) {
+        group_rows[tid] = rows;
+        __syncthreads();
+        const int wave = tid >> 6, lane = tid & 63;
+        for (int w = wave; w < 2 * PLAN_CAPS; w += 4) {   // wave-uniform
+            const int which = w / PLAN_CAPS, c = w % PLAN_CAPS;
+            if (!(which == 0 ? p.choose_up : p.choose_down)) continue;
+            const int groups = which == 0 ? ngroups : (Ns > 0 ? E + 1 : E);
+            const int nseg0 = which == 1 && Ns > 1 ? Ns : 1, nt = which == 0 ? p.nt_up : p.nt_down;
+            const bool tall = (which == 0 ? p.tall_up : p.tall_down) != 0;
+            float cost;
+            if (c == 0) cost = list_cost<plan_cap(0)>(group_rows, groups, nseg0, tall, nt, lane);
+            else if (c == 1) cost = list_cost<plan_cap(1)>(group_rows, groups, nseg0, tall, nt, lane);
+            else if (c == 2) cost = list_cost<plan_cap(2)>(group_rows, groups, nseg0, tall, nt, lane);
+            else if (c == 3) cost = list_cost<plan_cap(3)>(group_rows, groups, nseg0, tall, nt, lane);
+            else cost = list_cost<plan_cap(4)>(group_rows, groups, nseg0, tall, nt, lane);
+            if (lane == 0) cap_cost[which][c] = cost;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int which = 0; which < 2; ++which) {
+            if (!(which == 0 ? p.choose_up : p.choose_down)) continue;
+            float best = cap_cost[which][0] * 0.97f;   // the tallest unless another is clearly cheaper
+            for (int c = 1; c < PLAN_CAPS; ++c)
+                if (cap_cost[which][c] < best) { best = cap_cost[which][c]; tm_of[which] = plan_cap(c); }
+        }
+    }
+    for (int which = 0; which < 2; ++which) {
+        const int tm = tm_of[which];
+        TileDesc* descs = which == 0 ? p.descs_up : p.descs_down;
+        const int tall = which == 0 ? p.tall_up : p.tall_down;
+        const int last = which == 0 ? ngroups - 1 : (Ns > 0 ? E : E - 1);  // last group of this list
+        const bool mine = tid <= last;
+        const bool tails_last = (which == 0 ? p.tails_last_up : p.tails_last_down) != 0;
+        // Shared experts next to short routed groups (up to about a thousand tokens): theirs are the longest
+        // tiles.  Down GEMM, where they walk all shared experts' K: 128 rows at most (64 experts + 2 shared,
+        // 300 tokens 96 -> 85 us, 500: 92 -> 90).  Gate/up: not cut evenly up to 512 tokens, so that the short
+        // rest goes last (500 tokens: 147 -> 143 us).
+        const int cap = which == 1 && group >= E && p.T <= SHARED_LOW_TOKENS ? min(tm, 128) : tm;
+        const GroupCut cut = cut_group(mine ? rows : 0, cap, tall != 0, group < E || which == 1 || p.T > 512);
+        const int nfull = cut.nfull, tail = cut.tail, joined = cut.joined, h = cut.h;
+        const int blocks = (tail + 31) >> 5;   // 32-row blocks of the tail tile, 0 = none
+        // A tail higher than half a tile runs the full-height variant and takes as long as a full
+        // tile, so it stays with its group (keeps the group's W panels shared and the CUs in
+        // step); only a short tail is moved to the end of the list.
+        // (A shared expert's tail is not moved in a down list with K pieces: the pieces' partial
+        // sums are reduced into y_perm, while shared rows belong to y_shared.)
+        // (at most 128 rows: the K pieces' partial buffers hold SPLIT_TAIL_ROWS rows)
+        const bool moved = tails_last && blocks > 0 && !cut.even && p.small_tiles && blocks * 64 <= min(cap, 2 * SPLIT_TAIL_ROWS) &&
+                           !(which == 1 && p.down_splits > 1 && group >= E);
+        // tall_* = 2: the tall tile keeps its place in the group (it shares the W panels its
+        // neighbours stream, which is the point when a group is only a few tiles).  tall_* = 1 and
+        // tails_last: a tall tile takes longer than its neighbours and in a long launch puts the
+        // CUs it runs on out of step for the rest of it, so it leaves the group order too: tall
+        // tiles come first after the run region, one entry each, never cut along K.
+        const bool tall_moved = tails_last && joined > 0 && tall == 1;
+        const int nrun = nfull - (tall_moved ? 1 : 0) + (blocks > 0 && !moved);   // tiles listed in group order
+        // Positions by prefix sums over the groups (at most 256, one per thread): tiles listed in
+        // group order; tall tiles moved behind them; moved short tails, counted per height in
+        // 32-row blocks (1..4), three 10-bit counters to a word.
+        int base = nrun;
+        int k2 = (tall_moved ? 1 : 0) | (moved && blocks == 1 ? 1 << 10 : 0) | (moved && blocks == 2 ? 1 << 20 : 0);
+        int k3 = (moved && blocks == 3 ? 1 : 0) | (moved && blocks == 4 ? 1 << 10 : 0);
+        int tot[3];
+        block_scan3(base, k2, k3, tot, wsum, tid);
+        const int n_run_s = tot[0], n_tall_s = tot[1] & 1023;
+        const int cnt[5] = {0, (tot[1] >> 10) & 1023, (tot[1] >> 20) & 1023, tot[2] & 1023, (tot[2] >> 10) & 1023};
+        const int pre[5] = {0, (k2 >> 10) & 1023, (k2 >> 20) & 1023, k3 & 1023, (k3 >> 10) & 1023};
+        const int tails = cnt[1] + cnt[2] + cnt[3] + cnt[4];
+        // Down list with K pieces: only the moved tails of at most p.split_max_blocks 32-row blocks are
+        // cut (p.down_splits list entries each); the higher ones, which come first, stay whole.
+        // Whether to cut at all is decided here, where the tile counts are known.  Pieces make a
+        // launch faster in two cases only (measured on the Mixtral-shaped layer from 64 to 16384
+        // tokens): when EVERY tile of the launch is a short tail (a few tokens per expert: the
+        // pieces then shorten the longest tile and fill idle CUs, -10 %), and when the launch is
+        // many rounds of tiles long (the tails at its end then finish sooner: -2 % on the
+        // 16384-token, skewed workload).  In between, a launch of one to three rounds is as long
+        // as its full tiles whatever happens to the tails, and pieces only add a round and
+        // traffic (+6 ... +50 % measured).  p.split_rule_tiles: that many m-tiles or more count as
+        // "many rounds"; 0: always cut.
+        int n_whole = tails;
+        bool cutting = which == 1 && p.down_splits > 1;
+        if (cutting) {
+            n_whole = 0;
+            for (int b = p.split_max_blocks + 1; b <= 4; ++b) n_whole += cnt[b];
+            const int others = n_run_s + n_tall_s + n_whole;
+            cutting = p.split_rule_tiles == 0 || others == 0 || others + tails - n_whole >= p.split_rule_tiles;
+            if (!cutting) n_whole = tails;
+        }
+        const int n_cut = tails - n_whole;
+        if (tid == 0) {
+            const int total = n_run_s + n_tall_s + n_whole + n_cut * (cutting ? p.down_splits : 1);
+            // Tiles per XCD run (tile_order): 32, or 8 in a launch of a few rounds next to shared experts.
+            // Theirs are the first and longest tiles of the list; in runs of 32 a few rounds of them
+            // land on two or three XCDs, which then finish last (two shared experts next to 64 routed
+            // ones, down GEMM: 1000 tokens 129 -> 95 us, 3001 tokens 174 -> 149 us).
+            const int run = !p.xcd_remap ? 0 : (Ns > 0 && total * (which == 0 ? p.nt_up : p.nt_down) <= 10 * 256 ? 8 : 32);
+            if (which == 0) { p.plan->n_gate_up = total; p.plan->n_run_up = n_run_s; p.plan->xcd_run_up = run; }
+            else { p.plan->n_down = total; p.plan->n_run_down = n_run_s; p.plan->n_split_tails = n_cut; p.plan->xcd_run_down = run; }
+        }
+        if (mine) {
+            TileDesc d;
+            d.group = group;
+            d.srow = srow;
+            const int nlisted = nfull - (tall_moved ? 1 : 0);   // full tiles listed in group order
+            for (int i = 0; i < nrun; ++i) {
+                // entry nlisted (if any) is a tail that stays with its group; it starts after all full tiles
+                const int at = i < nlisted ? i : nfull;
+                d.row0 = row_begin + at * h;
+                d.nrows = min(h, rows - at * h) + ((at == nfull - 1 && !tall_moved) ? joined : 0);
+                descs[base + i] = d;
+            }
+            if (tall_moved) {
+                const int before = k2 & 1023;   // tall tiles of the groups before this one
+                d.row0 = row_begin + (nfull - 1) * h;
+                d.nrows = h + joined;
+                descs[n_run_s + before] = d;
+            }
+            if (moved) {
+                // tails that come before this one: the higher ones, and those as high of earlier groups
+                int rank = pre[blocks];
+                for (int b = blocks + 1; b <= 4; ++b) rank += cnt[b];
+                d.row0 = row_begin + nfull * h;
+                d.nrows = tail;
+                const int tbase = n_run_s + n_tall_s;
+                if (cutting && blocks <= p.split_max_blocks) {
+                    // one entry per K piece; the pieces' partial sums are added up after the launch
+                    const int q = rank - n_whole;   // falling height: the whole ones rank first
+                    for (int sp = 0; sp < p.down_splits; ++sp) {
+                        d.srow = -2 - (q * p.down_splits + sp);
+                        descs[tbase + n_whole + q * p.down_splits + sp] = d;
+                    }
+                    p.split_tails[q].row0 = d.row0;
+                    p.split_tails[q].nrows = tail;
+                } else {
+                    descs[tbase + rank] = d;
+                }
+            }
+        }
+    }
+}
+
+}  // namespace
+}  // namespace moe
