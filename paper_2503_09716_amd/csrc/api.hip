@@ -305,7 +305,11 @@ moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     GemmConfig cfg = c->gemm;
     cfg.waves = 4;
     cfg.wave_rows = 2;
-    HIP_TRY(c, launch_ffn_gemm(false, a, cfg, st));
+    // One wave per 16 tokens x 16 experts x K piece up to 1536 of them (stage time with cold weights: 64 experts, 1
+    // token 15.6 -> 11.7 us, 256: 19.4 -> 12.4, 1024 (1024 waves): 21.0 -> 16.6, 2048: 22.8 -> 22.4; 160 experts, 1 token
+    // 29.9 -> 17.4, 512 (1280 waves): 37.7 -> 28.2, 1024: 38.6 -> 39.4); beyond, x is re-read too often.  Same bits.
+    if ((int64_t)((s.T + 15) / 16) * (rg.ep / 16) * rg.splits <= 1536) HIP_TRY(c, launch_route_small(a, st));
+    else HIP_TRY(c, launch_ffn_gemm(false, a, cfg, st));
     HIP_TRY(c, launch_route_topk(s, (const float*)(ws + L.rt_logits), rg.splits, rg.ep, bias, idx, w, logits, st));
     return MOE_OK;
 }

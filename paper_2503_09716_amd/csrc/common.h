@@ -155,6 +155,7 @@ hipError_t launch_ffn_gemm(bool gated, const GemmArgs& a, const GemmConfig& cfg,
 // the same GEMMs with one wavefront per 16 * col_blocks columns (small batches): a.n_tiles column units per
 // m-tile, m-tiles of at most 64 * halves rows; gate/up: col_blocks = 2
 hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int halves, hipStream_t st);
+hipError_t launch_route_small(const GemmArgs& a, hipStream_t st);   // the router GEMM, one wavefront per 16 tokens x 16 experts x K piece
 hipError_t ffn_gemm_init();  // one-time function attributes (dynamic LDS size)
 
 hipError_t launch_combine(const moe_shape& s, const void* y_perm, const int32_t* inv_perm, const float* w,

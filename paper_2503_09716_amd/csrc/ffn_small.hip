@@ -24,14 +24,15 @@ typedef const __attribute__((address_space(1))) bf16x8* gfrag_t;
 constexpr int SMALL_ROWS = 64;   // rows of X per wave at most: an m-tile of up to 128 rows is two units
 
 // One unit: rows r0 .. r0 + 16 * XB - 1 of tile d (nrows of the tile are valid), columns n0 .. n0 + 16 * NB - 1.
-template <bool GATED, int NB, int XB, int RING>
+// ROUTER: the gate GEMM, K piece d.group of one packed matrix, fp32 partial logits.
+template <bool GATED, int NB, int XB, int RING, bool ROUTER = false>
 __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, const int r0, const int n0, const int lane) {
     constexpr int WQ = GATED ? 2 * NB : NB;   // W blocks per sub-tile
     const int rl = lane & 15, g = lane >> 4;
-    const bool shared = d.srow >= 0;
+    const bool shared = !ROUTER && d.srow >= 0;
     const int nseg = !GATED && shared ? p.nseg_shared : 1;
     const int KT = p.K >> 5;
-    const bool a_tiled = ((shared ? p.a_tiled >> 1 : p.a_tiled) & 1) != 0;
+    const bool a_tiled = !ROUTER && ((shared ? p.a_tiled >> 1 : p.a_tiled) & 1) != 0;
     const uint32_t xstep = a_tiled ? 1024 : 64;
     const size_t a_seg_stride = (size_t)p.t_pad * (size_t)p.K * 2;
     // per-lane byte offsets: row rl of each block, logical 16-byte piece g
@@ -40,7 +41,7 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
     for (int i = 0; i < XB; ++i) {
         int grow = d.row0 + min(r0 + i * 16 + rl, d.nrows - 1);   // padded rows re-read the last valid row
         if (!a_tiled) {
-            if (!shared && p.row_token) grow = p.row_token[grow];
+            if (!ROUTER && !shared && p.row_token) grow = p.row_token[grow];
             xoff[i] = (uint32_t)grow * (uint32_t)p.lda_bytes + (uint32_t)(g * 16);
         } else {
             const int rr = grow & 15;
@@ -56,8 +57,8 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
         for (int i = 0; i < XB; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
     bf16x8 wf[RING][WQ], xf[RING][XB];
 
-    gchar_t xb = (gchar_t)(shared ? p.a_shared : p.a_routed);
-    gchar_t wa = (gchar_t)p.w_a[d.group];
+    gchar_t xb = (gchar_t)(shared ? p.a_shared : p.a_routed) + (ROUTER ? (size_t)d.group * (size_t)p.K * 2 : 0);
+    gchar_t wa = ROUTER ? (gchar_t)p.w_uniform + (size_t)d.group * (size_t)p.w_uniform_stride : (gchar_t)p.w_a[d.group];
     gchar_t const wb = GATED ? (gchar_t)p.w_b[d.group] : (gchar_t)nullptr;
     auto load = [&](const int u, gchar_t x, gchar_t w, const int ks) __attribute__((always_inline)) {
 #pragma unroll
@@ -139,7 +140,7 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
         }
     } else {
         // lane: output column rl of W block j, rows 4g .. 4g+3 of X block i
-        const bool f32 = ((shared ? p.out_fp32 >> 1 : p.out_fp32) & 1) != 0;
+        const bool f32 = ROUTER || ((shared ? p.out_fp32 >> 1 : p.out_fp32) & 1) != 0;
         char* const out = shared ? p.out_shared : p.out_routed;
 #pragma unroll
         for (int i = 0; i < XB; ++i)
@@ -147,7 +148,7 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
             for (int q = 0; q < 4; ++q) {
                 const int r = r0 + i * 16 + g * 4 + q;
                 if (r >= d.nrows) continue;
-                const size_t at = (size_t)(d.row0 + r) * (size_t)p.N + (size_t)(n0 + rl);
+                const size_t at = (size_t)((ROUTER ? d.group * p.split_rows : 0) + d.row0 + r) * (size_t)p.N + (size_t)(n0 + rl);
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
                     if (f32) reinterpret_cast<float*>(out)[at + j * 16] = acc[j][i][q];
@@ -176,7 +177,26 @@ __global__ __launch_bounds__(64, 2) void ffn_small_kernel(const GemmArgs p, cons
     }
 }
 
+// Router GEMM of a small batch: one wave per 16 tokens, 16 experts and K piece.  The tile routine has one
+// workgroup per K piece and 128 tokens, four in all for a small batch, each of which reads a quarter of
+// the gate matrix by itself.
+__global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
+    const int cols = p.N >> 4, rows = (p.T + 15) >> 4;
+    const int nb = blockIdx.x % cols, m = (blockIdx.x / cols) % rows, s = blockIdx.x / (cols * rows);
+    TileDesc d;
+    d.group = s;
+    d.row0 = m * 16;
+    d.nrows = min(16, p.T - d.row0);
+    d.srow = -1;
+    small_unit<false, 1, 1, 16, true>(p, d, 0, nb * 16, threadIdx.x);
+}
+
 }  // namespace
+
+hipError_t launch_route_small(const GemmArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(route_small_kernel, dim3((unsigned)((a.N / 16) * ((a.T + 15) / 16) * a.uniform_splits)), dim3(64), 0, st, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int halves, hipStream_t st) {
     // one wave per workgroup: four to a workgroup leave CUs idle at the sizes this is for (1 token: 22 -> 31 us)

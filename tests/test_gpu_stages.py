@@ -8,6 +8,7 @@ import torch
 
 from oracle import moe_oracle as orc
 import parity as P
+from paper_2503_09716_amd import make_shape
 from workloads import get_config, make_layer_inputs, normal_bf16, scaled_config, torch_bf16_to_u16
 
 pytestmark = pytest.mark.gpu
@@ -135,6 +136,26 @@ def test_route_random_shapes(moe, seed):
     say(P.compare_routing(idx.cpu().numpy(), w.cpu().numpy(), ref, k, cfg.renormalize, cfg.routed_scale))
     err = np.abs(logits.cpu().numpy() - ref["logits"]).max()
     assert err < 5e-6, err
+
+
+@pytest.mark.parametrize("T,H,E,k", [(1, 128, 17, 4), (15, 1024, 64, 6), (16, 1088, 160, 8), (17, 2048, 33, 6), (40, 3520, 256, 16),
+                                     (513, 1024, 160, 6), (1536, 1024, 64, 6), (1537, 1024, 64, 6)])
+def test_route_small_batch_gives_a_large_batch_s_logits(moe, T, H, E, k):
+    """The router GEMM of a small batch (one wave per 16 tokens, 16 experts and K piece) and the tile routine of a large
+    one add a logit's products in the same order: rows computed alone equal the same rows in a batch of 2048 and more."""
+    cfg = scaled_config("C4", T=T + 2048, H=H, E=E, top_k=k, F=64, num_shared=0)
+    li = make_layer_inputs(cfg, device="cuda")
+    got = []
+    for rows in (T, T + 2048):
+        shape = make_shape(rows, H, 64, E, k, 0, False)
+        idx = torch.empty((rows, k), dtype=torch.int32, device="cuda")
+        w = torch.empty((rows, k), dtype=torch.float32, device="cuda")
+        lg = torch.full((rows, E), float("nan"), dtype=torch.float32, device="cuda")
+        moe.route(shape, li.x[:rows].contiguous(), li.wg, li.bias, idx, w, lg, moe.new_workspace(shape))
+        got.append((idx[:T], w[:T], lg[:T]))
+    torch.cuda.synchronize()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
 
 
 def random_routing(rng, T, E, k, skew=None):
