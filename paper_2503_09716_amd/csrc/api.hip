@@ -382,6 +382,7 @@ struct FfnSetup {
     SmallRule sm;
     int mtiles_up, mtiles_down;   // m-tiles each list can have at most
     int group_m_up, group_m_down;
+    bool nt;
 };
 
 FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets, char* ws, const FfnPass& ps) {
@@ -430,9 +431,14 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const double per_expert = (double)s.T * s.top_k / ((double)s.E * 256);
     int tall = c->gemm.tall_tiles >= 0 ? c->gemm.tall_tiles : (per_expert <= 8.0 ? 2 : 1);
     if (!tall_kernel) tall = 0;
+    // Non-temporal loads of weights that one tile reads: only if the layer's weights exceed the memory-side cache
+    // (256 MB); a small layer called again and again finds its weights there (tiny layer, 25 MB, 256 tokens: 31.5 us
+    // without, 34.5 with them).
+    const bool nt = (int64_t)(s.E + s.num_shared) * 6 * s.H * s.F > ((int64_t)256 << 20);
     FfnSetup f;
+    f.nt = nt;
     f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
-                      nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, ps.e_lo, ps.e_hi, ps.shared_on,
+                      nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, nt, ps.e_lo, ps.e_hi, ps.shared_on,
                       dsp, 4, split_rule_tiles, tall, tall, (SplitTail*)(ws + L.split_tails), (PlanHeader*)(ws + L.plan),
                       (TileDesc*)(ws + L.descs_up), (TileDesc*)(ws + L.descs_down)};
     f.sm = sm;
@@ -490,7 +496,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool plann
         StageTimer tm(c, st, MOE_STAGE_FFN_GATE_UP);
         if (sm.up) {
             a.n_tiles = s.F / 32;
-            HIP_TRY(c, launch_ffn_small(true, a, 2, sm.halves, st));
+            HIP_TRY(c, launch_ffn_small(true, a, 2, sm.halves, f.nt, st));
         } else {
             HIP_TRY(c, launch_ffn_gemm(true, a, c->gemm, st));
         }
@@ -521,7 +527,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool plann
         StageTimer tm(c, st, MOE_STAGE_FFN_DOWN);
         if (sm.down) {
             a.n_tiles = s.H / (16 * sm.down_cols);
-            HIP_TRY(c, launch_ffn_small(false, a, sm.down_cols, sm.halves, st));
+            HIP_TRY(c, launch_ffn_small(false, a, sm.down_cols, sm.halves, f.nt, st));
         } else {
             HIP_TRY(c, launch_ffn_gemm(false, a, c->gemm, st));
         }

@@ -21,10 +21,11 @@ __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_
 //   shared group : group = E + s,     row0 = first token,  srow = s * t_pad (row offset inside the shared region of h)
 //   K-split piece of a short tail of the down GEMM: group = expert id, row0 = permuted row,
 //                  srow = -2 - (q * splits + s) for piece s of the q-th split tail
+constexpr int TILE_ONCE = 1 << 16;
 struct TileDesc {
     int32_t group;
     int32_t row0;
-    int32_t nrows;
+    int32_t nrows;     // in a list: | TILE_ONCE where no other tile reads the same W panel at about the same time
     int32_t srow;
 };
 
@@ -86,6 +87,7 @@ struct PlanArgs {
     int32_t choose_up, choose_down;     // 1: a lower cap (down to 128) may be chosen from the row counts
     int32_t nt_up, nt_down;             // tiles along N
     int32_t tails_last_up, tails_last_down, small_tiles, xcd_remap;
+    int32_t mark_once;                  // 1: TILE_ONCE marks are wanted
     int32_t e_lo, e_hi, shared_on;      // the lists cover routed experts [e_lo, e_hi) and, if shared_on, the shared experts
     int32_t down_splits, split_max_blocks, split_rule_tiles, tall_up, tall_down;
     SplitTail* split_tails;
@@ -153,8 +155,8 @@ hipError_t launch_split_tail_reduce(const moe_shape& s, const PlanHeader* plan, 
                                     int splits, void* y_perm, bool y_fp32, hipStream_t st);
 hipError_t launch_ffn_gemm(bool gated, const GemmArgs& a, const GemmConfig& cfg, hipStream_t st);
 // the same GEMMs with one wavefront per 16 * col_blocks columns (small batches): a.n_tiles column units per
-// m-tile, m-tiles of at most 64 * halves rows; gate/up: col_blocks = 2
-hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int halves, hipStream_t st);
+// m-tile, m-tiles of at most 64 * halves rows; gate/up: col_blocks = 2; nt: non-temporal loads of W
+hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int halves, bool nt, hipStream_t st);
 hipError_t launch_route_small(const GemmArgs& a, hipStream_t st);   // the router GEMM, one wavefront per 16 tokens x 16 experts x K piece
 hipError_t ffn_gemm_init();  // one-time function attributes (dynamic LDS size)
 

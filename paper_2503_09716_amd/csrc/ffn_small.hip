@@ -7,7 +7,9 @@
 // whole of K, for up to 64 rows of X.  W goes straight from memory into registers - a 16 x 32 block of
 // the packed layout is one 1 KiB load, already in operand order up to a lane permutation - through
 // a ring of RING sub-tiles per wave (about 32 KiB in flight), with no LDS and no barrier.  X is read the
-// same way; its rows are few and come from L2.
+// same way; its rows are few and come from L2.  W is read once; in a layer that no
+// cache can hold it is marked non-temporal, which is worth a tenth (8x7B, 8 tokens: gate/up 297 -> 267 us, down 146 -> 128 = 7.3 TB/s; 64 experts, 16 tokens: 107 -> 98,
+// 53 -> 47).
 //
 // Every output element is one chain of v_mfma_f32_16x16x32_bf16 over K in ascending order with the
 // operands in the same roles as in the tile routine, so both give the same bits.
@@ -25,7 +27,8 @@ constexpr int SMALL_ROWS = 64;   // rows of X per wave at most: an m-tile of up 
 
 // One unit: rows r0 .. r0 + 16 * XB - 1 of tile d (nrows of the tile are valid), columns n0 .. n0 + 16 * NB - 1.
 // ROUTER: the gate GEMM, K piece d.group of one packed matrix, fp32 partial logits.
-template <bool GATED, int NB, int XB, int RING, bool ROUTER = false>
+// NT: W loads are non-temporal.
+template <bool GATED, int NB, int XB, int RING, bool NT, bool ROUTER = false>
 __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, const int r0, const int n0, const int lane) {
     constexpr int WQ = GATED ? 2 * NB : NB;   // W blocks per sub-tile
     const int rl = lane & 15, g = lane >> 4;
@@ -65,7 +68,7 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
         for (int j = 0; j < WQ; ++j) {
             gchar_t base = GATED && j >= NB ? wb : w;
             const uint32_t off = woff + (uint32_t)((GATED && j >= NB ? j - NB : j) * p.kt_w + ks) * 1024u;
-            wf[u][j] = *(gfrag_t)(base + off);
+            wf[u][j] = NT ? __builtin_nontemporal_load((gfrag_t)(base + off)) : *(gfrag_t)(base + off);
         }
 #pragma unroll
         for (int i = 0; i < XB; ++i) xf[u][i] = *(gfrag_t)(x + (xoff[i] + (uint32_t)ks * xstep));
@@ -160,20 +163,21 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
 
 // Units in the order: columns fastest, then the 64-row parts of an m-tile (`halves` of them side by
 // side; a unit takes every halves-th part, whatever the tile's height), then m-tiles.
-template <bool GATED, int NB>
+template <bool GATED, int NB, bool NT>
 __global__ __launch_bounds__(64, 2) void ffn_small_kernel(const GemmArgs p, const int halves) {
     const int lane = threadIdx.x;
     const int per = p.n_tiles * halves;
     const int mt = blockIdx.x / per;
     if (mt >= (GATED ? p.plan->n_gate_up : p.plan->n_down)) return;
     const int rem = blockIdx.x - mt * per, half = rem / p.n_tiles;
-    const TileDesc d = p.descs[mt];
+    TileDesc d = p.descs[mt];
+    d.nrows &= TILE_ONCE - 1;
     const int n0 = (rem - half * p.n_tiles) * 16 * NB;
     for (int r0 = half * SMALL_ROWS; r0 < d.nrows; r0 += halves * SMALL_ROWS) {
         const int blocks = (min(d.nrows - r0, SMALL_ROWS) + 15) >> 4;   // wave-uniform
-        if (blocks > 2) small_unit<GATED, NB, 4, GATED ? 4 : (NB == 2 ? 5 : 6)>(p, d, r0, n0, lane);
-        else if (blocks > 1) small_unit<GATED, NB, 2, GATED ? 6 : (NB == 2 ? 7 : 8)>(p, d, r0, n0, lane);
-        else small_unit<GATED, NB, 1, GATED ? 8 : (NB == 2 ? 8 : 16)>(p, d, r0, n0, lane);
+        if (blocks > 2) small_unit<GATED, NB, 4, GATED ? 4 : (NB == 2 ? 5 : 6), NT>(p, d, r0, n0, lane);
+        else if (blocks > 1) small_unit<GATED, NB, 2, GATED ? 6 : (NB == 2 ? 7 : 8), NT>(p, d, r0, n0, lane);
+        else small_unit<GATED, NB, 1, GATED ? 8 : (NB == 2 ? 8 : 16), NT>(p, d, r0, n0, lane);
     }
 }
 
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
     d.row0 = m * 16;
     d.nrows = min(16, p.T - d.row0);
     d.srow = -1;
-    small_unit<false, 1, 1, 16, true>(p, d, 0, nb * 16, threadIdx.x);
+    small_unit<false, 1, 1, 16, false, true>(p, d, 0, nb * 16, threadIdx.x);
 }
 
 }  // namespace
@@ -198,12 +202,18 @@ hipError_t launch_route_small(const GemmArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int halves, hipStream_t st) {
+hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int halves, bool nt, hipStream_t st) {
     // one wave per workgroup: four to a workgroup leave CUs idle at the sizes this is for (1 token: 22 -> 31 us)
     const dim3 grid((unsigned)a.max_mtiles * (unsigned)(a.n_tiles * halves)), block(64);
-    if (gated) hipLaunchKernelGGL((ffn_small_kernel<true, 2>), grid, block, 0, st, a, halves);
-    else if (col_blocks == 2) hipLaunchKernelGGL((ffn_small_kernel<false, 2>), grid, block, 0, st, a, halves);
-    else hipLaunchKernelGGL((ffn_small_kernel<false, 1>), grid, block, 0, st, a, halves);
+#define SMALL(G_, NB_)                                                                                   \
+    do {                                                                                                 \
+        if (nt) hipLaunchKernelGGL((ffn_small_kernel<G_, NB_, true>), grid, block, 0, st, a, halves);    \
+        else hipLaunchKernelGGL((ffn_small_kernel<G_, NB_, false>), grid, block, 0, st, a, halves);      \
+    } while (0)
+    if (gated) SMALL(true, 2);
+    else if (col_blocks == 2) SMALL(false, 2);
+    else SMALL(false, 1);
+#undef SMALL
     return hipGetLastError();
 }
 

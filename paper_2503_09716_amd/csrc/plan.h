@@ -52,8 +52,8 @@ __device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, cons
     c.even = even && c.tail > 0 && (c.nfull == 1 || c.nfull == 2);
     if (c.even) {
         const int m = c.nfull + 1;
-        c.h = ((rows + m - 1) / m + 31) & ~31;   // (m - 1) * h < rows: rows > tm * (m - 1) >= 128 * (m - 1)
-        c.nfull = rows / c.h;
+        c.h = ((m == 2 ? (rows + 1) >> 1 : (rows + 2) / 3) + 31) & ~31;
+        c.nfull = m - (rows < m * c.h);   // (m - 1) * h < rows: rows > tm * (m - 1) >= 128 * (m - 1)
         c.tail = rows - c.nfull * c.h;
     }
     return c;
@@ -245,18 +245,19 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
             TileDesc d;
             d.group = group;
             d.srow = srow;
+            const int once = p.mark_once && nfull + (blocks > 0) == 1 ? TILE_ONCE : 0;
             const int nlisted = nfull - (tall_moved ? 1 : 0);   // full tiles listed in group order
             for (int i = 0; i < nrun; ++i) {
                 // entry nlisted (if any) is a tail that stays with its group; it starts after all full tiles
                 const int at = i < nlisted ? i : nfull;
                 d.row0 = row_begin + at * h;
-                d.nrows = min(h, rows - at * h) + ((at == nfull - 1 && !tall_moved) ? joined : 0);
+                d.nrows = (min(h, rows - at * h) + ((at == nfull - 1 && !tall_moved) ? joined : 0)) | once;
                 descs[base + i] = d;
             }
             if (tall_moved) {
                 const int before = k2 & 1023;   // tall tiles of the groups before this one
                 d.row0 = row_begin + (nfull - 1) * h;
-                d.nrows = h + joined;
+                d.nrows = (h + joined) | once;
                 descs[n_run_s + before] = d;
             }
             if (moved) {
@@ -264,7 +265,7 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
                 int rank = pre[blocks];
                 for (int b = blocks + 1; b <= 4; ++b) rank += cnt[b];
                 d.row0 = row_begin + nfull * h;
-                d.nrows = tail;
+                d.nrows = tail | (p.mark_once ? TILE_ONCE : 0);   // runs after the group's other tiles, if there are any
                 const int tbase = n_run_s + n_tall_s;
                 if (cutting && blocks <= p.split_max_blocks) {
                     // one entry per K piece; the pieces' partial sums are added up after the launch

@@ -587,7 +587,7 @@ def test_accumulate_then_chunked_layer(moe):
 
 
 SMALL_CASES = [   # T, H, F, E, k, shared: edges of 16 / 32 / 64 rows, K shorter than, equal to and past a wave's ring of sub-tiles
-    (1, 64, 64, 1, 1, 0), (1, 2048, 1408, 64, 6, 2), (2, 512, 1024, 8, 2, 0), (15, 576, 320, 5, 4, 1), (16, 512, 512, 4, 4, 2),
+    (1, 64, 64, 1, 1, 0), (1, 2048, 1408, 64, 6, 2), (48, 2048, 1408, 64, 6, 2), (2, 512, 1024, 8, 2, 0), (15, 576, 320, 5, 4, 1), (16, 512, 512, 4, 4, 2),
     (17, 320, 832, 6, 3, 3), (32, 256, 448, 20, 6, 2), (33, 448, 256, 4, 2, 1), (63, 128, 192, 3, 3, 0), (64, 1024, 576, 40, 8, 2),
     (65, 512, 384, 4, 2, 1), (128, 512, 1024, 8, 2, 0), (129, 256, 512, 4, 4, 0), (200, 384, 256, 3, 1, 2), (256, 512, 1024, 8, 2, 0),
 ]
