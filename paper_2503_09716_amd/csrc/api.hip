@@ -23,9 +23,6 @@ constexpr int TABLE_SLOTS = 8;
 constexpr int MAX_GROUPS = 256;
 constexpr int PROF_MAX = 8192;
 constexpr int MAX_SLOTS = 8;
-// Streamed weights are copied on two streams, matrix by matrix in turn: while one engine sets up its next copy
-// the other keeps the host link busy (66 experts of 17 MB in matrices of 5.8 MB: 22.2 -> 20.6 ms, 51 -> 55 GB/s).
-constexpr int COPY_STREAMS = 2;
 
 struct ProfRec {
     int stage;
@@ -54,8 +51,8 @@ struct moe_ctx {
     hipStream_t tab_stream = nullptr;     // stream of the current table's upload
     std::vector<const void*> tab_shadow;  // contents of slot tab_cur
     // streamed weights: copy stream, slot hand-over events, pinned copy of expert_offsets, counters
-    hipStream_t copy_stream[COPY_STREAMS] = {nullptr};
-    hipEvent_t slot_ready[MAX_SLOTS][COPY_STREAMS] = {};
+    hipStream_t copy_stream = nullptr;
+    hipEvent_t slot_ready[MAX_SLOTS] = {nullptr};
     hipEvent_t slot_free[MAX_SLOTS] = {nullptr};
     int32_t* h_offsets = nullptr;
     uint64_t stream_bytes = 0;
@@ -337,13 +334,13 @@ int pick_group_m(const moe_ctx* c, const moe_shape& s, int tm) {
 
 // Which of the two GEMMs of a small batch run one wavefront per 16 or 32 output columns (ffn_small.hip).
 // Measured with cold weights against the tile routine, us (tile -> small):
-//   gate/up  64 experts top-6 + 2 shared, F = 1408: 1 token 27.8 -> 21.3, 4: 54 -> 49, 16: 103 -> 97, 32: 115 -> 120;
-//            8 experts top-2, F = 14336: 4: 222 -> 225, 16: 300 -> 302, 32: 301 -> 308;
-//            160 experts top-6 + 2 shared, F = 1536: 1: 74 -> 47, 16: 193 -> 205, 32: 281 -> 294;
+//   gate/up  64 experts top-6 + 2 shared, F = 1408: 1 token 29 -> 22, 4: 57 -> 54, 16: 111 -> 108, 32: 124 -> 132;
+//            8 experts top-2, F = 14336: 1: 92 -> 90, 8: 312 -> 295, 32: 335 -> 337;
+//            160 experts top-6 + 2 shared, F = 1536: 1: 77 -> 52, 32: 309 -> 317;
 //            8 experts top-2, H = 512, F = 1024: 16: 12.1 -> 9.2, 128: 13.1 -> 12.3, 256: 14.6 -> 15.3
-//   down     (default cache policy in both) 64 experts: 1: 37 -> 15, 4: 44 -> 28, 16: 62 -> 52, 32: 81 -> 68, 64: 85 -> 76;
-//            8 experts: 1: 66 -> 47, 8: 158 -> 145, 32: 177 -> 166, 64: 181 -> 175 (32 columns), 128: 186 -> 310;
-//            160 experts: 1: 43 -> 30, 32: 160 -> 161;  H = 512: 16: 16.2 -> 8.4, 128: 17.0 -> 11.2, 256: 17.9 -> 12.3
+//   down     the same: 1: 37 -> 15, 4: 44 -> 28, 16: 62 -> 52, 32: 81 -> 68, 64: 85 -> 76;
+//            1: 66 -> 47, 8: 158 -> 145, 32: 177 -> 166, 64: 181 -> 175 (32 columns), 128: 186 -> 310;
+//            1: 43 -> 30, 32: 160 -> 161;  16: 16.2 -> 8.4, 128: 17.0 -> 11.2, 256: 17.9 -> 12.3
 // So: the down GEMM up to 64 tokens, the gate/up GEMM up to 16 (every group one block of 16 rows; X is
 // re-read by every wave, which costs more than the idle CUs from then on), and both somewhat further
 // when the tile routine would have tiles for a quarter of the CUs at most.
@@ -632,14 +629,11 @@ moe_status moe_create(moe_ctx** out, int device) {
     bool ok = ffn_gemm_init() == hipSuccess;
     ok = ok && hipGetSymbolAddress((void**)&c->static_ws, HIP_SYMBOL(scratch)) == hipSuccess && c->static_ws != nullptr &&
          ((uintptr_t)c->static_ws & 255) == 0;
-    for (int i = 0; i < COPY_STREAMS && ok; ++i)
-        ok = hipStreamCreateWithFlags(&c->copy_stream[i], hipStreamNonBlocking) == hipSuccess;
-    ok = ok && hipHostMalloc((void**)&c->h_offsets, (MAX_GROUPS + 1) * sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
-    for (int i = 0; i < MAX_SLOTS && ok; ++i) {
-        ok = hipEventCreateWithFlags(&c->slot_free[i], hipEventDisableTiming) == hipSuccess;
-        for (int j = 0; j < COPY_STREAMS && ok; ++j)
-            ok = hipEventCreateWithFlags(&c->slot_ready[i][j], hipEventDisableTiming) == hipSuccess;
-    }
+    ok = ok && hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking) == hipSuccess &&
+         hipHostMalloc((void**)&c->h_offsets, (MAX_GROUPS + 1) * sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
+    for (int i = 0; i < MAX_SLOTS && ok; ++i)
+        ok = hipEventCreateWithFlags(&c->slot_ready[i], hipEventDisableTiming) == hipSuccess &&
+             hipEventCreateWithFlags(&c->slot_free[i], hipEventDisableTiming) == hipSuccess;
     for (int i = 0; i < TABLE_SLOTS && ok; ++i) {
         ok = hipMalloc((void**)&c->d_tab[i], 3 * MAX_GROUPS * sizeof(void*)) == hipSuccess &&
              hipHostMalloc((void**)&c->h_tab[i], 3 * MAX_GROUPS * sizeof(void*), hipHostMallocDefault) == hipSuccess &&
@@ -660,12 +654,10 @@ void moe_destroy(moe_ctx* c) {
         if (c->tab_done[i]) (void)hipEventDestroy(c->tab_done[i]);
     }
     for (int i = 0; i < MAX_SLOTS; ++i) {
-        for (hipEvent_t e : c->slot_ready[i])
-            if (e) (void)hipEventDestroy(e);
+        if (c->slot_ready[i]) (void)hipEventDestroy(c->slot_ready[i]);
         if (c->slot_free[i]) (void)hipEventDestroy(c->slot_free[i]);
     }
-    for (hipStream_t cs : c->copy_stream)
-        if (cs) (void)hipStreamDestroy(cs);
+    if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
     if (c->h_offsets) (void)hipHostFree(c->h_offsets);
     for (auto& r : c->recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
     for (auto e : c->pool) (void)hipEventDestroy(e);
@@ -901,13 +893,11 @@ moe_status moe_layer_streamed(moe_ctx* c, const moe_shape* s, const void* x, con
     if (Ns > 0) groups.push_back({E, E, true});
 
     std::vector<const void*> t1(E + Ns), t3(E + Ns), t2(E + Ns);
-    unsigned copies = 0;
     for (size_t g = 0; g < groups.size(); ++g) {
         const Group& G = groups[g];
         const int slot = (int)(g % (size_t)num_slots);
         char* base = (char*)slots + (size_t)slot * slot_bytes;
-        if (g >= (size_t)num_slots)
-            for (hipStream_t cs : c->copy_stream) HIP_TRY(c, hipStreamWaitEvent(cs, c->slot_free[slot], 0));
+        if (g >= (size_t)num_slots) HIP_TRY(c, hipStreamWaitEvent(c->copy_stream, c->slot_free[slot], 0));
         // every table entry must be a valid pointer; experts outside the group get no tiles
         for (int e = 0; e < E + Ns; ++e) { t1[e] = base; t3[e] = base; t2[e] = base; }
         int member = 0, mt = 0;
@@ -916,18 +906,16 @@ moe_status moe_layer_streamed(moe_ctx* c, const moe_shape* s, const void* x, con
             const int rows = e < E ? c->h_offsets[e + 1] - c->h_offsets[e] : s->T;
             if (rows == 0) continue;
             char* dst = base + (size_t)member * expert_bytes;
-            const void* const src[3] = {hw1[e], hw3[e], hw2[e]};
-            for (int i = 0; i < 3; ++i, ++copies)
-                HIP_TRY(c, hipMemcpyAsync(dst + i * mat_bytes, src[i], mat_bytes, hipMemcpyHostToDevice, c->copy_stream[copies % COPY_STREAMS]));
+            HIP_TRY(c, hipMemcpyAsync(dst, hw1[e], mat_bytes, hipMemcpyHostToDevice, c->copy_stream));
+            HIP_TRY(c, hipMemcpyAsync(dst + mat_bytes, hw3[e], mat_bytes, hipMemcpyHostToDevice, c->copy_stream));
+            HIP_TRY(c, hipMemcpyAsync(dst + 2 * mat_bytes, hw2[e], mat_bytes, hipMemcpyHostToDevice, c->copy_stream));
             t1[e] = dst; t3[e] = dst + mat_bytes; t2[e] = dst + 2 * mat_bytes;
             c->stream_bytes += expert_bytes;
             mt += (rows + 127) / 128;
             ++member;
         }
-        for (int i = 0; i < COPY_STREAMS; ++i) {
-            HIP_TRY(c, hipEventRecord(c->slot_ready[slot][i], c->copy_stream[i]));
-            HIP_TRY(c, hipStreamWaitEvent(hs, c->slot_ready[slot][i], 0));
-        }
+        HIP_TRY(c, hipEventRecord(c->slot_ready[slot], c->copy_stream));
+        HIP_TRY(c, hipStreamWaitEvent(hs, c->slot_ready[slot], 0));
         void** tab = nullptr;
         if (moe_status st = weight_table(c, E + Ns, t1.data(), t3.data(), t2.data(), hs, &tab)) return st;
         const FfnPass pass{G.shared ? 0 : G.lo, G.shared ? 0 : G.hi, G.shared, mt, G.shared ? (s->T + 127) / 128 : mt};
