@@ -334,13 +334,13 @@ int pick_group_m(const moe_ctx* c, const moe_shape& s, int tm) {
 
 // Which of the two GEMMs of a small batch run one wavefront per 16 or 32 output columns (ffn_small.hip).
 // Measured with cold weights against the tile routine, us (tile -> small):
-//   gate/up  64 experts top-6 + 2 shared, F = 1408: 1 token 29 -> 22, 4: 57 -> 54, 16: 111 -> 108, 32: 124 -> 132;
-//            8 experts top-2, F = 14336: 1: 92 -> 90, 8: 312 -> 295, 32: 335 -> 337;
-//            160 experts top-6 + 2 shared, F = 1536: 1: 77 -> 52, 32: 309 -> 317;
+//   gate/up  64 experts top-6 + 2 shared, F = 1408: 1 token 27.8 -> 21.3, 4: 54 -> 49, 16: 103 -> 97, 32: 115 -> 120;
+//            8 experts top-2, F = 14336: 4: 222 -> 225, 16: 300 -> 302, 32: 301 -> 308;
+//            160 experts top-6 + 2 shared, F = 1536: 1: 74 -> 47, 16: 193 -> 205, 32: 281 -> 294;
 //            8 experts top-2, H = 512, F = 1024: 16: 12.1 -> 9.2, 128: 13.1 -> 12.3, 256: 14.6 -> 15.3
-//   down     the same: 1: 37 -> 15, 4: 44 -> 28, 16: 62 -> 52, 32: 81 -> 68, 64: 85 -> 76;
-//            1: 66 -> 47, 8: 158 -> 145, 32: 177 -> 166, 64: 181 -> 175 (32 columns), 128: 186 -> 310;
-//            1: 43 -> 30, 32: 160 -> 161;  16: 16.2 -> 8.4, 128: 17.0 -> 11.2, 256: 17.9 -> 12.3
+//   down     (default cache policy in both) 64 experts: 1: 37 -> 15, 4: 44 -> 28, 16: 62 -> 52, 32: 81 -> 68, 64: 85 -> 76;
+//            8 experts: 1: 66 -> 47, 8: 158 -> 145, 32: 177 -> 166, 64: 181 -> 175 (32 columns), 128: 186 -> 310;
+//            160 experts: 1: 43 -> 30, 32: 160 -> 161;  H = 512: 16: 16.2 -> 8.4, 128: 17.0 -> 11.2, 256: 17.9 -> 12.3
 // So: the down GEMM up to 64 tokens, the gate/up GEMM up to 16 (every group one block of 16 rows; X is
 // re-read by every wave, which costs more than the idle CUs from then on), and both somewhat further
 // when the tile routine would have tiles for a quarter of the CUs at most.
