@@ -315,11 +315,11 @@ moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* 
 }
 
 // Whether the plan kernel may choose tiles lower than 256 rows for a launch: only where that can
-// fill idle CUs, in launches of at most four rounds of 256-row tiles on average (with more rounds
-// the tallest tiles win: 128-row tiles run at about 0.75 of their rate).
+// fill idle CUs, in launches of at most two rounds of 256-row tiles on average (with more rounds
+// the tallest tiles win: 128-row tiles run at about 0.75 of their rate; and choosing takes the plan 4 us).
 int may_choose_rows(const moe_shape& s, int n_tiles, int nseg) {
     const double tiles = ((double)s.T * s.top_k / 256 + 0.5 * s.E + (double)nseg * ((s.T + 255) / 256)) * n_tiles;
-    return tiles <= 4 * 256.0;
+    return tiles <= 2 * 256.0;
 }
 
 // m-tiles swept together before moving along n.  Tiles of one expert share W panels, so runs

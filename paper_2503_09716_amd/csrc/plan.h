@@ -42,10 +42,16 @@ struct GroupCut {
     int h, nfull, tail, joined;
     bool even;
 };
+__device__ __forceinline__ int div_small(const int a, const int b) {   // a / b for 0 <= a < 2^24, b >= 32: a short division
+    int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+    if (q * b > a) --q;
+    if ((q + 1) * b <= a) ++q;
+    return q;
+}
 __device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, const bool tall, const bool even = true) {
     GroupCut c;
     c.h = tm;
-    c.nfull = rows / tm;
+    c.nfull = rows < (1 << 24) ? div_small(rows, tm) : rows / tm;
     c.tail = rows - c.nfull * tm;
     c.joined = tall && tm == 256 && c.nfull > 0 && c.tail <= PLAN_MAX_ROWS - 256 ? c.tail : 0;
     c.tail -= c.joined;
@@ -74,8 +80,7 @@ __device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, cons
 constexpr int PLAN_CAPS = 5;
 __device__ constexpr int plan_cap(const int c) { return 256 - 32 * c; }
 
-template <int TM>
-__device__ __forceinline__ float list_cost(const int* rows, const int ngroups, const int nseg0, const bool tall,
+__device__ __forceinline__ float list_cost(const int* rows, const int ngroups, const int nseg0, const int tm, const bool tall,
                                            const int n_tiles, const int lane) {
     // n: tiles; alone: tiles that are their group's only one; sum: rows; longest: highest tile (shared experts
     // of the down GEMM walk nseg0 segments)
@@ -84,7 +89,7 @@ __device__ __forceinline__ float list_cost(const int* rows, const int ngroups, c
     for (int g = lane; g < ngroups; g += 64) {
         const int r = rows[g];
         if (r == 0) continue;
-        const GroupCut c = cut_group(r, TM, tall);
+        const GroupCut c = cut_group(r, tm, tall);
         const int m = c.nfull + (c.tail > 0);
         const int seg = g == 0 ? nseg0 : 1;
         n_alone += m + (m == 1 ? 1 << 16 : 0);
@@ -151,12 +156,8 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
             const int groups = which == 0 ? ngroups : (Ns > 0 ? E + 1 : E);
             const int nseg0 = which == 1 && Ns > 1 ? Ns : 1, nt = which == 0 ? p.nt_up : p.nt_down;
             const bool tall = (which == 0 ? p.tall_up : p.tall_down) != 0;
-            float cost;
-            if (c == 0) cost = list_cost<plan_cap(0)>(group_rows, groups, nseg0, tall, nt, lane);
-            else if (c == 1) cost = list_cost<plan_cap(1)>(group_rows, groups, nseg0, tall, nt, lane);
-            else if (c == 2) cost = list_cost<plan_cap(2)>(group_rows, groups, nseg0, tall, nt, lane);
-            else if (c == 3) cost = list_cost<plan_cap(3)>(group_rows, groups, nseg0, tall, nt, lane);
-            else cost = list_cost<plan_cap(4)>(group_rows, groups, nseg0, tall, nt, lane);
+            // (one copy of the code for all caps: what this costs is mostly fetching its instructions)
+            const float cost = list_cost(group_rows, groups, nseg0, plan_cap(c), tall, nt, lane);
             if (lane == 0) cap_cost[which][c] = cost;
         }
         __syncthreads();
