@@ -21,11 +21,12 @@ __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_
 //   shared group : group = E + s,     row0 = first token,  srow = s * t_pad (row offset inside the shared region of h)
 //   K-split piece of a short tail of the down GEMM: group = expert id, row0 = permuted row,
 //                  srow = -2 - (q * splits + s) for piece s of the q-th split tail
-constexpr int TILE_ONCE = 1 << 16;
+constexpr int TILE_ONCE = 1 << 16, TILE_FULL = 1 << 17, TILE_ROWS_MASK = TILE_ONCE - 1;
 struct TileDesc {
     int32_t group;
     int32_t row0;
-    int32_t nrows;     // in a list: | TILE_ONCE where no other tile reads the same W panel at about the same time
+    int32_t nrows;     // in a list: | TILE_ONCE where no other tile reads the same W panel at about the same time,
+                       // | TILE_FULL where it is to run the 256-row variant
     int32_t srow;
 };
 

@@ -500,8 +500,8 @@ __device__ __forceinline__ int tile_order(const int wg, const int total, const i
 // measured 5-12 % faster than runs fitted to each group.)  Entries past n_run are tail tiles
 // of different groups: they are walked along n, which shares the X panel.
 template <bool UNIFORM = false>
-__device__ __forceinline__ bool pick_tile(const GemmArgs& p, const bool gated, TileDesc& d, int& n_tile, bool& once) {
-    once = false;
+__device__ __forceinline__ bool pick_tile(const GemmArgs& p, const bool gated, TileDesc& d, int& n_tile, bool& once, bool& full) {
+    once = full = false;
     if (UNIFORM) {
         // Router GEMM: every K-split s covers all T rows in tiles of uniform_tm rows; nothing to look up.
         const int L = blockIdx.x;
@@ -542,8 +542,9 @@ __device__ __forceinline__ bool pick_tile(const GemmArgs& p, const bool gated, T
     }
     if (mt >= count) return false;  // uniform for the workgroup
     d = p.descs[mt];
-    once = d.nrows >= TILE_ONCE;
-    d.nrows &= TILE_ONCE - 1;
+    once = (d.nrows & TILE_ONCE) != 0;
+    full = (d.nrows & TILE_FULL) != 0;
+    d.nrows &= TILE_ROWS_MASK;
     return true;
 }
 
@@ -553,10 +554,10 @@ __global__ __launch_bounds__(256, 1) void ffn_gemm_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     TileDesc d;
     int n_tile;
-    bool once;
-    if (!pick_tile<UNIFORM>(p, GATED, d, n_tile, once)) return;
+    bool once, full;
+    if (!pick_tile<UNIFORM>(p, GATED, d, n_tile, once, full)) return;
     // 32-row blocks that hold real rows; 9 or 10: a tall tile (the plan kernel makes them for this wave grid only)
-    const int blocks = d.nrows > 256 ? (d.nrows + 31) >> 5 : (p.small_tiles ? (d.nrows + 31) >> 5 : 8);
+    const int blocks = d.nrows > 256 ? (d.nrows + 31) >> 5 : (p.small_tiles && !full ? (d.nrows + 31) >> 5 : 8);
     if (WM == 2) {
         if (blocks > 4) gemm_tile<4, 2, 4, GATED, UNIFORM>(p, d, n_tile, lds);
         else if (blocks > 2) gemm_tile<4, 2, 2, GATED, UNIFORM>(p, d, n_tile, lds);
@@ -588,8 +589,8 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel8(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     TileDesc d;
     int n_tile;
-    bool once;
-    if (!pick_tile(p, GATED, d, n_tile, once)) return;
+    bool once, full;
+    if (!pick_tile(p, GATED, d, n_tile, once, full)) return;
     const int blocks = p.small_tiles ? (d.nrows + 31) >> 5 : 8;
     if (WM == 2) {
         if (blocks > 4) gemm_tile<8, 2, 4, GATED>(p, d, n_tile, lds);

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(64, 2) void ffn_small_kernel(const GemmArgs p, cons
     if (mt >= (GATED ? p.plan->n_gate_up : p.plan->n_down)) return;
     const int rem = blockIdx.x - mt * per, half = rem / p.n_tiles;
     TileDesc d = p.descs[mt];
-    d.nrows &= TILE_ONCE - 1;
+    d.nrows &= TILE_ROWS_MASK;
     const int n0 = (rem - half * p.n_tiles) * 16 * NB;
     for (int r0 = half * SMALL_ROWS; r0 < d.nrows; r0 += halves * SMALL_ROWS) {
         const int blocks = (min(d.nrows - r0, SMALL_ROWS) + 15) >> 4;   // wave-uniform
