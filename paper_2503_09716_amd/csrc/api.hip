@@ -332,18 +332,28 @@ int pick_group_m(const moe_ctx* c, const moe_shape& s, int tm) {
     return g < 4 ? 4 : (g > 8 ? 8 : g);
 }
 
+// K pieces per short tail of the down GEMM in this call (1 = none): down_tail_splits where the options and
+// the matrix size allow them (tiny matrices: the reduction's launch costs more than pieces can save).
+int call_down_splits(const moe_ctx* c, const moe_shape& s) {
+    if (c->gemm.tails_last == 0 || !c->gemm.small_tiles || c->gemm.down_tail_splits == 0) return 1;
+    if (c->gemm.down_tail_splits == 1 && (int64_t)s.F * s.H < ((int64_t)1 << 21)) return 1;
+    return down_tail_splits(s);
+}
+
 // Which of the two GEMMs of a small batch run one wavefront per 16 or 32 output columns (ffn_small.hip).
 // Measured with cold weights against the tile routine, us (tile -> small):
-//   gate/up  64 experts top-6 + 2 shared, F = 1408: 1 token 27.8 -> 21.3, 4: 54 -> 49, 16: 103 -> 97, 32: 115 -> 120;
-//            8 experts top-2, F = 14336: 4: 222 -> 225, 16: 300 -> 302, 32: 301 -> 308;
-//            160 experts top-6 + 2 shared, F = 1536: 1: 74 -> 47, 16: 193 -> 205, 32: 281 -> 294;
-//            8 experts top-2, H = 512, F = 1024: 16: 12.1 -> 9.2, 128: 13.1 -> 12.3, 256: 14.6 -> 15.3
-//   down     (default cache policy in both) 64 experts: 1: 37 -> 15, 4: 44 -> 28, 16: 62 -> 52, 32: 81 -> 68, 64: 85 -> 76;
-//            8 experts: 1: 66 -> 47, 8: 158 -> 145, 32: 177 -> 166, 64: 181 -> 175 (32 columns), 128: 186 -> 310;
-//            160 experts: 1: 43 -> 30, 32: 160 -> 161;  H = 512: 16: 16.2 -> 8.4, 128: 17.0 -> 11.2, 256: 17.9 -> 12.3
-// So: the down GEMM up to 64 tokens, the gate/up GEMM up to 16 (every group one block of 16 rows; X is
-// re-read by every wave, which costs more than the idle CUs from then on), and both somewhat further
-// when the tile routine would have tiles for a quarter of the CUs at most.
+//   gate/up  64 experts top-6 + 2 shared, F = 1408: 1 token 28 -> 20, 4: 40 -> 42, 8: 68 -> 70, 16: 100 -> 89, 32: 110 -> 115;
+//            8 experts top-2, F = 14336: 1: 82 -> 79, 4: 203 -> 202, 8: 277 -> 258, 16: 288 -> 290, 32: 290 -> 295;
+//            160 experts top-6 + 2 shared, F = 1536: 1: 66 -> 43, 4: 155 -> 122, 16: 347 -> 350 (skewed routing 4: 91 -> 94,
+//            8: 157 -> 138, 16: 177 -> 192)
+//   down     64 experts: 1: 34 -> 15, 4: 40 -> 24, 16: 51 -> 44, 32: 73 -> 59, 64: 77 -> 65;
+//            8 experts: 1: 56 -> 40, 8: 131 -> 122, 32: 151 -> 147, 64: 157 -> 148 (one expert with 37 rows: 161 -> 175);
+//            160 experts, skewed: 1: 40 -> 28, 16: 108 -> 98; uniform 16: 171 -> 171, 64: 362 -> 373
+// Gate/up: up to 16 tokens (every group one block of 16 rows; X is re-read by every wave, which costs more
+// than the idle CUs from then on), and up to 128 when the tile routine would have tiles for a quarter of
+// the CUs at most.  The tile routine is ahead (by 10 % at most) where its launch is one full round.
+// Down: up to 64 tokens with at most 16 rows per group on average, except in launches of eight rounds of
+// tiles and more; and wherever small_down_wins says so.
 constexpr int SMALL_TILE_ROWS = 128;
 struct SmallRule {
     bool up, down;
@@ -351,15 +361,37 @@ struct SmallRule {
     int halves;        // 64-row units per m-tile
     int mtiles_up, mtiles_down;   // m-tiles of SMALL_TILE_ROWS rows at most (also if a token picks an expert twice)
 };
+
+// The down GEMM of few groups of any height up to 256 tokens (tiles for a quarter of the CUs at most).  The tile
+// routine then takes the longest tile's walk along K, 0.42 us a sub-tile (shared experts: all of theirs; with K
+// pieces a part and 10 us), or the time to read W.  In ffn_small.hip every 64 rows of a group read W again and
+// every 16 or 32 columns X, together at about 10.5 TB/s, or a unit's walk along K takes longest, 0.14 to 0.26 us
+// a sub-tile by its height.  15 % covers what the estimates miss by (tile -> small, us: 4 experts of 4,
+// H = 4096, F = 3072: 16 tokens 29 -> 25, 64: 32 -> 32, 96: 33 -> 42, 256: 53 -> 81; 4 experts top-2 + 2 shared,
+// H = 2048, F = 1408: 4: 38 -> 13, 256: 47 -> 30; 7 experts top-2, H = 2240, F = 7808: 110: 52 -> 74).
+bool small_down_wins(const moe_shape& s, int groups, int splits, int cols) {
+    const double rows = (double)s.T * s.top_k / groups, matrix = 2.0 * s.F * s.H;
+    const double x_bytes = 2.0 * s.T * (s.top_k + s.num_shared) * s.F * (s.H / (16 * cols));
+    const double w_bytes = matrix * (groups * (int)((rows + 63) / 64) + s.num_shared * ((s.T + 63) / 64));
+    const double steps = s.F / 32 * (s.num_shared > 1 ? s.num_shared : 1);
+    const double most = s.num_shared > 0 ? s.T : rows;
+    const double walk = steps * (most <= 16 ? 0.14 : (most <= 32 ? 0.18 : 0.26)), reads = (w_bytes + x_bytes) / 10.5e6;
+    const int pieces = s.num_shared == 0 && rows <= 128 ? splits : 1;
+    const double tile_walk = steps / pieces * 0.42 + (pieces > 1 ? 10 : 0), tile_reads = matrix * (groups + s.num_shared) / 5.8e6;
+    return 1.15 * (walk > reads ? walk : reads) < (tile_walk > tile_reads ? tile_walk : tile_reads);
+}
+
 SmallRule small_rule(const moe_ctx* c, const moe_shape& s) {
     SmallRule r;
     const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;   // tiles of the tile routine along N
     const int64_t pairs = (int64_t)s.T * s.top_k;
     const int groups = (int)(pairs < s.E ? pairs : s.E);   // routed groups with rows, at most
+    const int tiles_up = (groups + s.num_shared) * nt_up, tiles_down = (groups + (s.num_shared > 0)) * nt_down;
     const bool allowed = c->gemm.small_tiles && !c->gemm.tile_rows_up && !c->gemm.tile_rows_down && c->gemm.down_tail_splits != 2;
-    r.up = allowed && (s.T <= 16 || (s.T <= 128 && (groups + s.num_shared) * nt_up <= 64));
-    r.down = allowed && (s.T <= 64 || (s.T <= 256 && (groups + (s.num_shared > 0)) * nt_down <= 64));
     r.down_cols = s.T <= 32 ? 1 : 2;
+    r.up = allowed && (s.T <= 16 || (s.T <= 128 && tiles_up <= 64));
+    r.down = allowed && ((s.T <= 64 && pairs <= 16 * (int64_t)groups && tiles_down < 8 * 256) ||
+                         (s.T <= 256 && tiles_down <= 64 && small_down_wins(s, groups, call_down_splits(c, s), r.down_cols)));
     r.halves = s.T <= 64 ? 1 : 2;
     const int routed = groups + (int)(pairs / SMALL_TILE_ROWS), per_shared = (s.T + SMALL_TILE_ROWS - 1) / SMALL_TILE_ROWS;
     r.mtiles_up = routed + s.num_shared * per_shared;
@@ -414,10 +446,9 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     if (sm.up) { tm_up = SMALL_TILE_ROWS; choose_up = 0; }
     if (sm.down) tm_down = SMALL_TILE_ROWS;
     // K pieces for short tails of the down GEMM: the device-side plan decides from the real tile
-    // counts whether to cut (ffn_plan_kernel); here only what the shape alone rules out, which
-    // spares the launch of the reduction: tiny matrices (a launch costs more than it can save).
-    int dsp = (!sm.down && tl_down && c->gemm.small_tiles && c->gemm.down_tail_splits != 0) ? down_tail_splits(s) : 1;
-    if (c->gemm.down_tail_splits == 1 && (int64_t)s.F * s.H < ((int64_t)1 << 21)) dsp = 1;
+    // counts whether to cut (plan_lists); here only what the shape alone rules out, which
+    // spares the launch of the reduction.
+    const int dsp = sm.down ? 1 : call_down_splits(c, s);
     if (s.T <= 256 && dsp == 1 && !c->gemm.tile_rows_down) tm_down = 128;   // as above; not where short tails may be cut along K
     // Forced pieces: which rows are cut must not depend on what else a pass covers, so the heights are fixed.
     const int choose_down = tm_down == 256 && !c->gemm.tile_rows_down && may_choose_rows(s, nt_down, s.num_shared ? 1 : 0) &&

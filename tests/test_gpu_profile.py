@@ -59,3 +59,46 @@ def test_mfma_ceiling_is_plausible_and_validates_its_arguments(moe):
         moe.mfma_ceiling(None, None, iters, sink[:1000])      # sink too small
     with pytest.raises(MoeError):
         moe.mfma_ceiling(None, None, 0, sink)
+
+
+# What the library chooses for a launch by itself, against the same launch with an option that makes the other choice:
+# T, H, F, E, k, shared, stage, the option.  Weights of more than 256 MB, so that every pass reads them from memory.
+CHOICES = [
+    # down GEMM of few groups with many rows: gemm_tile_rows_down keeps it on the tile routine
+    (256, 4096, 3072, 4, 4, 0, "ffn_down", {"gemm_tile_rows_down": 128}),
+    (138, 2240, 7808, 7, 2, 0, "ffn_down", {"gemm_tile_rows_down": 256}),
+    (143, 2112, 5056, 6, 6, 2, "ffn_down", {"gemm_tile_rows_down": 128}),
+]
+
+
+@pytest.mark.parametrize("T,H,F,E,k,shared,stage,option", CHOICES)
+def test_default_choice_is_not_the_slower_one(moe, T, H, F, E, k, shared, stage, option):
+    """Median stage times in turn; 12 % is allowed for the spread of a median of 3 x 20 (2 % seen) and for choices that are
+    close.  (Packed weights are a permutation of the logical ones: random values will do.)"""
+    from paper_2503_09716_amd import make_shape
+    shape = make_shape(T, H, F, E, k, shared, True)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    normal = lambda *size, std=0.02: torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    n = E + shared
+    assert 6 * n * H * F > 256 << 20
+    tables = [[normal(H * F) for _ in range(n)] for _ in range(3)]
+    x, wg, out, ws = normal(T, H, std=1.0), normal(H, E), normal(T, H), moe.new_workspace(shape)
+    times = {"default": [], "option": []}
+    try:
+        for _ in range(3):
+            for name in times:
+                for key, value in option.items():
+                    moe.set_option(key, value if name == "option" else {"down_tail_splits": 1}.get(key, 0))
+                moe.layer(shape, x, wg, None, *tables, out, ws)
+                moe.profile_enable(True)
+                for _ in range(20):
+                    moe.layer(shape, x, wg, None, *tables, out, ws)
+                times[name] += moe.profile_read_intervals()[stage]
+                moe.profile_enable(False)
+    finally:
+        moe.profile_enable(False)
+        for key in option:
+            moe.set_option(key, {"down_tail_splits": 1}.get(key, 0))
+    default, other = (sorted(times[name])[len(times[name]) // 2] for name in ("default", "option"))
+    print("T", T, "H", H, "F", F, "E", E, "k", k, "shared", shared, stage, "default %.4f ms" % default, option, "%.4f ms" % other, flush=True)
+    assert default <= 1.12 * other
