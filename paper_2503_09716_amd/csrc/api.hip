@@ -359,6 +359,7 @@ struct SmallRule {
     bool up, down;
     int down_cols;     // 16-column blocks per wave of the down GEMM
     int halves;        // 64-row units per m-tile
+    bool once;         // one unit per group, as a rule: its W panels are read once
     int mtiles_up, mtiles_down;   // m-tiles of SMALL_TILE_ROWS rows at most (also if a token picks an expert twice)
 };
 
@@ -393,6 +394,7 @@ SmallRule small_rule(const moe_ctx* c, const moe_shape& s) {
     r.down = allowed && ((s.T <= 64 && pairs <= 16 * (int64_t)groups && tiles_down < 8 * 256) ||
                          (s.T <= 256 && tiles_down <= 64 && small_down_wins(s, groups, call_down_splits(c, s), r.down_cols)));
     r.halves = s.T <= 64 ? 1 : 2;
+    r.once = s.T <= 64 || (s.num_shared == 0 && pairs <= 52 * (int64_t)groups);
     const int routed = groups + (int)(pairs / SMALL_TILE_ROWS), per_shared = (s.T + SMALL_TILE_ROWS - 1) / SMALL_TILE_ROWS;
     r.mtiles_up = routed + s.num_shared * per_shared;
     r.mtiles_down = routed + (s.num_shared > 0) * per_shared;
@@ -462,7 +464,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const double per_expert = (double)s.T * s.top_k / ((double)s.E * 256);
     int tall = c->gemm.tall_tiles >= 0 ? c->gemm.tall_tiles : (per_expert <= 8.0 ? 2 : 1);
     if (!tall_kernel) tall = 0;
-    // Non-temporal loads of weights that one tile reads: only if the layer's weights exceed the memory-side cache
+    // Non-temporal loads of weights that one tile (in ffn_small.hip: one unit, SmallRule::once) reads: only if the layer's weights exceed the memory-side cache
     // (256 MB); a small layer called again and again finds its weights there (tiny layer, 25 MB, 256 tokens: 31.5 us
     // without, 34.5 with them).
     const bool nt = (int64_t)(s.E + s.num_shared) * 6 * s.H * s.F > ((int64_t)256 << 20);
@@ -527,7 +529,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool plann
         StageTimer tm(c, st, MOE_STAGE_FFN_GATE_UP);
         if (sm.up) {
             a.n_tiles = s.F / 32;
-            HIP_TRY(c, launch_ffn_small(true, a, 2, sm.halves, f.nt, st));
+            HIP_TRY(c, launch_ffn_small(true, a, 2, sm.halves, f.nt && sm.once, st));
         } else {
             HIP_TRY(c, launch_ffn_gemm(true, a, c->gemm, st));
         }
@@ -558,7 +560,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool plann
         StageTimer tm(c, st, MOE_STAGE_FFN_DOWN);
         if (sm.down) {
             a.n_tiles = s.H / (16 * sm.down_cols);
-            HIP_TRY(c, launch_ffn_small(false, a, sm.down_cols, sm.halves, f.nt, st));
+            HIP_TRY(c, launch_ffn_small(false, a, sm.down_cols, sm.halves, f.nt && sm.once, st));
         } else {
             HIP_TRY(c, launch_ffn_gemm(false, a, c->gemm, st));
         }

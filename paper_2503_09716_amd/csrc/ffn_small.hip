@@ -7,9 +7,11 @@
 // whole of K, for up to 64 rows of X.  W goes straight from memory into registers - a 16 x 32 block of
 // the packed layout is one 1 KiB load, already in operand order up to a lane permutation - through
 // a ring of RING sub-tiles per wave (about 32 KiB in flight), with no LDS and no barrier.  X is read the
-// same way; its rows are few and come from L2.  W is read once; in a layer that no
-// cache can hold it is marked non-temporal, which is worth a tenth (8x7B, 8 tokens: gate/up 297 -> 267 us, down 146 -> 128 = 7.3 TB/s; 64 experts, 16 tokens: 107 -> 98,
-// 53 -> 47).
+// same way; its rows are few and come from L2.  A group of up to 64 rows reads its W once; in a layer that no
+// cache can hold those loads are non-temporal, which is worth a tenth (8x7B, 8 tokens: gate/up 297 -> 267 us,
+// down 146 -> 128 = 7.3 TB/s; 64 experts, 16 tokens: 107 -> 98, 53 -> 47).  A taller group reads it once per 64
+// rows, and the hint then costs more than it gives (4 experts of 4, H = 8192, F = 1408, 100 tokens: gate/up
+// 92 us without, 115 with it).
 //
 // Every output element is one chain of v_mfma_f32_16x16x32_bf16 over K in ascending order with the
 // operands in the same roles as in the tile routine, so both give the same bits.

@@ -102,3 +102,27 @@ def test_default_choice_is_not_the_slower_one(moe, T, H, F, E, k, shared, stage,
     default, other = (sorted(times[name])[len(times[name]) // 2] for name in ("default", "option"))
     print("T", T, "H", H, "F", F, "E", E, "k", k, "shared", shared, stage, "default %.4f ms" % default, option, "%.4f ms" % other, flush=True)
     assert default <= 1.12 * other
+
+
+def test_weight_bytes_cost_the_same_on_both_sides_of_the_cache_size(moe):
+    """Layers of more than 256 MB load weights that one tile or wave reads non-temporally.  Groups of 100 rows are two waves
+    per panel in the gate/up GEMM, so a layer just above must not pay more per weight byte there than one just below
+    (two sets of weights in turn, so that neither is cached; 6 % for the spread of a median of 40)."""
+    from paper_2503_09716_amd import make_shape
+    per_byte = []
+    for F in (1280, 1408):
+        T, H, E = 100, 8192, 4
+        shape = make_shape(T, H, F, E, E, 0, True)
+        gen = torch.Generator(device="cuda").manual_seed(7)
+        normal = lambda *size, std=0.02: torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+        sets = [[[normal(H * F) for _ in range(E)] for _ in range(3)] for _ in range(2)]
+        x, wg, out, ws = normal(T, H, std=1.0), normal(H, E), normal(T, H), moe.new_workspace(shape)
+        for on in (False, True):
+            moe.profile_enable(on)
+            for i in range(40 if on else 4):
+                moe.layer(shape, x, wg, None, *sets[i % 2], out, ws)
+        ms = sorted(moe.profile_read_intervals()["ffn_gate_up"])
+        moe.profile_enable(False)
+        print("F", F, "%d MB" % (6 * E * H * F >> 20), "%.4f ms" % ms[len(ms) // 2], flush=True)
+        per_byte.append(ms[len(ms) // 2] / F)
+    assert per_byte[1] <= 1.06 * per_byte[0]
