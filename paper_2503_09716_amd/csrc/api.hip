@@ -422,11 +422,16 @@ struct FfnSetup {
 FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets, char* ws, const FfnPass& ps) {
     const Layout L = make_layout(s);
     const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;
-    // Up to 256 tokens a group of 129 to 256 rows (most often a shared expert) is two tiles: as one it would
-    // be the longest tile of a short launch (64 experts + 2 shared, 200 tokens: gate/up 137 -> 130 us).
-    int tm_up = c->gemm.tile_rows_up ? c->gemm.tile_rows_up : (s.T <= 256 ? 128 : 256);
+    // Up to 256 tokens a group of 129 to 256 rows is two tiles in a launch that would have tiles for half of the CUs at
+    // most: as one it would be the longest tile by itself (4 experts + 4 shared, H = 2112, F = 768, 148 tokens: gate/up
+    // 48 -> 38 us).  With more tiles the second pass over its W panels costs more (15 experts top-6 + 1 shared, H = 1408,
+    // F = 2048, 142 tokens: 37 us in one tile, 45 in two; 5 experts top-4, H = 3200, F = 5376, 168 tokens: 80, 101;
+    // 64 experts + 2 shared, F = 1408: 130 tokens 119, 126; 200 tokens 124, 120).
+    const int64_t pairs = (int64_t)s.T * s.top_k, groups = pairs < s.E ? pairs : s.E;
+    const bool idle_up = (groups + s.num_shared) * nt_up <= 128;
+    int tm_up = c->gemm.tile_rows_up ? c->gemm.tile_rows_up : (s.T <= 256 && idle_up ? 128 : 256);
     int tm_down = c->gemm.tile_rows_down ? c->gemm.tile_rows_down : 256;
-    int choose_up = tm_up == 256 && !c->gemm.tile_rows_up && may_choose_rows(s, nt_up, s.num_shared);
+    int choose_up = s.T > 256 && !c->gemm.tile_rows_up && may_choose_rows(s, nt_up, s.num_shared);
     // tiles above 256 rows exist for the 4-wave, 1-wave-row kernel only
     const bool tall_kernel = c->gemm.waves == 4 && c->gemm.wave_rows == 1;
     // Gate/up GEMM: 320-row tiles move 10 % fewer bytes per FLOP from L2 to LDS (the chip is
@@ -451,7 +456,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // counts whether to cut (plan_lists); here only what the shape alone rules out, which
     // spares the launch of the reduction.
     const int dsp = sm.down ? 1 : call_down_splits(c, s);
-    if (s.T <= 256 && dsp == 1 && !c->gemm.tile_rows_down) tm_down = 128;   // as above; not where short tails may be cut along K
+    if (s.T <= 256 && dsp == 1 && !c->gemm.tile_rows_down) tm_down = 128;   // the walk along K is long; not where short tails may be cut along K
     // Forced pieces: which rows are cut must not depend on what else a pass covers, so the heights are fixed.
     const int choose_down = tm_down == 256 && !c->gemm.tile_rows_down && may_choose_rows(s, nt_down, s.num_shared ? 1 : 0) &&
                             !(dsp > 1 && c->gemm.down_tail_splits == 2);
