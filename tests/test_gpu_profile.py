@@ -68,6 +68,10 @@ CHOICES = [
     (256, 4096, 3072, 4, 4, 0, "ffn_down", {"gemm_tile_rows_down": 128}),
     (138, 2240, 7808, 7, 2, 0, "ffn_down", {"gemm_tile_rows_down": 256}),
     (143, 2112, 5056, 6, 6, 2, "ffn_down", {"gemm_tile_rows_down": 128}),
+    # down GEMM, all tiles short: cut along K or not
+    (807, 2560, 3328, 24, 2, 0, "ffn_down", {"down_tail_splits": 0}),
+    (100, 6144, 8192, 8, 2, 0, "ffn_down", {"down_tail_splits": 0}),
+    (100, 2240, 7808, 7, 2, 0, "ffn_down", {"down_tail_splits": 0}),
     # gate/up GEMM, groups of 129 to 256 rows as one tile or two
     (168, 3200, 5376, 5, 4, 0, "ffn_gate_up", {"gemm_tile_rows_up": 256}),
     (142, 1408, 2048, 15, 6, 1, "ffn_gate_up", {"gemm_tile_rows_up": 256}),
