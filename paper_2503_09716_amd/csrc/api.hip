@@ -473,17 +473,19 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // (256 MB); a small layer called again and again finds its weights there (tiny layer, 25 MB, 256 tokens: 31.5 us
     // without, 34.5 with them).
     const bool nt = (int64_t)(s.E + s.num_shared) * 6 * s.H * s.F > ((int64_t)256 << 20);
+    // Up to a thousand tokens the shared experts' tiles of the down GEMM stay low (list_cut in plan.h).
+    const bool low_shared = s.num_shared > 0 && s.T <= 1024;
     FfnSetup f;
     f.nt = nt;
     f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
-                      nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, nt, ps.e_lo, ps.e_hi, ps.shared_on,
+                      nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, nt, low_shared, ps.e_lo, ps.e_hi, ps.shared_on,
                       dsp, 4, split_rule_tiles, s.F / (32 * dsp) >= 32, tall, tall, (SplitTail*)(ws + L.split_tails), (PlanHeader*)(ws + L.plan),
                       (TileDesc*)(ws + L.descs_up), (TileDesc*)(ws + L.descs_down)};
     f.sm = sm;
     f.mtiles_up = ps.mtiles_up > 0 ? ps.mtiles_up : (sm.up ? sm.mtiles_up : (int)max_mtiles(s, choose_up ? 128 : tm_up));
     f.mtiles_down = (ps.mtiles_down > 0 ? ps.mtiles_down : (sm.down ? sm.mtiles_down : (int)max_mtiles(s, choose_down ? 128 : tm_down))) +
                     s.E * (dsp - 1);
-    if (s.num_shared > 0 && s.T <= SHARED_LOW_TOKENS) f.mtiles_down += (s.T + 127) / 128;
+    if (low_shared) f.mtiles_down += (s.T + 127) / 128;
     f.group_m_up = pick_group_m(c, s, tm_up);
     f.group_m_down = pick_group_m(c, s, tm_down);
     return f;

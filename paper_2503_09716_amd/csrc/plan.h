@@ -39,7 +39,7 @@ __device__ __forceinline__ void block_scan3(int& a, int& b, int& c, int (&tot)[3
 // expert: gate/up GEMM 740 -> 600 us, down 351 -> 300).  A longer one is cut into full tiles and
 // a tail.  A tail of at most 64 rows next to full 256-row tiles joins the last of them.
 struct GroupCut {
-    int h, nfull, tail, joined;
+    int cap, h, nfull, tail, joined;
     bool even;
 };
 __device__ __forceinline__ int div_small(const int a, const int b) {   // a / b for 0 <= a < 2^24, b >= 32: a short division
@@ -48,9 +48,9 @@ __device__ __forceinline__ int div_small(const int a, const int b) {   // a / b 
     if ((q + 1) * b <= a) ++q;
     return q;
 }
-__device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, const bool tall, const bool even = true) {
+__device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, const bool tall, const bool even) {
     GroupCut c;
-    c.h = tm;
+    c.cap = c.h = tm;
     c.nfull = rows < (1 << 24) ? div_small(rows, tm) : rows / tm;
     c.tail = rows - c.nfull * tm;
     c.joined = tall && tm == 256 && c.nfull > 0 && c.tail <= PLAN_MAX_ROWS - 256 ? c.tail : 0;
@@ -63,6 +63,17 @@ __device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, cons
         c.tail = rows - c.nfull * c.h;
     }
     return c;
+}
+
+// The cut of one group for list `which` (0 gate/up, 1 down) with height cap tm; the cost of a list below and
+// the list itself both use it.
+// Shared experts next to short routed groups (up to about a thousand tokens): theirs are the longest
+// tiles.  Down GEMM, where they walk all shared experts' K: 128 rows at most
+// (64 experts + 2 shared, 300 tokens 96 -> 85 us, 500: 92 -> 90).  Gate/up: not cut evenly up to 512 tokens, so
+// that the short rest goes last (500 tokens: 147 -> 143 us).
+__device__ __forceinline__ GroupCut list_cut(const PlanArgs& p, const int which, const bool shared, const int rows, const int tm) {
+    return cut_group(rows, which == 1 && shared && p.low_shared ? min(tm, 128) : tm, (which == 0 ? p.tall_up : p.tall_down) != 0,
+                     !shared || which == 1 || p.T > 512);
 }
 
 // Height cap of a list's tiles, chosen from the call's real row counts (launches of a few rounds
@@ -80,8 +91,8 @@ __device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, cons
 constexpr int PLAN_CAPS = 5;
 __device__ constexpr int plan_cap(const int c) { return 256 - 32 * c; }
 
-__device__ __forceinline__ float list_cost(const int* rows, const int ngroups, const int nseg0, const int tm, const bool tall,
-                                           const int n_tiles, const int lane) {
+__device__ __forceinline__ float list_cost(const PlanArgs& p, const int which, const int* rows, const int ngroups, const int nseg0,
+                                           const int tm, const int n_tiles, const int lane) {
     // n: tiles; alone: tiles that are their group's only one; sum: rows; longest: highest tile (shared experts
     // of the down GEMM walk nseg0 segments)
     // (n and alone share a word: a launch with a choice has at most a few thousand m-tiles)
@@ -89,7 +100,7 @@ __device__ __forceinline__ float list_cost(const int* rows, const int ngroups, c
     for (int g = lane; g < ngroups; g += 64) {
         const int r = rows[g];
         if (r == 0) continue;
-        const GroupCut c = cut_group(r, tm, tall);
+        const GroupCut c = list_cut(p, which, p.Ns > 0 && (g == 0 || g > p.E), r, tm);
         const int m = c.nfull + (c.tail > 0);
         const int seg = g == 0 ? nseg0 : 1;
         n_alone += m + (m == 1 ? 1 << 16 : 0);
@@ -155,9 +166,8 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
             if (!(which == 0 ? p.choose_up : p.choose_down)) continue;
             const int groups = which == 0 ? ngroups : (Ns > 0 ? E + 1 : E);
             const int nseg0 = which == 1 && Ns > 1 ? Ns : 1, nt = which == 0 ? p.nt_up : p.nt_down;
-            const bool tall = (which == 0 ? p.tall_up : p.tall_down) != 0;
             // (one copy of the code for all caps: what this costs is mostly fetching its instructions)
-            const float cost = list_cost(group_rows, groups, nseg0, plan_cap(c), tall, nt, lane);
+            const float cost = list_cost(p, which, group_rows, groups, nseg0, plan_cap(c), nt, lane);
             if (lane == 0) cap_cost[which][c] = cost;
         }
         __syncthreads();
@@ -176,12 +186,7 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
         const int last = which == 0 ? ngroups - 1 : (Ns > 0 ? E : E - 1);  // last group of this list
         const bool mine = tid <= last;
         const bool tails_last = (which == 0 ? p.tails_last_up : p.tails_last_down) != 0;
-        // Shared experts next to short routed groups (up to about a thousand tokens): theirs are the longest
-        // tiles.  Down GEMM, where they walk all shared experts' K: 128 rows at most (64 experts + 2 shared,
-        // 300 tokens 96 -> 85 us, 500: 92 -> 90).  Gate/up: not cut evenly up to 512 tokens, so that the short
-        // rest goes last (500 tokens: 147 -> 143 us).
-        const int cap = which == 1 && group >= E && p.T <= SHARED_LOW_TOKENS ? min(tm, 128) : tm;
-        const GroupCut cut = cut_group(mine ? rows : 0, cap, tall != 0, group < E || which == 1 || p.T > 512);
+        const GroupCut cut = list_cut(p, which, group >= E, mine ? rows : 0, tm);
         const int nfull = cut.nfull, tail = cut.tail, joined = cut.joined, h = cut.h;
         const int blocks = (tail + 31) >> 5;   // 32-row blocks of the tail tile, 0 = none
         // A tail higher than half a tile runs the full-height variant and takes as long as a full
@@ -190,7 +195,7 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
         // (A shared expert's tail is not moved in a down list with K pieces: the pieces' partial
         // sums are reduced into y_perm, while shared rows belong to y_shared.)
         // (at most 128 rows: the K pieces' partial buffers hold SPLIT_TAIL_ROWS rows)
-        const bool moved = tails_last && blocks > 0 && !cut.even && p.small_tiles && blocks * 64 <= min(cap, 2 * SPLIT_TAIL_ROWS) &&
+        const bool moved = tails_last && blocks > 0 && !cut.even && p.small_tiles && blocks * 64 <= min(cut.cap, 2 * SPLIT_TAIL_ROWS) &&
                            !(which == 1 && p.down_splits > 1 && group >= E);
         // tall_* = 2: the tall tile keeps its place in the group (it shares the W panels its
         // neighbours stream, which is the point when a group is only a few tiles).  tall_* = 1 and

@@ -547,3 +547,70 @@ def test_empty_batch_is_a_no_op(moe):
     moe.layer(shape, empty16, wg, None, w1p, w3p, w2p, empty16, ws)
     moe.layer_chunked(shape, empty16, wg, None, w1p, w3p, w2p, 16, empty16, ws)
     torch.cuda.synchronize()
+
+
+def read_tile_lists(ws, s):
+    """The m-tile lists that a call left in its workspace (fixed order of regions, each 256-byte aligned): the two
+    headers' counts and the lists as arrays of (group, row0, nrows, srow, marks)."""
+    words = ws.cpu().numpy().view(np.int32)
+    at, R, chunks = 0, s.T * s.top_k, (s.T + 255) // 256
+    sizes = [R * 4, R * 4, (s.E + 1) * 4, R * 4, R * 4, R * 4, chunks * s.E * 4, 32]
+    max_mtiles = R // 128 + s.E + s.num_shared * ((s.T + 127) // 128)
+    for n in sizes[:-1]:
+        at += (n + 255) // 256 * 64
+    head = words[at:at + 8]
+    up = at + 64
+    down = up + (max_mtiles * 16 + 255) // 256 * 64
+    lists = []
+    for begin, count in ((up, head[0]), (down, head[1])):
+        d = words[begin:begin + 4 * count].reshape(count, 4)
+        lists.append([(int(g), int(r), int(n) & 0xffff, int(sr), int(n) >> 16) for g, r, n, sr in d])
+    return lists
+
+
+def lists_of(moe, T, H, F, E, k, shared, counts, **options):
+    """Lists of a grouped_ffn call whose routing gives expert e counts[e] rows (sum T * k); checks that they cover every
+    row of every group exactly once."""
+    assert sum(counts) == T * k
+    s = make_shape(T, H, F, E, k, shared, False)
+    idx = torch.from_numpy(np.repeat(np.arange(E, dtype=np.int32), counts).reshape(k, T).T.copy()).cuda()
+    weight = torch.zeros(H * F, dtype=torch.bfloat16, device="cuda")
+    tab = [weight] * (E + shared)
+    i32 = lambda n: torch.empty(n, dtype=torch.int32, device="cuda")
+    x = torch.zeros((T, H), dtype=torch.bfloat16, device="cuda")
+    off, perm, inv, rtok, ws = i32(E + 1), i32(T * k), i32(T * k), i32(T * k), moe.new_workspace(s)
+    y = torch.empty((T * k, H), dtype=torch.float32, device="cuda")
+    ysh = torch.empty((T, H), dtype=torch.float32, device="cuda")
+    moe.permute(s, x, idx, None, off, perm, inv, rtok, ws)
+    for key, value in options.items():
+        moe.set_option(key, value)
+    try:
+        moe.grouped_ffn(s, None, rtok, x, off, tab, tab, tab, moe.new_h_scratch(s), y, ysh if shared else None, ws)
+        torch.cuda.synchronize()
+    finally:
+        for key in options:
+            moe.set_option(key, {"down_tail_splits": 1, "small_tiles": 1}.get(key, 0))
+    begin = np.concatenate([[0], np.cumsum(counts)])
+    lists = read_tile_lists(ws, s)
+    for which, tiles in enumerate(lists):
+        got = {}
+        for g, r0, n, _, _ in tiles:
+            got.setdefault(g, []).append((r0 - (int(begin[g]) if g < E else 0), n))
+        want = {e: counts[e] for e in range(E) if counts[e]}
+        want.update({E + i: T for i in range(shared if which == 0 else min(shared, 1))})
+        assert set(got) == set(want), which
+        for g, rows in want.items():
+            at = 0
+            for r0, n in sorted(got[g]):
+                assert r0 == at and n > 0, (which, g, got[g])
+                at += n
+            assert at == rows, (which, g, got[g])
+    return lists
+
+
+def test_heights_are_chosen_for_the_list_that_is_built(moe):
+    """Four experts of 150 rows next to two shared ones (down GEMM of 8 tiles along N, 300 tokens): the shared tiles, the longest, are
+    at most 128 rows under every cap, so no cap can shorten the launch and the routed groups stay one tile."""
+    down = lists_of(moe, 300, 2048, 128, 4, 2, 2, [150] * 4)[1]
+    assert sorted(n for g, _, n, _, _ in down if g >= 4) == [44, 128, 128]
+    assert [n for g, _, n, _, _ in down if g < 4] == [150] * 4
