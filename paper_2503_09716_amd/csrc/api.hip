@@ -474,7 +474,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // without, 34.5 with them).
     const bool nt = (int64_t)(s.E + s.num_shared) * 6 * s.H * s.F > ((int64_t)256 << 20);
     // Up to a thousand tokens the shared experts' tiles of the down GEMM stay low (list_cut in plan.h).
-    const bool low_shared = s.num_shared > 0 && s.T <= 1024;
+    const bool low_shared = s.num_shared > 0 && s.T <= 1024 && !c->gemm.tile_rows_down;
     FfnSetup f;
     f.nt = nt;
     f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,

@@ -608,6 +608,16 @@ def lists_of(moe, T, H, F, E, k, shared, counts, **options):
     return lists
 
 
+def test_explicit_tile_rows_hold_for_shared_experts_too(moe):
+    """gemm_tile_rows_down is the most rows of an m-tile in the down GEMM, the shared experts' included; by default theirs are
+    at most 128 in a batch of this size."""
+    args = (512, 128, 128, 8, 2, 2, [128] * 8)
+    heights = lambda lists: sorted(n for g, _, n, _, _ in lists[1] if g >= 8)
+    assert heights(lists_of(moe, *args)) == [128] * 4
+    assert heights(lists_of(moe, *args, gemm_tile_rows_down=256)) == [256] * 2
+    assert heights(lists_of(moe, *args, gemm_tile_rows_down=128)) == [128] * 4
+
+
 def test_heights_are_chosen_for_the_list_that_is_built(moe):
     """Four experts of 150 rows next to two shared ones (down GEMM of 8 tiles along N, 300 tokens): the shared tiles, the longest, are
     at most 128 rows under every cap, so no cap can shorten the launch and the routed groups stay one tile."""
