@@ -124,8 +124,8 @@ size_t moe_h_scratch_bytes(const moe_shape* shape);
  *                             expert's short tail tile into 2 or 4 pieces run by different CUs and add the fp32
  *                             partial sums afterwards in fixed order.  0: never; 2: every eligible tail;
  *                             1 (default): where it pays, decided on the device from the call's tile counts
- *                             (launches in which every tile is a short tail, i.e. a few tokens per expert, and the
- *                             pieces fit the CUs, and launches many rounds of tiles long).  Cutting changes the summation order of
+ *                             (launches in which every tile is a short tail, i.e. a few tokens per expert, and too few
+ *                             of them read W to be bound by that, and launches many rounds of tiles long).  Cutting changes the summation order of
  *                             those rows only: results are deterministic for given inputs and options, but not
  *                             bit-identical between the three settings, nor, under 1, between calls that
  *                             cover the same tokens in differently sized passes.

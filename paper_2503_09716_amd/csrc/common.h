@@ -90,7 +90,7 @@ struct PlanArgs {
     int32_t mark_once;                  // 1: TILE_ONCE marks are wanted
     int32_t low_shared;                 // 1: the shared experts' tiles of the down GEMM are at most 128 rows
     int32_t e_lo, e_hi, shared_on;      // the lists cover routed experts [e_lo, e_hi) and, if shared_on, the shared experts
-    int32_t down_splits, split_max_blocks, split_rule_tiles, long_pieces, tall_up, tall_down;   // long_pieces: K pieces of 32 sub-tiles at least
+    int32_t down_splits, split_max_blocks, split_rule_tiles, split_room_tiles, tall_up, tall_down;
     SplitTail* split_tails;
     PlanHeader* plan;
     TileDesc *descs_up, *descs_down;

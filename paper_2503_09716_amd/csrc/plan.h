@@ -226,10 +226,11 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
         // Whether to cut at all is decided here, where the tile counts are known.  Pieces make a
         // launch faster in two cases only (measured on the Mixtral-shaped layer from 64 to 16384
         // tokens): when EVERY tile of the launch is a short tail (a few tokens per expert) and the
-        // pieces fill idle CUs instead of adding rounds: up to 256 of them, or of 128 tiles if a piece is at
-        // least 32 sub-tiles of K (whole -> cut, us: 7 experts, H = 2240, F = 7808, 63 tiles 97 -> 53; 8 of
-        // H = 4096, F = 14336, 128 tiles 190 -> 162; but 16 of H = 2048, F = 2048, 128 tiles 30 -> 35; 8 of H = 6144,
-        // F = 16384, 192 tiles 241 -> 279; 24 of H = 2560, F = 1664, 240 tiles 45 -> 72), and when the launch is
+        // launch is bound by the walk along K, 0.42 us a sub-tile, and not by reading W at 5.8 TB/s and the 7 us of the
+        // second launch: F / 32 * 0.42 > tiles * 512 F / 5.8e6 + 7, that is tiles <= 149 - 79000 / F =
+        // p.split_room_tiles (whole -> cut, us: H = 2240, F = 7808, 63 tiles 97 -> 53; H = 4096, F = 14336, 128 tiles
+        // 190 -> 162; H = 1216, F = 3072, 105 tiles 48 -> 42; but H = 2048, F = 2048, 128 tiles 30 -> 35; H = 6144,
+        // F = 16384, 192 tiles 241 -> 279; H = 2560, F = 1664, 240 tiles 45 -> 72), and when the launch is
         // many rounds of tiles long (the tails at its end then finish sooner: -2 % on the
         // 16384-token, skewed workload).  In between, a launch of one to three rounds is as long
         // as its full tiles whatever happens to the tails, and pieces only add a round and
@@ -241,9 +242,7 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
             n_whole = 0;
             for (int b = p.split_max_blocks + 1; b <= 4; ++b) n_whole += cnt[b];
             const int others = n_run_s + n_tall_s + n_whole;
-            const int tail_tiles = tails * p.nt_down;
-            const bool room = tail_tiles * p.down_splits <= 256 || (tail_tiles <= 128 && p.long_pieces);
-            cutting = p.split_rule_tiles == 0 || (others == 0 && room) || others + tails - n_whole >= p.split_rule_tiles;
+            cutting = p.split_rule_tiles == 0 || (others == 0 && tails * p.nt_down <= p.split_room_tiles) || others + tails - n_whole >= p.split_rule_tiles;
             if (!cutting) n_whole = tails;
         }
         const int n_cut = tails - n_whole;
