@@ -283,7 +283,11 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
                 int rank = pre[blocks];
                 for (int b = blocks + 1; b <= 4; ++b) rank += cnt[b];
                 d.row0 = row_begin + nfull * h;
-                d.nrows = tail | (p.mark_once ? TILE_ONCE : 0);   // runs after the group's other tiles, if there are any
+                // in more than one round it runs after the group's other tiles, if there are any; within one, next to them, and
+                // the hint then costs as much as elsewhere (9 experts top-1 + 2 shared, H = 4544, F = 1920, 140 tokens:
+                // gate/up 98 us with it, 73 without)
+                const bool later = (n_run_s + n_tall_s) * (which == 0 ? p.nt_up : p.nt_down) > 256;
+                d.nrows = tail | (p.mark_once && (nfull == 0 || later) ? TILE_ONCE : 0);
                 const int tbase = n_run_s + n_tall_s;
                 if (cutting && blocks <= p.split_max_blocks) {
                     // one entry per K piece; the pieces' partial sums are added up after the launch

@@ -78,6 +78,8 @@ CHOICES = [
     (142, 1408, 2048, 15, 6, 1, "ffn_gate_up", {"gemm_tile_rows_up": 256}),
     # gate/up GEMM, tall shared groups next to short routed ones in less than a round of tiles
     (300, 2560, 1536, 8, 1, 4, "ffn_gate_up", {"gemm_tile_rows_up": 128}),
+    # gate/up GEMM, short tails of tall shared groups in less than a round
+    (140, 4544, 1408, 9, 1, 2, "ffn_gate_up", {"gemm_tile_rows_up": 256}),
 ]
 
 
