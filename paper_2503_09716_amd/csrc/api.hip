@@ -423,13 +423,13 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const Layout L = make_layout(s);
     const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;
     // Up to 256 tokens a group of 129 to 256 rows is two tiles in a launch that would have tiles for half of the CUs at
-    // most: as one it would be the longest tile by itself (4 experts + 4 shared, H = 2112, F = 768, 148 tokens: gate/up
-    // 48 -> 38 us).  With more tiles the second pass over its W panels costs more (15 experts top-6 + 1 shared, H = 1408,
+    // most, and a shared expert's in one of up to a round: as one it would be the longest tile by itself
+    // (148 tokens, 4 experts + 4 shared, H = 2112, F = 768: gate/up 48 -> 38 us; 156 tokens, 5 top-1 + 4 shared, H = 2304, F = 2112:
+    // 56 -> 45).  With more tiles the second pass over its W panels costs more (15 experts top-6 + 1 shared, H = 1408,
     // F = 2048, 142 tokens: 37 us in one tile, 45 in two; 5 experts top-4, H = 3200, F = 5376, 168 tokens: 80, 101;
     // 64 experts + 2 shared, F = 1408: 130 tokens 119, 126; 200 tokens 124, 120).
-    const int64_t pairs = (int64_t)s.T * s.top_k, groups = pairs < s.E ? pairs : s.E;
-    const bool idle_up = (groups + s.num_shared) * nt_up <= 128;
-    int tm_up = c->gemm.tile_rows_up ? c->gemm.tile_rows_up : (s.T <= 256 && idle_up ? 128 : 256);
+    const int64_t pairs = (int64_t)s.T * s.top_k, groups = pairs < s.E ? pairs : s.E, tiles_up = (groups + s.num_shared) * nt_up;
+    int tm_up = c->gemm.tile_rows_up ? c->gemm.tile_rows_up : (s.T <= 256 && tiles_up <= 128 ? 128 : 256);
     int tm_down = c->gemm.tile_rows_down ? c->gemm.tile_rows_down : 256;
     int choose_up = s.T > 256 && !c->gemm.tile_rows_up && may_choose_rows(s, nt_up, s.num_shared);
     // tiles above 256 rows exist for the 4-wave, 1-wave-row kernel only
@@ -473,19 +473,21 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // (256 MB); a small layer called again and again finds its weights there (tiny layer, 25 MB, 256 tokens: 31.5 us
     // without, 34.5 with them).
     const bool nt = (int64_t)(s.E + s.num_shared) * 6 * s.H * s.F > ((int64_t)256 << 20);
-    // Up to a thousand tokens the shared experts' tiles of the down GEMM stay low (list_cut in plan.h).
-    const bool low_shared = s.num_shared > 0 && s.T <= 1024 && !c->gemm.tile_rows_down;
+    // Shared experts' tiles of at most 128 rows (list_cut in plan.h): gate/up as above, down up to a thousand tokens.
+    const bool low_up = s.num_shared > 0 && s.T <= 256 && tiles_up <= 256 && !c->gemm.tile_rows_up;
+    const bool low_down = s.num_shared > 0 && s.T <= 1024 && !c->gemm.tile_rows_down;
     FfnSetup f;
     f.nt = nt;
     f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
-                      nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, nt, low_shared, ps.e_lo, ps.e_hi, ps.shared_on,
+                      nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, nt, (low_up ? 1 : 0) | (low_down ? 2 : 0), ps.e_lo, ps.e_hi, ps.shared_on,
                       dsp, 4, split_rule_tiles, 149 - 79000 / s.F, tall, tall, (SplitTail*)(ws + L.split_tails), (PlanHeader*)(ws + L.plan),
                       (TileDesc*)(ws + L.descs_up), (TileDesc*)(ws + L.descs_down)};
     f.sm = sm;
     f.mtiles_up = ps.mtiles_up > 0 ? ps.mtiles_up : (sm.up ? sm.mtiles_up : (int)max_mtiles(s, choose_up ? 128 : tm_up));
     f.mtiles_down = (ps.mtiles_down > 0 ? ps.mtiles_down : (sm.down ? sm.mtiles_down : (int)max_mtiles(s, choose_down ? 128 : tm_down))) +
                     s.E * (dsp - 1);
-    if (low_shared) f.mtiles_down += (s.T + 127) / 128;
+    if (low_up) f.mtiles_up += s.num_shared * ((s.T + 127) / 128);
+    if (low_down) f.mtiles_down += (s.T + 127) / 128;
     f.group_m_up = pick_group_m(c, s, tm_up);
     f.group_m_down = pick_group_m(c, s, tm_down);
     return f;

@@ -68,11 +68,11 @@ __device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, cons
 // The cut of one group for list `which` (0 gate/up, 1 down) with height cap tm; the cost of a list below and
 // the list itself both use it.
 // Shared experts next to short routed groups (up to about a thousand tokens): theirs are the longest
-// tiles.  Down GEMM, where they walk all shared experts' K: 128 rows at most unless the height is set by option
-// (64 experts + 2 shared, 300 tokens 96 -> 85 us, 500: 92 -> 90).  Gate/up: not cut evenly up to 512 tokens, so
-// that the short rest goes last (500 tokens: 147 -> 143 us).
+// tiles.  Down GEMM, where they walk all shared experts' K, and small gate/up launches: 128 rows at most unless
+// the height is set by option (down GEMM, 64 experts + 2 shared, 300 tokens 96 -> 85 us, 500: 92 -> 90).  Gate/up:
+// not cut evenly up to 512 tokens, so that the short rest goes last (500 tokens: 147 -> 143 us).
 __device__ __forceinline__ GroupCut list_cut(const PlanArgs& p, const int which, const bool shared, const int rows, const int tm) {
-    return cut_group(rows, which == 1 && shared && p.low_shared ? min(tm, 128) : tm, (which == 0 ? p.tall_up : p.tall_down) != 0,
+    return cut_group(rows, shared && ((p.low_shared >> which) & 1) ? min(tm, 128) : tm, (which == 0 ? p.tall_up : p.tall_down) != 0,
                      !shared || which == 1 || p.T > 512);
 }
 

@@ -76,6 +76,7 @@ CHOICES = [
     # gate/up GEMM, groups of 129 to 256 rows as one tile or two
     (168, 3200, 5376, 5, 4, 0, "ffn_gate_up", {"gemm_tile_rows_up": 256}),
     (142, 1408, 2048, 15, 6, 1, "ffn_gate_up", {"gemm_tile_rows_up": 256}),
+    (143, 3328, 2112, 5, 1, 4, "ffn_gate_up", {"gemm_tile_rows_up": 128}),
     # gate/up GEMM, tall shared groups next to short routed ones in less than a round of tiles
     (300, 2560, 1536, 8, 1, 4, "ffn_gate_up", {"gemm_tile_rows_up": 128}),
     # gate/up GEMM, short tails of tall shared groups in less than a round
