@@ -423,7 +423,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const Layout L = make_layout(s);
     const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;
     // Up to 256 tokens a group of 129 to 256 rows is two tiles in a launch that would have tiles for half of the CUs at
-    // most, and a shared expert's in one of up to a round: as one it would be the longest tile by itself
+    // most, and a shared expert's in one of up to a round, the added tiles included: as one it would be the longest tile by itself
     // (148 tokens, 4 experts + 4 shared, H = 2112, F = 768: gate/up 48 -> 38 us; 156 tokens, 5 top-1 + 4 shared, H = 2304, F = 2112:
     // 56 -> 45).  With more tiles the second pass over its W panels costs more (15 experts top-6 + 1 shared, H = 1408,
     // F = 2048, 142 tokens: 37 us in one tile, 45 in two; 5 experts top-4, H = 3200, F = 5376, 168 tokens: 80, 101;
@@ -474,7 +474,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // without, 34.5 with them).
     const bool nt = (int64_t)(s.E + s.num_shared) * 6 * s.H * s.F > ((int64_t)256 << 20);
     // Shared experts' tiles of at most 128 rows (list_cut in plan.h): gate/up as above, down up to a thousand tokens.
-    const bool low_up = s.num_shared > 0 && s.T <= 256 && tiles_up <= 256 && !c->gemm.tile_rows_up;
+    const bool low_up = s.num_shared > 0 && s.T <= 256 && tiles_up + (int64_t)s.num_shared * nt_up <= 256 && !c->gemm.tile_rows_up;
     const bool low_down = s.num_shared > 0 && s.T <= 1024 && !c->gemm.tile_rows_down;
     FfnSetup f;
     f.nt = nt;
