@@ -1,5 +1,6 @@
 // C-ABI layer: argument validation, workspace carving, weight pointer tables, profiling events.
 // Every step of the path runs in the kernels of this library; this file only enqueues them.
+#include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -340,6 +341,9 @@ int call_down_splits(const moe_ctx* c, const moe_shape& s) {
     return down_tail_splits(s);
 }
 
+// A down launch of short tails only is cut along K up to this many tiles (plan_lists).
+int split_room_tiles(const moe_shape& s) { return 149 - 79000 / s.F; }
+
 // Which of the two GEMMs of a small batch run one wavefront per 16 or 32 output columns (ffn_small.hip).
 // Measured with cold weights against the tile routine, us (tile -> small):
 //   gate/up  64 experts top-6 + 2 shared, F = 1408: 1 token 28 -> 20, 4: 40 -> 42, 8: 68 -> 70, 16: 100 -> 89, 32: 110 -> 115;
@@ -353,7 +357,7 @@ int call_down_splits(const moe_ctx* c, const moe_shape& s) {
 // than the idle CUs from then on), and up to 128 when the tile routine would have tiles for a quarter of
 // the CUs at most.  The tile routine is ahead (by 10 % at most) where its launch is one full round.
 // Down: up to 64 tokens with at most 16 rows per group on average, except in launches of eight rounds of
-// tiles and more; and wherever small_down_wins says so.
+// tiles and more; and in launches of few tiles where small_down_wins says so.
 constexpr int SMALL_TILE_ROWS = 128;
 struct SmallRule {
     bool up, down;
@@ -363,23 +367,23 @@ struct SmallRule {
     int mtiles_up, mtiles_down;   // m-tiles of SMALL_TILE_ROWS rows at most (also if a token picks an expert twice)
 };
 
-// The down GEMM of few groups of any height up to 256 tokens (tiles for a quarter of the CUs at most).  The tile
-// routine then takes the longest tile's walk along K, 0.42 us a sub-tile (shared experts: all of theirs; with K
-// pieces a part and 10 us), or the time to read W.  In ffn_small.hip every 64 rows of a group read W again and
+// The down GEMM of few groups of any height (up to 64 tokens a round of tiles, up to 256 tokens tiles for a quarter of
+// the CUs).  The tile routine then takes the longest tile's walk along K, 0.42 us a sub-tile (shared experts: all of
+// theirs; K pieces, where plan_lists cuts: a part, and 10 us), or the time to read W.  In ffn_small.hip every 64 rows of a group read W again and
 // every 16 or 32 columns X, together at about 10.5 TB/s, or a unit's walk along K takes longest, 0.14 to 0.26 us
 // a sub-tile by its height.  15 % covers what the estimates miss by (tile -> small, us: 4 experts of 4,
 // H = 4096, F = 3072: 16 tokens 29 -> 25, 64: 32 -> 32, 96: 33 -> 42, 256: 53 -> 81; 4 experts top-2 + 2 shared,
 // H = 2048, F = 1408: 4: 38 -> 13, 256: 47 -> 30; 7 experts top-2, H = 2240, F = 7808: 110: 52 -> 74).
-bool small_down_wins(const moe_shape& s, int groups, int splits, int cols) {
+bool small_down_wins(const moe_shape& s, int groups, int tiles, int splits, int cols) {
     const double rows = (double)s.T * s.top_k / groups, matrix = 2.0 * s.F * s.H;
     const double x_bytes = 2.0 * s.T * (s.top_k + s.num_shared) * s.F * (s.H / (16 * cols));
     const double w_bytes = matrix * (groups * (int)((rows + 63) / 64) + s.num_shared * ((s.T + 63) / 64));
     const double steps = s.F / 32 * (s.num_shared > 1 ? s.num_shared : 1);
-    const double most = s.num_shared > 0 ? s.T : rows;
+    const double spread = rows + 2 * sqrt(rows), most = s.num_shared > 0 || spread > s.T ? s.T : spread;   // rows of the tallest group
     const double walk = steps * (most <= 16 ? 0.14 : (most <= 32 ? 0.18 : 0.26)), reads = (w_bytes + x_bytes) / 10.5e6;
-    const int pieces = s.num_shared == 0 && rows <= 128 ? splits : 1;
-    const double tile_walk = steps / pieces * 0.42 + (pieces > 1 ? 10 : 0), tile_reads = matrix * (groups + s.num_shared) / 5.8e6;
-    return 1.15 * (walk > reads ? walk : reads) < (tile_walk > tile_reads ? tile_walk : tile_reads);
+    const int pieces = s.num_shared == 0 && rows <= 128 && tiles <= split_room_tiles(s) ? splits : 1;
+    const double tile_walk = steps / pieces * 0.42, tile_reads = matrix * (groups + s.num_shared) / 5.8e6;
+    return 1.15 * (walk > reads ? walk : reads) < (tile_walk > tile_reads ? tile_walk : tile_reads) + (pieces > 1 ? 10 : 0);
 }
 
 SmallRule small_rule(const moe_ctx* c, const moe_shape& s) {
@@ -392,7 +396,8 @@ SmallRule small_rule(const moe_ctx* c, const moe_shape& s) {
     r.down_cols = s.T <= 32 ? 1 : 2;
     r.up = allowed && (s.T <= 16 || (s.T <= 128 && tiles_up <= 64));
     r.down = allowed && ((s.T <= 64 && pairs <= 16 * (int64_t)groups && tiles_down < 8 * 256) ||
-                         (s.T <= 256 && tiles_down <= 64 && small_down_wins(s, groups, call_down_splits(c, s), r.down_cols)));
+                         (s.T <= 256 && tiles_down <= (s.T <= 64 ? 256 : 64) &&
+                          small_down_wins(s, groups, tiles_down, call_down_splits(c, s), r.down_cols)));
     r.halves = s.T <= 64 ? 1 : 2;
     r.once = s.T <= 64 || (s.num_shared == 0 && pairs <= 52 * (int64_t)groups);
     const int routed = groups + (int)(pairs / SMALL_TILE_ROWS), per_shared = (s.T + SMALL_TILE_ROWS - 1) / SMALL_TILE_ROWS;
@@ -480,7 +485,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     f.nt = nt;
     f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
                       nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, nt, (low_up ? 1 : 0) | (low_down ? 2 : 0), ps.e_lo, ps.e_hi, ps.shared_on,
-                      dsp, 4, split_rule_tiles, 149 - 79000 / s.F, tall, tall, (SplitTail*)(ws + L.split_tails), (PlanHeader*)(ws + L.plan),
+                      dsp, 4, split_rule_tiles, split_room_tiles(s), tall, tall, (SplitTail*)(ws + L.split_tails), (PlanHeader*)(ws + L.plan),
                       (TileDesc*)(ws + L.descs_up), (TileDesc*)(ws + L.descs_down)};
     f.sm = sm;
     f.mtiles_up = ps.mtiles_up > 0 ? ps.mtiles_up : (sm.up ? sm.mtiles_up : (int)max_mtiles(s, choose_up ? 128 : tm_up));

@@ -139,3 +139,27 @@ def test_weight_bytes_cost_the_same_on_both_sides_of_the_cache_size(moe):
         print("F", F, "%d MB" % (6 * E * H * F >> 20), "%.4f ms" % ms[len(ms) // 2], flush=True)
         per_byte.append(ms[len(ms) // 2] / F)
     assert per_byte[1] <= 1.06 * per_byte[0]
+
+
+def test_a_few_tokens_more_do_not_change_the_time_by_half(moe):
+    """Down GEMM of 6 experts of 6 and two shared ones: 16 and 20 tokens read the same weights, and the walk along the shared
+    experts' K, which the tile routine has to make in one piece, is as long.  10 to 20 % are the second block of 16 rows."""
+    from paper_2503_09716_amd import make_shape
+    H, F, E, k, shared = 2944, 1728, 6, 6, 2
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    normal = lambda *size, std=0.02: torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    sets = [[[normal(H * F) for _ in range(E + shared)] for _ in range(3)] for _ in range(3)]   # 240 MB each
+    x, wg, out = normal(20, H, std=1.0), normal(H, E), normal(20, H)
+    ms = []
+    for T in (16, 20):
+        shape = make_shape(T, H, F, E, k, shared, True)
+        ws = moe.new_workspace(shape)
+        for on in (False, True):
+            moe.profile_enable(on)
+            for i in range(60 if on else 6):
+                moe.layer(shape, x[:T].contiguous(), wg, None, *sets[i % 3], out[:T], ws)
+        times = sorted(moe.profile_read_intervals()["ffn_down"])
+        moe.profile_enable(False)
+        ms.append(times[len(times) // 2])
+    print("16 tokens %.4f ms, 20 tokens %.4f ms" % tuple(ms), flush=True)
+    assert ms[1] <= 1.4 * ms[0]
