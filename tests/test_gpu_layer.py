@@ -614,3 +614,38 @@ def test_layer_small_batches_give_the_tile_routine_s_bits(moe, T, H, F, E, k, sh
     assert torch.equal(out, ref) and torch.equal(out16, ref16)
     if y_fp32 and F >= 128:
         say(json.dumps(P.check_layer_against_oracle(gl, out, out16=out16)["output"]))
+
+
+# Layers just above 256 MB, whose weights are loaded non-temporally where one tile or wave reads them: (H, F, experts, k); the second
+# shape has few enough tiles for one wavefront per 32 columns up to 128 tokens.
+READ_ONCE_SHAPES = [(4096, 3072, 4, 2), (4096, 3072, 4, 4), (8192, 1408, 4, 2), (8192, 1408, 4, 4)]
+
+
+@pytest.mark.parametrize("H,F,E,k", READ_ONCE_SHAPES)
+def test_layer_weights_read_once_give_the_tile_routine_s_bits(moe, H, F, E, k):
+    """Groups of up to 64 rows, of 65 to 128 (one tile of the non-temporal variants, or two waves per panel) and above, against
+    small_tiles = 0, which runs every tile on the 256-row variant with ordinary loads."""
+    cfg = scaled_config("C2", T=256, H=H, F=F, E=E, top_k=k)
+    li = make_layer_inputs(cfg, device="cuda")
+    gl = P.GpuLayer(moe, li, host_weights=False)
+    moe.set_option("layer_y_fp32", 1)
+    moe.set_option("down_tail_splits", 0)
+    try:
+        for T in (16, 65, 100, 128, 129, 200, 256):
+            say("read once", cfg, "tokens", T)
+            gl.shape.T = T
+            gl.x = li.x[:T].contiguous()
+            got = []
+            for small_tiles in (1, 0):
+                moe.set_option("small_tiles", small_tiles)
+                out = torch.empty((T, H), dtype=torch.float32, device="cuda")
+                moe.set_option("out_fp32", 1)
+                moe.layer(gl.shape, gl.x, gl.wg, gl.bias, gl.w1p, gl.w3p, gl.w2p, out, gl.ws, tables=gl.tables)
+                torch.cuda.synchronize()
+                got.append(out)
+            assert torch.equal(*got), T
+    finally:
+        moe.set_option("out_fp32", 0)
+        moe.set_option("small_tiles", 1)
+        moe.set_option("layer_y_fp32", -1)
+        moe.set_option("down_tail_splits", 1)

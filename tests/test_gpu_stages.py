@@ -624,3 +624,47 @@ def test_heights_are_chosen_for_the_list_that_is_built(moe):
     down = lists_of(moe, 300, 2048, 128, 4, 2, 2, [150] * 4)[1]
     assert sorted(n for g, _, n, _, _ in down if g >= 4) == [44, 128, 128]
     assert [n for g, _, n, _, _ in down if g < 4] == [150] * 4
+
+
+ONCE, FULL = 1, 2    # marks of a listed m-tile: its W panel is read once; it runs the 256-row variant
+
+# Groups of four tiles and more at a cap of 256 rows: the rest is a short tail, one of 129 to 224 rows that keeps the
+# 256-row variant, one above that, one that joins the last full tile, and none.
+LONG_COUNTS = [3 * 256 + 65, 3 * 256 + 129, 3 * 256 + 161, 3 * 256 + 193, 4 * 256 + 224, 3 * 256 + 225, 4 * 256 + 1, 3 * 256]
+
+
+def test_grouped_ffn_rest_of_long_groups(moe):
+    counts = np.array(LONG_COUNTS)
+    E, T = len(counts), int(counts.sum())
+    options = dict(gemm_tile_rows_up=256, gemm_tile_rows_down=256)
+    for tiles in lists_of(moe, T, 128, 128, E, 1, 0, LONG_COUNTS, **options):
+        assert sorted(n for _, _, n, _, marks in tiles if marks & FULL) == [129, 161, 193, 224]
+    cfg = scaled_config("C4", T=T, H=128, F=128, E=E, top_k=1, num_shared=0)
+    idx_h = np.repeat(np.arange(E, dtype=np.int32), counts)
+    idx_h = idx_h[np.random.default_rng(6).permutation(T)].reshape(T, 1)
+    for key, value in options.items():
+        moe.set_option(key, value)
+    try:
+        y, _, perm, off, li = run_ffn_stage(moe, cfg, idx_h, wave_rows=1)
+    finally:
+        for key in options:
+            moe.set_option(key, 0)
+    u = torch_bf16_to_u16
+    ref = orc.expert_rows(u(li.x)[perm], np.repeat(np.arange(E, dtype=np.int32), counts), [u(t) for t in li.w1],
+                          [u(t) for t in li.w3], [u(t) for t in li.w2])
+    say(P.assert_output(y.float().cpu().numpy(), ref, "y_perm"))
+
+
+@pytest.mark.parametrize("T,H,F,E,k,shared,counts,rows_up,want_up", [
+    # every group one tile; one of two tiles; a layer of less than 256 MB
+    (100, 4096, 3072, 4, 4, 0, [100] * 4, 0, {100: ONCE}),
+    (600, 4096, 3072, 4, 1, 0, [400, 200, 0, 0], 256, {224: 0, 176: 0, 200: ONCE}),
+    (100, 1024, 1024, 4, 4, 0, [100] * 4, 0, {100: 0}),
+    # a short tail, moved behind the other tiles: next to its group's in a launch of one round, later in a longer one
+    (140, 4544, 1408, 9, 1, 2, [20] * 6 + [10, 10, 0], 0, {128: 0, 12: 0, 20: ONCE, 10: ONCE}),
+    (6736, 2048, 1408, 64, 2, 0, [3 * 256 + 74] * 16 + [0] * 48, 0, {256: 0, 74: ONCE}),
+])
+def test_marks_of_tiles_whose_weights_are_read_once(moe, T, H, F, E, k, shared, counts, rows_up, want_up):
+    up = lists_of(moe, T, H, F, E, k, shared, counts, down_tail_splits=0, gemm_tile_rows_up=rows_up, gemm_tile_rows_down=256)[0]
+    got = {n: marks & ONCE for _, _, n, _, marks in up}
+    assert {n: got.get(n) for n in want_up} == want_up, up
