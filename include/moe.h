@@ -106,8 +106,12 @@ size_t moe_h_scratch_bytes(const moe_shape* shape);
  *                             is treated as 1), 2 or 4 with 8 waves (1 row is treated as 2)
  *   "gemm_group_m"    0..64   m-tiles swept together along n (L2 reuse of weight panels); 0 (default) picks
  *                             the typical number of tiles per expert, between 4 and 8
- *   "xcd_remap"       0 | 1   give each XCD runs of consecutive tiles
- *   "small_tiles"     0 | 1   use 128/64/32-row tiles for the ragged tail of an expert
+ *   "xcd_remap"       0 | 1   give each XCD runs of consecutive tiles (32, or 8 in short launches next to shared experts)
+ *   "small_tiles"     0 | 1   1 (default): every m-tile runs the lowest variant (32, 64, ... rows) that holds it, and small
+ *                             batches run one wavefront per 16 or 32 output columns instead of m-tiles, where it pays.
+ *                             0: tiles of up to 256 rows all run the 256-row variant.  Same results bit for bit
+ *                             where "down_tail_splits" cuts nothing ("gemm_waves", "gemm_wave_rows", "gemm_group_m",
+ *                             "xcd_remap" and "tails_last" do not apply to GEMMs without m-tiles)
  *   "gemm_tile_rows_up" / "gemm_tile_rows_down"  0 | 128 | 256 | 320   most rows per m-tile of the gate/up
  *                             and the down GEMM (groups of two or three tiles are cut evenly below that; "tall_tiles"
  *                             adds to 256); 0 (default) picks per launch from the tile count and the rows per expert
@@ -116,17 +120,18 @@ size_t moe_h_scratch_bytes(const moe_shape* shape);
  *                             where "down_tail_splits" cuts nothing.
  *   "x_tiled"         -1|0|1  moe_layer: 1 gathers x once into a block-tiled x_perm that the gate/up GEMM
  *                             loads in 1 KiB pieces, 0 fuses the gather into that GEMM's loads, -1 (default)
- *                             chooses by expert width.  Same results bit for bit.
+ *                             chooses by expert width and rows per expert.  Same results bit for bit.
  *   "tails_last"      -1|0|1  order of a GEMM's tiles: 1 or -1 (default) = every expert's short tail tile (at most
  *                             half a tile high) after all other tiles, longest first; 0 = behind its own
  *                             expert's tiles.  Same results bit for bit.
  *   "down_tail_splits" 0|1|2  with at most 32 experts the down projection can cut the contraction range of an
  *                             expert's short tail tile into 2 or 4 pieces run by different CUs and add the fp32
- *                             partial sums afterwards in fixed order.  0: never; 2: every eligible tail;
+ *                             partial sums afterwards in fixed order.  0: never; 2: every eligible tail (both
+ *                             GEMMs of a small batch then stay on m-tiles);
  *                             1 (default): where it pays, decided on the device from the call's tile counts
- *                             (launches in which every tile is a short tail, i.e. a few tokens per expert, and too few
- *                             of them read W to be bound by that, and launches many rounds of tiles long).  Cutting changes the summation order of
- *                             those rows only: results are deterministic for given inputs and options, but not
+ *                             (launches in which every tile is a short tail, i.e. a few tokens per expert, and that are
+ *                             not bound by reading the weights, and launches many rounds of tiles long).  Cutting
+ *                             changes the summation order of those rows only: results are deterministic for given inputs and options, but not
  *                             bit-identical between the three settings, nor, under 1, between calls that
  *                             cover the same tokens in differently sized passes.
  *   "tall_tiles"    -1|0|1|2  an expert's tail of at most 64 rows joins its last full 256-row tile (a tile of up to

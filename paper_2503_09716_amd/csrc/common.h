@@ -63,7 +63,7 @@ struct GemmArgs {
     int32_t n_tiles;           // tiles along N
     int32_t max_mtiles;        // grid = max_mtiles * n_tiles
     int32_t group_m;
-    int32_t small_tiles;       // 1: a short tail tile runs the 128/64/32-row variant
+    int32_t small_tiles;       // 1: a tile runs the lowest variant that holds its rows, 0: the 256-row one
     int32_t out_fp32;          // GEMM2: output stored as fp32 (else bf16): bit 0 routed tiles, bit 1 shared tiles (GEMM1 always stores bf16)
     int32_t lda_bytes;         // row stride of a row-major A operand
     int32_t kt_w;              // 1 KiB blocks per 16-row group of the packed W (its full K / 32)

@@ -44,10 +44,11 @@
 //   * ragged tails: rows past the end of a group are clamped on load and masked on store;
 //     a tile runs the lowest variant that holds its rows, so padded MFMA work stays small.
 //
-// Work distribution: a device-built list of m-tiles (ffn_plan) x n-tiles; workgroup ids are
+// Work distribution: a device-built list of m-tiles (plan.h) x n-tiles; workgroup ids are
 // remapped so each XCD (ids are dealt round-robin over the 8 XCDs) receives runs of 32
-// consecutive tiles, and consecutive tiles sweep `group_m` m-tiles before moving along n, so
-// the tiles resident on one XCD share weight panels and X panels in its L2.
+// consecutive tiles (8 in short launches next to shared experts), and consecutive tiles sweep
+// `group_m` m-tiles before moving along n, so the tiles resident on one XCD share weight panels
+// and X panels in its L2.
 #include <type_traits>
 
 #include "common.h"
@@ -517,7 +518,7 @@ __device__ __forceinline__ bool pick_tile(const GemmArgs& p, const bool gated, T
     }
     const int count = gated ? p.plan->n_gate_up : p.plan->n_down;
     const int n_run = gated ? p.plan->n_run_up : p.plan->n_run_down;
-    // Only whole rounds of 256 REAL tiles are dealt to the XCDs in runs of 32 (the grid is an upper
+    // Only whole rounds of 256 REAL tiles are dealt to the XCDs in runs of 32, stretches of 64 in runs of 8 (the grid is an upper
     // bound of the tile count, and how far the runs reach must not depend on it); the last,
     // partial round keeps the hardware's own order, which spreads it over all eight XCDs.  In
     // runs it would sit on the first few XCDs and leave the L2s and fabric links of the others

@@ -84,9 +84,9 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[u][i], wf[u][j], acc[j][i], 0, 0, 0);
     };
     // Sub-tile t sits in ring place t % RING (counted from the segment's start), and a place is
-    // refilled right after its last use.  No load is inside a branch (the compiler would have to wait
-    // for all loads behind it): past the end of K the places take the first sub-tiles of the next
-    // segment, or re-read the last sub-tile.
+    // refilled right after its last use.  No load in the loop over K is inside a branch (the compiler would have to
+    // wait for all loads behind it): past the end of K the places take the first sub-tiles of the next
+    // segment, or re-read the last sub-tile.  (The branch after it, once per segment, only loads where there is a next one.)
 #pragma unroll
     for (int u = 0; u < RING; ++u) load(u, xb, wa, min(u, KT - 1));
     for (int seg = 0; seg < nseg; ++seg) {

@@ -125,8 +125,8 @@ __device__ __forceinline__ float list_cost(const PlanArgs& p, const int which, c
 // from expert_offsets.  Group order: shared expert 0, routed experts, shared experts 1.. (the down
 // GEMM takes the first two parts only: shared experts are concatenated along K there).
 // cut_group says how a group's rows become tiles.  A tail higher than
-// half a tile runs the full-height variant and always stays with its group; a short tail runs
-// a short variant.  tails_last = 0: the short tail, too, directly follows its group's tiles,
+// half a tile always stays with its group (on the variant that holds it, or the 256-row one after three
+// full tiles and more: TILE_FULL).  tails_last = 0: the short tail, too, directly follows its group's tiles,
 // which keeps the load-bound short tiles mixed with the compute-bound full ones (better when
 // a launch has many rounds of tiles).  tails_last = 1: the short tails follow all other tiles,
 // sorted by falling height, ties in group order, so a launch with few rounds ends on its
@@ -194,9 +194,9 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
         const GroupCut cut = list_cut(p, which, group >= E, mine ? rows : 0, tm);
         const int nfull = cut.nfull, tail = cut.tail, joined = cut.joined, h = cut.h;
         const int blocks = (tail + 31) >> 5;   // 32-row blocks of the tail tile, 0 = none
-        // A tail higher than half a tile runs the full-height variant and takes as long as a full
-        // tile, so it stays with its group (keeps the group's W panels shared and the CUs in
-        // step); only a short tail is moved to the end of the list.
+        // A tail higher than half a tile takes nearly as long as a full tile, so it stays with its
+        // group (keeps the group's W panels shared and the CUs in step); only a short tail is moved
+        // to the end of the list.
         // (A shared expert's tail is not moved in a down list with K pieces: the pieces' partial
         // sums are reduced into y_perm, while shared rows belong to y_shared.)
         // (at most 128 rows: the K pieces' partial buffers hold SPLIT_TAIL_ROWS rows)
