@@ -475,7 +475,8 @@ def main():
         "gate_up": head["gate_up"], "down": head["down"],
         "stage_ms": head["stage_ms"],
         "timing": "ms_per_step / value: %d steps between two synchronisations, no events on the stream; step_ms and stage_ms: "
-                  "a second loop of %d steps with HIP events (median, min)" % (args.steps, args.steps),
+                  "a second loop of %d steps with HIP events (median, min); while stages are timed the m-tile lists are "
+                  "built in a launch of their own (stage plan), in the timed steps next to the permutation" % (args.steps, args.steps),
         "roofline": roofline,
     }
     if not args.no_hbm_stages:
