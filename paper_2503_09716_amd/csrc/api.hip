@@ -444,7 +444,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // that GEMM; not when an expert is only about four tiles (C2: 1024 rows = 3 tiles + a tail
     // that needs a pass of its own, +10 %).  In the down GEMM the 320-row variant measures within
     // 1 % of the 256-row one either way, so it keeps 256.
-    if (!c->gemm.tile_rows_up && tall_kernel && !choose_up && (double)s.T * s.top_k / s.E >= 1200.0) tm_up = 320;
+    if (!c->gemm.tile_rows_up && tall_kernel && (double)s.T * s.top_k / s.E >= 1200.0) tm_up = 320;
     if (!tall_kernel && tm_up > 256) tm_up = 256;
     if (!tall_kernel && tm_down > 256) tm_down = 256;
     // Short tail tiles go last by default: the other tiles of a launch then all take the same

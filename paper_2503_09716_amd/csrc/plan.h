@@ -88,8 +88,10 @@ __device__ __forceinline__ GroupCut list_cut(const PlanArgs& p, const int which,
 // expert of 250 rows is two tiles of 128: the down GEMM of eight such experts fills the chip
 // with one round of 256 tiles instead of half a round of 256-row ones (8x7B, 1000 tokens:
 // 310 -> 268 us).
-constexpr int PLAN_CAPS = 5;
-__device__ constexpr int plan_cap(const int c) { return 256 - 32 * c; }
+// Candidates: the cap the host passes (256, or 320 for experts of many rows: 2 experts of 1583 rows, H = 2816, F = 2752 are
+// 220 tiles of 320 rows, one round, and 264 of 256: gate/up 87 and 115 us), 256, 224, ... 128.
+constexpr int PLAN_CAPS = 6;
+__device__ constexpr int plan_cap(const int c, const int tm) { return c == 0 ? tm : 288 - 32 * c; }
 
 __device__ __forceinline__ float list_cost(const PlanArgs& p, const int which, const int* rows, const int ngroups, const int nseg0,
                                            const int tm, const int n_tiles, const int lane) {
@@ -172,7 +174,7 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
             const int groups = which == 0 ? ngroups : (Ns > 0 ? E + 1 : E);
             const int nseg0 = which == 1 && Ns > 1 ? Ns : 1, nt = which == 0 ? p.nt_up : p.nt_down;
             // (one copy of the code for all caps: what this costs is mostly fetching its instructions)
-            const float cost = list_cost(p, which, group_rows, groups, nseg0, plan_cap(c), nt, lane);
+            const float cost = list_cost(p, which, group_rows, groups, nseg0, plan_cap(c, tm_of[which]), nt, lane);
             if (lane == 0) cap_cost[which][c] = cost;
         }
         __syncthreads();
@@ -181,7 +183,7 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
             if (!(which == 0 ? p.choose_up : p.choose_down)) continue;
             float best = cap_cost[which][0] * 0.97f;   // the tallest unless another is clearly cheaper
             for (int c = 1; c < PLAN_CAPS; ++c)
-                if (cap_cost[which][c] < best) { best = cap_cost[which][c]; tm_of[which] = plan_cap(c); }
+                if (cap_cost[which][c] < best) { best = cap_cost[which][c]; tm_of[which] = plan_cap(c, 0); }
         }
     }
     for (int which = 0; which < 2; ++which) {
