@@ -478,9 +478,12 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // (256 MB); a small layer called again and again finds its weights there (tiny layer, 25 MB, 256 tokens: 31.5 us
     // without, 34.5 with them).
     const bool nt = (int64_t)(s.E + s.num_shared) * 6 * s.H * s.F > ((int64_t)256 << 20);
-    // Shared experts' tiles of at most 128 rows (list_cut in plan.h): gate/up as above, down up to a thousand tokens.
+    // Shared experts' tiles of at most 128 rows (list_cut in plan.h): gate/up as above, down up to a thousand tokens where
+    // that does not make a second round of the first (10 experts top-1 + 1 shared, H = 4544, F = 9088, 898 tokens: down 211 us, with the
+    // cap 264; of 312 points with shared experts the cap is the better choice in all but six others).
     const bool low_up = s.num_shared > 0 && s.T <= 256 && tiles_up + (int64_t)s.num_shared * nt_up <= 256 && !c->gemm.tile_rows_up;
-    const bool low_down = s.num_shared > 0 && s.T <= 1024 && !c->gemm.tile_rows_down;
+    const int64_t low_tiles = (groups + (s.T + 127) / 128) * nt_down, high_tiles = (groups + (s.T + 255) / 256) * nt_down;
+    const bool low_down = s.num_shared > 0 && s.T <= 1024 && !c->gemm.tile_rows_down && (low_tiles <= 256 || high_tiles > 256);
     FfnSetup f;
     f.nt = nt;
     f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,

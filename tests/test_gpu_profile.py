@@ -73,6 +73,8 @@ CHOICES = [
     (100, 6144, 8192, 8, 2, 0, "ffn_down", {"down_tail_splits": 0}),
     (100, 2240, 7808, 7, 2, 0, "ffn_down", {"down_tail_splits": 0}),
     (98, 1728, 2560, 12, 1, 0, "ffn_down", {"down_tail_splits": 2}),
+    # down GEMM, shared experts' tiles lower or not
+    (898, 4544, 9088, 10, 1, 1, "ffn_down", {"gemm_tile_rows_down": 256}),
     # gate/up GEMM, groups of 129 to 256 rows as one tile or two
     (168, 3200, 5376, 5, 4, 0, "ffn_gate_up", {"gemm_tile_rows_up": 256}),
     (142, 1408, 2048, 15, 6, 1, "ffn_gate_up", {"gemm_tile_rows_up": 256}),
