@@ -428,9 +428,9 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const Layout L = make_layout(s);
     const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;
     // Up to 256 tokens a group of 129 to 256 rows is two tiles in a launch that would have tiles for half of the CUs at
-    // most, and a shared expert's in one of up to a round, the added tiles included: as one it would be the longest tile by itself
-    // (148 tokens, 4 experts + 4 shared, H = 2112, F = 768: gate/up 48 -> 38 us; 156 tokens, 5 top-1 + 4 shared, H = 2304, F = 2112:
-    // 56 -> 45).  With more tiles the second pass over its W panels costs more (15 experts top-6 + 1 shared, H = 1408,
+    // most, and a shared expert's in one of up to a round, the added tiles included (low_up below): as one it would
+    // be the longest tile by itself (148 tokens, 4 experts + 4 shared, H = 2112, F = 768: gate/up 48 -> 38 us; 156
+    // tokens, 5 top-1 + 4 shared, H = 2304, F = 2112: 56 -> 45).  With more tiles the second pass over its W panels costs more (15 experts top-6 + 1 shared, H = 1408,
     // F = 2048, 142 tokens: 37 us in one tile, 45 in two; 5 experts top-4, H = 3200, F = 5376, 168 tokens: 80, 101;
     // 64 experts + 2 shared, F = 1408: 130 tokens 119, 126; 200 tokens 124, 120).
     const int64_t pairs = (int64_t)s.T * s.top_k, groups = pairs < s.E ? pairs : s.E, tiles_up = (groups + s.num_shared) * nt_up;
@@ -474,14 +474,18 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const double per_expert = (double)s.T * s.top_k / ((double)s.E * 256);
     int tall = c->gemm.tall_tiles >= 0 ? c->gemm.tall_tiles : (per_expert <= 8.0 ? 2 : 1);
     if (!tall_kernel) tall = 0;
-    // Non-temporal loads of weights that one tile (in ffn_small.hip: one unit, SmallRule::once) reads: only if the layer's weights exceed the memory-side cache
-    // (256 MB); a small layer called again and again finds its weights there (tiny layer, 25 MB, 256 tokens: 31.5 us
+    // Non-temporal loads of weights that one tile (in ffn_small.hip: one unit, SmallRule::once) reads: only if the
+    // layer's weights exceed the memory-side cache (256 MB); a small layer called again and again finds its weights there (tiny layer, 25 MB, 256 tokens: 31.5 us
     // without, 34.5 with them).
     const bool nt = (int64_t)(s.E + s.num_shared) * 6 * s.H * s.F > ((int64_t)256 << 20);
-    // Shared experts' tiles of at most 128 rows (list_cut in plan.h): gate/up as above, down up to a thousand tokens where
-    // that does not make a second round of the first (10 experts top-1 + 1 shared, H = 4544, F = 9088, 898 tokens: down 211 us, with the
-    // cap 264; of 312 points with shared experts the cap is the better choice in all but six others).
-    const bool low_up = s.num_shared > 0 && s.T <= 256 && tiles_up + (int64_t)s.num_shared * nt_up <= 256 && !c->gemm.tile_rows_up;
+    // Shared experts' tiles of at most 128 rows (list_cut in plan.h).  Gate/up: while a round holds them, as above and
+    // up to a thousand tokens next to routed groups of up to 128 rows on average (8 top-1 + 4 shared, H = 2560,
+    // F = 1536, 300 tokens: 71 -> 47 us; 8 top-1 + 1, H = 640, F = 2304, 550: 28 -> 20; but 16 top-8 + 1, H = 3712,
+    // F = 1280, 571 tokens = 285 rows each: 109 -> 147).  Down: up to a thousand tokens where that does not make a
+    // second round of the first (10 top-1 + 1, H = 4544, F = 9088, 898 tokens: 211 us, with the cap 264; over 312
+    // points the down GEMM takes 5 % longer on average without any cap).
+    const bool low_up = s.num_shared > 0 && s.T <= 1024 && (groups + s.num_shared * ((s.T + 127) / 128)) * nt_up <= 256 &&
+                        (s.T <= 256 || pairs <= 128 * groups) && !c->gemm.tile_rows_up;
     const int64_t low_tiles = (groups + (s.T + 127) / 128) * nt_down, high_tiles = (groups + (s.T + 255) / 256) * nt_down;
     const bool low_down = s.num_shared > 0 && s.T <= 1024 && !c->gemm.tile_rows_down && (low_tiles <= 256 || high_tiles > 256);
     FfnSetup f;

@@ -157,14 +157,9 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
         if (group < E ? (group < p.e_lo || group >= p.e_hi) : !p.shared_on) rows = 0;
     }
     int tm_of[2] = {p.tm_up, p.tm_down};
-    // Routed groups of at most 128 rows are one tile under every cap, and the shared experts by themselves are
-    // worth the 5 us that the choice takes only where each would be one tall tile in a gate/up launch that fills
-    // three quarters of the CUs at most (300 tokens: 8 experts top-1 + 4 shared, H = 2560, F = 1536, 144 tiles 72 -> 60 us;
-    // 6 top-1 + 1, H = 4096, F = 3072, 168 tiles 93 -> 68; but 20 top-2 + 1, H = 3072, F = 1408, 231 tiles 80 -> 86).
-    const bool choosing = p.choose_up || p.choose_down;
-    const int active = choosing ? __syncthreads_count(rows > 0) : 0;
-    const bool tall_shared = p.choose_up && p.T <= PLAN_MAX_ROWS && active * p.nt_up <= 192;
-    if (choosing && __syncthreads_or(rows > 128 && (group < E || tall_shared))) {
+    // routed groups of at most 128 rows are one tile under every cap, and the shared experts by themselves are
+    // not worth the 5 us that the choice takes (small launches: p.low_shared)
+    if ((p.choose_up || p.choose_down) && __syncthreads_or(group < E && rows > 128)) {
         group_rows[tid] = rows;
         __syncthreads();
         const int wave = tid >> 6, lane = tid & 63;

@@ -81,6 +81,7 @@ CHOICES = [
     (143, 3328, 2112, 5, 1, 4, "ffn_gate_up", {"gemm_tile_rows_up": 128}),
     # gate/up GEMM, tall shared groups next to short routed ones in less than a round of tiles
     (300, 2560, 1536, 8, 1, 4, "ffn_gate_up", {"gemm_tile_rows_up": 128}),
+    (550, 2560, 2304, 8, 1, 1, "ffn_gate_up", {"gemm_tile_rows_up": 128}),
     # gate/up GEMM of few wide experts: 320 rows, one round
     (3100, 8192, 2752, 2, 1, 0, "ffn_gate_up", {"gemm_tile_rows_up": 320}),
     # gate/up GEMM, short tails of tall shared groups in less than a round
