@@ -481,13 +481,15 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // Shared experts' tiles of at most 128 rows (list_cut in plan.h).  Gate/up: while a round holds them, as above and
     // up to a thousand tokens next to routed groups of up to 128 rows on average (8 top-1 + 4 shared, H = 2560,
     // F = 1536, 300 tokens: 71 -> 47 us; 8 top-1 + 1, H = 640, F = 2304, 550: 28 -> 20; but 16 top-8 + 1, H = 3712,
-    // F = 1280, 571 tokens = 285 rows each: 109 -> 147).  Down: up to a thousand tokens where that does not make a
-    // second round of the first (10 top-1 + 1, H = 4544, F = 9088, 898 tokens: 211 us, with the cap 264; over 312
-    // points the down GEMM takes 5 % longer on average without any cap).
+    // F = 1280, 571 tokens = 285 rows each: 109 -> 147).  Down: up to a thousand tokens, with one shared
+    // expert only where that does not make a second round of the first (10 top-1 + 1, H = 4544, F = 9088, 898
+    // tokens: 211 us, with the cap 264; but 46 top-4 + 2, whose shared tiles walk twice as far, H = 1152, F = 2048,
+    // 1000 tokens: 90 us, with the cap 65; over 312 points the down GEMM takes 5 % longer without any cap).
     const bool low_up = s.num_shared > 0 && s.T <= 1024 && (groups + s.num_shared * ((s.T + 127) / 128)) * nt_up <= 256 &&
                         (s.T <= 256 || pairs <= 128 * groups) && !c->gemm.tile_rows_up;
     const int64_t low_tiles = (groups + (s.T + 127) / 128) * nt_down, high_tiles = (groups + (s.T + 255) / 256) * nt_down;
-    const bool low_down = s.num_shared > 0 && s.T <= 1024 && !c->gemm.tile_rows_down && (low_tiles <= 256 || high_tiles > 256);
+    const bool low_down = s.num_shared > 0 && s.T <= 1024 && !c->gemm.tile_rows_down &&
+                          (s.num_shared > 1 || low_tiles <= 256 || high_tiles > 256);
     FfnSetup f;
     f.nt = nt;
     f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
