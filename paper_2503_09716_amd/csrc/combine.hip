@@ -2,63 +2,82 @@
 // (Sec. 2: the layer output is the weighted sum of the k experts' outputs, plus the shared
 // expert every token passes through.)
 //
-// combine: one workgroup per token; every lane owns 8 consecutive hidden elements (16 B) and
-// gathers the k expert rows of its token through inv_perm.  Sums are fp32 in the fixed order
-// j = 0..k-1 then shared, every output element is written exactly once: no atomics, and the
-// result is bit-identical from run to run.  HBM-bound: reads k+1 rows, writes 1 row per token.
+// combine: one thread per token and 16 bytes of its widest input (8 consecutive hidden elements where all rows are
+// bf16, else 4), which gathers the k expert rows of its token through inv_perm, all of them in flight at
+// once.  Sums are fp32 in the fixed order j = 0..k-1 then shared, every output element is written
+// exactly once: no atomics, and the result is bit-identical from run to run.  HBM-bound: reads k+1 rows,
+// writes 1 row per token.  Against one workgroup per token that walked its row 8 elements per thread and waited
+// for each expert's row before it asked for the next: 160 experts top-6 + 2 shared, H = 5120, 32768 tokens 614 -> 498 us
+// (3.0 GB = 6.0 TB/s), 64 experts, H = 2048, 16384 tokens 120 -> 94 us, 1 token 2 us less of the layer's 47.
 #include "common.h"
 
 namespace moe {
 namespace {
 
-// acc += w * (8 consecutive elements of a row, starting at element 8*c)
-template <bool F32>
-__device__ __forceinline__ void accum8(float (&acc)[8], const void* __restrict__ row, const int c, const float w) {
-    if (F32) {
-        const float4* p = reinterpret_cast<const float4*>(row) + 2 * c;
-        const float4 a = p[0], b = p[1];
-        const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+// N consecutive elements of a row, starting at element N*c, as they are stored.  NT: non-temporal
+template <bool F32, int N, bool NT>
+struct Piece {
+    typedef uint32_t words __attribute__((ext_vector_type(N * (F32 ? 4 : 2) / 4)));
+    words v;
+    __device__ __forceinline__ void load(const char* __restrict__ row, const int c) {
+        const words* p = reinterpret_cast<const words*>(row) + c;
+        v = NT ? __builtin_nontemporal_load(p) : *p;
+    }
+    // acc += w * piece
+    __device__ __forceinline__ void add_to(float (&acc)[N], const float w) const {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = fmaf(w, v[i], acc[i]);
-    } else {
-        const uint4 v = reinterpret_cast<const uint4*>(row)[c];
-        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            acc[2 * q] = fmaf(w, __uint_as_float(u[q] << 16), acc[2 * q]);
-            acc[2 * q + 1] = fmaf(w, __uint_as_float(u[q] & 0xffff0000u), acc[2 * q + 1]);
+        for (int i = 0; i < N; ++i) {
+            const uint32_t u = F32 ? v[i] : ((i & 1) ? v[i / 2] & 0xffff0000u : v[i / 2] << 16);
+            acc[i] = fmaf(w, __uint_as_float(u), acc[i]);
         }
     }
-}
+};
 
-// YF32 / SF32: y_perm / y_shared hold fp32 (else bf16); OF32: out is fp32 (else bf16, RNE).
-template <bool YF32, bool SF32, bool OF32>
-__global__ __launch_bounds__(256) void combine_kernel(const char* __restrict__ y_perm, const int32_t* __restrict__ inv_perm,
-                                                      const float* __restrict__ w, const char* __restrict__ y_shared,
-                                                      int k, int H, char* __restrict__ out) {
+// YF32 / SF32: y_perm / y_shared hold fp32 (else bf16); OF32: out is fp32 (else bf16, RNE).  K: rows a thread has in
+// flight at a time, k itself up to 8.
+constexpr int COMBINE_MAX_WAVES = 5;
+template <bool YF32, bool SF32, bool OF32, int K, bool NT>
+__global__ __launch_bounds__(COMBINE_MAX_WAVES * 64) void combine_kernel(const char* __restrict__ y_perm, const int32_t* __restrict__ inv_perm,
+                                                                         const float* __restrict__ w, const char* __restrict__ y_shared,
+                                                                         int k, int H, char* __restrict__ out) {
+    constexpr int N = YF32 || SF32 ? 4 : 8;
     const int t = blockIdx.x;
+    const int c = blockIdx.y * blockDim.x + threadIdx.x;
+    if (c >= H / N) return;
     const size_t ybytes = (size_t)H * (YF32 ? 4 : 2);
     const size_t sbytes = (size_t)H * (SF32 ? 4 : 2);
-    for (int c = threadIdx.x; c < H / 8; c += 256) {
-        float acc[8];
+    float acc[N];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-        for (int j = 0; j < k; ++j) {
-            const int r = inv_perm[(size_t)t * k + j];
-            const float wj = w[(size_t)t * k + j];
-            accum8<YF32>(acc, y_perm + (size_t)r * ybytes, c, wj);
-        }
-        if (y_shared) accum8<SF32>(acc, y_shared + (size_t)t * sbytes, c, 1.0f);
-        if (OF32) {
-            float4* o = reinterpret_cast<float4*>(out + (size_t)t * H * 4) + 2 * c;
-            o[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-            o[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
-        } else {
-            bf16x8 o;
+    for (int i = 0; i < N; ++i) acc[i] = 0.f;
+    Piece<SF32, N, NT> sh;
+    if (y_shared) sh.load(y_shared + (size_t)t * sbytes, c);
+    const int32_t* ip = inv_perm + (size_t)t * k;
+    const float* wp = w + (size_t)t * k;
+    Piece<YF32, N, NT> row[K];
+    int j = 0;
+    do {   // one pass unless k > 8
 #pragma unroll
-            for (int i = 0; i < 8; ++i) o[i] = (__bf16)acc[i];
-            reinterpret_cast<bf16x8*>(out + (size_t)t * H * 2)[c] = o;
+        for (int i = 0; i < K; ++i) row[i].load(y_perm + (size_t)ip[j + i] * ybytes, c);
+#pragma unroll
+        for (int i = 0; i < K; ++i) row[i].add_to(acc, wp[j + i]);
+        j += K;
+    } while (K == 8 && j + K <= k);
+    if (K == 8)
+        for (; j < k; ++j) {
+            row[0].load(y_perm + (size_t)ip[j] * ybytes, c);
+            row[0].add_to(acc, wp[j]);
         }
+    if (y_shared) sh.add_to(acc, 1.0f);
+    if (OF32) {
+        float4* o = reinterpret_cast<float4*>(out + (size_t)t * H * 4) + (N / 4) * c;
+#pragma unroll
+        for (int i = 0; i < N / 4; ++i) o[i] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+    } else {
+        typedef __bf16 bf16_n __attribute__((ext_vector_type(N)));
+        bf16_n o;
+#pragma unroll
+        for (int i = 0; i < N; ++i) o[i] = (__bf16)acc[i];
+        reinterpret_cast<bf16_n*>(out + (size_t)t * H * 2)[c] = o;
     }
 }
 
@@ -104,20 +123,46 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const uint16_t* __rest
 
 hipError_t launch_combine(const moe_shape& s, const void* y_perm, const int32_t* inv_perm, const float* w,
                           const void* y_shared, void* out, bool y_fp32, bool shared_fp32, bool out_fp32, hipStream_t st) {
-#define COMBINE(Y, S, O)                                                                                          \
-    hipLaunchKernelGGL((combine_kernel<Y, S, O>), dim3(s.T), dim3(256), 0, st, (const char*)y_perm, inv_perm, w,  \
+    // up to five waves to a workgroup, and as many workgroups to a token as its row then takes
+    const int per_thread = y_fp32 || shared_fp32 ? 4 : 8;
+    const int waves = (s.H / per_thread + 63) / 64, parts = (waves + COMBINE_MAX_WAVES - 1) / COMBINE_MAX_WAVES;
+    const dim3 grid((unsigned)s.T, (unsigned)parts), block((unsigned)((waves + parts - 1) / parts * 64));
+    // Non-temporal loads where the rows exceed the memory-side cache (256 MB): they are read once, most of them from memory
+    // (16384 tokens above: 117 us without, 94 with).  Rows that fit are still there from the down GEMM's stores, and
+    // the hint costs: 8 experts top-2, H = 4096, fp32, 4096 tokens (134 MB) 28.6 -> 29.9 us.
+    const int64_t row_bytes = s.top_k * (y_fp32 ? 4 : 2) + (y_shared ? (shared_fp32 ? 4 : 2) : 0);
+    const bool nt = (int64_t)s.T * s.H * row_bytes > ((int64_t)256 << 20);
+#define COMBINE_NT(Y, S, O, K, NT)                                                                                        \
+    hipLaunchKernelGGL((combine_kernel<Y, S, O, K, NT>), grid, block, 0, st, (const char*)y_perm, inv_perm, w,            \
                        (const char*)y_shared, s.top_k, s.H, (char*)out)
-#define COMBINE_O(Y, S)                 \
-    do {                                \
-        if (out_fp32) COMBINE(Y, S, true); \
-        else COMBINE(Y, S, false);      \
+#define COMBINE(Y, S, O, K)                         \
+    do {                                            \
+        if (nt) COMBINE_NT(Y, S, O, K, true);       \
+        else COMBINE_NT(Y, S, O, K, false);         \
+    } while (0)
+#define COMBINE_K(Y, S, O)                \
+    switch (s.top_k) {                    \
+        case 1: COMBINE(Y, S, O, 1); break; \
+        case 2: COMBINE(Y, S, O, 2); break; \
+        case 3: COMBINE(Y, S, O, 3); break; \
+        case 4: COMBINE(Y, S, O, 4); break; \
+        case 5: COMBINE(Y, S, O, 5); break; \
+        case 6: COMBINE(Y, S, O, 6); break; \
+        case 7: COMBINE(Y, S, O, 7); break; \
+        default: COMBINE(Y, S, O, 8); break; \
+    }
+#define COMBINE_O(Y, S)                      \
+    do {                                     \
+        if (out_fp32) COMBINE_K(Y, S, true)  \
+        else COMBINE_K(Y, S, false)          \
     } while (0)
     if (y_fp32 && shared_fp32) COMBINE_O(true, true);
-    else if (y_fp32) COMBINE_O(true, false);
     else if (shared_fp32) COMBINE_O(false, true);
-    else COMBINE_O(false, false);
+    else COMBINE_O(false, false);   // (fp32 y_perm comes with fp32 y_shared)
 #undef COMBINE_O
+#undef COMBINE_K
 #undef COMBINE
+#undef COMBINE_NT
     return hipGetLastError();
 }
 

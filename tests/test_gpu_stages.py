@@ -469,6 +469,42 @@ def test_combine(moe, T, H, k, shared, y_fp32):
         moe.set_option("out_fp32", 0)
 
 
+# every number of rows in flight and past it (k > 8), rows that end inside a wavefront, a workgroup and at their edges,
+# and one batch on either side of the size from which the rows are loaded non-temporally
+@pytest.mark.parametrize("T,H,k,shared,y_fp32", [(5, 64 + 192 * k, k, k % 2 == 0, k % 3 == 0) for k in range(1, 10)] + [
+    (3, 1280, 16, True, True), (3, 1344, 17, True, False), (2, 2560, 64, False, False), (4, 2624, 8, False, True),
+    (2047, 4096, 8, False, True), (2049, 4096, 8, False, True)])
+def test_combine_rows_in_flight(moe, T, H, k, shared, y_fp32):
+    from paper_2503_09716_amd import make_shape
+    say("combine rows", T, H, k, shared, y_fp32)
+    gen = torch.Generator(device="cuda").manual_seed(T + H + k)
+    dtype = torch.float32 if y_fp32 else torch.bfloat16
+    y = torch.randn((T * k, H), device="cuda", generator=gen).to(dtype)
+    ysh = torch.randn((T, H), device="cuda", generator=gen).to(dtype) if shared else None
+    inv = torch.randperm(T * k, device="cuda", generator=gen).int()
+    w = torch.rand((T, k), device="cuda", generator=gen)
+    shape = make_shape(T, H, 64, max(k, 8), k, 1 if shared else 0, False)
+    out = torch.empty((T, H), dtype=torch.float32, device="cuda")
+    moe.set_option("y_fp32", 1 if y_fp32 else 0)
+    moe.set_option("out_fp32", 1)
+    try:
+        moe.combine(shape, y, inv, w, ysh, out)
+    finally:
+        moe.set_option("y_fp32", 1)
+        moe.set_option("out_fp32", 0)
+    ref = torch.zeros((T, H), dtype=torch.float64, device="cuda")
+    size = torch.zeros_like(ref)
+    for j in range(k):
+        term = w[:, j, None].double() * y[inv.view(T, k)[:, j].long()].double()
+        ref += term
+        size += term.abs()
+    if shared:
+        ref += ysh.double()
+        size += ysh.double().abs()
+    # one rounding (2^-24) per fused multiply-add, each of a partial sum that is at most the sum of the absolute terms
+    assert bool(((out.double() - ref).abs() <= (k + 1) * 2.0 ** -24 * size).all())
+
+
 def packed_reference(w: np.ndarray) -> np.ndarray:
     """The packed layout as include/moe.h words it, written out element by element."""
     K, N = w.shape
