@@ -315,12 +315,11 @@ moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     return MOE_OK;
 }
 
-// Whether the plan kernel may choose tiles lower than 256 rows for a launch: only where that can
-// fill idle CUs, in launches of at most two rounds of 256-row tiles on average (with more rounds
-// the tallest tiles win: 128-row tiles run at about 0.75 of their rate; and choosing takes the plan 4 us).
+// Which heights the plan may choose from for a launch (plan.h): 1, up to two rounds of 256-row tiles on average, where lower
+// tiles can fill idle CUs; 2, longer ones: 256 rows and more (128-row tiles run at about 0.75 of their rate).
 int may_choose_rows(const moe_shape& s, int n_tiles, int nseg) {
     const double tiles = ((double)s.T * s.top_k / 256 + 0.5 * s.E + (double)nseg * ((s.T + 255) / 256)) * n_tiles;
-    return tiles <= 2 * 256.0;
+    return tiles <= 2 * 256.0 ? 1 : 2;
 }
 
 // m-tiles swept together before moving along n.  Tiles of one expert share W panels, so runs
@@ -436,15 +435,15 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const int64_t pairs = (int64_t)s.T * s.top_k, groups = pairs < s.E ? pairs : s.E, tiles_up = (groups + s.num_shared) * nt_up;
     int tm_up = c->gemm.tile_rows_up ? c->gemm.tile_rows_up : (s.T <= 256 && tiles_up <= 128 ? 128 : 256);
     int tm_down = c->gemm.tile_rows_down ? c->gemm.tile_rows_down : 256;
-    int choose_up = s.T > 256 && !c->gemm.tile_rows_up && may_choose_rows(s, nt_up, s.num_shared);
+    int choose_up = s.T > 256 && !c->gemm.tile_rows_up ? may_choose_rows(s, nt_up, s.num_shared) : 0;
     // tiles above 256 rows exist for the 4-wave, 1-wave-row kernel only
     const bool tall_kernel = c->gemm.waves == 4 && c->gemm.wave_rows == 1;
     // Gate/up GEMM: 320-row tiles move 10 % fewer bytes per FLOP from L2 to LDS (the chip is
     // power-limited, and what the loads cost is clock), measured -1.3 % (C3) to -3.9 % (C4, C5) on
     // that GEMM; not when an expert is only about four tiles (C2: 1024 rows = 3 tiles + a tail
-    // that needs a pass of its own, +10 %).  In the down GEMM the 320-row variant measures within
-    // 1 % of the 256-row one either way, so it keeps 256.
+    // that needs a pass of its own, +10 %).  This is the usual height; the plan takes another where that is clearly cheaper.
     if (!c->gemm.tile_rows_up && tall_kernel && (double)s.T * s.top_k / s.E >= 1200.0) tm_up = 320;
+    if (!tall_kernel && choose_up) choose_up = choose_up == 1 ? 3 : 0;
     if (!tall_kernel && tm_up > 256) tm_up = 256;
     if (!tall_kernel && tm_down > 256) tm_down = 256;
     // Short tail tiles go last by default: the other tiles of a launch then all take the same
@@ -463,8 +462,9 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const int dsp = sm.down ? 1 : call_down_splits(c, s);
     if (s.T <= 256 && dsp == 1 && !c->gemm.tile_rows_down) tm_down = 128;   // the walk along K is long; not where short tails may be cut along K
     // Forced pieces: which rows are cut must not depend on what else a pass covers, so the heights are fixed.
-    const int choose_down = tm_down == 256 && !c->gemm.tile_rows_down && may_choose_rows(s, nt_down, s.num_shared ? 1 : 0) &&
-                            !(dsp > 1 && c->gemm.down_tail_splits == 2);
+    int choose_down = tm_down == 256 && !c->gemm.tile_rows_down && !(dsp > 1 && c->gemm.down_tail_splits == 2)
+                          ? may_choose_rows(s, nt_down, s.num_shared ? 1 : 0) : 0;
+    if (!tall_kernel && choose_down) choose_down = choose_down == 1 ? 3 : 0;
     // "many rounds" for the plan's rule: eight rounds of 256 tiles (at two to three rounds pieces
     // measured +6 %, at four to five +-0, at thirteen -2 %)
     const int split_rule_tiles = c->gemm.down_tail_splits == 2 ? 0 : (2048 + nt_down - 1) / nt_down;
@@ -497,8 +497,8 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
                       dsp, 4, split_rule_tiles, split_room_tiles(s), tall, tall, (SplitTail*)(ws + L.split_tails), (PlanHeader*)(ws + L.plan),
                       (TileDesc*)(ws + L.descs_up), (TileDesc*)(ws + L.descs_down)};
     f.sm = sm;
-    f.mtiles_up = ps.mtiles_up > 0 ? ps.mtiles_up : (sm.up ? sm.mtiles_up : (int)max_mtiles(s, choose_up ? 128 : tm_up));
-    f.mtiles_down = (ps.mtiles_down > 0 ? ps.mtiles_down : (sm.down ? sm.mtiles_down : (int)max_mtiles(s, choose_down ? 128 : tm_down))) +
+    f.mtiles_up = ps.mtiles_up > 0 ? ps.mtiles_up : (sm.up ? sm.mtiles_up : (int)max_mtiles(s, choose_up ? (choose_up == 2 ? 256 : 128) : tm_up));
+    f.mtiles_down = (ps.mtiles_down > 0 ? ps.mtiles_down : (sm.down ? sm.mtiles_down : (int)max_mtiles(s, choose_down ? (choose_down == 2 ? 256 : 128) : tm_down))) +
                     s.E * (dsp - 1);
     if (low_up) f.mtiles_up += s.num_shared * ((s.T + 127) / 128);
     if (low_down) f.mtiles_down += (s.T + 127) / 128;

@@ -15,13 +15,12 @@
 // unless a tiled copy exists.
 //
 // Tile routine (one workgroup = NW wavefronts in a WM x WN grid):
-//   * macro tile: BM rows of X (32, 64, ... 320) x 256 rows of W (GEMM 1: 128 gate + 128
+//   * macro tile: BM rows of X (32, 64, ... 384) x 256 rows of W (GEMM 1: 128 gate + 128
 //     up rows, so the SiLU-gate product is formed in registers); K advances in sub-tiles of 32.
-//     The 288- and 320-row tiles (4 waves side by side only) keep the accumulators of their last
-//     2-4 X blocks in VGPRs, the 256 AGPRs being full; they serve as the standard tile of GEMM 1
-//     for large experts (fewer bytes from L2 per FLOP) and take in an expert's short tail.
+//     The tiles above 256 rows (4 waves side by side only) keep the accumulators of their last X blocks in VGPRs, the
+//     256 AGPRs being full: fewer bytes from L2 per FLOP, and other numbers of rounds to choose from (plan.h).
 //   * global -> LDS with buffer_load_dwordx4 ... lds (no VGPR round trip) into a ring of NS = 4
-//     LDS stages (4 x 32 KiB at BM = 256): the loads of sub-tile t+3 are issued while sub-tile t
+//     LDS stages (4 x 32 KiB at BM = 256, all 160 KiB at 384): the loads of sub-tile t+3 are issued while sub-tile t
 //     is multiplied, so HBM latency has three sub-tiles of MFMA work to hide behind, and they
 //     are spread between the MFMAs (one every few) instead of bursting after the barrier.
 //     One barrier per sub-tile; s_waitcnt vmcnt(n) waits only for the sub-tile needed next.
@@ -37,8 +36,10 @@
 //     of bf16 h), GEMM 2 feeds X as the row operand (a lane owns one output column: a store
 //     instruction writes 4 rows x 64 contiguous bytes of fp32 y).
 //   * each operand fragment has one register copy; it is refilled from the next LDS stage
-//     right after its last use, so reads run half a sub-tile ahead of the MFMAs that need
-//     them.  The instruction stream is laid out by hand in small groups {MFMAs of one X block,
+//     right after its last use, so reads run ahead of the MFMAs that need them.  Up to 320 rows all X fragments
+//     of a sub-tile are live; above, two chunks of them (a quarter of the rows each), which are walked with both halves of
+//     W one after the other (more or smaller chunks, and chunks in lower tiles: the same or slower).  The
+//     instruction stream is laid out by hand in small groups {MFMAs of one X block,
 //     one or two LDS reads, at most one global load} fenced by scheduling barriers, so the
 //     matrix pipe always has independent work queued.
 //   * ragged tails: rows past the end of a group are clamped on load and masked on store;
@@ -50,6 +51,7 @@
 // `group_m` m-tiles before moving along n, so the tiles resident on one XCD share weight panels
 // and X panels in its L2.
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "plan.h"
@@ -62,7 +64,7 @@ constexpr int ROWB = BK * 2;        // bytes per LDS row
 constexpr int WROWS = 256;          // W rows per macro tile
 constexpr int NS = 4;               // LDS ring depth (deeper rings for the low tiles, up to 8 stages, measured the same)
 constexpr int MAX_ROWS = PLAN_MAX_ROWS;   // tallest macro tile
-constexpr int MAX_STAGE = (MAX_ROWS + WROWS) * ROWB;     // 36 KiB
+constexpr int MAX_STAGE = (MAX_ROWS + WROWS) * ROWB;     // 40 KiB
 constexpr int MAX_LDS = NS * MAX_STAGE;
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
@@ -161,7 +163,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
     constexpr int NQX = NLX * NW;                  // X wave-loads per stage (region padded to a multiple of NW)
     constexpr int XBYTES = NQX * 1024;
     constexpr int NL = NLX + (WROWS / 16) / NW;    // all wave-loads per wave per stage
-    constexpr int NL0 = NL / 2;                    // issued in the first half of an iteration
     constexpr int RING_STRIDE = NL * NW * 1024;    // bytes per ring stage
     static_assert(NS * RING_STRIDE <= MAX_LDS, "ring does not fit");
     constexpr int BN = GATED ? 128 : 256;    // output columns per macro tile
@@ -174,6 +175,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
     constexpr int WB = 2 * TJ;
     constexpr int WBH = WB / 2;
     constexpr int XB_A = 64 / WB;            // X blocks whose accumulators fit the 256 AGPRs; the rest live in VGPRs
+    // The X blocks are walked in NC chunks of CB, each chunk with both halves of W before the next.  XD fragments of X
+    // are live: all of them (one chunk) up to 320 rows, two chunks above, where the accumulators leave no room for all.
+    constexpr int NC = XB == 24 ? 4 : (XB == 22 ? 2 : 1);
+    constexpr int CB = XB / NC;
+    constexpr int XD = NC == 1 ? XB : 2 * CB;
+    static_assert(NC * CB == XB && XB % XD == 0, "X blocks do not divide into chunks");
+    // The hand-over of the ring comes before the first part (chunk, half of W) that reads the next stage.
+    constexpr int SYNC_PART = NC == 1 ? 1 : 2 * NC - 3;
+    constexpr int NL0 = SYNC_PART * CB * NL / (2 * XB);   // loads of an iteration issued before that
     static_assert(TJ >= 1 && (!GATED || TJ >= 2), "wave grid too wide");
     static_assert(BM <= MAX_ROWS, "tile too tall");
 
@@ -269,14 +279,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[j][i][r] = 0.f;
 
-    // Operand fragments of one sub-tile: all X blocks, and the W blocks in two halves.  wA is
-    // used by the first half of a sub-tile and refilled (from the NEXT stage) during the second;
-    // wB the other way round; X block i is refilled from the next stage right after its last
-    // MFMA of the second half.  So no fragment needs a second copy.
-    bf16x8 xf[XB], wA[WBH], wB[WBH];
+    // Operand fragments: XD X blocks, and the W blocks of one sub-tile in two halves.  wA is used by the first half of
+    // every chunk and refilled (from the NEXT stage) during the second half of the last; wB by the second
+    // halves, refilled during the first half of the first chunk; an X fragment is refilled with the block XD
+    // further on (past the last one: of the next stage) right after its last MFMA.  So no fragment needs a second copy.
+    bf16x8 xf[XD], wA[WBH], wB[WBH];
     typedef __attribute__((address_space(3))) const bf16x8* frag_ptr_t;
     auto read_x = [&](const int stage, const int i) __attribute__((always_inline)) {
-        xf[i] = *(frag_ptr_t)(ring + stage * RING_STRIDE + offX + i * 16 * ROWB);
+        xf[i % XD] = *(frag_ptr_t)(ring + stage * RING_STRIDE + offX + i * 16 * ROWB);
     };
     // W block jj of half hf: GEMM 2: rows (hf*WBH + jj)*16; GEMM 1: gate rows jj*16 | up rows 128 + jj*16
     auto read_w = [&](const int stage, const int hf, const int jj) __attribute__((always_inline)) {
@@ -286,49 +296,60 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
         else wB[jj] = v;
     };
 
-    // One half of a sub-tile: XB groups, group i = the WBH MFMAs of X block i with this half's W
-    // blocks.  HF = 0 reads the second half's W blocks of the same stage; HF = 1 reads the
-    // next sub-tile's X blocks and first-half W blocks from stage `rd_stage` (RD).  Direct-to-LDS
-    // loads LD0..LD1-1 are spread over the groups (LD).
-    auto half = [&](auto hf_tag, auto rd_tag, auto ld_tag, auto ld0_tag, auto ld1_tag, const int rd_stage,
-                    const int ld_stage) __attribute__((always_inline)) {
-        constexpr int HF = decltype(hf_tag)::value;
+    // Part P of a sub-tile: chunk P / 2 with half HF = P % 2 of the W blocks, CB groups of WBH MFMAs with one X block.
+    // Second halves refill X fragments, from stage `cur` or, where RD, from stage `nxt`; W as above.
+    // The direct-to-LDS loads of an iteration are spread over its 2 * XB groups (LD).
+    auto part = [&](auto p_tag, auto rd_tag, auto ld_tag, const int cur, const int nxt, const int ld_stage) __attribute__((always_inline)) {
+        constexpr int P = decltype(p_tag)::value, C = P / 2, HF = P % 2;
         constexpr bool RD = decltype(rd_tag)::value;
         constexpr bool LD = decltype(ld_tag)::value;
-        constexpr int LD0 = decltype(ld0_tag)::value, LD1 = decltype(ld1_tag)::value;
-        constexpr int NLD = LD1 - LD0;
 #pragma unroll
-        for (int i = 0; i < XB; ++i) {
+        for (int u = 0; u < CB; ++u) {
+            const int i = C * CB + u;
 #pragma unroll
             for (int jj = 0; jj < WBH; ++jj) {
                 const int j = HF * WBH + jj;
                 const bf16x8 w = HF == 0 ? wA[jj] : wB[jj];
                 if (i < XB_A) {
-                    if (GATED) mfma_16x16x32(acc[j][i], w, xf[i]);
-                    else mfma_16x16x32(acc[j][i], xf[i], w);
+                    if (GATED) mfma_16x16x32(acc[j][i], w, xf[i % XD]);
+                    else mfma_16x16x32(acc[j][i], xf[i % XD], w);
                 } else {
-                    if (GATED) mfma_16x16x32_v(acc[j][i], w, xf[i]);
-                    else mfma_16x16x32_v(acc[j][i], xf[i], w);
+                    if (GATED) mfma_16x16x32_v(acc[j][i], w, xf[i % XD]);
+                    else mfma_16x16x32_v(acc[j][i], xf[i % XD], w);
                 }
             }
-            if (RD) {
-                if (HF == 1) read_x(rd_stage, i);
-                // the WBH W reads of this half go out with the first groups
-                constexpr int RPGW = (WBH + XB - 1) / XB;
+            if (HF == 1) {
+                if (i + XD < XB) read_x(cur, i + XD);
+                else if (RD) read_x(nxt, i + XD - XB);
+            }
+            // the WBH W reads of a half go out with the first groups
+            constexpr int RPGW = (WBH + CB - 1) / CB;
+            if (P == 0 || (P == 2 * NC - 1 && RD)) {
 #pragma unroll
-                for (int jj = i * RPGW; jj < (i + 1) * RPGW && jj < WBH; ++jj) read_w(rd_stage, 1 - HF, jj);
+                for (int jj = u * RPGW; jj < (u + 1) * RPGW && jj < WBH; ++jj) read_w(P == 0 ? cur : nxt, P == 0 ? 1 : 0, jj);
             }
             if (LD) {
+                constexpr int G = 2 * XB;
+                const int q = P * CB + u;
 #pragma unroll
-                for (int l = (i * NLD) / XB; l < ((i + 1) * NLD) / XB; ++l) issue_one(LD0 + l, ld_stage);
+                for (int l = (q * NL) / G; l < ((q + 1) * NL) / G; ++l) issue_one(l, ld_stage);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
+    // One sub-tile: its parts in order, `sync` before part SYNC_PART.
+    auto sub_tile = [&](auto rd_tag, auto ld_tag, const int cur, const int nxt, const int ld_stage, auto sync) __attribute__((always_inline)) {
+        auto run = [&](auto p_tag) __attribute__((always_inline)) {
+            if (decltype(p_tag)::value == SYNC_PART) sync();
+            part(p_tag, rd_tag, ld_tag, cur, nxt, ld_stage);
+        };
+        [&]<int... P>(std::integer_sequence<int, P...>) __attribute__((always_inline)) {
+            (run(std::integral_constant<int, P>{}), ...);
+        }(std::make_integer_sequence<int, 2 * NC>{});
+    };
     using T_ = std::true_type;
     using F_ = std::false_type;
 
-    using I0 = std::integral_constant<int, 0>;
     // GEMM 2 on shared experts walks `nseg` K-concatenated segments (one per shared expert);
     // every other tile has one segment.  The pipeline drains and restarts between segments.
     for (int seg = 0; seg < nseg; ++seg) {
@@ -361,40 +382,30 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
         // first MFMAs need.  With the W blocks read last here (where the scheduler puts them if
         // left alone), that was a wait for every read of the previous iteration at the top of
         // each sub-tile.
-        constexpr int RPGW0 = (WBH + XB - 1) / XB;
+        constexpr int RPGW0 = (WBH + XD - 1) / XD;
 #pragma unroll
-        for (int i = 0; i < XB; ++i) {
+        for (int i = 0; i < XD; ++i) {
             read_x(0, i);
 #pragma unroll
             for (int jj = i * RPGW0; jj < (i + 1) * RPGW0 && jj < WBH; ++jj) read_w(0, 0, jj);
             __builtin_amdgcn_sched_barrier(0);   // keeps the compiler from moving the W reads to the end
         }
 
-        using H0 = std::integral_constant<int, 0>;
-        using H1 = std::integral_constant<int, 1>;
         int t = 0;
         // steady state: sub-tile t is multiplied, sub-tile t+NS-1 is loaded
         for (; t + NS - 1 < KT; ++t) {
-            const int cur = t % NS, nxt = (t + 1) % NS, ld = (t + NS - 1) % NS;
-            half(H0{}, T_{}, T_{}, I0{}, std::integral_constant<int, NL0>{}, cur, ld);
             // Sub-tile t+1 has landed once only the younger loads are outstanding.  The same
-            // barrier frees stage `cur` for the loads of the NEXT iteration: its last reads were
-            // issued above and have returned (lgkmcnt(0)) before any wave passes.
-            ring_sync<(NS - 3) * NL + NL0>();
-            half(H1{}, T_{}, T_{}, std::integral_constant<int, NL0>{}, std::integral_constant<int, NL>{}, nxt, ld);
+            // barrier frees stage t % NS for the loads of the NEXT iteration: its last reads were
+            // issued before and have returned (lgkmcnt(0)) before any wave passes.
+            sub_tile(T_{}, T_{}, t % NS, (t + 1) % NS, (t + NS - 1) % NS,
+                     [] __attribute__((always_inline)) { ring_sync<(NS - 3) * NL + NL0>(); });
             koff_x += kstep_x;
             koff_w += kstep_w;
         }
         // tail: nothing left to load; conservative waits
-        for (; t < KT - 1; ++t) {
-            const int cur = t % NS, nxt = (t + 1) % NS;
-            half(H0{}, T_{}, F_{}, I0{}, I0{}, cur, 0);
-            ring_sync<0>();
-            half(H1{}, T_{}, F_{}, I0{}, I0{}, nxt, 0);
-        }
-        half(H0{}, T_{}, F_{}, I0{}, I0{}, t % NS, 0);
-        ring_sync<0>();    // every wave is done reading the ring before the next segment refills it
-        half(H1{}, F_{}, F_{}, I0{}, I0{}, 0, 0);
+        auto drain = [] __attribute__((always_inline)) { ring_sync<0>(); };
+        for (; t < KT - 1; ++t) sub_tile(T_{}, F_{}, t % NS, (t + 1) % NS, 0, drain);
+        sub_tile(F_{}, F_{}, t % NS, 0, 0, drain);   // its barrier: every wave is done reading the ring before the next segment refills it
     }
 
     // ------------------------------------------------------------------ epilogue
@@ -564,7 +575,9 @@ __global__ __launch_bounds__(256, 1) void ffn_gemm_kernel(const GemmArgs p) {
         else if (blocks > 2) gemm_tile<4, 2, 2, GATED, UNIFORM>(p, d, n_tile, lds);
         else gemm_tile<4, 2, 1, GATED, UNIFORM>(p, d, n_tile, lds);
     } else {
-        if (blocks > 9) gemm_tile<4, 1, 10, GATED>(p, d, n_tile, lds);
+        if (blocks > 11) gemm_tile<4, 1, 12, GATED>(p, d, n_tile, lds);
+        else if (blocks > 10) gemm_tile<4, 1, 11, GATED>(p, d, n_tile, lds);
+        else if (blocks > 9) gemm_tile<4, 1, 10, GATED>(p, d, n_tile, lds);
         else if (blocks > 8) gemm_tile<4, 1, 9, GATED>(p, d, n_tile, lds);
         else if (blocks > 7) gemm_tile<4, 1, 8, GATED>(p, d, n_tile, lds);
         else if (blocks > 6) gemm_tile<4, 1, 7, GATED>(p, d, n_tile, lds);

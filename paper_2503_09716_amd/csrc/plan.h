@@ -5,7 +5,8 @@
 namespace moe {
 namespace {
 
-constexpr int PLAN_MAX_ROWS = 320;   // tallest m-tile: a full 256-row tile that also takes a short tail of its group
+constexpr int PLAN_MAX_ROWS = 384;   // tallest m-tile
+constexpr int PLAN_JOIN_ROWS = 64;   // a tail of up to that many rows joins its group's last full 256-row tile
 
 // Exclusive prefix sums of three per-thread counters over the 256 threads of a workgroup, and
 // their totals (every thread gets them): a wave-level scan, then the four wave sums through LDS.
@@ -36,7 +37,8 @@ __device__ __forceinline__ void block_scan3(int& a, int& b, int& c, int (&tot)[3
 // last one with the rest.  A group of two or three tiles is cut evenly, in steps of 32 rows: its
 // tiles then run side by side, share the W panels they stream and finish together, where a short
 // tail moved to the end of the list read them a second time (8x7B, 1511 tokens = 378 rows per
-// expert: gate/up GEMM 740 -> 600 us, down 351 -> 300).  A longer one is cut into full tiles and
+// expert: gate/up GEMM 740 -> 600 us, down 351 -> 300), and under a cap above 256 rows one of four (5003 tokens, 1250 rows =
+// 4 x 320 instead of 3 x 352 and 194: down 940 -> 811).  A longer one is cut into full tiles and
 // a tail.  A tail of at most 64 rows next to full 256-row tiles joins the last of them.
 struct GroupCut {
     int cap, h, nfull, tail, joined;
@@ -53,12 +55,12 @@ __device__ __forceinline__ GroupCut cut_group(const int rows, const int tm, cons
     c.cap = c.h = tm;
     c.nfull = rows < (1 << 24) ? div_small(rows, tm) : rows / tm;
     c.tail = rows - c.nfull * tm;
-    c.joined = tall && tm == 256 && c.nfull > 0 && c.tail <= PLAN_MAX_ROWS - 256 ? c.tail : 0;
+    c.joined = tall && tm == 256 && c.nfull > 0 && c.tail <= PLAN_JOIN_ROWS ? c.tail : 0;
     c.tail -= c.joined;
-    c.even = even && c.tail > 0 && (c.nfull == 1 || c.nfull == 2);
+    c.even = even && c.tail > 0 && c.nfull >= 1 && c.nfull <= (tm > 256 ? 3 : 2);
     if (c.even) {
         const int m = c.nfull + 1;
-        c.h = ((m == 2 ? (rows + 1) >> 1 : (rows + 2) / 3) + 31) & ~31;
+        c.h = ((m == 2 ? (rows + 1) >> 1 : m == 4 ? (rows + 3) >> 2 : (rows + 2) / 3) + 31) & ~31;
         c.nfull = m - (rows < m * c.h);   // (m - 1) * h < rows: rows > tm * (m - 1) >= 128 * (m - 1)
         c.tail = rows - c.nfull * c.h;
     }
@@ -76,51 +78,74 @@ __device__ __forceinline__ GroupCut list_cut(const PlanArgs& p, const int which,
                      !shared || which == 1 || p.T > 512);
 }
 
-// Height cap of a list's tiles, chosen from the call's real row counts (launches of a few rounds
-// of tiles only; with more the tallest is best).  What a tile costs per K sub-tile, in rows of
-// matrix work (1.3 ns), is its height plus a constant for what it loads: 290 while at most half
-// of the CUs are busy (a CU fills its LDS at about 44 GB/s), more when all of them are and share
-// the memory's bandwidth: 520 for a tile that streams its W panel alone, 340 next to another
-// tile of its group.  (Uniform groups on the 8x7B layer: 0.72 us at 32 rows, 0.81 at 128, 1.01 at
-// 256, 1.14 at 320 with 1792 tiles; 0.42, 0.52 and 0.68 at 32, 128 and 256 rows with 128 tiles;
-// 0.74 at 192 and 0.83 at 256 rows, two tiles to a panel.)  A launch costs its whole rounds of
-// 256 tiles times the mean tile, and no less than its longest tile.  With caps below 256 an
-// expert of 250 rows is two tiles of 128: the down GEMM of eight such experts fills the chip
-// with one round of 256 tiles instead of half a round of 256-row ones (8x7B, 1000 tokens:
-// 310 -> 268 us).
-// Candidates: the cap the host passes (256, or 320 for experts of many rows: 2 experts of 1583 rows, H = 2816, F = 2752 are
-// 220 tiles of 320 rows, one round, and 264 of 256: gate/up 87 and 115 us), 256, 224, ... 128.
-constexpr int PLAN_CAPS = 6;
-__device__ constexpr int plan_cap(const int c, const int tm) { return c == 0 ? tm : 288 - 32 * c; }
+// Height cap of a list's tiles, chosen from the call's real row counts.  What a tile costs per K
+// sub-tile, in rows of matrix work (1.3 ns), is its height plus a constant for what it loads (a CU fills
+// its LDS at about 44 GB/s): 290, and more where all CUs share the memory's bandwidth: 520 for a tile
+// that streams its W panel alone, 340 next to another tile of its group.  (Uniform groups on the 8x7B layer: 0.72 us at
+// 32 rows, 0.81 at 128, 1.01 at 256 with 1792 tiles; 0.42, 0.52 and 0.68 at 32, 128 and 256 rows
+// with 128 tiles; 0.74 at 192 and 0.83 at 256 rows, two tiles to a panel.)  Above 256 rows the matrix cores take
+// longer than the loads, 2.3 ns a row (8 experts, H = 6144, F = 16384, 16384 tokens, gate/up: 0.72 us at 256 rows, 0.88 at 320, 1.02
+// at 384).  A launch costs its whole rounds of 256 tiles times the mean tile, and no less than its longest
+// tile; the last round of a long one only half (by then the CUs are out of step).
+//   short launches (up to two rounds of 256-row tiles, p.choose_* = 1): all eight caps.  With caps below 256 an expert of
+//     250 rows is two tiles of 128: the down GEMM of eight such experts fills the chip with one round of 256 tiles instead
+//     of half a round of 256-row ones (8x7B, 1000 tokens: 310 -> 268 us); with 352, one of 628 rows two tiles instead of three
+//     (2500 tokens: one round instead of one and a half, 590 -> 424 us).
+//   longer ones (2): 384, 352, 320 and 256 rows.  A taller tile moves fewer bytes from L2 to LDS per multiply-add, and its height
+//     decides how the rounds come out: gate/up of 160 experts, 32768 tokens, 320 -> 384 rows 6230 -> 6110 us, down 256 -> 384
+//     3450 -> 3260; 8 experts above 9190 -> 8910, 4860 -> 4740; 8x7B, 5003 tokens, down 256 -> 320 941 -> 808; 64 experts,
+//     6000 tokens 484 -> 450, 278 -> 256; but 8x7B, 1511 tokens (378 rows per expert), gate/up 586 in two tiles of 192 rows,
+//     657 in one.  Over 164 random layers of 257 to 16384 tokens the gate/up GEMM takes 0.979 of its time with fixed
+//     heights, the down GEMM 0.987, and no call 3 % longer.  What another height must gain by the estimate to be taken: 3 to 4 %,
+//     where 320 rows is the usual one (host) 1.5 %.
+constexpr int PLAN_CAPS = 8, PLAN_CAPS_LONG = 4;
+__device__ constexpr int plan_cap(const int c) { return (c < 3 ? 384 : 352) - 32 * c; }   // 384, 352, 320, 256, 224, ... 128
+// whether cap c is a candidate (3: as 1, for the wave grids that have no tiles above 256 rows)
+__device__ constexpr bool plan_candidate(const int c, const int choose) { return choose == 1 || (choose == 2 ? c < PLAN_CAPS_LONG : choose == 3 && c >= 3); }
 
-__device__ __forceinline__ float list_cost(const PlanArgs& p, const int which, const int* rows, const int ngroups, const int nseg0,
-                                           const int tm, const int n_tiles, const int lane) {
-    // n: tiles; alone: tiles that are their group's only one; sum: rows; longest: highest tile (shared experts
-    // of the down GEMM walk nseg0 segments)
-    // (n and alone share a word: a launch with a choice has at most a few thousand m-tiles)
-    int n_alone = 0, sum = 0, longest = 0;
-    for (int g = lane; g < ngroups; g += 64) {
+// What a list's tiles add up to under one cap.  n: tiles; alone: their group's only one; beside: next to one or two others of
+// their group (in a long launch a panel that four tiles and more share costs nothing extra); longest: highest tile.
+struct ListSum {
+    int n, alone, beside, longest;
+    float sum;
+};
+
+// Groups first, first + step, ... of list `which`, cut with cap tm (shared experts of the down GEMM walk nseg0 segments).
+__device__ __forceinline__ ListSum list_sum(const PlanArgs& p, const int which, const int* rows, const int ngroups, const int nseg0,
+                                            const int tm, const int choose, const int first, const int step) {
+    // cost of a tile of r rows, apart from what sharing the memory adds
+    const int base = choose == 2 ? 310 : 290;
+    auto tile = [=](const int r) { const int v = (r + 31) & ~31; return max(base + v, (v + 38) * 7 / 4); };
+    ListSum s = {0, 0, 0, 0, 0.f};
+    for (int g = first; g < ngroups; g += step) {
         const int r = rows[g];
         if (r == 0) continue;
         const GroupCut c = list_cut(p, which, p.Ns > 0 && (g == 0 || g > p.E), r, tm);
         const int m = c.nfull + (c.tail > 0);
         const int seg = g == 0 ? nseg0 : 1;
-        n_alone += m + (m == 1 ? 1 << 16 : 0);
-        sum += ((r + 31) & ~31) + (seg - 1) * (r + 290 * m);
-        longest = max(longest, (290 + (((m > 1 ? c.h : r) + 31) & ~31)) * seg);
+        s.n += m;
+        if (m == 1) ++s.alone;
+        else if (choose != 2 || m < 4) s.beside += m;
+        const int high = tile(m > 1 ? c.h : r);
+        s.sum += (float)seg * (float)(c.nfull * high + (c.tail > 0 ? tile(c.tail) : 0) + (m > 1 ? c.joined : 0));
+        s.longest = max(s.longest, high * seg);
     }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        n_alone += __shfl_xor(n_alone, d, 64);
-        sum += __shfl_xor(sum, d, 64);
-        longest = max(longest, __shfl_xor(longest, d, 64));
-    }
-    const int n = n_alone & 0xffff, alone = n_alone >> 16;
-    if (n == 0) return 0.f;
-    const int tiles = n * n_tiles;
+    return s;
+}
+
+__device__ __forceinline__ ListSum add_sums(const ListSum& a, const ListSum& b) {
+    return {a.n + b.n, a.alone + b.alone, a.beside + b.beside, max(a.longest, b.longest), a.sum + b.sum};
+}
+
+__device__ __forceinline__ float list_cost(const ListSum& s, const int choose, const int n_tiles) {
+    if (s.n == 0) return 0.f;
+    const int tiles = s.n * n_tiles;
     const float busy = fminf(fmaxf((float)(tiles - 128) / 128.f, 0.f), 1.f);
-    const float mean = ((float)sum + 290.f * n + busy * (50.f * (n - alone) + 230.f * alone)) / (float)n;
-    return fmaxf((float)((tiles + 255) / 256) * mean, (float)longest);
+    const float mean = (s.sum + busy * (50.f * s.beside + 230.f * s.alone)) / (float)s.n;
+    // over many rounds the CUs get out of step, and the last one matters half
+    float rounds = (float)((tiles + 255) / 256);
+    if (choose == 2) rounds = 0.5f * (rounds + (float)tiles / 256.f + 0.5f);
+    return fmaxf(rounds * mean, (float)s.longest);
 }
 
 // Builds the two m-tile lists (gate/up GEMM with tiles of up to tm_up rows, down GEMM with tm_down)
@@ -140,6 +165,7 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
     __shared__ int wsum[4][3];
     __shared__ int group_rows[256];
     __shared__ float cap_cost[2][PLAN_CAPS];
+    __shared__ ListSum half_sum[2][2][PLAN_CAPS];
     const int tid = threadIdx.x;
     const int E = p.E, Ns = p.Ns;
     // group order: g = 0 -> shared 0 (if any), then routed 0..E-1, then shared 1..Ns-1
@@ -162,23 +188,29 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
     if ((p.choose_up || p.choose_down) && __syncthreads_or(group < E && rows > 128)) {
         group_rows[tid] = rows;
         __syncthreads();
-        const int wave = tid >> 6, lane = tid & 63;
-        for (int w = wave; w < 2 * PLAN_CAPS; w += 4) {   // wave-uniform
-            const int which = w / PLAN_CAPS, c = w % PLAN_CAPS;
-            if (!(which == 0 ? p.choose_up : p.choose_down)) continue;
-            const int groups = which == 0 ? ngroups : (Ns > 0 ? E + 1 : E);
-            const int nseg0 = which == 1 && Ns > 1 ? Ns : 1, nt = which == 0 ? p.nt_up : p.nt_down;
-            // (one copy of the code for all caps: what this costs is mostly fetching its instructions)
-            const float cost = list_cost(p, which, group_rows, groups, nseg0, plan_cap(c, tm_of[which]), nt, lane);
-            if (lane == 0) cap_cost[which][c] = cost;
-        }
+        // waves 0 and 1 take half of the groups each for the gate/up list, 2 and 3 for the down list; eight lanes to a cap
+        const int which = tid >> 7, c = (tid & 63) >> 3, choose = which == 0 ? p.choose_up : p.choose_down;
+        const int groups = which == 0 ? ngroups : (Ns > 0 ? E + 1 : E), nseg0 = which == 1 && Ns > 1 ? Ns : 1;
+        ListSum sum = {0, 0, 0, 0, 0.f};
+        if (plan_candidate(c, choose)) sum = list_sum(p, which, group_rows, groups, nseg0, plan_cap(c), choose, (tid >> 6 & 1) * 8 + (tid & 7), 16);
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1)
+            sum = add_sums(sum, {__shfl_xor(sum.n, d, 64), __shfl_xor(sum.alone, d, 64), __shfl_xor(sum.beside, d, 64),
+                                 __shfl_xor(sum.longest, d, 64), __shfl_xor(sum.sum, d, 64)});
+        if ((tid & 7) == 0) half_sum[which][tid >> 6 & 1][c] = sum;
+        __syncthreads();
+        if ((tid & 71) == 0) cap_cost[which][c] = list_cost(add_sums(half_sum[which][0][c], half_sum[which][1][c]), choose, which == 0 ? p.nt_up : p.nt_down);
         __syncthreads();
 #pragma unroll
         for (int which = 0; which < 2; ++which) {
-            if (!(which == 0 ? p.choose_up : p.choose_down)) continue;
-            float best = cap_cost[which][0] * 0.97f;   // the tallest unless another is clearly cheaper
-            for (int c = 1; c < PLAN_CAPS; ++c)
-                if (cap_cost[which][c] < best) { best = cap_cost[which][c]; tm_of[which] = plan_cap(c, 0); }
+            const int choose = which == 0 ? p.choose_up : p.choose_down;
+            if (!choose) continue;
+            // 256 rows, or 320 where the host says so, unless another height is clearly cheaper
+            const int usual = choose == 2 && tm_of[which] == 320 ? 2 : 3;
+            float best = cap_cost[which][usual] * (usual == 2 ? 0.985f : (choose == 2 && which == 0 ? 0.96f : 0.97f));
+            tm_of[which] = plan_cap(usual);
+            for (int c = 0; c < PLAN_CAPS; ++c)
+                if (plan_candidate(c, choose) && cap_cost[which][c] < best) { best = cap_cost[which][c]; tm_of[which] = plan_cap(c); }
         }
     }
     for (int which = 0; which < 2; ++which) {

@@ -691,6 +691,35 @@ def test_grouped_ffn_rest_of_long_groups(moe):
     say(P.assert_output(y.float().cpu().numpy(), ref, "y_perm"))
 
 
+# One tile of 321 to 384 rows per expert (one round of 224 tiles instead of two) at the edges of both heights, and
+# experts that four such tiles share evenly.
+HIGH_COUNTS = {"one": [321, 322, 351, 352, 353, 354, 383, 384] * 3 + [335, 368, 369, 370], "four": [1153, 1249, 1300, 1408, 1440, 1500, 1535, 1536]}
+
+
+@pytest.mark.parametrize("which,H,F", [(1, 2048, 64), (1, 2048, 192), (0, 128, 1024)])
+@pytest.mark.parametrize("kind", sorted(HIGH_COUNTS))
+def test_grouped_ffn_tiles_above_320_rows(moe, kind, which, H, F):
+    """The GEMM with eight tiles along N takes the high tiles, K of 2 and 6 sub-tiles among them; every row against the oracle, and
+    bf16 y as the rounding of fp32 y.  With a wave grid that has no tiles above 256 rows, the same bits."""
+    counts = np.array(HIGH_COUNTS[kind])
+    E, T = len(counts), int(counts.sum())
+    heights = [(n + 31) // 32 * 32 for _, _, n, _, _ in lists_of(moe, T, H, F, E, 1, 0, counts.tolist())[which]]
+    assert {352, 384} <= set(heights) and len(heights) == (E if kind == "one" else 4 * E)
+    cfg = scaled_config("C4", T=T, H=H, F=F, E=E, top_k=1, num_shared=0)
+    idx_h = np.repeat(np.arange(E, dtype=np.int32), counts)
+    idx_h = idx_h[np.random.default_rng(7).permutation(T)].reshape(T, 1)
+    say("high tiles", cfg)
+    y, _, perm, _, li = run_ffn_stage(moe, cfg, idx_h, wave_rows=1)
+    u = torch_bf16_to_u16
+    ref = orc.expert_rows(u(li.x)[perm], np.repeat(np.arange(E, dtype=np.int32), counts), [u(t) for t in li.w1],
+                          [u(t) for t in li.w3], [u(t) for t in li.w2])
+    if F >= 128:
+        say(P.assert_output(y.float().cpu().numpy(), ref, "y_perm"))
+    y16 = run_ffn_stage(moe, cfg, idx_h, wave_rows=1, y_fp32=False)[0]
+    assert torch.equal(y16.view(torch.int16), y.to(torch.bfloat16).view(torch.int16))
+    assert torch.equal(run_ffn_stage(moe, cfg, idx_h, wave_rows=2)[0], y)
+
+
 @pytest.mark.parametrize("T,H,F,E,k,shared,counts,rows_up,want_up", [
     # every group one tile; one of two tiles; a layer of less than 256 MB
     (100, 4096, 3072, 4, 4, 0, [100] * 4, 0, {100: ONCE}),
