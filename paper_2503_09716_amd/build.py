@@ -25,7 +25,7 @@ def _stale(target: str, deps) -> bool:
 
 def build(force: bool = False, verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    headers = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "plan.h"), os.path.join(ROOT, "include", "moe.h")]
+    headers = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "plan.h"), os.path.join(CSRC, "topk.h"), os.path.join(ROOT, "include", "moe.h")]
     jobs = []
     for src in SOURCES:
         s = os.path.join(CSRC, src)

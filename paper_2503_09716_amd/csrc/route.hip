@@ -15,32 +15,10 @@
 #include <type_traits>
 
 #include "common.h"
+#include "topk.h"
 
 namespace moe {
 namespace {
-
-// Butterfly step M of a wave-wide reduction: the value held by this lane's partner, the lane
-// that differs from it in bit log2(M) and agrees in all higher bits.  Inside a row of 16 lanes
-// the partner comes through the VALU's data-parallel-primitive path (quad permutes for M = 1, 2;
-// half-row and row mirrors for M = 4, 8: lane i with 7-i, 15-i, which also flip the lower bits,
-// and any partner with the same higher bits will do for a reduction); only M = 16, 32 go
-// through the LDS crossbar, whose throughput per CU is what bounded the top-k kernels.
-template <int CTRL>
-__device__ __forceinline__ int dpp_move(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
-}
-template <int M>
-__device__ __forceinline__ int pair_i(int v) {
-    if constexpr (M == 1) return dpp_move<0xB1>(v);        // quad_perm [1,0,3,2]
-    else if constexpr (M == 2) return dpp_move<0x4E>(v);   // quad_perm [2,3,0,1]
-    else if constexpr (M == 4) return dpp_move<0x141>(v);  // row_half_mirror
-    else if constexpr (M == 8) return dpp_move<0x140>(v);  // row_mirror
-    else return __shfl_xor(v, M, 64);
-}
-template <int M>
-__device__ __forceinline__ float pair_f(float v) {
-    return __int_as_float(pair_i<M>(__float_as_int(v)));
-}
 
 __device__ __forceinline__ float wave_max(float v) {
     v = fmaxf(v, pair_f<1>(v));
@@ -144,92 +122,6 @@ __device__ __forceinline__ void route_finish(const float (&v)[NV], const int lan
 constexpr int ROUTE_MFMA_WAVES = 8;
 constexpr int ROUTE_MFMA_AHEAD = 16;   // sub-tiles whose loads a wave issues before its first multiply
 
-__device__ __forceinline__ float row16_max(float v) {
-    v = fmaxf(v, pair_f<1>(v));
-    v = fmaxf(v, pair_f<2>(v));
-    v = fmaxf(v, pair_f<4>(v));
-    v = fmaxf(v, pair_f<8>(v));
-    return v;
-}
-__device__ __forceinline__ float row16_sum(float v) {
-    v += pair_f<1>(v);
-    v += pair_f<2>(v);
-    v += pair_f<4>(v);
-    v += pair_f<8>(v);
-    return v;
-}
-
-// Softmax over all experts + top-k (k <= 16) for the token held by one ROW of 16 lanes: the lane
-// with row index c holds the logits of experts c, c+16, ... in v[] (-inf past E); a wavefront
-// finishes four tokens at once.  Max, sum and the k arg-max rounds (ties -> lower expert id, on
-// the logits, so rounding in exp / division can never change the selection) are four butterfly
-// steps inside the row, all on the VALU's DPP path.  Lane j of the row ends up with the j-th pick.
-// WIDE: the lane holds experts 4c..4c+3, 64+4c..64+4c+3, ... instead (what 16-byte loads of a
-// row of logits deliver); either way its experts ascend with i.
-template <bool WIDE>
-__device__ __forceinline__ int row16_expert(const int row, const int i) {
-    return WIDE ? row * 4 + (i & 3) + 64 * (i >> 2) : row + 16 * i;
-}
-template <int NV, bool WIDE = false>
-__device__ __forceinline__ void route_finish_row16(const float (&v)[NV], const int row, const int tok, const bool valid,
-                                                   const int E, const int k, const int renorm, const float scale,
-                                                   int32_t* __restrict__ idx_out, float* __restrict__ w_out,
-                                                   float* __restrict__ logits_out) {
-    float p[NV];
-    float m = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int e = row16_expert<WIDE>(row, i);
-        m = fmaxf(m, v[i]);
-        if (logits_out && valid && e < E) logits_out[(size_t)tok * E + e] = v[i];
-    }
-    m = row16_max(m);
-    float z = 0.f;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        p[i] = expf(v[i] - m);   // exp(-inf) = 0 for padded experts
-        z += p[i];
-    }
-    const float rz = 1.0f / row16_sum(z);
-    float my_w = 0.f;
-    int my_e = 0;
-    unsigned taken = 0;
-    for (int j = 0; j < k; ++j) {
-        // lane-local best among the not-yet-selected (ascending expert id, strict >)
-        float bv = -INFINITY, bp = 0.f;
-        int be = 0x7fffffff;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int e = row16_expert<WIDE>(row, i);
-            const bool ok = e < E && !((taken >> i) & 1u);
-            if (ok && (be == 0x7fffffff || v[i] > bv)) { bv = v[i]; be = e; bp = p[i]; }
-        }
-        auto step = [&](auto m_tag) __attribute__((always_inline)) {
-            constexpr int M = decltype(m_tag)::value;
-            const float ov = pair_f<M>(bv);
-            const int oe = pair_i<M>(be);
-            const float op = pair_f<M>(bp);
-            // (value, -id) is a total order over the lanes that still hold a candidate
-            if (oe != 0x7fffffff && (be == 0x7fffffff || ov > bv || (ov == bv && oe < be))) { bv = ov; be = oe; bp = op; }
-        };
-        step(std::integral_constant<int, 1>{});
-        step(std::integral_constant<int, 2>{});
-        step(std::integral_constant<int, 4>{});
-        step(std::integral_constant<int, 8>{});
-        if (row == j) { my_e = be; my_w = bp * rz; }
-#pragma unroll
-        for (int i = 0; i < NV; ++i)
-            if (row16_expert<WIDE>(row, i) == be) taken |= 1u << i;
-    }
-    const float wsum = row16_sum(row < k ? my_w : 0.f);
-    if (valid && row < k) {
-        float wv = my_w;
-        if (renorm) wv = wv / wsum;
-        idx_out[(size_t)tok * k + row] = my_e;
-        w_out[(size_t)tok * k + row] = wv * scale;
-    }
-}
-
 __global__ __launch_bounds__(ROUTE_MFMA_WAVES * 64) void route_mfma_kernel(
     const char* __restrict__ x, const char* __restrict__ wg_packed, const float* __restrict__ bias, int T, int H, int E, int k,
     int renorm, float scale, int32_t* __restrict__ idx_out, float* __restrict__ w_out, float* __restrict__ logits_out) {
@@ -306,20 +198,8 @@ __global__ __launch_bounds__(256) void route_topk_row16_kernel(const float* __re
                                                                int E, int k, const float* __restrict__ bias, int renorm,
                                                                float scale, int32_t* __restrict__ idx_out,
                                                                float* __restrict__ w_out, float* __restrict__ logits_out) {
-    const int lane = threadIdx.x & 63, row = lane & 15;
-    const int tok = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 4 + (lane >> 4);
-    const int t = min(tok, T - 1);   // rows past the end redo the last token and write nothing
-    float v[4 * NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int e0 = row * 4 + 64 * b;
-        f32x4 a = {0.f, 0.f, 0.f, 0.f};
-        if (e0 < EP)   // EP is a multiple of 32: the four values are all inside the row or all outside
-            for (int s = 0; s < splits; ++s) a += *reinterpret_cast<const f32x4*>(partial + ((size_t)s * T + t) * EP + e0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[4 * b + q] = e0 + q < E ? a[q] + (bias ? bias[e0 + q] : 0.f) : -INFINITY;
-    }
-    route_finish_row16<4 * NB, true>(v, row, tok, tok < T, E, k, renorm, scale, idx_out, w_out, logits_out);
+    topk_row16<NB>(partial, splits, T, EP, E, k, bias, renorm, scale, blockIdx.x * 4 + (threadIdx.x >> 6), threadIdx.x & 63, idx_out, w_out,
+                   logits_out);
 }
 
 }  // namespace

@@ -112,6 +112,31 @@ def test_route_exact_ties_pick_lowest_expert(moe, T, H, E, k):
     np.testing.assert_allclose(w.cpu().numpy(), 1.0 / E, rtol=1e-6)
 
 
+@pytest.mark.parametrize("E,k", [(8, 3), (16, 16), (20, 5), (64, 6), (130, 16), (160, 6), (256, 8)])
+def test_route_logits_that_are_not_finite(moe, E, k):
+    """-inf logits are picked last, lower id first; with NaN or +inf among them the picks stay distinct experts."""
+    from paper_2503_09716_amd import make_shape
+    T, H = 37, 128
+    s = make_shape(T, H, 64, E, k, 0, False)
+    x, wg, ws = normal_bf16(3, 0, (T, H), 1.0, "cuda"), normal_bf16(3, 1, (H, E), 0.02, "cuda"), moe.new_workspace(s)
+    idx, w = torch.empty((T, k), dtype=torch.int32, device="cuda"), torch.empty((T, k), device="cuda")
+    logits = torch.empty((T, E), device="cuda")
+    finite = sorted(np.random.default_rng(E).permutation(E)[:max(1, k // 2)].tolist())
+    bias = torch.full((E,), float("-inf"), device="cuda")
+    bias[finite] = 0.0
+    moe.route(s, x, wg, bias, idx, w, logits, ws)
+    rest = [e for e in range(E) if e not in finite][:k - len(finite)]
+    for t in range(T):
+        assert sorted(idx[t, :len(finite)].tolist()) == finite and idx[t, len(finite):].tolist() == rest
+    assert torch.all(w[:, len(finite):] == 0) and torch.allclose(w.sum(1), torch.ones(T, device="cuda"), atol=1e-5)
+    for value in (float("nan"), float("inf")):
+        bias = torch.zeros(E, device="cuda")
+        bias[::3] = value
+        moe.route(s, x, wg, bias, idx, w, logits, ws)
+        got = idx.cpu().numpy()
+        assert got.min() >= 0 and got.max() < E and all(len(set(r)) == k for r in got.tolist())
+
+
 @pytest.mark.parametrize("seed", range(FUZZ_SEEDS))
 def test_route_random_shapes(moe, seed):
     """Seeded random router shapes (T up to 9000, H up to 6336 in steps of 64, 1..256 experts, k up to 16, the
