@@ -259,8 +259,9 @@ moe_status weight_table(moe_ctx* c, int n, const void* const* w1, const void* co
     return MOE_OK;
 }
 
+// partial_only (more than 16 experts): stops at the partial logits.
 moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* wg, const float* bias, int32_t* idx,
-                     float* w, float* logits, char* ws, hipStream_t st) {
+                     float* w, float* logits, char* ws, hipStream_t st, bool partial_only = false) {
     const RouteGemm rg = route_gemm_config(s);
     const Layout L = make_layout(s);
     // The gate matrix is static: a caller that packs it once (moe_pack_gate, option "gate_packed")
@@ -311,6 +312,7 @@ moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     // 29.9 -> 17.4, 512 (1280 waves): 37.7 -> 28.2, 1024: 38.6 -> 39.4); beyond, x is re-read too often.  Same bits.
     if ((int64_t)((s.T + 15) / 16) * (rg.ep / 16) * rg.splits <= 1536) HIP_TRY(c, launch_route_small(a, st));
     else HIP_TRY(c, launch_ffn_gemm(false, a, cfg, st));
+    if (partial_only) return MOE_OK;
     HIP_TRY(c, launch_route_topk(s, (const float*)(ws + L.rt_logits), rg.splits, rg.ep, bias, idx, w, logits, st));
     return MOE_OK;
 }
@@ -508,38 +510,36 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
 }
 
 // x_perm_tiled: when non-null, the routed rows of GEMM 1 are read from it (tiled layout) and
-// x_perm / row_token are not used for them.  planned: the m-tile lists are there already.
-moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool planned, const void* x_perm, const int32_t* row_token,
-                   const void* x, const void* x_perm_tiled, void** tab, char* ws, void* h, void* y_perm, void* y_shared,
-                   bool y_fp32, bool shared_fp32, hipStream_t st) {
-    const Layout L = make_layout(s);
-    const SmallRule& sm = f.sm;
-    const int nt_up = f.plan.nt_up, nt_down = f.plan.nt_down, dsp = f.plan.down_splits;
+// x_perm / row_token are not used for them.
+struct FfnBuffers {
+    const void* x_perm;
+    const int32_t* row_token;
+    const void *x, *x_perm_tiled;
+    void** tab;
+    void *h, *y_perm, *y_shared;
+    bool y_fp32, shared_fp32;
+};
+
+// GEMM 1: [rows, H] x W1p/W3p [F, H] -> h [rows, F]
+GemmArgs gate_up_args(const moe_ctx* c, const moe_shape& s, const FfnSetup& f, const FfnBuffers& b) {
     const size_t Rpad = ((size_t)s.T * s.top_k + 15) & ~(size_t)15;   // shared experts' rows of h start block-aligned
-    if (!planned) {
-        StageTimer tm(c, st, MOE_STAGE_PLAN);
-        HIP_TRY(c, launch_ffn_plan(f.plan, st));
-    }
     GemmArgs a;
     memset(&a, 0, sizeof(a));
     a.plan = f.plan.plan;
     a.T = s.T;
     a.small_tiles = c->gemm.small_tiles;
-    a.out_fp32 = 0;
     a.t_pad = (s.T + 15) & ~15;
-    a.split_rows = 0;
-    // GEMM 1: [rows, H] x W1p/W3p [F, H] -> h [rows, F]
     a.descs = f.plan.descs_up;
     a.group_m = f.group_m_up;
     a.max_mtiles = f.mtiles_up;
-    a.a_routed = (const char*)(x_perm_tiled ? x_perm_tiled : (row_token ? x : x_perm));
-    a.a_shared = (const char*)x;
-    a.row_token = x_perm_tiled ? nullptr : row_token;
-    a.a_tiled = x_perm_tiled ? 1 : 0;
-    a.w_a = (const void* const*)tab;
-    a.w_b = (const void* const*)(tab + MAX_GROUPS);
-    a.out_routed = (char*)h;
-    a.out_shared = (char*)h + Rpad * s.F * 2;
+    a.a_routed = (const char*)(b.x_perm_tiled ? b.x_perm_tiled : (b.row_token ? b.x : b.x_perm));
+    a.a_shared = (const char*)b.x;
+    a.row_token = b.x_perm_tiled ? nullptr : b.row_token;
+    a.a_tiled = b.x_perm_tiled ? 1 : 0;
+    a.w_a = (const void* const*)b.tab;
+    a.w_b = (const void* const*)(b.tab + MAX_GROUPS);
+    a.out_routed = (char*)b.h;
+    a.out_shared = (char*)b.h + Rpad * s.F * 2;
     a.K = s.H;
     a.N = s.F;
     a.lda_bytes = s.H * 2;
@@ -547,48 +547,58 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool plann
     a.kt_a = s.H / 32;
     a.tail_splits = 1;
     a.nseg_shared = 1;
-    a.n_tiles = nt_up;
-    {
-        StageTimer tm(c, st, MOE_STAGE_FFN_GATE_UP);
-        if (sm.up) {
-            a.n_tiles = s.F / 32;
-            HIP_TRY(c, launch_ffn_small(true, a, 2, sm.halves, f.nt && sm.once, st));
-        } else {
-            HIP_TRY(c, launch_ffn_gemm(true, a, c->gemm, st));
-        }
-    }
-    // GEMM 2: h [rows, F] x W2p [H, F] -> y [rows, H]
+    a.n_tiles = f.sm.up ? s.F / 32 : f.plan.nt_up;
+    return a;
+}
+
+// GEMM 2: h [rows, F] x W2p [H, F] -> y [rows, H]
+GemmArgs down_args(const moe_ctx* c, const moe_shape& s, const FfnSetup& f, const FfnBuffers& b, char* ws) {
+    GemmArgs a = gate_up_args(c, s, f, b);
     a.descs = f.plan.descs_down;
     a.group_m = f.group_m_down;
     a.max_mtiles = f.mtiles_down;
-    a.a_routed = (const char*)h;
-    a.a_shared = (const char*)h + Rpad * s.F * 2;
+    a.a_routed = (const char*)b.h;
+    a.a_shared = a.out_shared;
     a.row_token = nullptr;
     a.a_tiled = 3;
-    a.w_a = (const void* const*)(tab + 2 * MAX_GROUPS);
+    a.w_a = (const void* const*)(b.tab + 2 * MAX_GROUPS);
     a.w_b = nullptr;
-    a.out_routed = (char*)y_perm;
-    a.out_shared = (char*)y_shared;
+    a.out_routed = (char*)b.y_perm;
+    a.out_shared = (char*)b.y_shared;
     a.K = s.F;
     a.N = s.H;
     a.lda_bytes = s.F * 2;
     a.kt_w = s.F / 32;
     a.kt_a = s.F / 32;
-    a.tail_splits = dsp;
-    a.out_partial = ws + L.split_partial;
+    a.tail_splits = f.plan.down_splits;
+    a.out_partial = ws + make_layout(s).split_partial;
     a.nseg_shared = s.num_shared > 0 ? s.num_shared : 1;
-    a.out_fp32 = (y_fp32 ? 1 : 0) | (shared_fp32 ? 2 : 0);
-    a.n_tiles = nt_down;
+    a.out_fp32 = (b.y_fp32 ? 1 : 0) | (b.shared_fp32 ? 2 : 0);
+    a.n_tiles = f.sm.down ? s.H / (16 * f.sm.down_cols) : f.plan.nt_down;
+    return a;
+}
+
+// planned: the m-tile lists are there already.
+moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool planned, const FfnBuffers& b, char* ws, hipStream_t st) {
+    const SmallRule& sm = f.sm;
+    const int dsp = f.plan.down_splits;
+    if (!planned) {
+        StageTimer tm(c, st, MOE_STAGE_PLAN);
+        HIP_TRY(c, launch_ffn_plan(f.plan, st));
+    }
     {
+        const GemmArgs a = gate_up_args(c, s, f, b);
+        StageTimer tm(c, st, MOE_STAGE_FFN_GATE_UP);
+        if (sm.up) HIP_TRY(c, launch_ffn_small(true, a, 2, sm.halves, f.nt && sm.once, st));
+        else HIP_TRY(c, launch_ffn_gemm(true, a, c->gemm, st));
+    }
+    {
+        const GemmArgs a = down_args(c, s, f, b, ws);
         StageTimer tm(c, st, MOE_STAGE_FFN_DOWN);
-        if (sm.down) {
-            a.n_tiles = s.H / (16 * sm.down_cols);
-            HIP_TRY(c, launch_ffn_small(false, a, sm.down_cols, sm.halves, f.nt && sm.once, st));
-        } else {
-            HIP_TRY(c, launch_ffn_gemm(false, a, c->gemm, st));
-        }
+        if (sm.down) HIP_TRY(c, launch_ffn_small(false, a, sm.down_cols, sm.halves, f.nt && sm.once, st));
+        else HIP_TRY(c, launch_ffn_gemm(false, a, c->gemm, st));
         if (dsp > 1)
-            HIP_TRY(c, launch_split_tail_reduce(s, f.plan.plan, f.plan.split_tails, (const float*)(ws + L.split_partial), dsp, y_perm, y_fp32, st));
+            HIP_TRY(c, launch_split_tail_reduce(s, f.plan.plan, f.plan.split_tails, (const float*)a.out_partial, dsp, b.y_perm, b.y_fp32, st));
     }
     return MOE_OK;
 }
@@ -604,9 +614,9 @@ struct LayerFront {
     bool planned;          // the m-tile lists were built next to the permutation
 };
 
-moe_status run_front(moe_ctx* c, const moe_shape& s, const void* x, const void* wg, const float* bias, char* w8,
-                     hipStream_t hs, const PlanArgs* plan, LayerFront* f) {
+LayerFront layer_front(const moe_ctx* c, const moe_shape& s, char* w8) {
     const Layout L = make_layout(s);
+    LayerFront v, *f = &v;
     f->topk_idx = (int32_t*)(w8 + L.topk_idx);
     f->topk_w = (float*)(w8 + L.topk_w);
     f->offsets = (int32_t*)(w8 + L.offsets);
@@ -616,6 +626,25 @@ moe_status run_front(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     f->h = w8 + L.h;
     f->y_perm = w8 + L.y_perm;
     f->y_shared = s.num_shared > 0 ? (void*)(w8 + L.y_shared) : nullptr;
+    f->x_tiled = nullptr;
+    f->planned = false;
+    // y_perm in bf16 halves the down projection's stores and the combine's loads.  Its rounding
+    // moves out[t] by at most sum_j w_j * 2^-8 * |y_j|.  Chosen when that is small against the
+    // output: at least 4 routed terms next to shared experts of weight 1, which then carry most
+    // of the output (measured at full size: no change of the error).  Without shared experts the
+    // routed terms are the whole output and their rounding would use up most of the error bar
+    // whatever their weights: fp32 there (measured on the Mixtral-shaped workloads against the
+    // oracle, every token: bf16 y_perm would take 1 % off the step and move the worst element
+    // from 1.04e-2 to 1.97e-2 x RMS on the 8x7B shape and to 2.1e-2, past the bar, on the 8x22B shape).
+    // y_shared (weight 1) is always fp32.
+    f->y32 = c->layer_y >= 0 ? c->layer_y != 0 : !(s.top_k >= 4 && s.num_shared > 0);
+    return v;
+}
+
+moe_status run_front(moe_ctx* c, const moe_shape& s, const void* x, const void* wg, const float* bias, char* w8,
+                     hipStream_t hs, const PlanArgs* plan, LayerFront* f) {
+    const Layout L = make_layout(s);
+    *f = layer_front(c, s, w8);
     {
         StageTimer tm(c, hs, MOE_STAGE_ROUTE);
         if (moe_status st = run_route(c, s, x, wg, bias, f->topk_idx, f->topk_w, nullptr, w8, hs)) return st;
@@ -632,23 +661,18 @@ moe_status run_front(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     // gather + gate/up GEMM, tiled against fused: 347 / 341 us at 16 rows per expert, 366 / 362 at 64,
     // 410 / 440 at 175).
     const bool tiled = c->gemm.x_tiled == 1 || (c->gemm.x_tiled < 0 && s.F >= 4096 && (int64_t)s.T * s.top_k > 64 * (int64_t)s.E);
-    f->x_tiled = nullptr;
     if (tiled) {
         StageTimer tm(c, hs, MOE_STAGE_PERMUTE_GATHER);
         HIP_TRY(c, launch_permute_gather_tiled(s, x, f->row_token, w8 + L.x_tiled, hs));
         f->x_tiled = w8 + L.x_tiled;
     }
-    // y_perm in bf16 halves the down projection's stores and the combine's loads.  Its rounding
-    // moves out[t] by at most sum_j w_j * 2^-8 * |y_j|.  Chosen when that is small against the
-    // output: at least 4 routed terms next to shared experts of weight 1, which then carry most
-    // of the output (measured at full size: no change of the error).  Without shared experts the
-    // routed terms are the whole output and their rounding would use up most of the error bar
-    // whatever their weights: fp32 there (measured on the Mixtral-shaped workloads against the
-    // oracle, every token: bf16 y_perm would take 1 % off the step and move the worst element
-    // from 1.04e-2 to 1.97e-2 x RMS on the 8x7B shape and to 2.1e-2, past the bar, on the 8x22B shape).
-    // y_shared (weight 1) is always fp32.
-    f->y32 = c->layer_y >= 0 ? c->layer_y != 0 : !(s.top_k >= 4 && s.num_shared > 0);
     return MOE_OK;
+}
+
+// A layer of up to 16 tokens whose two GEMMs both run one wavefront per 16 or 32 columns goes without m-tile lists
+// (launch_decode); not while its stages are timed, which it does not keep apart.
+bool decode_rule(const moe_ctx* c, const moe_shape& s, const SmallRule& sm) {
+    return !c->prof && sm.up && sm.down && sm.down_cols == 1 && s.T <= 16 && s.top_k <= 16 && c->gemm.x_tiled != 1;
 }
 
 // The whole layer with its intermediates in `ws` (validated by the caller).
@@ -659,11 +683,22 @@ moe_status layer_with_workspace(moe_ctx* c, const moe_shape* s, const void* x, c
     if (moe_status st = weight_table(c, s->E + s->num_shared, w1p, w3p, w2p, hs, &tab)) return st;
     const FfnSetup fs = ffn_setup(c, *s, (const int32_t*)(ws + make_layout(*s).offsets), ws, whole_layer(*s));
     LayerFront f;
+    if (decode_rule(c, *s, fs.sm)) {
+        f = layer_front(c, *s, ws);
+        const FfnBuffers b{nullptr, f.row_token, x, nullptr, tab, f.h, f.y_perm, f.y_shared, f.y32, true};
+        const RouteGemm rg = route_gemm_config(*s);
+        if (moe_status st = run_route(c, *s, x, wg, bias, f.topk_idx, f.topk_w, nullptr, ws, hs, true)) return st;
+        const DecodeArgs d{rg.splits ? (const float*)(ws + make_layout(*s).rt_logits) : nullptr, bias, rg.splits, rg.ep, s->renormalize,
+                           s->routed_scale, f.topk_idx, f.offsets, f.perm, f.inv_perm, f.row_token, f.topk_w,
+                           s->T * s->top_k, s->top_k, s->E, s->num_shared};
+        HIP_TRY(c, launch_decode(gate_up_args(c, *s, fs, b), down_args(c, *s, fs, b, ws), d, fs.nt, hs));
+        HIP_TRY(c, launch_combine(*s, f.y_perm, f.inv_perm, f.topk_w, f.y_shared, out, f.y32, true, c->out_fp32, hs));
+        return MOE_OK;
+    }
     // While stages are timed the lists are built by a launch of their own, so that it can be told from the permutation.
     if (moe_status st = run_front(c, *s, x, wg, bias, ws, hs, c->prof ? nullptr : &fs.plan, &f)) return st;
-    if (moe_status st = run_ffn(c, *s, fs, f.planned, nullptr, f.row_token, x, f.x_tiled, tab, ws, f.h, f.y_perm,
-                                f.y_shared, f.y32, true, hs))
-        return st;
+    const FfnBuffers b{nullptr, f.row_token, x, f.x_tiled, tab, f.h, f.y_perm, f.y_shared, f.y32, true};
+    if (moe_status st = run_ffn(c, *s, fs, f.planned, b, ws, hs)) return st;
     {
         StageTimer tm(c, hs, MOE_STAGE_COMBINE);
         HIP_TRY(c, launch_combine(*s, f.y_perm, f.inv_perm, f.topk_w, f.y_shared, out, f.y32, true, c->out_fp32, hs));
@@ -831,8 +866,8 @@ moe_status moe_grouped_ffn(moe_ctx* c, const moe_shape* s, const void* x_perm, c
     hipStream_t hs = (hipStream_t)stream;
     void** tab = nullptr;
     if (moe_status st = weight_table(c, s->E + s->num_shared, w1p, w3p, w2p, hs, &tab)) return st;
-    return run_ffn(c, *s, ffn_setup(c, *s, offsets, (char*)ws, whole_layer(*s)), false, x_perm, row_token, x, nullptr, tab,
-                   (char*)ws, h, y_perm, y_shared, c->y_fp32, c->y_fp32, hs);
+    const FfnBuffers b{x_perm, row_token, x, nullptr, tab, h, y_perm, y_shared, c->y_fp32, c->y_fp32};
+    return run_ffn(c, *s, ffn_setup(c, *s, offsets, (char*)ws, whole_layer(*s)), false, b, (char*)ws, hs);
 }
 
 moe_status moe_combine(moe_ctx* c, const moe_shape* s, const void* y_perm, const int32_t* inv_perm, const float* w,
@@ -975,9 +1010,8 @@ moe_status moe_layer_streamed(moe_ctx* c, const moe_shape* s, const void* x, con
         void** tab = nullptr;
         if (moe_status st = weight_table(c, E + Ns, t1.data(), t3.data(), t2.data(), hs, &tab)) return st;
         const FfnPass pass{G.shared ? 0 : G.lo, G.shared ? 0 : G.hi, G.shared, mt, G.shared ? (s->T + 127) / 128 : mt};
-        if (moe_status st = run_ffn(c, *s, ffn_setup(c, *s, f.offsets, (char*)ws, pass), false, nullptr, f.row_token, x, f.x_tiled,
-                                    tab, (char*)ws, f.h, f.y_perm, f.y_shared, f.y32, true, hs))
-            return st;
+        const FfnBuffers b{nullptr, f.row_token, x, f.x_tiled, tab, f.h, f.y_perm, f.y_shared, f.y32, true};
+        if (moe_status st = run_ffn(c, *s, ffn_setup(c, *s, f.offsets, (char*)ws, pass), false, b, (char*)ws, hs)) return st;
         HIP_TRY(c, hipEventRecord(c->slot_free[slot], hs));
         ++c->stream_groups;
     }

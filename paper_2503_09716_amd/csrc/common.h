@@ -96,6 +96,17 @@ struct PlanArgs {
     TileDesc *descs_up, *descs_down;
 };
 
+// A layer of up to 16 tokens (ffn_small.hip): what its launches need beside the two GEMMs' arguments.
+struct DecodeArgs {
+    const float* partial;      // more than 16 experts: partial logits [splits][T][ep], top-k still to be done; else nullptr
+    const float* bias;
+    int32_t splits, ep, renorm;
+    float scale;
+    int32_t *topk_idx, *offsets, *perm, *inv_perm, *row_token;
+    float* topk_w;
+    int32_t pairs, k, E, Ns;
+};
+
 struct GemmConfig {
     int wave_rows;    // rows of the wave grid: 1 or 2 with 4 waves, 2 or 4 with 8 waves
     int waves;        // wavefronts per workgroup: 4 or 8
@@ -158,6 +169,9 @@ hipError_t launch_ffn_gemm(bool gated, const GemmArgs& a, const GemmConfig& cfg,
 // the same GEMMs with one wavefront per 16 * col_blocks columns (small batches): a.n_tiles column units per
 // m-tile, m-tiles of at most 64 * halves rows; gate/up: col_blocks = 2; nt: non-temporal loads of W
 hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int halves, bool nt, hipStream_t st);
+// a layer of up to 16 tokens from the router's partial logits (none: from topk_idx and topk_w) to the down GEMM, with the
+// permutation's index arrays
+hipError_t launch_decode(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st);
 hipError_t launch_route_small(const GemmArgs& a, hipStream_t st);   // the router GEMM, one wavefront per 16 tokens x 16 experts x K piece
 hipError_t ffn_gemm_init();  // one-time function attributes (dynamic LDS size)
 

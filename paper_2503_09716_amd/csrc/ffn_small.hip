@@ -16,6 +16,7 @@
 // Every output element is one chain of v_mfma_f32_16x16x32_bf16 over K in ascending order with the
 // operands in the same roles as in the tile routine, so both give the same bits.
 #include "common.h"
+#include "topk.h"
 
 namespace moe {
 namespace {
@@ -29,9 +30,10 @@ constexpr int SMALL_ROWS = 64;   // rows of X per wave at most: an m-tile of up 
 
 // One unit: rows r0 .. r0 + 16 * XB - 1 of tile d (nrows of the tile are valid), columns n0 .. n0 + 16 * NB - 1.
 // ROUTER: the gate GEMM, K piece d.group of one packed matrix, fp32 partial logits.
-// NT: W loads are non-temporal.
+// NT: W loads are non-temporal.  tokens: row r of a routed tile is token tokens[r] (LDS) instead of row_token's.
 template <bool GATED, int NB, int XB, int RING, bool NT, bool ROUTER = false>
-__device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, const int r0, const int n0, const int lane) {
+__device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, const int r0, const int n0, const int lane,
+                                           const int* tokens = nullptr) {
     constexpr int WQ = GATED ? 2 * NB : NB;   // W blocks per sub-tile
     const int rl = lane & 15, g = lane >> 4;
     const bool shared = !ROUTER && d.srow >= 0;
@@ -46,7 +48,8 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
     for (int i = 0; i < XB; ++i) {
         int grow = d.row0 + min(r0 + i * 16 + rl, d.nrows - 1);   // padded rows re-read the last valid row
         if (!a_tiled) {
-            if (!ROUTER && !shared && p.row_token) grow = p.row_token[grow];
+            if (!ROUTER && !shared && tokens) grow = tokens[grow - d.row0];
+            else if (!ROUTER && !shared && p.row_token) grow = p.row_token[grow];
             xoff[i] = (uint32_t)grow * (uint32_t)p.lda_bytes + (uint32_t)(g * 16);
         } else {
             const int rr = grow & 15;
@@ -197,6 +200,163 @@ __global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
     small_unit<false, 1, 1, 16, false, true>(p, d, 0, nb * 16, threadIdx.x);
 }
 
+// ---- a layer of up to 16 tokens --------------------------------------------------------------------------
+// Every group is then one block of 16 rows, and what a wave needs to know of the routing - its expert's
+// tokens and where their rows begin - it reads off topk_idx itself (at most 256 pairs, a vote per 64).  So no launch
+// stands between the selection and the gate/up GEMM: the permutation's index arrays are written by one wave of that
+// GEMM's launch.  Shared experts wait for nothing: with more than 16 experts their gate/up GEMM runs next to the
+// top-k, whose launch leaves the memory idle, and their down GEMM, the longest walk of all, next to the routed gate/up
+// GEMM.  (The first
+// part of that next to the router GEMM instead: 2 us slower.)  Same bits as the launches by list.  Layer, us: 64 experts
+// top-6 + 2 shared, F = 1408, 1 token 42.2 -> 35.7, 4: 85 -> 79, 16: 167 -> 155; 160 experts, 1: 82 -> 74, 16: 583 -> 568; 8
+// experts top-2, F = 14336, 1: 125 -> 116, 16: 441 -> 430; H = 512, F = 1024, 8 tokens 23 -> 17.
+struct Group {
+    int expert, row0, rows;
+};
+// Candidate c of the routed groups: expert c, or with fewer pairs than experts the expert of pair c, of which the first
+// pair that has it is taken.  False: no rows.
+__device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[16]) {
+    const bool by_pair = a.pairs <= a.E;
+    const int e = __builtin_amdgcn_readfirstlane(by_pair ? a.topk_idx[c] : c);
+    int n = 0, before = 0;
+    for (int base = 0; base < a.pairs; base += 64) {
+        const int p = base + lane, v = p < a.pairs ? a.topk_idx[p] : 0x7fffffff;
+        const uint64_t eq = __ballot(v == e);
+        if (by_pair && n == 0 && eq && base + __builtin_ctzll(eq) != c) return false;
+        const int rank = n + __popcll(eq & ((1ull << lane) - 1));
+        if (v == e && rank < 16) tokens[rank] = p / a.k;
+        n += __popcll(eq);
+        before += __popcll(__ballot(v < e));
+    }
+    __syncthreads();   // one wave: orders its LDS writes and reads
+    g.expert = e;
+    g.row0 = before;
+    g.rows = min(n, 16);   // a token has an expert once
+    return n > 0;
+}
+
+// expert_offsets and the index arrays of the permutation, by one wave (E <= 256, pairs in chunks of 64).
+__device__ __forceinline__ void decode_index(const DecodeArgs& a, const int lane) {
+    __shared__ int cursor[256];
+    __shared__ unsigned long long mask[256];
+    for (int e = lane; e < 256; e += 64) { cursor[e] = 0; mask[e] = 0; }
+    __syncthreads();
+    for (int p = lane; p < a.pairs; p += 64) atomicAdd(&cursor[a.topk_idx[p]], 1);
+    __syncthreads();
+    int count[4], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { count[i] = cursor[4 * lane + i]; sum += count[i]; }
+    int before = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(before, d, 64);
+        if (lane >= d) before += t;
+    }
+    before -= sum;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = 4 * lane + i;
+        cursor[e] = before;
+        if (e < a.E) a.offsets[e] = before;
+        before += count[i];
+    }
+    if (lane == 0) a.offsets[a.E] = a.pairs;
+    __syncthreads();
+    for (int base = 0; base < a.pairs; base += 64) {
+        const int p = base + lane;
+        const bool valid = p < a.pairs;
+        const int e = valid ? a.topk_idx[p] : 0;
+        if (valid) atomicOr(&mask[e], 1ull << lane);
+        __syncthreads();
+        const unsigned long long m = mask[e];
+        const int rank = __popcll(m & ((1ull << lane) - 1));
+        if (valid) {
+            const int slot = cursor[e] + rank;
+            a.perm[slot] = p;
+            a.inv_perm[p] = slot;
+            a.row_token[slot] = p / a.k;
+        }
+        __syncthreads();
+        if (valid && rank == 0) { cursor[e] += __popcll(m); mask[e] = 0; }
+        __syncthreads();
+    }
+}
+
+__device__ __forceinline__ TileDesc shared_tile(const DecodeArgs& a, const GemmArgs& p, const int s) { return {a.E + s, 0, p.T, s * p.t_pad}; }
+
+// Units of 16 columns while the weights come from memory: twice the waves, and so bytes in flight, of units of 32 (64
+// experts, 1 token 38.9 -> 35.7 us, 160: 83.9 -> 74.5, 16 tokens 159 -> 155); a layer that the cache holds is faster with 32 (H =
+// 512, F = 1024, 16 tokens 17.3 us, 18.1 with 16).
+template <bool NT>
+__host__ __device__ constexpr int up_blocks() { return NT ? 1 : 2; }
+template <bool NT>
+__device__ __forceinline__ void up_unit(const GemmArgs& up, const TileDesc& d, const int unit, const int lane, const int* tokens = nullptr) {
+    constexpr int UB = up_blocks<NT>();
+    small_unit<true, UB, 1, 16 / UB, NT>(up, d, 0, unit * 16 * UB, lane, tokens);
+}
+// Gate/up unit `unit` of all shared experts'.
+template <bool NT>
+__device__ __forceinline__ void shared_up_unit(const GemmArgs& up, const DecodeArgs& a, const int unit, const int lane) {
+    const int s = unit / up.n_tiles;
+    up_unit<NT>(up, shared_tile(a, up, s), unit - s * up.n_tiles, lane);
+}
+
+// Top-k of four tokens per workgroup, then the shared experts' gate/up units.
+template <int NB, bool NT>
+__global__ __launch_bounds__(64, 2) void decode_topk_kernel(const GemmArgs up, const DecodeArgs a) {
+    const int lane = threadIdx.x, quads = (up.T + 3) >> 2, b = blockIdx.x;
+    if (b < quads) topk_row16<NB>(a.partial, a.splits, up.T, a.ep, a.E, a.k, a.bias, a.renorm, a.scale, b, lane, a.topk_idx, a.topk_w, nullptr);
+    else shared_up_unit<NT>(up, a, b - quads, lane);
+}
+
+// Workgroup 0: the index arrays.  Then the shared experts' down units (early: their gate/up units are done) or gate/up units,
+// then the routed gate/up units.
+template <bool NT>
+__global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, const GemmArgs down, const DecodeArgs a, const bool early) {
+    __shared__ int tokens[16];
+    const int lane = threadIdx.x;
+    if (blockIdx.x == 0) {
+        decode_index(a, lane);
+        return;
+    }
+    int b = blockIdx.x - 1;
+    if (early) {
+        if (b < down.n_tiles) {
+            small_unit<false, 1, 1, 16, NT>(down, shared_tile(a, down, 0), 0, b * 16, lane);
+            return;
+        }
+        b -= down.n_tiles;
+    } else if (b < a.Ns * up.n_tiles) {
+        shared_up_unit<NT>(up, a, b, lane);
+        return;
+    } else {
+        b -= a.Ns * up.n_tiles;
+    }
+    const int c = b / up.n_tiles;
+    Group g;
+    if (!decode_group(a, c, lane, g, tokens)) return;
+    up_unit<NT>(up, {g.expert, g.row0, g.rows, -1}, b - c * up.n_tiles, lane, tokens);
+}
+
+// The shared experts' down units (unless early), then the routed ones.
+template <bool NT>
+__global__ __launch_bounds__(64, 2) void decode_down_kernel(const GemmArgs down, const DecodeArgs a, const bool early) {
+    __shared__ int tokens[16];
+    const int lane = threadIdx.x;
+    int b = blockIdx.x;
+    if (!early && a.Ns > 0) {
+        if (b < down.n_tiles) {
+            small_unit<false, 1, 1, 16, NT>(down, shared_tile(a, down, 0), 0, b * 16, lane);
+            return;
+        }
+        b -= down.n_tiles;
+    }
+    const int c = b / down.n_tiles;
+    Group g;
+    if (!decode_group(a, c, lane, g, tokens)) return;
+    small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, (b - c * down.n_tiles) * 16, lane);
+}
+
 }  // namespace
 
 hipError_t launch_route_small(const GemmArgs& a, hipStream_t st) {
@@ -217,6 +377,33 @@ hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int h
     else SMALL(false, 1);
 #undef SMALL
     return hipGetLastError();
+}
+
+namespace {
+template <bool NT>
+hipError_t launch_decode_nt(GemmArgs up, const GemmArgs& down, const DecodeArgs& a, hipStream_t st) {
+    const int candidates = a.pairs < a.E ? a.pairs : a.E;
+    const bool early = a.partial && a.Ns > 0;
+    const dim3 block(64);
+    up.n_tiles = up.N / (16 * up_blocks<NT>());
+    const int shared_units = a.Ns * up.n_tiles;
+#define DECODE(grid_, K_, ...) hipLaunchKernelGGL((K_), dim3((unsigned)(grid_)), block, 0, st, __VA_ARGS__)
+    if (a.partial) {
+        const int grid = (up.T + 3) / 4 + shared_units;
+        if (a.E <= 64) DECODE(grid, (decode_topk_kernel<1, NT>), up, a);
+        else if (a.E <= 128) DECODE(grid, (decode_topk_kernel<2, NT>), up, a);
+        else if (a.E <= 192) DECODE(grid, (decode_topk_kernel<3, NT>), up, a);
+        else DECODE(grid, (decode_topk_kernel<4, NT>), up, a);
+    }
+    DECODE(1 + (early ? down.n_tiles : shared_units) + candidates * up.n_tiles, (decode_up_kernel<NT>), up, down, a, early);
+    DECODE((early || !a.Ns ? 0 : down.n_tiles) + candidates * down.n_tiles, (decode_down_kernel<NT>), down, a, early);
+#undef DECODE
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_decode(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st) {
+    return nt ? launch_decode_nt<true>(up, down, a, st) : launch_decode_nt<false>(up, down, a, st);
 }
 
 }  // namespace moe

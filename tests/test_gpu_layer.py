@@ -616,6 +616,38 @@ def test_layer_small_batches_give_the_tile_routine_s_bits(moe, T, H, F, E, k, sh
         say(json.dumps(P.check_layer_against_oracle(gl, out, out16=out16)["output"]))
 
 
+# Layers of up to 16 tokens, whose waves read the routing off topk_idx: fewer pairs than experts, as many, more; pairs in one chunk
+# of 64, at its edges and in several; every width of the top-k; shared experts next to it and next to the gate/up GEMM.
+DECODE_CASES = [(1, 17, 1, 0), (1, 64, 16, 1), (2, 32, 16, 0), (4, 16, 16, 2), (4, 20, 16, 1), (5, 65, 13, 0), (8, 128, 8, 2), (13, 200, 5, 8),
+                (16, 256, 16, 0), (16, 248, 16, 8), (16, 17, 16, 1), (16, 4, 1, 0), (3, 1, 1, 1), (16, 2, 2, 3)]
+
+
+@pytest.mark.parametrize("T,E,k,shared", DECODE_CASES)
+def test_layer_of_few_tokens_leaves_the_same_routing_and_bits(moe, T, E, k, shared):
+    """Against the launches by tile list (small_tiles = 0): offsets, inverse permutation, selection and output."""
+    cfg = scaled_config("C4", T=T, H=192, F=128, E=E, top_k=k, num_shared=shared)
+    say("few tokens", cfg)
+    gl = P.GpuLayer(moe, make_layer_inputs(cfg, device="cuda"))
+    moe.set_option("layer_y_fp32", 1)
+    moe.set_option("down_tail_splits", 0)
+    got = []
+    try:
+        for small_tiles in (1, 0):
+            moe.set_option("small_tiles", small_tiles)
+            gl.ws.fill_(255)
+            out, out16 = gl.run_layer_both()
+            views = moe.layer_views(gl.shape, gl.ws)
+            got.append([out, out16] + [v.clone() for _, v in sorted(views.items())])
+    finally:
+        moe.set_option("small_tiles", 1)
+        moe.set_option("layer_y_fp32", -1)
+        moe.set_option("down_tail_splits", 1)
+    assert len(got[0]) == 6
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    say(json.dumps(P.check_layer_against_oracle(gl, got[0][0], out16=got[0][1])["routing"]))
+
+
 # Layers just above 256 MB, whose weights are loaded non-temporally where one tile or wave reads them: (H, F, experts, k); the second
 # shape has few enough tiles for one wavefront per 32 columns up to 128 tokens.
 READ_ONCE_SHAPES = [(4096, 3072, 4, 2), (4096, 3072, 4, 4), (8192, 1408, 4, 2), (8192, 1408, 4, 4)]
