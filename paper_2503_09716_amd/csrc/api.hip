@@ -395,7 +395,7 @@ SmallRule small_rule(const moe_ctx* c, const moe_shape& s) {
     const int tiles_up = (groups + s.num_shared) * nt_up, tiles_down = (groups + (s.num_shared > 0)) * nt_down;
     const bool allowed = c->gemm.small_tiles && !c->gemm.tile_rows_up && !c->gemm.tile_rows_down && c->gemm.down_tail_splits != 2;
     r.down_cols = s.T <= 32 ? 1 : 2;
-    r.up = allowed && (s.T <= 16 || (s.T <= 128 && tiles_up <= 64));
+    r.up = allowed && (s.T <= 16 || (tiles_up <= 64 && (s.T <= 128 || (s.T <= 256 && pairs <= 64 * (int64_t)groups))));
     r.down = allowed && ((s.T <= 64 && pairs <= 16 * (int64_t)groups && tiles_down < 8 * 256) ||
                          (s.T <= 256 && tiles_down <= (s.T <= 64 ? 256 : 64) &&
                           small_down_wins(s, groups, tiles_down, call_down_splits(c, s), r.down_cols)));
@@ -669,10 +669,12 @@ moe_status run_front(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     return MOE_OK;
 }
 
-// A layer of up to 16 tokens whose two GEMMs both run one wavefront per 16 or 32 columns goes without m-tile lists
-// (launch_decode); not while its stages are timed, which it does not keep apart.
-bool decode_rule(const moe_ctx* c, const moe_shape& s, const SmallRule& sm) {
-    return !c->prof && sm.up && sm.down && sm.down_cols == 1 && s.T <= 16 && s.top_k <= 16 && c->gemm.x_tiled != 1;
+// Layers whose two GEMMs both run one wavefront per 16 or 32 columns go without m-tile lists: 1, up to 16 tokens
+// (launch_decode); 2, up to 256 tokens and 1024 pairs (launch_decode_wide).  Not while stages are timed, which these launches do not
+// keep apart.
+int decode_rule(const moe_ctx* c, const moe_shape& s, const SmallRule& sm) {
+    if (c->prof || !sm.up || !sm.down || s.top_k > 16 || c->gemm.x_tiled == 1) return 0;
+    return s.T <= 16 ? 1 : (s.T <= 256 && s.T * s.top_k <= 1024 ? 2 : 0);
 }
 
 // The whole layer with its intermediates in `ws` (validated by the caller).
@@ -683,15 +685,17 @@ moe_status layer_with_workspace(moe_ctx* c, const moe_shape* s, const void* x, c
     if (moe_status st = weight_table(c, s->E + s->num_shared, w1p, w3p, w2p, hs, &tab)) return st;
     const FfnSetup fs = ffn_setup(c, *s, (const int32_t*)(ws + make_layout(*s).offsets), ws, whole_layer(*s));
     LayerFront f;
-    if (decode_rule(c, *s, fs.sm)) {
+    if (const int decode = decode_rule(c, *s, fs.sm)) {
         f = layer_front(c, *s, ws);
         const FfnBuffers b{nullptr, f.row_token, x, nullptr, tab, f.h, f.y_perm, f.y_shared, f.y32, true};
         const RouteGemm rg = route_gemm_config(*s);
-        if (moe_status st = run_route(c, *s, x, wg, bias, f.topk_idx, f.topk_w, nullptr, ws, hs, true)) return st;
-        const DecodeArgs d{rg.splits ? (const float*)(ws + make_layout(*s).rt_logits) : nullptr, bias, rg.splits, rg.ep, s->renormalize,
+        if (moe_status st = run_route(c, *s, x, wg, bias, f.topk_idx, f.topk_w, nullptr, ws, hs, decode == 1)) return st;
+        const DecodeArgs d{rg.splits && decode == 1 ? (const float*)(ws + make_layout(*s).rt_logits) : nullptr, bias, rg.splits, rg.ep, s->renormalize,
                            s->routed_scale, f.topk_idx, f.offsets, f.perm, f.inv_perm, f.row_token, f.topk_w,
                            s->T * s->top_k, s->top_k, s->E, s->num_shared};
-        HIP_TRY(c, launch_decode(gate_up_args(c, *s, fs, b), down_args(c, *s, fs, b, ws), d, fs.nt, hs));
+        const GemmArgs up = gate_up_args(c, *s, fs, b), down = down_args(c, *s, fs, b, ws);
+        if (decode == 1) HIP_TRY(c, launch_decode(up, down, d, fs.nt, hs));
+        else HIP_TRY(c, launch_decode_wide(up, down, d, fs.sm.down_cols, fs.nt && fs.sm.once, hs));
         HIP_TRY(c, launch_combine(*s, f.y_perm, f.inv_perm, f.topk_w, f.y_shared, out, f.y32, true, c->out_fp32, hs));
         return MOE_OK;
     }

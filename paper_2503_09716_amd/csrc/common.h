@@ -96,7 +96,7 @@ struct PlanArgs {
     TileDesc *descs_up, *descs_down;
 };
 
-// A layer of up to 16 tokens (ffn_small.hip): what its launches need beside the two GEMMs' arguments.
+// A layer of few pairs (ffn_small.hip): what its launches need beside the two GEMMs' arguments.
 struct DecodeArgs {
     const float* partial;      // more than 16 experts: partial logits [splits][T][ep], top-k still to be done; else nullptr
     const float* bias;
@@ -172,6 +172,8 @@ hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int h
 // a layer of up to 16 tokens from the router's partial logits (none: from topk_idx and topk_w) to the down GEMM, with the
 // permutation's index arrays
 hipError_t launch_decode(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st);
+// the same from topk_idx and topk_w on, for up to 256 tokens; n_tiles: units of 32 and of 16 * col_blocks columns
+hipError_t launch_decode_wide(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, int col_blocks, bool nt, hipStream_t st);
 hipError_t launch_route_small(const GemmArgs& a, hipStream_t st);   // the router GEMM, one wavefront per 16 tokens x 16 experts x K piece
 hipError_t ffn_gemm_init();  // one-time function attributes (dynamic LDS size)
 

@@ -166,6 +166,18 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
     }
 }
 
+// Part `part` of `parts` of tile d: every parts-th 64 rows, columns n0 ..
+template <bool GATED, int NB, bool NT>
+__device__ __forceinline__ void small_rows(const GemmArgs& p, const TileDesc& d, const int part, const int parts, const int n0, const int lane,
+                                           const int* tokens = nullptr) {
+    for (int r0 = part * SMALL_ROWS; r0 < d.nrows; r0 += parts * SMALL_ROWS) {
+        const int blocks = (min(d.nrows - r0, SMALL_ROWS) + 15) >> 4;   // wave-uniform
+        if (blocks > 2) small_unit<GATED, NB, 4, GATED ? 4 : (NB == 2 ? 5 : 6), NT>(p, d, r0, n0, lane, tokens);
+        else if (blocks > 1) small_unit<GATED, NB, 2, GATED ? 6 : (NB == 2 ? 7 : 8), NT>(p, d, r0, n0, lane, tokens);
+        else small_unit<GATED, NB, 1, GATED ? 8 : (NB == 2 ? 8 : 16), NT>(p, d, r0, n0, lane, tokens);
+    }
+}
+
 // Units in the order: columns fastest, then the 64-row parts of an m-tile (`halves` of them side by
 // side; a unit takes every halves-th part, whatever the tile's height), then m-tiles.
 template <bool GATED, int NB, bool NT>
@@ -177,13 +189,7 @@ __global__ __launch_bounds__(64, 2) void ffn_small_kernel(const GemmArgs p, cons
     const int rem = blockIdx.x - mt * per, half = rem / p.n_tiles;
     TileDesc d = p.descs[mt];
     d.nrows &= TILE_ROWS_MASK;
-    const int n0 = (rem - half * p.n_tiles) * 16 * NB;
-    for (int r0 = half * SMALL_ROWS; r0 < d.nrows; r0 += halves * SMALL_ROWS) {
-        const int blocks = (min(d.nrows - r0, SMALL_ROWS) + 15) >> 4;   // wave-uniform
-        if (blocks > 2) small_unit<GATED, NB, 4, GATED ? 4 : (NB == 2 ? 5 : 6), NT>(p, d, r0, n0, lane);
-        else if (blocks > 1) small_unit<GATED, NB, 2, GATED ? 6 : (NB == 2 ? 7 : 8), NT>(p, d, r0, n0, lane);
-        else small_unit<GATED, NB, 1, GATED ? 8 : (NB == 2 ? 8 : 16), NT>(p, d, r0, n0, lane);
-    }
+    small_rows<GATED, NB, NT>(p, d, half, halves, (rem - half * p.n_tiles) * 16 * NB, lane);
 }
 
 // Router GEMM of a small batch: one wave per 16 tokens, 16 experts and K piece.  The tile routine has one
@@ -200,11 +206,11 @@ __global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
     small_unit<false, 1, 1, 16, false, true>(p, d, 0, nb * 16, threadIdx.x);
 }
 
-// ---- a layer of up to 16 tokens --------------------------------------------------------------------------
-// Every group is then one block of 16 rows, and what a wave needs to know of the routing - its expert's
-// tokens and where their rows begin - it reads off topk_idx itself (at most 256 pairs, a vote per 64).  So no launch
+// ---- layers of few pairs: up to 16 tokens, or up to 256 in small layers ---------------------------------------
+// What a wave needs to know of the routing - its expert's
+// tokens and where their rows begin - it reads off topk_idx itself (at most 1024 pairs, a vote per 64).  So no launch
 // stands between the selection and the gate/up GEMM: the permutation's index arrays are written by one wave of that
-// GEMM's launch.  Shared experts wait for nothing: with more than 16 experts their gate/up GEMM runs next to the
+// GEMM's launch.  Up to 16 tokens every group is one block of 16 rows, and shared experts wait for nothing: with more than 16 experts their gate/up GEMM runs next to the
 // top-k, whose launch leaves the memory idle, and their down GEMM, the longest walk of all, next to the routed gate/up
 // GEMM.  (The first
 // part of that next to the router GEMM instead: 2 us slower.)  Same bits as the launches by list.  Layer, us: 64 experts
@@ -215,33 +221,52 @@ struct Group {
 };
 // Candidate c of the routed groups: expert c, or with fewer pairs than experts the expert of pair c, of which the first
 // pair that has it is taken.  False: no rows.
-__device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[16]) {
+// MAX: tokens at most; the pairs come 64 * CHUNKS at a time, all loads of which are in flight together.
+template <int MAX>
+__device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[MAX]) {
+    constexpr int CHUNKS = MAX <= 16 ? 1 : 8;   // (few pairs: more code costs more than loads in turn, 1 token 0.8 us)
     const bool by_pair = a.pairs <= a.E;
     const int e = __builtin_amdgcn_readfirstlane(by_pair ? a.topk_idx[c] : c);
     int n = 0, before = 0;
-    for (int base = 0; base < a.pairs; base += 64) {
-        const int p = base + lane, v = p < a.pairs ? a.topk_idx[p] : 0x7fffffff;
-        const uint64_t eq = __ballot(v == e);
-        if (by_pair && n == 0 && eq && base + __builtin_ctzll(eq) != c) return false;
-        const int rank = n + __popcll(eq & ((1ull << lane) - 1));
-        if (v == e && rank < 16) tokens[rank] = p / a.k;
-        n += __popcll(eq);
-        before += __popcll(__ballot(v < e));
+    for (int base = 0; base < a.pairs; base += 64 * CHUNKS) {
+        int v[CHUNKS];
+#pragma unroll
+        for (int u = 0; u < CHUNKS; ++u) {
+            const int p = base + u * 64 + lane;
+            v[u] = p < a.pairs ? a.topk_idx[p] : 0x7fffffff;
+        }
+#pragma unroll
+        for (int u = 0; u < CHUNKS; ++u) {
+            const uint64_t eq = __ballot(v[u] == e);
+            if (by_pair && n == 0 && eq && base + u * 64 + __builtin_ctzll(eq) != c) return false;
+            if (eq) {
+                const int rank = n + __popcll(eq & ((1ull << lane) - 1));
+                if (v[u] == e && rank < MAX) tokens[rank] = (base + u * 64 + lane) / a.k;
+                n += __popcll(eq);
+            }
+            before += __popcll(__ballot(v[u] < e));
+        }
     }
     __syncthreads();   // one wave: orders its LDS writes and reads
     g.expert = e;
     g.row0 = before;
-    g.rows = min(n, 16);   // a token has an expert once
+    g.rows = min(n, MAX);   // a token has an expert once
     return n > 0;
 }
 
-// expert_offsets and the index arrays of the permutation, by one wave (E <= 256, pairs in chunks of 64).
+// expert_offsets and the index arrays of the permutation, by one wave (E <= 256, at most 64 * CHUNKS pairs).
+template <int CHUNKS>
 __device__ __forceinline__ void decode_index(const DecodeArgs& a, const int lane) {
     __shared__ int cursor[256];
     __shared__ unsigned long long mask[256];
+    int v[CHUNKS];
+#pragma unroll
+    for (int u = 0; u < CHUNKS; ++u) v[u] = u * 64 + lane < a.pairs ? a.topk_idx[u * 64 + lane] : -1;
     for (int e = lane; e < 256; e += 64) { cursor[e] = 0; mask[e] = 0; }
     __syncthreads();
-    for (int p = lane; p < a.pairs; p += 64) atomicAdd(&cursor[a.topk_idx[p]], 1);
+#pragma unroll
+    for (int u = 0; u < CHUNKS; ++u)
+        if (v[u] >= 0) atomicAdd(&cursor[v[u]], 1);
     __syncthreads();
     int count[4], sum = 0;
 #pragma unroll
@@ -253,32 +278,40 @@ __device__ __forceinline__ void decode_index(const DecodeArgs& a, const int lane
         if (lane >= d) before += t;
     }
     before -= sum;
+    int start[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int e = 4 * lane + i;
         cursor[e] = before;
-        if (e < a.E) a.offsets[e] = before;
+        start[i] = before;
         before += count[i];
     }
-    if (lane == 0) a.offsets[a.E] = a.pairs;
     __syncthreads();
-    for (int base = 0; base < a.pairs; base += 64) {
-        const int p = base + lane;
-        const bool valid = p < a.pairs;
-        const int e = valid ? a.topk_idx[p] : 0;
-        if (valid) atomicOr(&mask[e], 1ull << lane);
+    int slot[CHUNKS];   // written at the end: a barrier waits for the stores before it
+#pragma unroll
+    for (int u = 0; u < CHUNKS; ++u) {
+        if (u * 64 >= a.pairs) break;
+        const int e = max(v[u], 0);
+        if (v[u] >= 0) atomicOr(&mask[e], 1ull << lane);
         __syncthreads();
         const unsigned long long m = mask[e];
         const int rank = __popcll(m & ((1ull << lane) - 1));
-        if (valid) {
-            const int slot = cursor[e] + rank;
-            a.perm[slot] = p;
-            a.inv_perm[p] = slot;
-            a.row_token[slot] = p / a.k;
-        }
+        slot[u] = cursor[e] + rank;
         __syncthreads();
-        if (valid && rank == 0) { cursor[e] += __popcll(m); mask[e] = 0; }
+        if (v[u] >= 0 && rank == 0) { cursor[e] += __popcll(m); mask[e] = 0; }
         __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (4 * lane + i < a.E) a.offsets[4 * lane + i] = start[i];
+    if (lane == 0) a.offsets[a.E] = a.pairs;
+#pragma unroll
+    for (int u = 0; u < CHUNKS; ++u) {
+        const int p = u * 64 + lane;
+        if (v[u] < 0) continue;
+        a.perm[slot[u]] = p;
+        a.inv_perm[p] = slot[u];
+        a.row_token[slot[u]] = p / a.k;
     }
 }
 
@@ -316,7 +349,7 @@ __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, con
     __shared__ int tokens[16];
     const int lane = threadIdx.x;
     if (blockIdx.x == 0) {
-        decode_index(a, lane);
+        decode_index<4>(a, lane);
         return;
     }
     int b = blockIdx.x - 1;
@@ -355,6 +388,40 @@ __global__ __launch_bounds__(64, 2) void decode_down_kernel(const GemmArgs down,
     Group g;
     if (!decode_group(a, c, lane, g, tokens)) return;
     small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, (b - c * down.n_tiles) * 16, lane);
+}
+
+// More than 16 tokens: the same with `parts` waves for every 64 rows of a group.  Workgroup 0: the index arrays; then all
+// groups' first 64 rows (shared experts first), their second, and so on.  (Parts of a group next to each other: most are empty and
+// the dispatch lines up the others on the same CUs, H = 512, F = 1024, 8 experts, 256 tokens, four parts: gate/up 9 -> 19 us.)
+constexpr int WIDE_TOKENS = 256;
+template <bool NT>
+__global__ __launch_bounds__(64, 2) void decode_wide_up_kernel(const GemmArgs up, const DecodeArgs a, const int parts, const int groups) {
+    __shared__ int tokens[WIDE_TOKENS];
+    const int lane = threadIdx.x;
+    if (blockIdx.x == 0) {
+        decode_index<16>(a, lane);
+        return;
+    }
+    const int b = blockIdx.x - 1, unit = b % up.n_tiles, q = b / up.n_tiles, part = q / groups, c = q - part * groups - a.Ns;
+    if (c < 0) {
+        small_rows<true, 2, NT>(up, shared_tile(a, up, c + a.Ns), part, parts, unit * 32, lane);
+        return;
+    }
+    Group g;
+    if (!decode_group(a, c, lane, g, tokens)) return;
+    small_rows<true, 2, NT>(up, {g.expert, g.row0, g.rows, -1}, part, parts, unit * 32, lane, tokens);
+}
+template <int NB, bool NT>
+__global__ __launch_bounds__(64, 2) void decode_wide_down_kernel(const GemmArgs down, const DecodeArgs a, const int parts, const int groups) {
+    __shared__ int tokens[WIDE_TOKENS];
+    const int lane = threadIdx.x, b = blockIdx.x, unit = b % down.n_tiles, q = b / down.n_tiles, part = q / groups, c = q - part * groups - (a.Ns > 0);
+    if (c < 0) {
+        small_rows<false, NB, NT>(down, shared_tile(a, down, 0), part, parts, unit * 16 * NB, lane);
+        return;
+    }
+    Group g;
+    if (!decode_group(a, c, lane, g, tokens)) return;
+    small_rows<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, part, parts, unit * 16 * NB, lane);
 }
 
 }  // namespace
@@ -404,6 +471,21 @@ hipError_t launch_decode_nt(GemmArgs up, const GemmArgs& down, const DecodeArgs&
 
 hipError_t launch_decode(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st) {
     return nt ? launch_decode_nt<true>(up, down, a, st) : launch_decode_nt<false>(up, down, a, st);
+}
+
+hipError_t launch_decode_wide(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, int col_blocks, bool nt, hipStream_t st) {
+    const int candidates = a.pairs < a.E ? a.pairs : a.E, parts = (up.T + SMALL_ROWS - 1) / SMALL_ROWS;
+    const int groups_up = a.Ns + candidates, groups_down = (a.Ns > 0) + candidates;
+    const dim3 grid_up((unsigned)(1 + groups_up * parts * up.n_tiles)), grid_down((unsigned)(groups_down * parts * down.n_tiles)), block(64);
+#define WIDE(grid_, K_, args_, groups_) hipLaunchKernelGGL((K_), grid_, block, 0, st, args_, a, parts, groups_)
+    if (nt) WIDE(grid_up, decode_wide_up_kernel<true>, up, groups_up);
+    else WIDE(grid_up, decode_wide_up_kernel<false>, up, groups_up);
+    if (col_blocks == 2 && nt) WIDE(grid_down, (decode_wide_down_kernel<2, true>), down, groups_down);
+    else if (col_blocks == 2) WIDE(grid_down, (decode_wide_down_kernel<2, false>), down, groups_down);
+    else if (nt) WIDE(grid_down, (decode_wide_down_kernel<1, true>), down, groups_down);
+    else WIDE(grid_down, (decode_wide_down_kernel<1, false>), down, groups_down);
+#undef WIDE
+    return hipGetLastError();
 }
 
 }  // namespace moe

@@ -616,10 +616,13 @@ def test_layer_small_batches_give_the_tile_routine_s_bits(moe, T, H, F, E, k, sh
         say(json.dumps(P.check_layer_against_oracle(gl, out, out16=out16)["output"]))
 
 
-# Layers of up to 16 tokens, whose waves read the routing off topk_idx: fewer pairs than experts, as many, more; pairs in one chunk
+# Layers of few pairs, whose waves read the routing off topk_idx: fewer pairs than experts, as many, more; pairs in one chunk
 # of 64, at its edges and in several; every width of the top-k; shared experts next to it and next to the gate/up GEMM.
 DECODE_CASES = [(1, 17, 1, 0), (1, 64, 16, 1), (2, 32, 16, 0), (4, 16, 16, 2), (4, 20, 16, 1), (5, 65, 13, 0), (8, 128, 8, 2), (13, 200, 5, 8),
-                (16, 256, 16, 0), (16, 248, 16, 8), (16, 17, 16, 1), (16, 4, 1, 0), (3, 1, 1, 1), (16, 2, 2, 3)]
+                (16, 256, 16, 0), (16, 248, 16, 8), (16, 17, 16, 1), (16, 4, 1, 0), (3, 1, 1, 1), (16, 2, 2, 3),
+                # more than 16 tokens: one to four parts of 64 rows, pairs up to 1024 and one call above
+                (17, 8, 2, 0), (64, 5, 3, 1), (65, 4, 4, 2), (128, 8, 8, 0), (129, 3, 3, 1), (192, 20, 5, 0), (256, 4, 4, 1), (256, 16, 4, 0), (205, 6, 5, 0),
+                (24, 200, 13, 2)]
 
 
 @pytest.mark.parametrize("T,E,k,shared", DECODE_CASES)
