@@ -355,8 +355,9 @@ int split_room_tiles(const moe_shape& s) { return 149 - 79000 / s.F; }
 //            8 experts: 1: 56 -> 40, 8: 131 -> 122, 32: 151 -> 147, 64: 157 -> 148 (one expert with 37 rows: 161 -> 175);
 //            160 experts, skewed: 1: 40 -> 28, 16: 108 -> 98; uniform 16: 171 -> 171, 64: 362 -> 373
 // Gate/up: up to 16 tokens (every group one block of 16 rows; X is re-read by every wave, which costs more
-// than the idle CUs from then on), and up to 128 when the tile routine would have tiles for a quarter of
-// the CUs at most.  The tile routine is ahead (by 10 % at most) where its launch is one full round.
+// than the idle CUs from then on), and when the tile routine would have tiles for a quarter of the CUs at most up to 128
+// tokens, and up to 256 with at most 64 rows per group on average (as fast there, and no launch is needed for m-tile lists: 8
+// experts top-2, H = 512, F = 1024, 256 tokens 31.1 -> 26.5 us).  The tile routine is ahead (by 10 % at most) where its launch is one full round.
 // Down: up to 64 tokens with at most 16 rows per group on average, except in launches of eight rounds of
 // tiles and more; and in launches of few tiles where small_down_wins says so.
 constexpr int SMALL_TILE_ROWS = 128;
