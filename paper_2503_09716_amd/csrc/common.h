@@ -83,7 +83,7 @@ struct GemmArgs {
 struct PlanArgs {
     const int32_t* offsets;
     int32_t T, t_pad, E, Ns;
-    int32_t tm_up, tm_down;             // height cap of the m-tiles: 128 .. 320, a multiple of 32
+    int32_t tm_up, tm_down;             // height cap of the m-tiles: 128 .. 384, a multiple of 32
     int32_t choose_up, choose_down;     // 1 .. 3: another cap may be chosen from the row counts (plan_candidate in plan.h)
     int32_t nt_up, nt_down;             // tiles along N
     int32_t tails_last_up, tails_last_down, small_tiles, xcd_remap;
