@@ -10,10 +10,8 @@
 //   E  > 16 : the logits go through the MFMA tile routine of the grouped GEMM (K cut into
 //             independent chains); route_topk_kernel then sums the partials, adds the bias and
 //             selects: 64 lanes hold a token's logits.
-// Selection: max / sum are butterfly reductions and top-k is k rounds of an arg-max on the
-// logits (ties resolved towards the lower expert id).
-#include <type_traits>
-
+// Selection: max / sum are butterfly reductions and top-k is k rounds of "largest logit, then lowest
+// expert id that has it", on integer keys of the logits' order.
 #include "common.h"
 #include "topk.h"
 
@@ -39,71 +37,63 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    v = row16_max(v);
+    v = max(v, (uint32_t)pair_i<16>((int)v));
+    v = max(v, (uint32_t)pair_i<32>((int)v));
+    return v;
+}
+__device__ __forceinline__ int wave_min(int v) {
+    v = row16_min(v);
+    v = min(v, pair_i<16>(v));
+    v = min(v, pair_i<32>(v));
+    return v;
+}
+
 // Softmax over all experts + top-k for ONE token held by one wavefront: lane l holds the logits
-// of experts l, l+64, ... in v[] (-inf past E).  Max and sum are butterfly reductions; top-k is
-// k rounds of a wave-wide arg-max on the logits (ties -> lower expert id), so rounding in exp /
-// division can never change the selection.
+// of experts l, l+64, ... in v[] (-inf past E).  Selection as in route_select_row16 (topk.h), over 64 lanes: per pick
+// the largest key, then the lowest expert that holds it.  Keys are totally ordered, so every pick is another
+// expert below E whatever the logits are; a comparison of the logits themselves is not an order where one
+// is NaN, the lanes then disagree about the winner and picks past the last expert come out.
 template <int NV>
 __device__ __forceinline__ void route_finish(const float (&v)[NV], const int lane, const int t, const int E, const int k,
                                              const int renorm, const float scale, int32_t* __restrict__ idx_out,
                                              float* __restrict__ w_out, float* __restrict__ logits_out) {
-    float p[NV];
     float m = -INFINITY;
+    uint32_t key[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int e = lane + 64 * i;
         m = fmaxf(m, v[i]);
+        key[i] = e < E ? logit_key(v[i]) : 0u;
         if (logits_out && e < E) logits_out[(size_t)t * E + e] = v[i];
     }
     m = wave_max(m);
     float z = 0.f;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        p[i] = expf(v[i] - m);  // exp(-inf) = 0 for padded experts
-        z += p[i];
-    }
-    z = wave_sum(z);
-    const float rz = 1.0f / z;
-    float my_w = 0.f;
+    for (int i = 0; i < NV; ++i) z += expf(v[i] - m);   // exp(-inf) = 0 for padded experts
+    const float rz = 1.0f / wave_sum(z);
+    uint32_t my_key = KEY_OF_ZERO;
     int my_e = 0;
-    unsigned taken = 0;
     for (int j = 0; j < k; ++j) {
-        // lane-local best among the not-yet-selected (ascending expert id, strict >)
-        float bv = -INFINITY, bp = 0.f;
-        int be = 0x7fffffff;
+        uint32_t best = 0;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int e = lane + 64 * i;
-            const bool ok = e < E && !((taken >> i) & 1u);
-            if (ok && (be == 0x7fffffff || v[i] > bv)) { bv = v[i]; be = e; bp = p[i]; }
-        }
-        // wave arg-max, ties -> lower expert id ((value, -id) is a total order, so the result does
-        // not depend on how the lanes are paired)
-        auto step = [&](auto m_tag) __attribute__((always_inline)) {
-            constexpr int M = decltype(m_tag)::value;
-            const float ov = pair_f<M>(bv);
-            const int oe = pair_i<M>(be);
-            const float op = pair_f<M>(bp);
-            if (ov > bv || (ov == bv && oe < be)) { bv = ov; be = oe; bp = op; }
-        };
-        step(std::integral_constant<int, 1>{});
-        step(std::integral_constant<int, 2>{});
-        step(std::integral_constant<int, 4>{});
-        step(std::integral_constant<int, 8>{});
-        step(std::integral_constant<int, 16>{});
-        step(std::integral_constant<int, 32>{});
-        if (lane == j) { my_e = be; my_w = bp * rz; }
-        // retire the winner
+        for (int i = 0; i < NV; ++i) best = max(best, key[i]);
+        best = wave_max(best);
+        int e = 0x7fffffff;
 #pragma unroll
-        for (int i = 0; i < NV; ++i)
-            if (lane + 64 * i == be) taken |= 1u << i;
+        for (int i = NV - 1; i >= 0; --i) e = key[i] == best ? lane + 64 * i : e;
+        e = wave_min(e);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) key[i] = lane + 64 * i == e ? 0u : key[i];
+        if (lane == j) { my_e = e; my_key = best; }
     }
+    float my_w = expf(key_logit(my_key) - m) * rz;
     const float wsum = wave_sum(lane < k ? my_w : 0.f);
     if (lane < k) {
-        float wv = my_w;
-        if (renorm) wv = wv / wsum;
+        if (renorm) my_w = my_w / wsum;
         idx_out[(size_t)t * k + lane] = my_e;
-        w_out[(size_t)t * k + lane] = wv * scale;
+        w_out[(size_t)t * k + lane] = my_w * scale;
     }
 }
 

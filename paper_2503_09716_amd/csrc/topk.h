@@ -57,13 +57,14 @@ __device__ __forceinline__ int row16_min(int v) {
     return v;
 }
 
-// A logit as an unsigned integer of the same order (-0 as +0).  NaN comes below everything else; 0 is left for "not a candidate".
+// A logit as an unsigned integer of the same order (-0 as +0).  NaN comes below everything else (1); 0 is left for "not a candidate".
+constexpr uint32_t KEY_OF_NAN = 1u, KEY_OF_ZERO = 0x80000000u;
 __device__ __forceinline__ uint32_t logit_key(const float v) {
     const uint32_t u = __float_as_uint(v + 0.f);
-    return v == v ? ((int32_t)u < 0 ? ~u : u | 0x80000000u) : 1u;
+    return v == v ? ((int32_t)u < 0 ? ~u : u | 0x80000000u) : KEY_OF_NAN;
 }
 __device__ __forceinline__ float key_logit(const uint32_t k) {
-    return __uint_as_float(k & 0x80000000u ? k & 0x7fffffffu : ~k);
+    return __uint_as_float(k == KEY_OF_NAN ? 0x7fc00000u : (k & 0x80000000u ? k & 0x7fffffffu : ~k));
 }
 
 // Softmax over all experts + top-k (k <= 16) for the token held by one ROW of 16 lanes: the lane
@@ -96,7 +97,7 @@ __device__ __forceinline__ void route_select_row16(const float (&v)[NV], const i
 #pragma unroll
     for (int i = 0; i < NV; ++i) z += expf(v[i] - m);   // exp(-inf) = 0 for padded experts
     const float rz = 1.0f / row16_sum(z);
-    uint32_t my_key = 0x80000000u;
+    uint32_t my_key = KEY_OF_ZERO;
     my_e = 0;
     for (int j = 0; j < k; ++j) {
         uint32_t best = 0;
@@ -111,8 +112,7 @@ __device__ __forceinline__ void route_select_row16(const float (&v)[NV], const i
         for (int i = 0; i < NV; ++i) key[i] = row16_expert<WIDE>(row, i) == e ? 0u : key[i];
         if (row == j) { my_e = e; my_key = best; }
     }
-    const float picked = my_key == 1u ? __uint_as_float(0x7fc00000u) : key_logit(my_key);
-    my_w = expf(picked - m) * rz;
+    my_w = expf(key_logit(my_key) - m) * rz;
     const float wsum = row16_sum(row < k ? my_w : 0.f);
     if (renorm) my_w = my_w / wsum;
     my_w *= scale;

@@ -112,7 +112,8 @@ def test_route_exact_ties_pick_lowest_expert(moe, T, H, E, k):
     np.testing.assert_allclose(w.cpu().numpy(), 1.0 / E, rtol=1e-6)
 
 
-@pytest.mark.parametrize("E,k", [(8, 3), (16, 16), (20, 5), (64, 6), (130, 16), (160, 6), (256, 8)])
+@pytest.mark.parametrize("E,k", [(8, 3), (16, 16), (20, 5), (64, 6), (130, 16), (160, 6), (256, 8),
+                                 (17, 17), (20, 20), (64, 17), (100, 33), (150, 64), (256, 64)])
 def test_route_logits_that_are_not_finite(moe, E, k):
     """-inf logits are picked last, lower id first; with NaN or +inf among them the picks stay distinct experts."""
     from paper_2503_09716_amd import make_shape
