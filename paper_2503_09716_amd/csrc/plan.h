@@ -86,25 +86,31 @@ __device__ __forceinline__ GroupCut list_cut(const PlanArgs& p, const int which,
 // with 128 tiles; 0.74 at 192 and 0.83 at 256 rows, two tiles to a panel.)  Above 256 rows the matrix cores take
 // longer than the loads, 2.3 ns a row (8 experts, H = 6144, F = 16384, 16384 tokens, gate/up: 0.72 us at 256 rows, 0.88 at 320, 1.02
 // at 384).  A launch costs its whole rounds of 256 tiles times the mean tile, and no less than its longest
-// tile; the last round of a long one only half (by then the CUs are out of step).
+// tile.
 //   short launches (up to two rounds of 256-row tiles, p.choose_* = 1): all eight caps.  With caps below 256 an expert of
 //     250 rows is two tiles of 128: the down GEMM of eight such experts fills the chip with one round of 256 tiles instead
 //     of half a round of 256-row ones (8x7B, 1000 tokens: 310 -> 268 us); with 352, one of 628 rows two tiles instead of three
 //     (2500 tokens: one round instead of one and a half, 590 -> 424 us).
 //   longer ones (2): 384, 352, 320 and 256 rows.  A taller tile moves fewer bytes from L2 to LDS per multiply-add, and its height
 //     decides how the rounds come out: gate/up of 160 experts, 32768 tokens, 320 -> 384 rows 6230 -> 6110 us, down 256 -> 384
-//     3450 -> 3260; 8 experts above 9190 -> 8910, 4860 -> 4740; 8x7B, 5003 tokens, down 256 -> 320 941 -> 808; 64 experts,
-//     6000 tokens 484 -> 450, 278 -> 256; but 8x7B, 1511 tokens (378 rows per expert), gate/up 586 in two tiles of 192 rows,
-//     657 in one.  Over 164 random layers of 257 to 16384 tokens the gate/up GEMM takes 0.979 of its time with fixed
-//     heights, the down GEMM 0.987, and no call 3 % longer.  What another height must gain by the estimate to be taken: 3 to 4 %,
-//     where 320 rows is the usual one (host) 1.5 %.
+//     3450 -> 3260; 8 experts above 9190 -> 8910, 4860 -> 4740; 8x7B, 5003 tokens, down 256 -> 384 956 -> 825; 64 experts,
+//     6000 tokens 491 -> 462, 282 -> 243.  Here a tile next to others of its group pays nothing extra for the panel (310 in all), a
+//     lone one 500, and a tile of the shared experts' K-concatenated down GEMM counts as so many.  Groups just around a height
+//     are what this has to get right (8x7B, gate/up, us): all of 350 to 380 rows, eight tiles of 384 rows per column 543 and
+//     sixteen of 192 587; three of the eight above 384 rows, eleven tiles = 4.8 rounds 620 to 640 against 600 to 607, and the
+//     even tiles stay.  (With half of the last round and 50 rows for the neighbour of a tile, the estimate took the
+//     eleven, +7 %.)  Every height forced and timed, 485 launches of 280 to 16384 tokens, 2 to 160 experts: against the usual
+//     height the chosen one takes 0.962 of the time (gate/up; the best of the four 0.954), 0.943 (down; 0.932), and no launch is
+//     more than 1.5 % longer, which is what two timings of one launch differ by; over 96 more (64 and 160 experts, 2400 to
+//     14000 tokens) one, 3 %.  What another height must gain by the estimate to be taken: 4 to 5 %, where 320 rows is the
+//     usual one (host, from 1200 rows per expert on) 1.5 %.
 constexpr int PLAN_CAPS = 8, PLAN_CAPS_LONG = 4;
 __device__ constexpr int plan_cap(const int c) { return (c < 3 ? 384 : 352) - 32 * c; }   // 384, 352, 320, 256, 224, ... 128
 // whether cap c is a candidate (3: as 1, for the wave grids that have no tiles above 256 rows)
 __device__ constexpr bool plan_candidate(const int c, const int choose) { return choose == 1 || (choose == 2 ? c < PLAN_CAPS_LONG : choose == 3 && c >= 3); }
 
-// What a list's tiles add up to under one cap.  n: tiles; alone: their group's only one; beside: next to one or two others of
-// their group (in a long launch a panel that four tiles and more share costs nothing extra); longest: highest tile.
+// What a list's tiles add up to under one cap.  n: tiles; alone: their group's only one; beside: next to others of
+// their group (short launches); longest: highest tile.
 struct ListSum {
     int n, alone, beside, longest;
     float sum;
@@ -122,10 +128,10 @@ __device__ __forceinline__ ListSum list_sum(const PlanArgs& p, const int which, 
         if (r == 0) continue;
         const GroupCut c = list_cut(p, which, p.Ns > 0 && (g == 0 || g > p.E), r, tm);
         const int m = c.nfull + (c.tail > 0);
-        const int seg = g == 0 ? nseg0 : 1;
-        s.n += m;
-        if (m == 1) ++s.alone;
-        else if (choose != 2 || m < 4) s.beside += m;
+        const int seg = g == 0 ? nseg0 : 1, weight = choose == 2 ? seg : 1;
+        s.n += m * weight;
+        if (m == 1) s.alone += weight;
+        else if (choose != 2) s.beside += m;
         const int high = tile(m > 1 ? c.h : r);
         s.sum += (float)seg * (float)(c.nfull * high + (c.tail > 0 ? tile(c.tail) : 0) + (m > 1 ? c.joined : 0));
         s.longest = max(s.longest, high * seg);
@@ -141,11 +147,8 @@ __device__ __forceinline__ float list_cost(const ListSum& s, const int choose, c
     if (s.n == 0) return 0.f;
     const int tiles = s.n * n_tiles;
     const float busy = fminf(fmaxf((float)(tiles - 128) / 128.f, 0.f), 1.f);
-    const float mean = (s.sum + busy * (50.f * s.beside + 230.f * s.alone)) / (float)s.n;
-    // over many rounds the CUs get out of step, and the last one matters half
-    float rounds = (float)((tiles + 255) / 256);
-    if (choose == 2) rounds = 0.5f * (rounds + (float)tiles / 256.f + 0.5f);
-    return fmaxf(rounds * mean, (float)s.longest);
+    const float mean = (s.sum + busy * (50.f * s.beside + (choose == 2 ? 190.f : 230.f) * s.alone)) / (float)s.n;
+    return fmaxf((float)((tiles + 255) / 256) * mean, (float)s.longest);
 }
 
 // Builds the two m-tile lists (gate/up GEMM with tiles of up to tm_up rows, down GEMM with tm_down)
@@ -207,7 +210,7 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
             if (!choose) continue;
             // 256 rows, or 320 where the host says so, unless another height is clearly cheaper
             const int usual = choose == 2 && tm_of[which] == 320 ? 2 : 3;
-            float best = cap_cost[which][usual] * (usual == 2 ? 0.985f : (choose == 2 && which == 0 ? 0.96f : 0.97f));
+            float best = cap_cost[which][usual] * (usual == 2 ? 0.985f : (choose != 2 ? 0.97f : (which == 0 ? 0.96f : 0.95f)));
             tm_of[which] = plan_cap(usual);
             for (int c = 0; c < PLAN_CAPS; ++c)
                 if (plan_candidate(c, choose) && cap_cost[which][c] < best) { best = cap_cost[which][c]; tm_of[which] = plan_cap(c); }

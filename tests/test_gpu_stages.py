@@ -746,6 +746,40 @@ def test_grouped_ffn_tiles_above_320_rows(moe, kind, which, H, F):
     assert torch.equal(run_ffn_stage(moe, cfg, idx_h, wave_rows=2)[0], y)
 
 
+# Launches of more than two rounds of 256-row tiles: T, H, F, E, k, shared, rows per expert, GEMM (0 gate/up, 1 down),
+# tiles in its list, highest tile
+LONG_LISTS = [
+    # three of eight groups above 384 rows: eleven tiles are 4.8 rounds and slower than sixteen even ones (7 rounds)
+    (1511, 64, 14336, 8, 2, 0, [353, 388, 367, 406, 352, 381, 372, 403], 0, 16, 224),
+    (1500, 64, 14336, 8, 2, 0, [395, 367, 352, 395, 344, 409, 371, 367], 0, 16, 224),
+    # one of them: nine tiles, four rounds
+    (1450, 64, 14336, 8, 2, 0, [383, 312, 381, 377, 400, 329, 348, 370], 0, 9, 383),
+    # 320 rows are the usual height of the gate/up GEMM from 1200 rows per expert on, and stay; 256 rows are clearly better,
+    # every group's tail joins its last tile, and those tiles are moved (more than eight tiles per expert)
+    (14556, 64, 1920, 8, 1, 0, [1812, 1844, 1840, 1867, 1809, 1795, 1803, 1786], 0, 48, 320),
+    (12489, 64, 1920, 5, 1, 0, [2572, 2830, 2355, 2623, 2109], 0, 48, 319),
+    # high tiles next to those of two shared experts, which walk twice as far
+    (6306, 896, 128, 14, 5, 2, [2252] * 12 + [2253] * 2, 1, 101, 384),
+    (7248, 2816, 64, 11, 1, 2, [644, 643, 668, 646, 668, 646, 668, 643, 662, 685, 675], 1, 43, 352),
+]
+
+
+@pytest.mark.parametrize("T,H,F,E,k,shared,counts,which,tiles,highest", LONG_LISTS)
+def test_heights_of_long_launches(moe, T, H, F, E, k, shared, counts, which, tiles, highest):
+    """The list of a launch whose height is chosen among 256 to 384 rows, and, where the matrices are small, the same bits as
+    a wave grid that has no tiles above 256 rows."""
+    heights = [n for _, _, n, _, _ in lists_of(moe, T, H, F, E, k, shared, counts)[which]]
+    assert (len(heights), max(heights)) == (tiles, highest), heights
+    if F > 2048:
+        return
+    cfg = scaled_config("C4", T=T, H=H, F=F, E=E, top_k=k, num_shared=shared)
+    idx_h = np.repeat(np.arange(E, dtype=np.int32), counts).reshape(k, T).T.copy()
+    got, ref = (run_ffn_stage(moe, cfg, idx_h, wave_rows=rows)[:2] for rows in (1, 2))
+    assert torch.equal(got[0], ref[0]) and bool(torch.isfinite(got[0]).all())
+    if shared:
+        assert torch.equal(got[1], ref[1])
+
+
 @pytest.mark.parametrize("T,H,F,E,k,shared,counts,rows_up,want_up", [
     # every group one tile; one of two tiles; a layer of less than 256 MB
     (100, 4096, 3072, 4, 4, 0, [100] * 4, 0, {100: ONCE}),
