@@ -186,9 +186,11 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
         if (group < E ? (group < p.e_lo || group >= p.e_hi) : !p.shared_on) rows = 0;
     }
     int tm_of[2] = {p.tm_up, p.tm_down};
-    // routed groups of at most 128 rows are one tile under every cap, and the shared experts by themselves are
-    // not worth the 5 us that the choice takes (small launches: p.low_shared)
-    if ((p.choose_up || p.choose_down) && __syncthreads_or(group < E && rows > 128)) {
+    // Routed groups that are one tile under every candidate cap leave nothing to choose, and the shared experts by themselves are
+    // not worth the 5 us that it takes (small launches: p.low_shared; 64 experts + 2 shared, 1500 tokens: the plan 12.8 us
+    // with the choice and 9.1 without, the layer 350 and 347; 160 + 2, 3000 tokens: 15.6 and 9.4, 408 and 404).
+    const int lowest = p.choose_up % 2 || p.choose_down % 2 ? 128 : 256;   // lowest cap: 2 has none below 256 rows
+    if ((p.choose_up || p.choose_down) && __syncthreads_or(group < E && rows > lowest)) {
         group_rows[tid] = rows;
         __syncthreads();
         // waves 0 and 1 take half of the groups each for the gate/up list, 2 and 3 for the down list; eight lanes to a cap

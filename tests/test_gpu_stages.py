@@ -760,6 +760,8 @@ LONG_LISTS = [
     (12489, 64, 1920, 5, 1, 0, [2572, 2830, 2355, 2623, 2109], 0, 48, 319),
     # high tiles next to those of two shared experts, which walk twice as far
     (6306, 896, 128, 14, 5, 2, [2252] * 12 + [2253] * 2, 1, 101, 384),
+    # every routed group one tile under every height
+    (1536, 64, 1408, 64, 6, 2, [144] * 64, 0, 76, 256),
     (7248, 2816, 64, 11, 1, 2, [644, 643, 668, 646, 668, 646, 668, 643, 662, 685, 675], 1, 43, 352),
 ]
 
