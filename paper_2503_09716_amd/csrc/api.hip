@@ -356,8 +356,11 @@ int split_room_tiles(const moe_shape& s) { return 149 - 79000 / s.F; }
 //            160 experts, skewed: 1: 40 -> 28, 16: 108 -> 98; uniform 16: 171 -> 171, 64: 362 -> 373
 // Gate/up: up to 16 tokens (every group one block of 16 rows; X is re-read by every wave, which costs more
 // than the idle CUs from then on), and when the tile routine would have tiles for a quarter of the CUs at most up to 128
-// tokens, and up to 256 with at most 64 rows per group on average (as fast there, and no launch is needed for m-tile lists: 8
-// experts top-2, H = 512, F = 1024, 256 tokens 31.1 -> 26.5 us).  The tile routine is ahead (by 10 % at most) where its launch is one full round.
+// tokens.  From 129 to 256 tokens, with at most 64 rows per group on average (79 layers of 2 to 32 experts, up to 89 MB,
+// weights cached): an eighth of the CUs at most, 0.52 to 0.95 of the tile routine's time; up to a quarter
+// 0.6 to 1.17 (24 top-4, H = 512, F = 256, 255 tokens 10.1 -> 11.8 us), so only where the layer then goes
+// without the launches of the permutation and the lists (6 us), and X, which every 32 columns re-read, is
+// narrow: layers 0.71 to 0.99 (one of H = 2240: 1.03).  The tile routine is ahead (by 10 % at most) where its launch is one full round.
 // Down: up to 64 tokens with at most 16 rows per group on average, except in launches of eight rounds of
 // tiles and more; and in launches of few tiles where small_down_wins says so.
 constexpr int SMALL_TILE_ROWS = 128;
@@ -367,6 +370,7 @@ struct SmallRule {
     int halves;        // 64-row units per m-tile
     bool once;         // one unit per group, as a rule: its W panels are read once
     int mtiles_up, mtiles_down;   // m-tiles of SMALL_TILE_ROWS rows at most (also if a token picks an expert twice)
+    bool no_lists;     // a layer that launches neither the permutation nor the lists
 };
 
 // The down GEMM of few groups of any height (up to 64 tokens a round of tiles, up to 256 tokens tiles for a quarter of
@@ -388,7 +392,8 @@ bool small_down_wins(const moe_shape& s, int groups, int tiles, int splits, int 
     return 1.15 * (walk > reads ? walk : reads) < (tile_walk > tile_reads ? tile_walk : tile_reads) + (pieces > 1 ? 10 : 0);
 }
 
-SmallRule small_rule(const moe_ctx* c, const moe_shape& s) {
+// layer: a call of moe_layer, not the GEMMs alone or a streamed pass.
+SmallRule small_rule(const moe_ctx* c, const moe_shape& s, bool layer) {
     SmallRule r;
     const int nt_up = (s.F + 127) / 128, nt_down = (s.H + 255) / 256;   // tiles of the tile routine along N
     const int64_t pairs = (int64_t)s.T * s.top_k;
@@ -396,10 +401,14 @@ SmallRule small_rule(const moe_ctx* c, const moe_shape& s) {
     const int tiles_up = (groups + s.num_shared) * nt_up, tiles_down = (groups + (s.num_shared > 0)) * nt_down;
     const bool allowed = c->gemm.small_tiles && !c->gemm.tile_rows_up && !c->gemm.tile_rows_down && c->gemm.down_tail_splits != 2;
     r.down_cols = s.T <= 32 ? 1 : 2;
-    r.up = allowed && (s.T <= 16 || (tiles_up <= 64 && (s.T <= 128 || (s.T <= 256 && pairs <= 64 * (int64_t)groups))));
     r.down = allowed && ((s.T <= 64 && pairs <= 16 * (int64_t)groups && tiles_down < 8 * 256) ||
                          (s.T <= 256 && tiles_down <= (s.T <= 64 ? 256 : 64) &&
                           small_down_wins(s, groups, tiles_down, call_down_splits(c, s), r.down_cols)));
+    // Both GEMMs without m-tile lists: launch_decode up to 16 tokens, launch_decode_wide above.
+    const bool no_lists = layer && r.down && s.top_k <= 16 && c->gemm.x_tiled != 1 && s.T <= 256 && pairs <= 1024;
+    r.up = allowed && (s.T <= 16 || (s.T <= 128 && tiles_up <= 64) ||
+                       (s.T <= 256 && pairs <= 64 * (int64_t)groups && tiles_up <= (no_lists && s.H < 2048 ? 64 : 32)));
+    r.no_lists = no_lists && r.up;
     r.halves = s.T <= 64 ? 1 : 2;
     r.once = s.T <= 64 || (s.num_shared == 0 && pairs <= 52 * (int64_t)groups);
     const int routed = groups + (int)(pairs / SMALL_TILE_ROWS), per_shared = (s.T + SMALL_TILE_ROWS - 1) / SMALL_TILE_ROWS;
@@ -414,8 +423,9 @@ struct FfnPass {
     int e_lo, e_hi;
     bool shared_on;
     int mtiles_up, mtiles_down;
+    bool layer;   // the GEMMs of a moe_layer call
 };
-FfnPass whole_layer(const moe_shape& s) { return FfnPass{0, s.E, true, 0, 0}; }
+FfnPass all_groups(const moe_shape& s, bool layer) { return FfnPass{0, s.E, true, 0, 0, layer}; }
 
 // What both GEMMs of one call (or one streamed pass) run with, fixed on the host from the shape.
 struct FfnSetup {
@@ -456,7 +466,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const bool tl_up = c->gemm.tails_last != 0;
     const bool tl_down = c->gemm.tails_last != 0;
     // Small batches: one wavefront per 16 or 32 columns instead of a workgroup per 256 (ffn_small.hip)
-    const SmallRule sm = small_rule(c, s);
+    const SmallRule sm = small_rule(c, s, ps.layer);
     if (sm.up) { tm_up = SMALL_TILE_ROWS; choose_up = 0; }
     if (sm.down) tm_down = SMALL_TILE_ROWS;
     // K pieces for short tails of the down GEMM: the device-side plan decides from the real tile
@@ -670,32 +680,26 @@ moe_status run_front(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     return MOE_OK;
 }
 
-// Layers whose two GEMMs both run one wavefront per 16 or 32 columns go without m-tile lists: 1, up to 16 tokens
-// (launch_decode); 2, up to 256 tokens and 1024 pairs (launch_decode_wide).  Not while stages are timed, which these launches do not
-// keep apart.
-int decode_rule(const moe_ctx* c, const moe_shape& s, const SmallRule& sm) {
-    if (c->prof || !sm.up || !sm.down || s.top_k > 16 || c->gemm.x_tiled == 1) return 0;
-    return s.T <= 16 ? 1 : (s.T <= 256 && s.T * s.top_k <= 1024 ? 2 : 0);
-}
-
 // The whole layer with its intermediates in `ws` (validated by the caller).
 moe_status layer_with_workspace(moe_ctx* c, const moe_shape* s, const void* x, const void* wg, const float* bias,
                                 const void* const* w1p, const void* const* w3p, const void* const* w2p, void* out,
                                 char* ws, hipStream_t hs) {
     void** tab = nullptr;
     if (moe_status st = weight_table(c, s->E + s->num_shared, w1p, w3p, w2p, hs, &tab)) return st;
-    const FfnSetup fs = ffn_setup(c, *s, (const int32_t*)(ws + make_layout(*s).offsets), ws, whole_layer(*s));
+    const FfnSetup fs = ffn_setup(c, *s, (const int32_t*)(ws + make_layout(*s).offsets), ws, all_groups(*s, true));
     LayerFront f;
-    if (const int decode = decode_rule(c, *s, fs.sm)) {
+    // Not while stages are timed, which these launches do not keep apart.
+    if (fs.sm.no_lists && !c->prof) {
+        const bool few = s->T <= 16;   // launch_decode, else launch_decode_wide
         f = layer_front(c, *s, ws);
         const FfnBuffers b{nullptr, f.row_token, x, nullptr, tab, f.h, f.y_perm, f.y_shared, f.y32, true};
         const RouteGemm rg = route_gemm_config(*s);
-        if (moe_status st = run_route(c, *s, x, wg, bias, f.topk_idx, f.topk_w, nullptr, ws, hs, decode == 1)) return st;
-        const DecodeArgs d{rg.splits && decode == 1 ? (const float*)(ws + make_layout(*s).rt_logits) : nullptr, bias, rg.splits, rg.ep, s->renormalize,
+        if (moe_status st = run_route(c, *s, x, wg, bias, f.topk_idx, f.topk_w, nullptr, ws, hs, few)) return st;
+        const DecodeArgs d{rg.splits && few ? (const float*)(ws + make_layout(*s).rt_logits) : nullptr, bias, rg.splits, rg.ep, s->renormalize,
                            s->routed_scale, f.topk_idx, f.offsets, f.perm, f.inv_perm, f.row_token, f.topk_w,
                            s->T * s->top_k, s->top_k, s->E, s->num_shared};
         const GemmArgs up = gate_up_args(c, *s, fs, b), down = down_args(c, *s, fs, b, ws);
-        if (decode == 1) HIP_TRY(c, launch_decode(up, down, d, fs.nt, hs));
+        if (few) HIP_TRY(c, launch_decode(up, down, d, fs.nt, hs));
         else HIP_TRY(c, launch_decode_wide(up, down, d, fs.sm.down_cols, fs.nt && fs.sm.once, hs));
         HIP_TRY(c, launch_combine(*s, f.y_perm, f.inv_perm, f.topk_w, f.y_shared, out, f.y32, true, c->out_fp32, hs));
         return MOE_OK;
@@ -872,7 +876,7 @@ moe_status moe_grouped_ffn(moe_ctx* c, const moe_shape* s, const void* x_perm, c
     void** tab = nullptr;
     if (moe_status st = weight_table(c, s->E + s->num_shared, w1p, w3p, w2p, hs, &tab)) return st;
     const FfnBuffers b{x_perm, row_token, x, nullptr, tab, h, y_perm, y_shared, c->y_fp32, c->y_fp32};
-    return run_ffn(c, *s, ffn_setup(c, *s, offsets, (char*)ws, whole_layer(*s)), false, b, (char*)ws, hs);
+    return run_ffn(c, *s, ffn_setup(c, *s, offsets, (char*)ws, all_groups(*s, false)), false, b, (char*)ws, hs);
 }
 
 moe_status moe_combine(moe_ctx* c, const moe_shape* s, const void* y_perm, const int32_t* inv_perm, const float* w,
@@ -1014,7 +1018,7 @@ moe_status moe_layer_streamed(moe_ctx* c, const moe_shape* s, const void* x, con
         HIP_TRY(c, hipStreamWaitEvent(hs, c->slot_ready[slot], 0));
         void** tab = nullptr;
         if (moe_status st = weight_table(c, E + Ns, t1.data(), t3.data(), t2.data(), hs, &tab)) return st;
-        const FfnPass pass{G.shared ? 0 : G.lo, G.shared ? 0 : G.hi, G.shared, mt, G.shared ? (s->T + 127) / 128 : mt};
+        const FfnPass pass{G.shared ? 0 : G.lo, G.shared ? 0 : G.hi, G.shared, mt, G.shared ? (s->T + 127) / 128 : mt, false};
         const FfnBuffers b{nullptr, f.row_token, x, f.x_tiled, tab, f.h, f.y_perm, f.y_shared, f.y32, true};
         if (moe_status st = run_ffn(c, *s, ffn_setup(c, *s, f.offsets, (char*)ws, pass), false, b, (char*)ws, hs)) return st;
         HIP_TRY(c, hipEventRecord(c->slot_free[slot], hs));

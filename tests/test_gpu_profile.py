@@ -122,6 +122,39 @@ def test_default_choice_is_not_the_slower_one(moe, T, H, F, E, k, shared, stage,
     assert default <= 1.12 * other
 
 
+@pytest.mark.parametrize("T,H,F,E,k", [(255, 512, 256, 24, 4), (180, 2240, 448, 12, 3)])
+def test_gate_up_of_staged_calls_with_cached_weights(moe, T, H, F, E, k):
+    """GEMMs called alone save no launch by going without m-tile lists: with 40 to 45 rows per expert and 48 tiles the gate/up GEMM stays
+    on the tile routine, against which one wavefront per 32 columns takes 1.17 times as long.  8 % for the spread of a median of 60."""
+    from paper_2503_09716_amd import make_shape
+    shape = make_shape(T, H, F, E, k, 0, True)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    normal = lambda *size, std=0.02: torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    i32 = lambda *size: torch.empty(size, dtype=torch.int32, device="cuda")
+    tab, x, ws = [[normal(H * F) for _ in range(E)] for _ in range(3)], normal(T, H, std=1.0), moe.new_workspace(shape)
+    idx, w, off, perm, inv, rtok = i32(T, k), torch.empty((T, k), device="cuda"), i32(E + 1), i32(T * k), i32(T * k), i32(T * k)
+    h, y = moe.new_h_scratch(shape), torch.empty((T * k, H), device="cuda")
+    moe.route(shape, x, normal(H, E), None, idx, w, None, ws)
+    moe.permute(shape, x, idx, None, off, perm, inv, rtok, ws)
+    times = {0: [], 128: []}
+    try:
+        for _ in range(3):
+            for rows in times:
+                moe.set_option("gemm_tile_rows_up", rows)
+                moe.grouped_ffn(shape, None, rtok, x, off, *tab, h, y, None, ws)
+                moe.profile_enable(True)
+                for _ in range(20):
+                    moe.grouped_ffn(shape, None, rtok, x, off, *tab, h, y, None, ws)
+                times[rows] += moe.profile_read_intervals()["ffn_gate_up"]
+                moe.profile_enable(False)
+    finally:
+        moe.profile_enable(False)
+        moe.set_option("gemm_tile_rows_up", 0)
+    default, tiles = (sorted(times[rows])[30] for rows in (0, 128))
+    print("T", T, "H", H, "F", F, "E", E, "k", k, "default %.4f ms" % default, "on tiles %.4f ms" % tiles, flush=True)
+    assert default <= 1.08 * tiles
+
+
 def test_weight_bytes_cost_the_same_on_both_sides_of_the_cache_size(moe):
     """Layers of more than 256 MB load weights that one tile or wave reads non-temporally.  Groups of 100 rows are two waves
     per panel in the gate/up GEMM, so a layer just above must not pay more per weight byte there than one just below
