@@ -356,11 +356,11 @@ int split_room_tiles(const moe_shape& s) { return 149 - 79000 / s.F; }
 //            160 experts, skewed: 1: 40 -> 28, 16: 108 -> 98; uniform 16: 171 -> 171, 64: 362 -> 373
 // Gate/up: up to 16 tokens (every group one block of 16 rows; X is re-read by every wave, which costs more
 // than the idle CUs from then on), and when the tile routine would have tiles for a quarter of the CUs at most up to 128
-// tokens.  From 129 to 256 tokens, with at most 64 rows per group on average (79 layers of 2 to 32 experts, up to 89 MB,
+// tokens.  From 129 to 256 tokens, with at most 64 rows per group on average (139 layers of 2 to 32 experts, up to 100 MB,
 // weights cached): an eighth of the CUs at most, 0.52 to 0.95 of the tile routine's time; up to a quarter
-// 0.6 to 1.17 (24 top-4, H = 512, F = 256, 255 tokens 10.1 -> 11.8 us), so only where the layer then goes
+// 0.6 to 1.25 (24 top-4, H = 512, F = 256, 255 tokens 10.1 -> 11.8 us), so only where the layer then goes
 // without the launches of the permutation and the lists (6 us), and X, which every 32 columns re-read, is
-// narrow: layers 0.71 to 0.99 (one of H = 2240: 1.03).  The tile routine is ahead (by 10 % at most) where its launch is one full round.
+// narrow: layers 0.71 to 0.99 (H from 2048 on: up to 1.06).  The tile routine is ahead (by 10 % at most) where its launch is one full round.
 // Down: up to 64 tokens with at most 16 rows per group on average, except in launches of eight rounds of
 // tiles and more; and in launches of few tiles where small_down_wins says so.
 constexpr int SMALL_TILE_ROWS = 128;
