@@ -324,7 +324,11 @@ moe_status moe_layer_views(const moe_shape* shape, void* workspace, int32_t** to
  * the call's stream.  moe_profile_read waits for the recorded events, adds the elapsed
  * milliseconds per stage into ms_sum[MOE_STAGE_COUNT] and the number of intervals into
  * launches[MOE_STAGE_COUNT], and clears the record.  At most 8192 intervals are kept
- * between reads (further ones are dropped). */
+ * between reads (further ones are dropped).
+ * moe_layer on a small batch (up to 256 tokens and 1024 pairs, where both GEMMs run without m-tile lists) launches no
+ * permutation and no list: those stages then have no intervals, the gate/up launch writes the index arrays, and with up to 16 tokens and
+ * more than 16 experts the shared experts' gate/up tiles run in the route stage's last launch and their down tiles in the gate/up
+ * stage's.  Larger layers build the lists in a launch of their own while profiling is on, else next to the permutation. */
 moe_status moe_profile_enable(moe_ctx* ctx, int32_t on);
 moe_status moe_profile_read(moe_ctx* ctx, double* ms_sum, int32_t* launches);
 /* The same record interval by interval, in the order the calls enqueued them: stage[i] is a

@@ -688,20 +688,35 @@ moe_status layer_with_workspace(moe_ctx* c, const moe_shape* s, const void* x, c
     if (moe_status st = weight_table(c, s->E + s->num_shared, w1p, w3p, w2p, hs, &tab)) return st;
     const FfnSetup fs = ffn_setup(c, *s, (const int32_t*)(ws + make_layout(*s).offsets), ws, all_groups(*s, true));
     LayerFront f;
-    // Not while stages are timed, which these launches do not keep apart.
-    if (fs.sm.no_lists && !c->prof) {
+    if (fs.sm.no_lists) {
         const bool few = s->T <= 16;   // launch_decode, else launch_decode_wide
         f = layer_front(c, *s, ws);
         const FfnBuffers b{nullptr, f.row_token, x, nullptr, tab, f.h, f.y_perm, f.y_shared, f.y32, true};
         const RouteGemm rg = route_gemm_config(*s);
-        if (moe_status st = run_route(c, *s, x, wg, bias, f.topk_idx, f.topk_w, nullptr, ws, hs, few)) return st;
         const DecodeArgs d{rg.splits && few ? (const float*)(ws + make_layout(*s).rt_logits) : nullptr, bias, rg.splits, rg.ep, s->renormalize,
                            s->routed_scale, f.topk_idx, f.offsets, f.perm, f.inv_perm, f.row_token, f.topk_w,
                            s->T * s->top_k, s->top_k, s->E, s->num_shared};
         const GemmArgs up = gate_up_args(c, *s, fs, b), down = down_args(c, *s, fs, b, ws);
-        if (few) HIP_TRY(c, launch_decode(up, down, d, fs.nt, hs));
-        else HIP_TRY(c, launch_decode_wide(up, down, d, fs.sm.down_cols, fs.nt && fs.sm.once, hs));
-        HIP_TRY(c, launch_combine(*s, f.y_perm, f.inv_perm, f.topk_w, f.y_shared, out, f.y32, true, c->out_fp32, hs));
+        auto launch = [&](const DecodeStep step) {
+            return few ? launch_decode(step, up, down, d, fs.nt, hs) : launch_decode_wide(step, up, down, d, fs.sm.down_cols, fs.nt && fs.sm.once, hs);
+        };
+        {
+            StageTimer tm(c, hs, MOE_STAGE_ROUTE);
+            if (moe_status st = run_route(c, *s, x, wg, bias, f.topk_idx, f.topk_w, nullptr, ws, hs, few)) return st;
+            HIP_TRY(c, launch(DECODE_TOPK));
+        }
+        {
+            StageTimer tm(c, hs, MOE_STAGE_FFN_GATE_UP);
+            HIP_TRY(c, launch(DECODE_UP));
+        }
+        {
+            StageTimer tm(c, hs, MOE_STAGE_FFN_DOWN);
+            HIP_TRY(c, launch(DECODE_DOWN));
+        }
+        {
+            StageTimer tm(c, hs, MOE_STAGE_COMBINE);
+            HIP_TRY(c, launch_combine(*s, f.y_perm, f.inv_perm, f.topk_w, f.y_shared, out, f.y32, true, c->out_fp32, hs));
+        }
         return MOE_OK;
     }
     // While stages are timed the lists are built by a launch of their own, so that it can be told from the permutation.

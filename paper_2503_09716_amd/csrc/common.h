@@ -169,11 +169,12 @@ hipError_t launch_ffn_gemm(bool gated, const GemmArgs& a, const GemmConfig& cfg,
 // the same GEMMs with one wavefront per 16 * col_blocks columns (small batches): a.n_tiles column units per
 // m-tile, m-tiles of at most 64 * halves rows; gate/up: col_blocks = 2; nt: non-temporal loads of W
 hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int halves, bool nt, hipStream_t st);
-// a layer of up to 16 tokens from the router's partial logits (none: from topk_idx and topk_w) to the down GEMM, with the
-// permutation's index arrays
-hipError_t launch_decode(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st);
-// the same from topk_idx and topk_w on, for up to 256 tokens; n_tiles: units of 32 and of 16 * col_blocks columns
-hipError_t launch_decode_wide(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, int col_blocks, bool nt, hipStream_t st);
+// A layer of up to 16 tokens from the router's partial logits (none: from topk_idx and topk_w) to the down GEMM, with the
+// permutation's index arrays, in three launches (the first only from partial logits).
+enum DecodeStep { DECODE_TOPK, DECODE_UP, DECODE_DOWN };
+hipError_t launch_decode(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st);
+// The same from topk_idx and topk_w on, for up to 256 tokens; n_tiles: units of 32 and of 16 * col_blocks columns.
+hipError_t launch_decode_wide(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, int col_blocks, bool nt, hipStream_t st);
 hipError_t launch_route_small(const GemmArgs& a, hipStream_t st);   // the router GEMM, one wavefront per 16 tokens x 16 experts x K piece
 hipError_t ffn_gemm_init();  // one-time function attributes (dynamic LDS size)
 

@@ -449,42 +449,45 @@ hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int h
 
 namespace {
 template <bool NT>
-hipError_t launch_decode_nt(GemmArgs up, const GemmArgs& down, const DecodeArgs& a, hipStream_t st) {
+hipError_t launch_decode_nt(const DecodeStep step, GemmArgs up, const GemmArgs& down, const DecodeArgs& a, hipStream_t st) {
     const int candidates = a.pairs < a.E ? a.pairs : a.E;
     const bool early = a.partial && a.Ns > 0;
     const dim3 block(64);
     up.n_tiles = up.N / (16 * up_blocks<NT>());
     const int shared_units = a.Ns * up.n_tiles;
 #define DECODE(grid_, K_, ...) hipLaunchKernelGGL((K_), dim3((unsigned)(grid_)), block, 0, st, __VA_ARGS__)
-    if (a.partial) {
+    if (step == DECODE_TOPK && a.partial) {
         const int grid = (up.T + 3) / 4 + shared_units;
         if (a.E <= 64) DECODE(grid, (decode_topk_kernel<1, NT>), up, a);
         else if (a.E <= 128) DECODE(grid, (decode_topk_kernel<2, NT>), up, a);
         else if (a.E <= 192) DECODE(grid, (decode_topk_kernel<3, NT>), up, a);
         else DECODE(grid, (decode_topk_kernel<4, NT>), up, a);
     }
-    DECODE(1 + (early ? down.n_tiles : shared_units) + candidates * up.n_tiles, (decode_up_kernel<NT>), up, down, a, early);
-    DECODE((early || !a.Ns ? 0 : down.n_tiles) + candidates * down.n_tiles, (decode_down_kernel<NT>), down, a, early);
+    if (step == DECODE_UP) DECODE(1 + (early ? down.n_tiles : shared_units) + candidates * up.n_tiles, (decode_up_kernel<NT>), up, down, a, early);
+    if (step == DECODE_DOWN) DECODE((early || !a.Ns ? 0 : down.n_tiles) + candidates * down.n_tiles, (decode_down_kernel<NT>), down, a, early);
 #undef DECODE
     return hipGetLastError();
 }
 }  // namespace
 
-hipError_t launch_decode(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st) {
-    return nt ? launch_decode_nt<true>(up, down, a, st) : launch_decode_nt<false>(up, down, a, st);
+hipError_t launch_decode(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st) {
+    return nt ? launch_decode_nt<true>(step, up, down, a, st) : launch_decode_nt<false>(step, up, down, a, st);
 }
 
-hipError_t launch_decode_wide(const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, int col_blocks, bool nt, hipStream_t st) {
+hipError_t launch_decode_wide(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, int col_blocks, bool nt, hipStream_t st) {
     const int candidates = a.pairs < a.E ? a.pairs : a.E, parts = (up.T + SMALL_ROWS - 1) / SMALL_ROWS;
     const int groups_up = a.Ns + candidates, groups_down = (a.Ns > 0) + candidates;
     const dim3 grid_up((unsigned)(1 + groups_up * parts * up.n_tiles)), grid_down((unsigned)(groups_down * parts * down.n_tiles)), block(64);
 #define WIDE(grid_, K_, args_, groups_) hipLaunchKernelGGL((K_), grid_, block, 0, st, args_, a, parts, groups_)
-    if (nt) WIDE(grid_up, decode_wide_up_kernel<true>, up, groups_up);
-    else WIDE(grid_up, decode_wide_up_kernel<false>, up, groups_up);
-    if (col_blocks == 2 && nt) WIDE(grid_down, (decode_wide_down_kernel<2, true>), down, groups_down);
-    else if (col_blocks == 2) WIDE(grid_down, (decode_wide_down_kernel<2, false>), down, groups_down);
-    else if (nt) WIDE(grid_down, (decode_wide_down_kernel<1, true>), down, groups_down);
-    else WIDE(grid_down, (decode_wide_down_kernel<1, false>), down, groups_down);
+    if (step == DECODE_UP) {
+        if (nt) WIDE(grid_up, decode_wide_up_kernel<true>, up, groups_up);
+        else WIDE(grid_up, decode_wide_up_kernel<false>, up, groups_up);
+    } else if (step == DECODE_DOWN) {
+        if (col_blocks == 2 && nt) WIDE(grid_down, (decode_wide_down_kernel<2, true>), down, groups_down);
+        else if (col_blocks == 2) WIDE(grid_down, (decode_wide_down_kernel<2, false>), down, groups_down);
+        else if (nt) WIDE(grid_down, (decode_wide_down_kernel<1, true>), down, groups_down);
+        else WIDE(grid_down, (decode_wide_down_kernel<1, false>), down, groups_down);
+    }
 #undef WIDE
     return hipGetLastError();
 }

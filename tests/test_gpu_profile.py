@@ -43,6 +43,23 @@ def test_stage_intervals_cover_every_stage_of_every_step(moe):
     assert all(v[1] == 0 for v in moe.profile_read().values())                   # disabled: nothing recorded
 
 
+@pytest.mark.parametrize("T,H,F,E,k,shared", [(1, 256, 192, 64, 6, 2), (16, 256, 192, 8, 2, 1), (200, 512, 1024, 8, 2, 0)])
+def test_stage_intervals_of_a_small_layer_are_of_the_launches_it_makes(moe, T, H, F, E, k, shared):
+    """No permutation and no tile lists: profiling does not bring back the launches that a small layer goes without."""
+    cfg = scaled_config("C4", T=T, H=H, F=F, E=E, top_k=k, num_shared=shared)
+    gl = P.GpuLayer(moe, make_layer_inputs(cfg, device="cuda"), host_weights=False)
+    ref = gl.run_layer().clone()
+    moe.profile_enable(True)
+    try:
+        moe.profile_read()
+        for _ in range(3):
+            assert torch.equal(gl.run_layer(), ref)
+        counts = {stage: len(v) for stage, v in moe.profile_read_intervals().items()}
+    finally:
+        moe.profile_enable(False)
+    assert counts == {"route": 3, "permute_index": 0, "permute_gather": 0, "plan": 0, "ffn_gate_up": 3, "ffn_down": 3, "combine": 3}
+
+
 def test_mfma_ceiling_is_plausible_and_validates_its_arguments(moe):
     from paper_2503_09716_amd import MoeError
     sink = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
