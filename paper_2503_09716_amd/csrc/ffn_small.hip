@@ -220,14 +220,37 @@ __global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
 struct Group {
     int expert, row0, rows;
 };
-// Candidate c of the routed groups: expert c, or with fewer pairs than experts the expert of pair c, of which the first
-// pair that has it is taken.  False: no rows.
+// The c-th expert that has rows, -1: there are no more than c.  One wave.
+__device__ __forceinline__ int active_expert(const DecodeArgs& a, const int c, const int lane) {
+    __shared__ uint32_t present[8];   // bit e: expert e has rows
+    if (a.pairs == a.k) return a.topk_idx[c];   // one token
+    if (lane < 8) present[lane] = 0;
+    __syncthreads();   // one wave: orders its LDS writes and reads
+    for (int p = lane; p < a.pairs; p += 64) atomicOr(&present[a.topk_idx[p] >> 5], 1u << (a.topk_idx[p] & 31));
+    __syncthreads();
+    int left = c, word = -1;
+    uint32_t bits = 0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+        const uint32_t m = present[w];
+        if (word < 0 && left < __popc(m)) { word = w; bits = m; }
+        if (word < 0) left -= __popc(m);
+    }
+    if (word < 0) return -1;
+    return word * 32 + __builtin_ctzll(__ballot(lane < 32 && (bits >> lane & 1) && __popc(bits & ((1u << lane) - 1)) == left));
+}
+// Candidate c of the routed groups.  False: no rows.  Expert c, or with fewer pairs than experts the expert of pair c, of which the first
+// pair that has it is taken; DENSE: the c-th expert that has rows, so that the waves without work are the launch's last.  Spread
+// between the others they leave some CUs a wave more than others, which counts where a launch fills the chip about once (8
+// experts top-2, H = 6144, F = 16384, 3 tokens that pick 4 experts: gate/up 262 -> 239 us, 4 tokens, 6 experts 374 -> 352, 64 experts
+// top-6, 10 tokens 90 -> 85), and not in a small layer, whose waves take longer to find it (256 tokens 26.8 -> 29.4).
 // MAX: tokens at most; the pairs come 64 * CHUNKS at a time, all loads of which are in flight together.
-template <int MAX>
+template <int MAX, bool DENSE>
 __device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[MAX]) {
     constexpr int CHUNKS = MAX <= 16 ? 1 : 8;   // (few pairs: more code costs more than loads in turn, 1 token 0.8 us)
-    const bool by_pair = a.pairs <= a.E;
-    const int e = __builtin_amdgcn_readfirstlane(by_pair ? a.topk_idx[c] : c);
+    const bool by_pair = !DENSE && a.pairs <= a.E;
+    const int e = __builtin_amdgcn_readfirstlane(DENSE ? active_expert(a, c, lane) : by_pair ? a.topk_idx[c] : c);
+    if (DENSE && e < 0) return false;
     int n = 0, before = 0;
     for (int base = 0; base < a.pairs; base += 64 * CHUNKS) {
         int v[CHUNKS];
@@ -248,7 +271,7 @@ __device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, c
             before += __popcll(__ballot(v[u] < e));
         }
     }
-    __syncthreads();   // one wave: orders its LDS writes and reads
+    __syncthreads();
     g.expert = e;
     g.row0 = before;
     g.rows = min(n, MAX);   // a token has an expert once
@@ -368,7 +391,7 @@ __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, con
     }
     const int c = b / up.n_tiles;
     Group g;
-    if (!decode_group(a, c, lane, g, tokens)) return;
+    if (!decode_group<16, NT>(a, c, lane, g, tokens)) return;
     up_unit<NT>(up, {g.expert, g.row0, g.rows, -1}, b - c * up.n_tiles, lane, tokens);
 }
 
@@ -387,7 +410,7 @@ __global__ __launch_bounds__(64, 2) void decode_down_kernel(const GemmArgs down,
     }
     const int c = b / down.n_tiles;
     Group g;
-    if (!decode_group(a, c, lane, g, tokens)) return;
+    if (!decode_group<16, NT>(a, c, lane, g, tokens)) return;
     small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, (b - c * down.n_tiles) * 16, lane);
 }
 
@@ -409,7 +432,7 @@ __global__ __launch_bounds__(64, 2) void decode_wide_up_kernel(const GemmArgs up
         return;
     }
     Group g;
-    if (!decode_group(a, c, lane, g, tokens)) return;
+    if (!decode_group<WIDE_TOKENS, false>(a, c, lane, g, tokens)) return;
     small_rows<true, 2, NT>(up, {g.expert, g.row0, g.rows, -1}, part, parts, unit * 32, lane, tokens);
 }
 template <int NB, bool NT>
@@ -421,7 +444,7 @@ __global__ __launch_bounds__(64, 2) void decode_wide_down_kernel(const GemmArgs 
         return;
     }
     Group g;
-    if (!decode_group(a, c, lane, g, tokens)) return;
+    if (!decode_group<WIDE_TOKENS, false>(a, c, lane, g, tokens)) return;
     small_rows<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, part, parts, unit * 16 * NB, lane);
 }
 
