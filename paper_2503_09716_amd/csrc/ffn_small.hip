@@ -472,15 +472,14 @@ hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int h
 
 namespace {
 template <bool NT>
-hipError_t launch_decode_nt(const DecodeStep step, GemmArgs up, const GemmArgs& down, const DecodeArgs& a, hipStream_t st) {
+hipError_t launch_decode_nt(const DecodeStep step, GemmArgs up, const GemmArgs& down, const DecodeArgs& a, const bool early, hipStream_t st) {
     const int candidates = a.pairs < a.E ? a.pairs : a.E;
-    const bool early = a.partial && a.Ns > 0;
     const dim3 block(64);
     up.n_tiles = up.N / (16 * up_blocks<NT>());
     const int shared_units = a.Ns * up.n_tiles;
 #define DECODE(grid_, K_, ...) hipLaunchKernelGGL((K_), dim3((unsigned)(grid_)), block, 0, st, __VA_ARGS__)
     if (step == DECODE_TOPK && a.partial) {
-        const int grid = (up.T + 3) / 4 + shared_units;
+        const int grid = (up.T + 3) / 4 + (early ? shared_units : 0);
         if (a.E <= 64) DECODE(grid, (decode_topk_kernel<1, NT>), up, a);
         else if (a.E <= 128) DECODE(grid, (decode_topk_kernel<2, NT>), up, a);
         else if (a.E <= 192) DECODE(grid, (decode_topk_kernel<3, NT>), up, a);
@@ -494,7 +493,15 @@ hipError_t launch_decode_nt(const DecodeStep step, GemmArgs up, const GemmArgs& 
 }  // namespace
 
 hipError_t launch_decode(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st) {
-    return nt ? launch_decode_nt<true>(step, up, down, a, st) : launch_decode_nt<false>(step, up, down, a, st);
+    // The shared experts run ahead, next to the top-k and to the routed gate/up GEMM, where the walk along their Ns * F of K (0.09 us
+    // a sub-tile) hides behind the reads of that GEMM (4 H F bytes an expert at 5.8 TB/s): F cancels.  The experts that will be picked, at
+    // least: one token's, three tenths of those that the batch can have.  Elsewhere the walk holds the launch up (layer, shared experts
+    // ahead and not, us: 60 experts top-1 + 1 shared, H = 512, F = 12544, 1 token 64 and 45; 21 top-2 + 1, H = 576, F = 14720, 3
+    // tokens 92 and 75; 19 top-2 + 2, H = 960, F = 7552, 1 token 69 and 58).
+    const int candidates = a.pairs < a.E ? a.pairs : a.E;
+    const float picked = fmaxf((float)a.k, 0.3f * candidates);
+    const bool early = a.partial && a.Ns > 0 && picked * up.K >= 4078.f * a.Ns;
+    return nt ? launch_decode_nt<true>(step, up, down, a, early, st) : launch_decode_nt<false>(step, up, down, a, early, st);
 }
 
 hipError_t launch_decode_wide(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, int col_blocks, bool nt, hipStream_t st) {

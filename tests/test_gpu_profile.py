@@ -172,6 +172,51 @@ def test_gate_up_of_staged_calls_with_cached_weights(moe, T, H, F, E, k):
     assert default <= 1.08 * tiles
 
 
+# Layers of up to 16 tokens, whose launches need no tile lists, against the launches by list (x_tiled = 1, which adds a gather of 2 us):
+# T, H, F, E, k, shared, the experts that each token picks (None: as the gate matrix has it).
+FEW_TOKENS = [
+    # pairs that pick the same expert: four groups of 512 waves fill the chip exactly once, with two empty ones between them not
+    (3, 6144, 16384, 8, 2, 0, [[0, 3], [3, 5], [0, 6]]),
+    # few routed bytes next to a shared expert's long walk
+    (1, 512, 12544, 60, 1, 1, None),
+    (3, 576, 14720, 21, 2, 1, None),
+    (1, 2048, 1408, 64, 6, 2, None),
+]
+
+
+@pytest.mark.parametrize("T,H,F,E,k,shared,picks", FEW_TOKENS)
+def test_few_tokens_are_not_slower_than_by_tile_list(moe, T, H, F, E, k, shared, picks):
+    """Median of 9 x 20 layers in turn; 3 % for its spread (1 % seen)."""
+    from paper_2503_09716_amd import make_shape
+    shape = make_shape(T, H, F, E, k, shared, True)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    normal = lambda *size, std=0.02: torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tab = [[normal(H * F) for _ in range(E + shared)] for _ in range(3)]
+    x, wg, out, ws = normal(T, H, std=1.0), normal(H, E), normal(T, H), moe.new_workspace(shape)
+    if picks:
+        wg = torch.stack([sum((x[t].float() * 10 / H for t in range(T) if e in picks[t]), torch.zeros(H, device="cuda")) for e in range(E)], 1).bfloat16()
+    tables, times = moe.tables(*tab), {-1: [], 1: []}
+    try:
+        for _ in range(9):
+            for x_tiled in times:
+                moe.set_option("x_tiled", x_tiled)
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                moe.layer(shape, x, wg, None, None, None, None, out, ws, tables=tables)
+                a.record()
+                for _ in range(20):
+                    moe.layer(shape, x, wg, None, None, None, None, out, ws, tables=tables)
+                b.record()
+                b.synchronize()
+                times[x_tiled].append(a.elapsed_time(b) / 20)
+    finally:
+        moe.set_option("x_tiled", -1)
+    if picks:
+        assert [sorted(v) for v in moe.layer_views(shape, ws)["topk_idx"].tolist()] == picks
+    default, lists = (sorted(times[v])[4] for v in (-1, 1))
+    print("T", T, "H", H, "F", F, "E", E, "k", k, "shared", shared, "default %.4f ms" % default, "by list %.4f ms" % lists, flush=True)
+    assert default <= 1.03 * lists
+
+
 def test_weight_bytes_cost_the_same_on_both_sides_of_the_cache_size(moe):
     """Layers of more than 256 MB load weights that one tile or wave reads non-temporally.  Groups of 100 rows are two waves
     per panel in the gate/up GEMM, so a layer just above must not pay more per weight byte there than one just below
