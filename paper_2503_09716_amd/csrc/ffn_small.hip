@@ -341,34 +341,34 @@ __device__ __forceinline__ void decode_index(const DecodeArgs& a, const int lane
 
 __device__ __forceinline__ TileDesc shared_tile(const DecodeArgs& a, const GemmArgs& p, const int s) { return {a.E + s, 0, p.T, s * p.t_pad}; }
 
-// Units of 16 columns while the weights come from memory: twice the waves, and so bytes in flight, of units of 32 (64
+// Gate/up units of 16 columns (UB = 1) while the weights come from memory: twice the waves, and so bytes in flight, of units of 32 (64
 // experts, 1 token 38.9 -> 35.7 us, 160: 83.9 -> 74.5, 16 tokens 159 -> 155); a layer that the cache holds is faster with 32 (H =
-// 512, F = 1024, 16 tokens 17.3 us, 18.1 with 16).
-template <bool NT>
-__host__ __device__ constexpr int up_blocks() { return NT ? 1 : 2; }
-template <bool NT>
+// 512, F = 1024, 16 tokens 17.3 us, 18.1 with 16), and so are those above the cache
+// size whose walk along K is no longer than it takes a wave to find its group and fill its ring (H < 768) or whose units of 32 fill
+// the chip, two to a SIMD, about once, so that 16 add half a round (550 layers of 1 to 16 tokens: 16 columns take 1.05 and 1.03 of
+// the time of 32 there, 1.10 and 1.09 at most, elsewhere 0.98).
+template <int UB, bool NT>
 __device__ __forceinline__ void up_unit(const GemmArgs& up, const TileDesc& d, const int unit, const int lane, const int* tokens = nullptr) {
-    constexpr int UB = up_blocks<NT>();
     small_unit<true, UB, 1, 16 / UB, NT>(up, d, 0, unit * 16 * UB, lane, tokens);
 }
 // Gate/up unit `unit` of all shared experts'.
-template <bool NT>
+template <int UB, bool NT>
 __device__ __forceinline__ void shared_up_unit(const GemmArgs& up, const DecodeArgs& a, const int unit, const int lane) {
     const int s = unit / up.n_tiles;
-    up_unit<NT>(up, shared_tile(a, up, s), unit - s * up.n_tiles, lane);
+    up_unit<UB, NT>(up, shared_tile(a, up, s), unit - s * up.n_tiles, lane);
 }
 
 // Top-k of four tokens per workgroup, then the shared experts' gate/up units.
-template <int NB, bool NT>
+template <int NB, int UB, bool NT>
 __global__ __launch_bounds__(64, 2) void decode_topk_kernel(const GemmArgs up, const DecodeArgs a) {
     const int lane = threadIdx.x, quads = (up.T + 3) >> 2, b = blockIdx.x;
     if (b < quads) topk_row16<NB>(a.partial, a.splits, up.T, a.ep, a.E, a.k, a.bias, a.renorm, a.scale, b, lane, a.topk_idx, a.topk_w, nullptr);
-    else shared_up_unit<NT>(up, a, b - quads, lane);
+    else shared_up_unit<UB, NT>(up, a, b - quads, lane);
 }
 
 // Workgroup 0: the index arrays.  Then the shared experts' down units (early: their gate/up units are done) or gate/up units,
 // then the routed gate/up units.
-template <bool NT>
+template <int UB, bool NT>
 __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, const GemmArgs down, const DecodeArgs a, const bool early) {
     __shared__ int tokens[16];
     const int lane = threadIdx.x;
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, con
         }
         b -= down.n_tiles;
     } else if (b < a.Ns * up.n_tiles) {
-        shared_up_unit<NT>(up, a, b, lane);
+        shared_up_unit<UB, NT>(up, a, b, lane);
         return;
     } else {
         b -= a.Ns * up.n_tiles;
@@ -392,7 +392,7 @@ __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, con
     const int c = b / up.n_tiles;
     Group g;
     if (!decode_group<16, NT>(a, c, lane, g, tokens)) return;
-    up_unit<NT>(up, {g.expert, g.row0, g.rows, -1}, b - c * up.n_tiles, lane, tokens);
+    up_unit<UB, NT>(up, {g.expert, g.row0, g.rows, -1}, b - c * up.n_tiles, lane, tokens);
 }
 
 // The shared experts' down units (unless early), then the routed ones.
@@ -471,21 +471,21 @@ hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int h
 }
 
 namespace {
-template <bool NT>
-hipError_t launch_decode_nt(const DecodeStep step, GemmArgs up, const GemmArgs& down, const DecodeArgs& a, const bool early, hipStream_t st) {
+template <int UB, bool NT>
+hipError_t launch_decode_units(const DecodeStep step, GemmArgs up, const GemmArgs& down, const DecodeArgs& a, const bool early, hipStream_t st) {
     const int candidates = a.pairs < a.E ? a.pairs : a.E;
     const dim3 block(64);
-    up.n_tiles = up.N / (16 * up_blocks<NT>());
+    up.n_tiles = up.N / (16 * UB);
     const int shared_units = a.Ns * up.n_tiles;
 #define DECODE(grid_, K_, ...) hipLaunchKernelGGL((K_), dim3((unsigned)(grid_)), block, 0, st, __VA_ARGS__)
     if (step == DECODE_TOPK && a.partial) {
         const int grid = (up.T + 3) / 4 + (early ? shared_units : 0);
-        if (a.E <= 64) DECODE(grid, (decode_topk_kernel<1, NT>), up, a);
-        else if (a.E <= 128) DECODE(grid, (decode_topk_kernel<2, NT>), up, a);
-        else if (a.E <= 192) DECODE(grid, (decode_topk_kernel<3, NT>), up, a);
-        else DECODE(grid, (decode_topk_kernel<4, NT>), up, a);
+        if (a.E <= 64) DECODE(grid, (decode_topk_kernel<1, UB, NT>), up, a);
+        else if (a.E <= 128) DECODE(grid, (decode_topk_kernel<2, UB, NT>), up, a);
+        else if (a.E <= 192) DECODE(grid, (decode_topk_kernel<3, UB, NT>), up, a);
+        else DECODE(grid, (decode_topk_kernel<4, UB, NT>), up, a);
     }
-    if (step == DECODE_UP) DECODE(1 + (early ? down.n_tiles : shared_units) + candidates * up.n_tiles, (decode_up_kernel<NT>), up, down, a, early);
+    if (step == DECODE_UP) DECODE(1 + (early ? down.n_tiles : shared_units) + candidates * up.n_tiles, (decode_up_kernel<UB, NT>), up, down, a, early);
     if (step == DECODE_DOWN) DECODE((early || !a.Ns ? 0 : down.n_tiles) + candidates * down.n_tiles, (decode_down_kernel<NT>), down, a, early);
 #undef DECODE
     return hipGetLastError();
@@ -501,7 +501,10 @@ hipError_t launch_decode(DecodeStep step, const GemmArgs& up, const GemmArgs& do
     const int candidates = a.pairs < a.E ? a.pairs : a.E;
     const float picked = fmaxf((float)a.k, 0.3f * candidates);
     const bool early = a.partial && a.Ns > 0 && picked * up.K >= 4078.f * a.Ns;
-    return nt ? launch_decode_nt<true>(step, up, down, a, early, st) : launch_decode_nt<false>(step, up, down, a, early, st);
+    const int units = (candidates + (early ? 0 : a.Ns)) * (up.N / 32);
+    if (!nt) return launch_decode_units<2, false>(step, up, down, a, early, st);
+    return up.K < 24 * 32 || (units > 1200 && units <= 2048) ? launch_decode_units<2, true>(step, up, down, a, early, st)
+                                                             : launch_decode_units<1, true>(step, up, down, a, early, st);
 }
 
 hipError_t launch_decode_wide(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, int col_blocks, bool nt, hipStream_t st) {

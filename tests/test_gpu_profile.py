@@ -181,6 +181,8 @@ FEW_TOKENS = [
     (1, 512, 12544, 60, 1, 1, None),
     (3, 576, 14720, 21, 2, 1, None),
     (1, 2048, 1408, 64, 6, 2, None),
+    # a walk along K of 22 sub-tiles: half as many waves of twice the columns
+    (13, 704, 12992, 21, 4, 0, [sorted((t + i) % 12 for i in (0, 3, 5, 7)) for t in range(13)]),
 ]
 
 
