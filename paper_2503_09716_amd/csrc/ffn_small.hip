@@ -220,37 +220,25 @@ __global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
 struct Group {
     int expert, row0, rows;
 };
-// The c-th expert that has rows, -1: there are no more than c.  One wave.
-__device__ __forceinline__ int active_expert(const DecodeArgs& a, const int c, const int lane) {
-    __shared__ uint32_t present[8];   // bit e: expert e has rows
-    if (a.pairs == a.k) return a.topk_idx[c];   // one token
-    if (lane < 8) present[lane] = 0;
-    __syncthreads();   // one wave: orders its LDS writes and reads
-    for (int p = lane; p < a.pairs; p += 64) atomicOr(&present[a.topk_idx[p] >> 5], 1u << (a.topk_idx[p] & 31));
-    __syncthreads();
-    int left = c, word = -1;
-    uint32_t bits = 0;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) {
-        const uint32_t m = present[w];
-        if (word < 0 && left < __popc(m)) { word = w; bits = m; }
-        if (word < 0) left -= __popc(m);
+// The pairs v (of index base + lane) that have expert e: their tokens and number, and the number of those with lower ones.
+template <int MAX>
+__device__ __forceinline__ void count_pairs(const DecodeArgs& a, const int e, const int v, const uint64_t eq, const int base, const int lane, int (&tokens)[MAX],
+                                            int& n, int& before) {
+    if (eq) {
+        const int rank = n + __popcll(eq & ((1ull << lane) - 1));
+        if (v == e && rank < MAX) tokens[rank] = (base + lane) / a.k;
+        n += __popcll(eq);
     }
-    if (word < 0) return -1;
-    return word * 32 + __builtin_ctzll(__ballot(lane < 32 && (bits >> lane & 1) && __popc(bits & ((1u << lane) - 1)) == left));
+    before += __popcll(__ballot(v < e));
 }
-// Candidate c of the routed groups.  False: no rows.  Expert c, or with fewer pairs than experts the expert of pair c, of which the first
-// pair that has it is taken; DENSE: the c-th expert that has rows, so that the waves without work are the launch's last.  Spread
-// between the others they leave some CUs a wave more than others, which counts where a launch fills the chip about once (8
-// experts top-2, H = 6144, F = 16384, 3 tokens that pick 4 experts: gate/up 262 -> 239 us, 4 tokens, 6 experts 374 -> 352, 64 experts
-// top-6, 10 tokens 90 -> 85), and not in a small layer, whose waves take longer to find it (256 tokens 26.8 -> 29.4).
+// Candidate c of the routed groups: expert c, or with fewer pairs than experts the expert of pair c, of which the first
+// pair that has it is taken.  False: no rows.
 // MAX: tokens at most; the pairs come 64 * CHUNKS at a time, all loads of which are in flight together.
-template <int MAX, bool DENSE>
-__device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[MAX]) {
+template <int MAX>
+__device__ __forceinline__ bool candidate_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[MAX]) {
     constexpr int CHUNKS = MAX <= 16 ? 1 : 8;   // (few pairs: more code costs more than loads in turn, 1 token 0.8 us)
-    const bool by_pair = !DENSE && a.pairs <= a.E;
-    const int e = __builtin_amdgcn_readfirstlane(DENSE ? active_expert(a, c, lane) : by_pair ? a.topk_idx[c] : c);
-    if (DENSE && e < 0) return false;
+    const bool by_pair = a.pairs <= a.E;
+    const int e = __builtin_amdgcn_readfirstlane(by_pair ? a.topk_idx[c] : c);
     int n = 0, before = 0;
     for (int base = 0; base < a.pairs; base += 64 * CHUNKS) {
         int v[CHUNKS];
@@ -263,19 +251,55 @@ __device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, c
         for (int u = 0; u < CHUNKS; ++u) {
             const uint64_t eq = __ballot(v[u] == e);
             if (by_pair && n == 0 && eq && base + u * 64 + __builtin_ctzll(eq) != c) return false;
-            if (eq) {
-                const int rank = n + __popcll(eq & ((1ull << lane) - 1));
-                if (v[u] == e && rank < MAX) tokens[rank] = (base + u * 64 + lane) / a.k;
-                n += __popcll(eq);
-            }
-            before += __popcll(__ballot(v[u] < e));
+            count_pairs(a, e, v[u], eq, base + u * 64, lane, tokens, n, before);
         }
     }
-    __syncthreads();
+    __syncthreads();   // one wave: orders its LDS writes and reads
     g.expert = e;
     g.row0 = before;
     g.rows = min(n, MAX);   // a token has an expert once
     return n > 0;
+}
+// The c-th expert that has rows, of up to 256 pairs, so that the waves without work are the launch's last.  Spread
+// between the others (candidate_group) they leave some CUs a wave more than others, which counts where a launch fills the chip about once (8
+// experts top-2, H = 6144, F = 16384, 3 tokens that pick 4 experts: gate/up 262 -> 239 us, 4 tokens, 6 experts 374 -> 352, 64 experts
+// top-6, 10 tokens 90 -> 85), and not in a small layer, whose waves take longer to find it (256 tokens 26.8 -> 29.4).
+__device__ __forceinline__ bool active_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[16]) {
+    __shared__ uint32_t present[8];   // bit e: expert e has rows
+    if (a.pairs == a.k) return candidate_group(a, c, lane, g, tokens);   // one token: every pair another expert
+    int v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = u * 64 + lane < a.pairs ? a.topk_idx[u * 64 + lane] : 0x7fffffff;
+    if (lane < 8) present[lane] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (u * 64 + lane < a.pairs) atomicOr(&present[v[u] >> 5], 1u << (v[u] & 31));
+    __syncthreads();
+    int left = c, word = -1;
+    uint32_t bits = 0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+        const uint32_t m = present[w];
+        if (word < 0 && left < __popc(m)) { word = w; bits = m; }
+        if (word < 0) left -= __popc(m);
+    }
+    if (word < 0) return false;
+    const uint64_t hit = __ballot(lane < 32 && (bits >> lane & 1) && __popc(bits & ((1u << lane) - 1)) == left);
+    const int e = __builtin_amdgcn_readfirstlane(word * 32 + __builtin_ctzll(hit));
+    int n = 0, before = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (u * 64 < a.pairs) count_pairs(a, e, v[u], __ballot(v[u] == e), u * 64, lane, tokens, n, before);
+    __syncthreads();
+    g.expert = e;
+    g.row0 = before;
+    g.rows = min(n, 16);
+    return true;
+}
+template <bool DENSE>
+__device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[16]) {
+    return DENSE ? active_group(a, c, lane, g, tokens) : candidate_group(a, c, lane, g, tokens);
 }
 
 // expert_offsets and the index arrays of the permutation, by one wave (E <= 256, at most 64 * CHUNKS pairs).
@@ -391,7 +415,7 @@ __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, con
     }
     const int c = b / up.n_tiles;
     Group g;
-    if (!decode_group<16, NT>(a, c, lane, g, tokens)) return;
+    if (!decode_group<NT>(a, c, lane, g, tokens)) return;
     up_unit<UB, NT>(up, {g.expert, g.row0, g.rows, -1}, b - c * up.n_tiles, lane, tokens);
 }
 
@@ -410,7 +434,7 @@ __global__ __launch_bounds__(64, 2) void decode_down_kernel(const GemmArgs down,
     }
     const int c = b / down.n_tiles;
     Group g;
-    if (!decode_group<16, NT>(a, c, lane, g, tokens)) return;
+    if (!decode_group<NT>(a, c, lane, g, tokens)) return;
     small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, (b - c * down.n_tiles) * 16, lane);
 }
 
@@ -432,7 +456,7 @@ __global__ __launch_bounds__(64, 2) void decode_wide_up_kernel(const GemmArgs up
         return;
     }
     Group g;
-    if (!decode_group<WIDE_TOKENS, false>(a, c, lane, g, tokens)) return;
+    if (!candidate_group(a, c, lane, g, tokens)) return;
     small_rows<true, 2, NT>(up, {g.expert, g.row0, g.rows, -1}, part, parts, unit * 32, lane, tokens);
 }
 template <int NB, bool NT>
@@ -444,7 +468,7 @@ __global__ __launch_bounds__(64, 2) void decode_wide_down_kernel(const GemmArgs 
         return;
     }
     Group g;
-    if (!decode_group<WIDE_TOKENS, false>(a, c, lane, g, tokens)) return;
+    if (!candidate_group(a, c, lane, g, tokens)) return;
     small_rows<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, part, parts, unit * 16 * NB, lane);
 }
 
