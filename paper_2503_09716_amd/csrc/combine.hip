@@ -123,6 +123,8 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const uint16_t* __rest
 
 hipError_t launch_combine(const moe_shape& s, const void* y_perm, const int32_t* inv_perm, const float* w,
                           const void* y_shared, void* out, bool y_fp32, bool shared_fp32, bool out_fp32, hipStream_t st) {
+    if (!y_shared) shared_fp32 = y_fp32;   // no rows, so no say in what a thread loads
+    if (y_fp32 && !shared_fp32) return hipErrorInvalidValue;   // no caller has fp32 y_perm next to bf16 y_shared
     // up to five waves to a workgroup, and as many workgroups to a token as its row then takes
     const int per_thread = y_fp32 || shared_fp32 ? 4 : 8;
     const int waves = (s.H / per_thread + 63) / 64, parts = (waves + COMBINE_MAX_WAVES - 1) / COMBINE_MAX_WAVES;
@@ -158,7 +160,7 @@ hipError_t launch_combine(const moe_shape& s, const void* y_perm, const int32_t*
     } while (0)
     if (y_fp32 && shared_fp32) COMBINE_O(true, true);
     else if (shared_fp32) COMBINE_O(false, true);
-    else COMBINE_O(false, false);   // (fp32 y_perm comes with fp32 y_shared)
+    else COMBINE_O(false, false);
 #undef COMBINE_O
 #undef COMBINE_K
 #undef COMBINE
