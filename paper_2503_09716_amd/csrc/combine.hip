@@ -2,13 +2,13 @@
 // (Sec. 2: the layer output is the weighted sum of the k experts' outputs, plus the shared
 // expert every token passes through.)
 //
-// combine: one thread per token and 16 bytes of its widest input (8 consecutive hidden elements where all rows are
-// bf16, else 4), which gathers the k expert rows of its token through inv_perm, all of them in flight at
-// once.  Sums are fp32 in the fixed order j = 0..k-1 then shared, every output element is written
-// exactly once: no atomics, and the result is bit-identical from run to run.  HBM-bound: reads k+1 rows,
-// writes 1 row per token.  Against one workgroup per token that walked its row 8 elements per thread and waited
-// for each expert's row before it asked for the next: 160 experts top-6 + 2 shared, H = 5120, 32768 tokens 614 -> 498 us
-// (3.0 GB = 6.0 TB/s), 64 experts, H = 2048, 16384 tokens 120 -> 94 us, 1 token 2 us less of the layer's 47.
+// combine: one thread per token and 4 or 8 consecutive hidden elements (combine_elements), which gathers the k expert
+// rows of its token through inv_perm, all of them in flight at once.  Sums are fp32 in the fixed order j = 0..k-1 then
+// shared, every output element is written exactly once: no atomics, and the result is bit-identical from run to run.
+// HBM-bound: reads k+1 rows, writes 1 row per token.  Against one workgroup per token that walked its row 8 elements per
+// thread and waited for each expert's row before it asked for the next: 160 experts top-6 + 2 shared, H = 5120, 32768
+// tokens 614 -> 500 to 545 us by box (3.0 GB = 5.5 to 6.0 TB/s), 64 experts, H = 2048, 16384 tokens 120 -> 94 us, 1 token
+// 2 us less of the layer's 47.
 #include "common.h"
 
 namespace moe {
@@ -36,11 +36,14 @@ struct Piece {
 // YF32 / SF32: y_perm / y_shared hold fp32 (else bf16); OF32: out is fp32 (else bf16, RNE).  K: rows a thread has in
 // flight at a time, k itself up to 8.
 constexpr int COMBINE_MAX_WAVES = 5;
+// Elements per thread: 16 bytes of its widest input, twice that for one or two fp32 rows that the cache holds (8 experts top-2, H =
+// 6144, 4242 tokens 45.8 -> 38.8 us, H = 4096, 8000 tokens 59.2 -> 55.5; but 16384 tokens, H = 6144, from memory 155 -> 171).
+constexpr int combine_elements(const bool fp32, const int k, const bool nt) { return fp32 && (k > 2 || nt) ? 4 : 8; }
 template <bool YF32, bool SF32, bool OF32, int K, bool NT>
 __global__ __launch_bounds__(COMBINE_MAX_WAVES * 64) void combine_kernel(const char* __restrict__ y_perm, const int32_t* __restrict__ inv_perm,
                                                                          const float* __restrict__ w, const char* __restrict__ y_shared,
                                                                          int k, int H, char* __restrict__ out) {
-    constexpr int N = YF32 || SF32 ? 4 : 8;
+    constexpr int N = combine_elements(YF32 || SF32, K, NT);
     const int t = blockIdx.x;
     const int c = blockIdx.y * blockDim.x + threadIdx.x;
     if (c >= H / N) return;
@@ -125,15 +128,15 @@ hipError_t launch_combine(const moe_shape& s, const void* y_perm, const int32_t*
                           const void* y_shared, void* out, bool y_fp32, bool shared_fp32, bool out_fp32, hipStream_t st) {
     if (!y_shared) shared_fp32 = y_fp32;   // no rows, so no say in what a thread loads
     if (y_fp32 && !shared_fp32) return hipErrorInvalidValue;   // no caller has fp32 y_perm next to bf16 y_shared
-    // up to five waves to a workgroup, and as many workgroups to a token as its row then takes
-    const int per_thread = y_fp32 || shared_fp32 ? 4 : 8;
-    const int waves = (s.H / per_thread + 63) / 64, parts = (waves + COMBINE_MAX_WAVES - 1) / COMBINE_MAX_WAVES;
-    const dim3 grid((unsigned)s.T, (unsigned)parts), block((unsigned)((waves + parts - 1) / parts * 64));
     // Non-temporal loads where the rows exceed the memory-side cache (256 MB): they are read once, most of them from memory
     // (16384 tokens above: 117 us without, 94 with).  Rows that fit are still there from the down GEMM's stores, and
     // the hint costs: 8 experts top-2, H = 4096, fp32, 4096 tokens (134 MB) 28.6 -> 29.9 us.
     const int64_t row_bytes = s.top_k * (y_fp32 ? 4 : 2) + (y_shared ? (shared_fp32 ? 4 : 2) : 0);
     const bool nt = (int64_t)s.T * s.H * row_bytes > ((int64_t)256 << 20);
+    // up to five waves to a workgroup, and as many workgroups to a token as its row then takes
+    const int per_thread = combine_elements(y_fp32 || shared_fp32, s.top_k, nt);
+    const int waves = (s.H / per_thread + 63) / 64, parts = (waves + COMBINE_MAX_WAVES - 1) / COMBINE_MAX_WAVES;
+    const dim3 grid((unsigned)s.T, (unsigned)parts), block((unsigned)((waves + parts - 1) / parts * 64));
 #define COMBINE_NT(Y, S, O, K, NT)                                                                                        \
     hipLaunchKernelGGL((combine_kernel<Y, S, O, K, NT>), grid, block, 0, st, (const char*)y_perm, inv_perm, w,            \
                        (const char*)y_shared, s.top_k, s.H, (char*)out)

@@ -499,7 +499,8 @@ def test_combine(moe, T, H, k, shared, y_fp32):
 # and one batch on either side of the size from which the rows are loaded non-temporally
 @pytest.mark.parametrize("T,H,k,shared,y_fp32", [(5, 64 + 192 * k, k, k % 2 == 0, k % 3 == 0) for k in range(1, 10)] + [
     (3, 1280, 16, True, True), (3, 1344, 17, True, False), (2, 2560, 64, False, False), (4, 2624, 8, False, True),
-    (2047, 4096, 8, False, True), (2049, 4096, 8, False, True)])
+    (2047, 4096, 8, False, True), (2049, 4096, 8, False, True), (8192, 4096, 2, False, True), (8193, 4096, 2, False, True),
+    (4112, 5440, 2, True, True), (4113, 5440, 2, True, True)])
 def test_combine_rows_in_flight(moe, T, H, k, shared, y_fp32):
     from paper_2503_09716_amd import make_shape
     say("combine rows", T, H, k, shared, y_fp32)
