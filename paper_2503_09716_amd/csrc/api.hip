@@ -694,7 +694,7 @@ moe_status layer_with_workspace(moe_ctx* c, const moe_shape* s, const void* x, c
         const FfnBuffers b{nullptr, f.row_token, x, nullptr, tab, f.h, f.y_perm, f.y_shared, f.y32, true};
         const RouteGemm rg = route_gemm_config(*s);
         const DecodeArgs d{rg.splits && few ? (const float*)(ws + make_layout(*s).rt_logits) : nullptr, bias, rg.splits, rg.ep, s->renormalize,
-                           s->routed_scale, f.topk_idx, f.offsets, f.perm, f.inv_perm, f.row_token, f.topk_w,
+                           s->routed_scale, f.topk_idx, f.offsets, f.inv_perm, f.topk_w,
                            s->T * s->top_k, s->top_k, s->E, s->num_shared};
         const GemmArgs up = gate_up_args(c, *s, fs, b), down = down_args(c, *s, fs, b, ws);
         auto launch = [&](const DecodeStep step) {

@@ -102,7 +102,7 @@ struct DecodeArgs {
     const float* bias;
     int32_t splits, ep, renorm;
     float scale;
-    int32_t *topk_idx, *offsets, *perm, *inv_perm, *row_token;
+    int32_t *topk_idx, *offsets, *inv_perm;
     float* topk_w;
     int32_t pairs, k, E, Ns;
 };
@@ -169,8 +169,8 @@ hipError_t launch_ffn_gemm(bool gated, const GemmArgs& a, const GemmConfig& cfg,
 // the same GEMMs with one wavefront per 16 * col_blocks columns (small batches): a.n_tiles column units per
 // m-tile, m-tiles of at most 64 * halves rows; gate/up: col_blocks = 2; nt: non-temporal loads of W
 hipError_t launch_ffn_small(bool gated, const GemmArgs& a, int col_blocks, int halves, bool nt, hipStream_t st);
-// A layer of up to 16 tokens from the router's partial logits (none: from topk_idx and topk_w) to the down GEMM, with the
-// permutation's index arrays, in three launches (the first only from partial logits).
+// A layer of up to 16 tokens from the router's partial logits (none: from topk_idx and topk_w) to the down GEMM, with
+// expert_offsets and inv_perm, in three launches (the first only from partial logits).
 enum DecodeStep { DECODE_TOPK, DECODE_UP, DECODE_DOWN };
 hipError_t launch_decode(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st);
 // The same from topk_idx and topk_w on, for up to 256 tokens; n_tiles: units of 32 and of 16 * col_blocks columns.

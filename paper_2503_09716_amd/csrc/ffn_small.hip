@@ -209,7 +209,7 @@ __global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
 // ---- layers of few pairs: up to 16 tokens, or up to 256 in small layers ---------------------------------------
 // What a wave needs to know of the routing - its expert's
 // tokens and where their rows begin - it reads off topk_idx itself (at most 1024 pairs, a vote per 64).  So no launch
-// stands between the selection and the gate/up GEMM: the permutation's index arrays are written by one wave of that
+// stands between the selection and the gate/up GEMM: expert_offsets and inv_perm are written by one wave of that
 // GEMM's launch.  Up to 16 tokens every group is one block of 16 rows, and shared experts wait for nothing: with more than 16 experts their gate/up GEMM runs next to the
 // top-k, whose launch leaves the memory idle, and their down GEMM, the longest walk of all, next to the routed gate/up
 // GEMM.  (The first
@@ -302,7 +302,8 @@ __device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, c
     return DENSE ? active_group(a, c, lane, g, tokens) : candidate_group(a, c, lane, g, tokens);
 }
 
-// expert_offsets and the index arrays of the permutation, by one wave (E <= 256, at most 64 * CHUNKS pairs).
+// expert_offsets and inv_perm, by one wave (E <= 256, at most 64 * CHUNKS pairs): what the combine and moe_layer_views read.  perm
+// and row_token have no reader in these layers.
 template <int CHUNKS>
 __device__ __forceinline__ void decode_index(const DecodeArgs& a, const int lane) {
     __shared__ int cursor[256];
@@ -357,9 +358,7 @@ __device__ __forceinline__ void decode_index(const DecodeArgs& a, const int lane
     for (int u = 0; u < CHUNKS; ++u) {
         const int p = u * 64 + lane;
         if (v[u] < 0) continue;
-        a.perm[slot[u]] = p;
         a.inv_perm[p] = slot[u];
-        a.row_token[slot[u]] = p / a.k;
     }
 }
 
@@ -390,7 +389,7 @@ __global__ __launch_bounds__(64, 2) void decode_topk_kernel(const GemmArgs up, c
     else shared_up_unit<UB, NT>(up, a, b - quads, lane);
 }
 
-// Workgroup 0: the index arrays.  Then the shared experts' down units (early: their gate/up units are done) or gate/up units,
+// Workgroup 0: expert_offsets and inv_perm.  Then the shared experts' down units (early: their gate/up units are done) or gate/up units,
 // then the routed gate/up units.
 template <int UB, bool NT>
 __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, const GemmArgs down, const DecodeArgs a, const bool early) {
@@ -438,7 +437,7 @@ __global__ __launch_bounds__(64, 2) void decode_down_kernel(const GemmArgs down,
     small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, (b - c * down.n_tiles) * 16, lane);
 }
 
-// More than 16 tokens: the same with `parts` waves for every 64 rows of a group.  Workgroup 0: the index arrays; then all
+// More than 16 tokens: the same with `parts` waves for every 64 rows of a group.  Workgroup 0: expert_offsets and inv_perm; then all
 // groups' first 64 rows (shared experts first), their second, and so on.  (Parts of a group next to each other: most are empty and
 // the dispatch lines up the others on the same CUs, H = 512, F = 1024, 8 experts, 256 tokens, four parts: gate/up 9 -> 19 us.)
 constexpr int WIDE_TOKENS = 256;
