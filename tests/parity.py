@@ -200,18 +200,18 @@ def check_layer_against_oracle(gl: GpuLayer, out: torch.Tensor, tokens=None, che
     return report
 
 
-TILE_ROWS = (128, 256, 320)      # every m-tile height the grouped GEMMs use for full tiles
+TILE_ROWS = (128, 256, 320, 352, 384)      # every m-tile height the grouped GEMMs use for full tiles at full size
 
 
 def sample_tokens(idx: np.ndarray, E: int, n: int, seed: int, every_tile: bool = True) -> np.ndarray:
     """At least n tokens chosen so that EVERY m-tile of every expert's row group holds a checked
     row, whichever tile height a launch uses: per group (rows are in ascending token order) one
-    random row from each block of 128, of 256 and of 320 rows; the rows on both sides of the first
-    tile boundaries (127..129, 255..257, 319..321); the first and the last row; the rows on both
+    random row from each block of 128, 256, 320, 352 and 384 rows; the rows on both sides of the first
+    tile boundaries (127..129, 255..257, ... 383..385); the first and the last row; the rows on both
     sides of the place where a short tail (the rows past the last multiple of 256) joins the last
     full tile.  The same positions of the token range itself cover the shared experts, whose
     groups are all T tokens.  The rest uniformly at random.  every_tile=False keeps only the
-    boundary rows of each group (no row per block): about 20 tokens per expert."""
+    boundary rows of each group (no row per block): about 26 tokens per expert."""
     rng = np.random.default_rng(seed)
     T, k = idx.shape
     flat_e = idx.reshape(-1).astype(np.int64)

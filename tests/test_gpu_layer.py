@@ -658,15 +658,16 @@ READ_ONCE_SHAPES = [(4096, 3072, 4, 2), (4096, 3072, 4, 4), (8192, 1408, 4, 2), 
 
 @pytest.mark.parametrize("H,F,E,k", READ_ONCE_SHAPES)
 def test_layer_weights_read_once_give_the_tile_routine_s_bits(moe, H, F, E, k):
-    """Groups of up to 64 rows, of 65 to 128 (one tile of the non-temporal variants, or two waves per panel) and above, against
-    small_tiles = 0, which runs every tile on the 256-row variant with ordinary loads."""
+    """Groups of up to 64 rows (up to 32 tokens without tile lists in the third and fourth shape), of 65 to 128 (one tile of the
+    non-temporal variants, or two waves per panel) and above, against small_tiles = 0, which runs every tile on the 256-row variant with
+    ordinary loads."""
     cfg = scaled_config("C2", T=256, H=H, F=F, E=E, top_k=k)
     li = make_layer_inputs(cfg, device="cuda")
     gl = P.GpuLayer(moe, li, host_weights=False)
     moe.set_option("layer_y_fp32", 1)
     moe.set_option("down_tail_splits", 0)
     try:
-        for T in (16, 65, 100, 128, 129, 200, 256):
+        for T in (16, 17, 24, 32, 65, 100, 128, 129, 200, 256):
             say("read once", cfg, "tokens", T)
             gl.shape.T = T
             gl.x = li.x[:T].contiguous()
@@ -679,6 +680,47 @@ def test_layer_weights_read_once_give_the_tile_routine_s_bits(moe, H, F, E, k):
                 torch.cuda.synchronize()
                 got.append(out)
             assert torch.equal(*got), T
+    finally:
+        moe.set_option("out_fp32", 0)
+        moe.set_option("small_tiles", 1)
+        moe.set_option("layer_y_fp32", -1)
+        moe.set_option("down_tail_splits", 1)
+
+
+# Layers of up to 16 tokens above 256 MB: E, k, shared, H, F.  Gate/up units of 16 columns, and of 32 (a short walk along K; units that fill the
+# chip once); shared experts ahead of the routed ones and not; every width of the top-k; experts without rows.
+FEW_ABOVE_CACHE = [(64, 6, 2, 2048, 384), (160, 6, 2, 1024, 320), (20, 2, 2, 768, 2752), (40, 16, 0, 576, 2048), (8, 2, 1, 1600, 3328), (130, 1, 1, 2048, 192),
+                   (256, 4, 0, 832, 256)]
+
+
+@pytest.mark.parametrize("E,k,shared,H,F", FEW_ABOVE_CACHE)
+def test_layer_of_few_tokens_above_the_cache_size(moe, E, k, shared, H, F):
+    """Against the launches by tile list with ordinary loads (small_tiles = 0): offsets, inverse permutation, selection and output bit for
+    bit; tokens that all pick the same experts, too."""
+    assert 6 * (E + shared) * H * F > 256 << 20
+    cfg = scaled_config("C4", T=16, H=H, F=F, E=E, top_k=k, num_shared=shared)
+    li = make_layer_inputs(cfg, device="cuda")
+    gl = P.GpuLayer(moe, li, host_weights=False)
+    moe.set_option("layer_y_fp32", 1)
+    moe.set_option("down_tail_splits", 0)
+    moe.set_option("out_fp32", 1)
+    try:
+        for T, equal in ((1, False), (2, False), (2, True), (7, False), (16, False), (16, True)):
+            say("few above the cache", cfg, "tokens", T, "equal rows", equal)
+            gl.shape.T = T
+            x = (li.x[:1].expand(T, H) if equal else li.x[:T]).contiguous()
+            got = []
+            for small_tiles in (1, 0):
+                moe.set_option("small_tiles", small_tiles)
+                gl.ws.fill_(255)
+                out = torch.full((T, H), float("nan"), device="cuda")
+                moe.layer(gl.shape, x, gl.wg, gl.bias, gl.w1p, gl.w3p, gl.w2p, out, gl.ws, tables=gl.tables)
+                torch.cuda.synchronize()
+                views = moe.layer_views(gl.shape, gl.ws)
+                got.append([out] + [v.clone() for _, v in sorted(views.items())])
+            assert len(got[0]) == 5
+            for a, b in zip(*got):
+                assert torch.equal(a, b), (T, equal)
     finally:
         moe.set_option("out_fp32", 0)
         moe.set_option("small_tiles", 1)
