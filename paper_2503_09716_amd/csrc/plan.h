@@ -85,8 +85,8 @@ __device__ __forceinline__ GroupCut list_cut(const PlanArgs& p, const int which,
 // 32 rows, 0.81 at 128, 1.01 at 256 with 1792 tiles; 0.42, 0.52 and 0.68 at 32, 128 and 256 rows
 // with 128 tiles; 0.74 at 192 and 0.83 at 256 rows, two tiles to a panel.)  Above 256 rows the matrix cores take
 // longer than the loads, 2.3 ns a row (8 experts, H = 6144, F = 16384, 16384 tokens, gate/up: 0.72 us at 256 rows, 0.88 at 320, 1.02
-// at 384).  A launch costs its whole rounds of 256 tiles times the mean tile, and no less than its longest
-// tile.
+// at 384).  A launch costs its whole rounds of 256 tiles times the mean tile (of more than twelve the last one only half: by then the
+// CUs are out of step), and no less than its longest tile.
 //   short launches (up to two rounds of 256-row tiles, p.choose_* = 1): all eight caps.  With caps below 256 an expert of
 //     250 rows is two tiles of 128: the down GEMM of eight such experts fills the chip with one round of 256 tiles instead
 //     of half a round of 256-row ones (8x7B, 1000 tokens: 310 -> 268 us); with 352, one of 628 rows two tiles instead of three
@@ -99,11 +99,11 @@ __device__ __forceinline__ GroupCut list_cut(const PlanArgs& p, const int which,
 //     are what this has to get right (8x7B, gate/up, us): all of 350 to 380 rows, eight tiles of 384 rows per column 543 and
 //     sixteen of 192 587; three of the eight above 384 rows, eleven tiles = 4.8 rounds 620 to 640 against 600 to 607, and the
 //     even tiles stay.  (With half of the last round and 50 rows for the neighbour of a tile, the estimate took the
-//     eleven, +7 %.)  Every height forced and timed, 485 launches of 280 to 16384 tokens, 2 to 160 experts: against the usual
-//     height the chosen one takes 0.962 of the time (gate/up; the best of the four 0.954), 0.943 (down; 0.932), and no launch is
-//     more than 1.5 % longer, which is what two timings of one launch differ by; over 96 more (64 and 160 experts, 2400 to
-//     14000 tokens) one, 3 %.  What another height must gain by the estimate to be taken: 4 to 5 %, where 320 rows is the
-//     usual one (host, from 1200 rows per expert on) 1.5 %.
+//     eleven, +7 %.)  Every height forced and timed, 633 launches of 280 to 32768 tokens, 2 to 160 experts: against the usual
+//     height the chosen one takes 0.962 of the time (gate/up; the best of the four 0.954), 0.949 (down; 0.937), and no launch is
+//     more than 3 % longer (one in 300 more than 1.5 %, which is what two timings of one launch differ by).  What another
+//     height must gain by the estimate to be taken: 4 to 5 %, where 320 rows is the usual one (host, from 1200 rows per expert
+//     on) 1.5 %.
 constexpr int PLAN_CAPS = 8, PLAN_CAPS_LONG = 4;
 __device__ constexpr int plan_cap(const int c) { return (c < 3 ? 384 : 352) - 32 * c; }   // 384, 352, 320, 256, 224, ... 128
 // whether cap c is a candidate (3: as 1, for the wave grids that have no tiles above 256 rows)
@@ -148,7 +148,9 @@ __device__ __forceinline__ float list_cost(const ListSum& s, const int choose, c
     const int tiles = s.n * n_tiles;
     const float busy = fminf(fmaxf((float)(tiles - 128) / 128.f, 0.f), 1.f);
     const float mean = (s.sum + busy * (50.f * s.beside + (choose == 2 ? 190.f : 230.f) * s.alone)) / (float)s.n;
-    return fmaxf((float)((tiles + 255) / 256) * mean, (float)s.longest);
+    float rounds = (float)((tiles + 255) / 256);
+    if (rounds > 12.f) rounds = 0.5f * (rounds + (float)tiles / 256.f + 0.5f);
+    return fmaxf(rounds * mean, (float)s.longest);
 }
 
 // Builds the two m-tile lists (gate/up GEMM with tiles of up to tm_up rows, down GEMM with tm_down)
