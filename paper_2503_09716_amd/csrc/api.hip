@@ -358,7 +358,7 @@ int split_room_tiles(const moe_shape& s) { return 149 - 79000 / s.F; }
 // than the idle CUs from then on), and when the tile routine would have tiles for a quarter of the CUs at most up to 128
 // tokens.  From 129 to 256 tokens, with at most 64 rows per group on average (139 layers of 2 to 32 experts, up to 100 MB,
 // weights cached): an eighth of the CUs at most, 0.52 to 0.95 of the tile routine's time; up to a quarter
-// 0.6 to 1.25 (24 top-4, H = 512, F = 256, 255 tokens 10.1 -> 11.8 us), so only where the layer then goes
+// 0.8 to 1.00 with at most 16 rows, else 0.7 to 1.25 (24 top-4, H = 512, F = 256, 255 tokens 10.1 -> 11.8 us), so only where the layer then goes
 // without the launches of the permutation and the lists (6 us), and X, which every 32 columns re-read, is
 // narrow: layers 0.71 to 0.99 (H from 2048 on: up to 1.06).  The tile routine is ahead (by 10 % at most) where its launch is one full round.
 // Down: up to 64 tokens with at most 16 rows per group on average, except in launches of eight rounds of
@@ -407,7 +407,7 @@ SmallRule small_rule(const moe_ctx* c, const moe_shape& s, bool layer) {
     // Both GEMMs without m-tile lists: launch_decode up to 16 tokens, launch_decode_wide above.
     const bool no_lists = layer && r.down && s.top_k <= 16 && c->gemm.x_tiled != 1 && s.T <= 256 && pairs <= 1024;
     r.up = allowed && (s.T <= 16 || (s.T <= 128 && tiles_up <= 64) ||
-                       (s.T <= 256 && pairs <= 64 * (int64_t)groups && tiles_up <= (no_lists && s.H < 2048 ? 64 : 32)));
+                       (s.T <= 256 && pairs <= 64 * (int64_t)groups && tiles_up <= ((no_lists && s.H < 2048) || pairs <= 16 * (int64_t)groups ? 64 : 32)));
     r.no_lists = no_lists && r.up;
     r.halves = s.T <= 64 ? 1 : 2;
     r.once = s.T <= 64 || (s.num_shared == 0 && pairs <= 52 * (int64_t)groups);
