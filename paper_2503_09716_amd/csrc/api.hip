@@ -454,7 +454,8 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // Gate/up GEMM: 320-row tiles move 10 % fewer bytes per FLOP from L2 to LDS (the chip is
     // power-limited, and what the loads cost is clock), measured -1.3 % (C3) to -3.9 % (C4, C5) on
     // that GEMM; not when an expert is only about four tiles (C2: 1024 rows = 3 tiles + a tail
-    // that needs a pass of its own, +10 %).  This is the usual height; the plan takes another where that is clearly cheaper.
+    // that needs a pass of its own, +10 %).  In launches of more than two rounds this is the usual height, and the plan takes
+    // another where that is clearly cheaper; in shorter ones all heights are compared with 256 rows.
     if (!c->gemm.tile_rows_up && tall_kernel && (double)s.T * s.top_k / s.E >= 1200.0) tm_up = 320;
     if (!tall_kernel && choose_up) choose_up = choose_up == 1 ? 3 : 0;
     if (!tall_kernel && tm_up > 256) tm_up = 256;

@@ -207,14 +207,13 @@ __global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
 }
 
 // ---- layers of few pairs: up to 16 tokens, or up to 256 in small layers ---------------------------------------
-// What a wave needs to know of the routing - its expert's
-// tokens and where their rows begin - it reads off topk_idx itself (at most 1024 pairs, a vote per 64).  So no launch
-// stands between the selection and the gate/up GEMM: expert_offsets and inv_perm are written by one wave of that
-// GEMM's launch.  Up to 16 tokens every group is one block of 16 rows, and shared experts wait for nothing: with more than 16 experts their gate/up GEMM runs next to the
-// top-k, whose launch leaves the memory idle, and their down GEMM, the longest walk of all, next to the routed gate/up
-// GEMM.  (The first
+// What a wave needs to know of the routing - its expert's tokens and where their rows begin - it reads off topk_idx itself
+// (at most 1024 pairs, a vote per 64).  So no launch stands between the selection and the gate/up GEMM: expert_offsets and
+// inv_perm are written by one wave of that GEMM's launch.  Up to 16 tokens every group is one block of 16 rows, and with more
+// than 16 experts the shared ones can run ahead (launch_decode says where): their gate/up GEMM next to the top-k, whose
+// launch leaves the memory idle, and their down GEMM, the longest walk of all, next to the routed gate/up GEMM.  (The first
 // part of that next to the router GEMM instead: 2 us slower.)  Same bits as the launches by list.  Layer, us: 64 experts
-// top-6 + 2 shared, F = 1408, 1 token 42.2 -> 35.7, 4: 85 -> 79, 16: 167 -> 155; 160 experts, 1: 82 -> 74, 16: 583 -> 568; 8
+// top-6 + 2 shared, F = 1408, 1 token 42.2 -> 35.7, 4: 85 -> 79, 16: 167 -> 158; 160 experts, 1: 82 -> 74, 16: 583 -> 568; 8
 // experts top-2, F = 14336, 1: 125 -> 116, 16: 441 -> 430; H = 512, F = 1024, 8 tokens 23 -> 17, 40: 24.7 -> 21.1,
 // 256: 31.1 -> 26.5.
 struct Group {
