@@ -113,8 +113,8 @@ size_t moe_h_scratch_bytes(const moe_shape* shape);
  *                             where "down_tail_splits" cuts nothing ("gemm_waves", "gemm_wave_rows", "gemm_group_m",
  *                             "xcd_remap" and "tails_last" do not apply to GEMMs without m-tiles)
  *   "gemm_tile_rows_up" / "gemm_tile_rows_down"  0 | 128 | 256 | 320   most rows per m-tile of the gate/up
- *                             and the down GEMM (groups of two or three tiles are cut evenly below that; "tall_tiles"
- *                             adds to 256); 0 (default) picks per launch from the tile count and the rows per expert, up to 384
+ *                             and the down GEMM (groups of two or three tiles, above 256 rows of four, are cut evenly below that;
+ *                             "tall_tiles" adds to 256); 0 (default) picks per launch from the tile count and the rows per expert, up to 384
  *                             (320 and above: 4 waves x 1 wave row only, else treated as 256).  Other than 0, either
  *                             of them also keeps both GEMMs of a small batch on m-tiles.  Same results bit for bit
  *                             where "down_tail_splits" cuts nothing.
