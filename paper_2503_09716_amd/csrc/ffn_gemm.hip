@@ -111,6 +111,26 @@ __device__ __forceinline__ void buffer_store_bf16(__amdgpu_buffer_rsrc_t rsrc, u
 #endif
 }
 
+__device__ __forceinline__ void buffer_store_b128(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff, u32x4 v) {
+#if defined(__gfx950__)
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, voff, 0, 0);
+#endif
+}
+
+// Lanes 16..31 and 48..63 of a and lanes 0..15 and 32..47 of b change places; both halves as one piece.
+__device__ __forceinline__ u32x4 swap_rows16(const u32x2 a, const u32x2 b) {
+    u32x4 o = {0u, 0u, 0u, 0u};
+#if defined(__gfx950__)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(a[i], b[i], false, false));
+        o[i] = r[0];
+        o[2 + i] = r[1];
+    }
+#endif
+    return o;
+}
+
 // c += a (16 x 32, row operand) * b (32 x 16, column operand).  Written as inline assembly with
 // the accumulator tied to an AGPR quad: left to itself the register allocator (all 256 AGPRs
 // hold accumulators) routes part of them through temporaries, two to four copies per MFMA.
@@ -418,29 +438,41 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
     if (GATED) {
         // W is the row operand: the lane owns output row (X row) lane%16 of block i and the 4
         // consecutive columns 4*(lane/16) .. +3 of gate block j; the up value of the same
-        // element sits in the same lane and register of block WBH + j.  h is written tiled:
-        // block (row/16, col/32), row%16 at 64 bytes each, piece slot = piece ^ block_swizzle(row%16);
-        // a store instruction covers 16 rows x 32 contiguous bytes.
+        // element sits in the same lane and register of block WBH + j.  Gate blocks j and j + 1 are the two halves
+        // of one 32-column block of h (row%16 at 64 bytes each, piece slot = piece ^ block_swizzle(row%16)).  Lanes 16 apart
+        // swap halves, so that each has one 16-byte piece and a store instruction covers 16 rows x 64 contiguous bytes.
+        // VALU-bound (a quarter-rate exponential and reciprocal per element), so: no branch between the elements, whose
+        // chains then overlap, and no address arithmetic (row block i is i * hstep bytes on, rows past the group's end
+        // get an offset that the descriptor drops).
+        const int orow = orow_base + bx0 * 32, rr = (orow + rl) & 15;
+        const uint32_t hstep = (uint32_t)(N >> 5) * 1024u;   // bytes of 16 rows of h
+        const uint32_t hblocks = (uint32_t)(((orow_base & 15) + d.nrows + 15) >> 4);
+        const __amdgpu_buffer_rsrc_t rs_h = tile_rsrc(out + (size_t)(orow_base >> 4) * hstep, hblocks * hstep);
+        const uint32_t hoff = (uint32_t)(((orow + rl) >> 4) - (orow_base >> 4)) * hstep +
+                              (uint32_t)(rr * 64 + ((((g >> 1) + 2 * (g & 1)) ^ block_swizzle(rr)) << 4));
 #pragma unroll
-        for (int i = 0; i < XB; ++i) {
-            const int r = bx0 * 32 + i * 16 + rl;
-            const bool row_ok = r < d.nrows;
-            const int ro = orow_base + r, rr = ro & 15, sw = block_swizzle(rr);
-            char* hrow = out + ((size_t)(ro >> 4) * (size_t)(N >> 5)) * 1024 + rr * 64;
+        for (int j = 0; j < WBH; j += 2) {
+            const int col = n0 + bw0 * 32 + j * 16;   // wave-uniform; N is a multiple of 64
+            if (col >= N) break;
+            const uint32_t at = hoff + (uint32_t)(col >> 5) * 1024u;
 #pragma unroll
-            for (int j = 0; j < WBH; ++j) {
-                const int col = n0 + bw0 * 32 + j * 16 + g * 4;
-                bf16x4 o;
+            for (int i = 0; i < XB; ++i) {
+                u32x2 o[2];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float gv = acc[j][i][q], uv = acc[WBH + j][i][q];
-                    // silu(g) * u with the hardware reciprocal (1 ulp): far below the bf16 rounding of h
-                    o[q] = (__bf16)(gv * __builtin_amdgcn_rcpf(1.0f + __expf(-gv)) * uv);
+                for (int b = 0; b < 2; ++b) {
+                    bf16x4 v;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float gv = acc[j + b][i][q], uv = acc[WBH + j + b][i][q];
+                        // silu(g) * u with the hardware reciprocal (1 ulp): far below the bf16 rounding of h
+                        v[q] = (__bf16)(gv * __builtin_amdgcn_rcpf(1.0f + __expf(-gv)) * uv);
+                    }
+                    o[b] = __builtin_bit_cast(u32x2, v);
                 }
-                if (row_ok && col < N)
-                    *reinterpret_cast<bf16x4*>(hrow + (size_t)(col >> 5) * 1024 + ((((col & 31) >> 3) ^ sw) << 4) + (col & 7) * 2) = o;
+                const bool row_ok = bx0 * 32 + i * 16 + rl < d.nrows;
+                buffer_store_b128(rs_h, row_ok ? at + (uint32_t)i * hstep : 0xFFFFFFFFu, swap_rows16(o[0], o[1]));
+                if (i % 2) __builtin_amdgcn_sched_barrier(0);   // two block rows at a time: keeps accumulator reads from piling up
             }
-            __builtin_amdgcn_sched_barrier(0);   // one block row at a time: keeps accumulator reads from piling up
         }
     } else {
         // GEMM 2 / router GEMM: X is the row operand, so the lane owns output column lane%16 of W
