@@ -277,8 +277,8 @@ moe_status moe_layer_chunked(moe_ctx* ctx, const moe_shape* shape, const void* x
  * another while the next expert's weights are prefetched into a second buffer; App. A: only
  * experts that received tokens are fetched).  Experts are taken in groups of
  * `experts_per_group` consecutive non-empty experts; group g is copied into staging slot
- * g % num_slots with hipMemcpyAsync on a stream the context owns while the GEMMs of earlier
- * groups run on `hip_stream`; events hand the slots back and forth.  The shared experts form
+ * g % num_slots on a stream the context owns (with hipMemcpyAsync, or small matrices in pinned
+ * memory by a kernel that reads them over the link) while the GEMMs of earlier groups run on `hip_stream`; events hand the slots back and forth.  The shared experts form
  * the last group.  Same kernels and same results as moe_layer, bit for bit (with option
  * "down_tail_splits" at 0 or 2; under its default rule a pass over one group of experts and a
  * pass over all of them may decide differently whether to cut a short tail, which changes the

@@ -259,6 +259,58 @@ moe_status weight_table(moe_ctx* c, int n, const void* const* w1, const void* co
     return MOE_OK;
 }
 
+// The address at which kernels read [p, p + bytes) of pinned host memory; nullptr if they cannot, or not 16 bytes at a time.
+const void* device_view(const void* p, size_t bytes) {
+    hipPointerAttribute_t first, last;
+    if (hipPointerGetAttributes(&first, p) != hipSuccess || hipPointerGetAttributes(&last, (const char*)p + bytes - 1) != hipSuccess) {
+        (void)hipGetLastError();   // memory that HIP does not know; the launches' checks must not find this error
+        return nullptr;
+    }
+    if (first.type != hipMemoryTypeHost || last.type != hipMemoryTypeHost || !first.devicePointer || !last.devicePointer) return nullptr;
+    const char* const d = (const char*)first.devicePointer;
+    return (const char*)last.devicePointer == d + bytes - 1 && ((uintptr_t)d & 15) == 0 ? d : nullptr;
+}
+
+// Whether a group of streamed experts with that many rows in all is fetched by kernel.  The copy engine loses 9 us a matrix, the
+// kernel nothing, but where the program's other streams leave both of the call's no hardware queue each, the GEMMs wait for the
+// kernel as they do not for the engine.  So only groups whose GEMMs take less than the engine's gaps (1.2 PFLOP/s, weights at 5 TB/s):
+// those lose nothing even then.  64 experts + 2 shared, F = 1408, groups of 8, one queue each: 4096 tokens 22.3 -> 20.4 ms, 16384 tokens 22.7 -> 20.8,
+// on one queue 21.5 and 22.6; 8 experts, F = 14336, 16384 tokens, one at a time: 51.0 ms by engine, 50.7 by kernel, on one queue 57.8.
+bool fetch_by_kernel(const moe_shape& s, int experts, int64_t rows) {
+    const double matrix = (double)s.H * s.F;
+    return 5e-9 * matrix * rows + experts * 6 * matrix / 5e6 < experts * 3 * 9.0;
+}
+
+// Host matrices of one size to consecutive places of a staging slot: by kernel (stream.hip) those in pinned memory, as many at a
+// time as a launch takes, others by the copy engine.
+struct HostFetch {
+    HostMatrices run;
+    char* dst;   // place of the next matrix
+    size_t bytes;
+    hipStream_t st;
+    bool by_kernel;
+    HostFetch(char* dst_, size_t bytes_, hipStream_t st_, bool by_kernel_) : dst(dst_), bytes(bytes_), st(st_), by_kernel(by_kernel_) { run.n = 0; }
+    hipError_t flush() {
+        if (run.n == 0) return hipSuccess;
+        run.bytes = (uint32_t)bytes;   // a matrix is under 4 GiB (shape_problem)
+        const hipError_t e = launch_host_copy(run, st);
+        run.n = 0;
+        return e;
+    }
+    hipError_t add(const void* src) {
+        char* const to = dst;
+        dst += bytes;
+        const void* const seen = by_kernel ? device_view(src, bytes) : nullptr;
+        if (!seen) {
+            if (const hipError_t e = flush()) return e;
+            return hipMemcpyAsync(to, src, bytes, hipMemcpyHostToDevice, st);
+        }
+        if (run.n == 0) run.dst = to;
+        run.src[run.n++] = seen;
+        return run.n == HOST_MATRICES ? flush() : hipSuccess;
+    }
+};
+
 // partial_only (more than 16 experts): stops at the partial logits.
 moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* wg, const float* bias, int32_t* idx,
                      float* w, float* logits, char* ws, hipStream_t st, bool partial_only = false) {
@@ -1018,18 +1070,22 @@ moe_status moe_layer_streamed(moe_ctx* c, const moe_shape* s, const void* x, con
         for (int e = 0; e < E + Ns; ++e) { t1[e] = base; t3[e] = base; t2[e] = base; }
         int member = 0, mt = 0;
         const int e0 = G.shared ? E : G.lo, e1 = G.shared ? E + Ns : G.hi;
+        auto rows_of = [&](const int e) { return e < E ? c->h_offsets[e + 1] - c->h_offsets[e] : s->T; };
+        int live = 0;
+        int64_t all_rows = 0;
+        for (int e = e0; e < e1; ++e) { live += rows_of(e) > 0; all_rows += rows_of(e); }
+        HostFetch fetch(base, mat_bytes, c->copy_stream, fetch_by_kernel(*s, live, all_rows));
         for (int e = e0; e < e1; ++e) {
-            const int rows = e < E ? c->h_offsets[e + 1] - c->h_offsets[e] : s->T;
+            const int rows = rows_of(e);
             if (rows == 0) continue;
             char* dst = base + (size_t)member * expert_bytes;
-            HIP_TRY(c, hipMemcpyAsync(dst, hw1[e], mat_bytes, hipMemcpyHostToDevice, c->copy_stream));
-            HIP_TRY(c, hipMemcpyAsync(dst + mat_bytes, hw3[e], mat_bytes, hipMemcpyHostToDevice, c->copy_stream));
-            HIP_TRY(c, hipMemcpyAsync(dst + 2 * mat_bytes, hw2[e], mat_bytes, hipMemcpyHostToDevice, c->copy_stream));
+            for (const void* src : {hw1[e], hw3[e], hw2[e]}) HIP_TRY(c, fetch.add(src));
             t1[e] = dst; t3[e] = dst + mat_bytes; t2[e] = dst + 2 * mat_bytes;
             c->stream_bytes += expert_bytes;
             mt += (rows + 127) / 128;
             ++member;
         }
+        HIP_TRY(c, fetch.flush());
         HIP_TRY(c, hipEventRecord(c->slot_ready[slot], c->copy_stream));
         HIP_TRY(c, hipStreamWaitEvent(hs, c->slot_ready[slot], 0));
         void** tab = nullptr;

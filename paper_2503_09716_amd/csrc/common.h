@@ -185,6 +185,17 @@ hipError_t launch_combine(const moe_shape& s, const void* y_perm, const int32_t*
 // in: logical [rows = K, cols] row-major; out: packed [cols_padded x K] (cols_padded % 32 == 0, columns >= cols are zero)
 hipError_t launch_pack_weight(const void* in, int rows, int cols, int cols_padded, void* out, hipStream_t st);
 
+// n matrices of `bytes` bytes each, at device-visible addresses of pinned host memory, to consecutive places from dst on.
+// By value: the launch takes its own copy.
+constexpr int HOST_MATRICES = 96;
+struct HostMatrices {
+    const void* src[HOST_MATRICES];
+    char* dst;
+    uint32_t bytes;
+    int32_t n;
+};
+hipError_t launch_host_copy(const HostMatrices& m, hipStream_t st);   // bytes: a multiple of 4096; 16-byte aligned addresses
+
 // register-only MFMA loop (profile.hip): sink holds blocks*256 floats
 constexpr int CEILING_BLOCKS = 1024;
 double mfma_ceiling_flops(int blocks, int iters);

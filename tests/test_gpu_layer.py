@@ -348,6 +348,39 @@ def test_streamed_weights_equal_resident(moe, name, over, per_group, num_slots):
                            max(2, per_group), out, gl.ws)
 
 
+@pytest.mark.parametrize("place", ["aligned", "odd", "pageable", "mixed"])
+def test_streamed_weights_wherever_they_lie(moe, place):
+    """Host matrices that kernels can read 16 bytes at a time (groups of more of them than one launch takes), pinned ones
+    that are not aligned for that, and memory that is not pinned at all: the bits of moe_layer from each, in one call too."""
+    import ctypes as C
+    from paper_2503_09716_amd import binding as B
+    cfg = scaled_config("C5", T=500, H=192, F=128, E=45, top_k=5)
+    say("streamed from", place, cfg)
+    gl = P.GpuLayer(moe, make_layer_inputs(cfg, device="cuda"), host_weights=False)
+    ref = gl.run_layer(True)
+    n, numel = cfg.E + cfg.num_shared, cfg.H * cfg.F
+    pinned = torch.empty(3 * n * (numel + 8) + 8, dtype=torch.bfloat16).pin_memory()
+    host = []
+    for i, w in enumerate(w for ws in (gl.w1p, gl.w3p, gl.w2p) for w in ws):
+        kind = place if place != "mixed" else ("aligned", "aligned", "odd", "pageable")[i % 4]
+        at = i * (numel + 8) + (4 if kind == "odd" else 0)   # 8 bytes off
+        host.append(w.cpu() if kind == "pageable" else pinned[at:at + numel].copy_(w.cpu()))
+    tables = [(C.c_void_p * n)(*[w.data_ptr() for w in host[i * n:(i + 1) * n]]) for i in range(3)]
+    per_group, num_slots = 40, 2
+    slot_bytes = per_group * 3 * numel * 2
+    slots = torch.empty(num_slots * slot_bytes, dtype=torch.uint8, device="cuda")
+    out = torch.full_like(ref, float("nan"))
+    moe.set_option("out_fp32", 1)
+    try:
+        moe._check(moe.lib.moe_layer_streamed(moe.h, C.byref(gl.shape), B._ptr(gl.x), B._ptr(gl.wg), B._ptr(gl.bias), *tables,
+                                              B._ptr(slots), slot_bytes, num_slots, per_group, B._ptr(out), B._ptr(gl.ws),
+                                              gl.ws.numel(), B._stream()))
+        torch.cuda.synchronize()
+    finally:
+        moe.set_option("out_fp32", 0)
+    assert torch.equal(ref, out)
+
+
 def test_layer_in_a_hip_graph(moe):
     """moe_layer enqueues kernels only (no memsets, no host synchronisation once its pointer
     table is uploaded), so it can be captured; every replay, with eager work and
