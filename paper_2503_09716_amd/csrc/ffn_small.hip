@@ -28,13 +28,54 @@ typedef const __attribute__((address_space(1))) bf16x8* gfrag_t;
 
 constexpr int SMALL_ROWS = 64;   // rows of X per wave at most: an m-tile of up to 128 rows is two units
 
+// Where a unit's W comes from: rows n0 .. of expert `group`'s matrices, per lane row lane % 16 of a block, logical piece lane / 16.
+template <bool GATED, int NB>
+struct Panel {
+    static constexpr int WQ = GATED ? 2 * NB : NB;   // W blocks per sub-tile
+    gchar_t a, b;
+    uint32_t off;
+    __device__ __forceinline__ Panel(const GemmArgs& p, gchar_t wa, gchar_t wb, const int n0, const int lane) : a(wa), b(wb) {
+        const int rl = lane & 15, g = lane >> 4;
+        off = (uint32_t)(n0 >> 4) * (uint32_t)(p.kt_w * 1024) + (uint32_t)(rl * 64 + ((g ^ block_swizzle(rl)) << 4));
+    }
+    __device__ __forceinline__ Panel(const GemmArgs& p, const int group, const int n0, const int lane)
+        : Panel(p, (gchar_t)p.w_a[group], GATED ? (gchar_t)p.w_b[group] : (gchar_t)nullptr, n0, lane) {}
+    // sub-tile ks
+    template <bool NT>
+    __device__ __forceinline__ void load(const GemmArgs& p, const int ks, bf16x8 (&f)[WQ]) const {
+#pragma unroll
+        for (int j = 0; j < WQ; ++j) {
+            gchar_t base = GATED && j >= NB ? b : a;
+            const uint32_t at = off + (uint32_t)((GATED && j >= NB ? j - NB : j) * p.kt_w + ks) * 1024u;
+            f[j] = NT ? __builtin_nontemporal_load((gfrag_t)(base + at)) : *(gfrag_t)(base + at);
+        }
+    }
+};
+
+// The first sub-tiles of a unit's W, asked for before the unit's rows are known: their latency passes while the rows are looked up.
+// Down GEMM, us: 8 experts top-2, H = 512, F = 1024, 256 tokens 12.1 -> 11.0, 128 tokens 11.2 -> 9.9, 9 top-3, H = 896, F = 768, 166 tokens
+// 10.9 -> 10.0; layers of one token 35.0 -> 33.9 (64 experts, F = 1408), 116.7 -> 114.9 (8 experts, F = 14336).  Not in the gate/up GEMM
+// of more than 16 tokens, whose registers are full (12.7 -> 13.2), nor where the expert has to be searched first (no change).
+constexpr int EARLY = 4;
+template <bool GATED, int NB>
+struct EarlyW {
+    bf16x8 f[EARLY][Panel<GATED, NB>::WQ];
+    template <bool NT>
+    __device__ __forceinline__ void ask(const GemmArgs& p, const int group, const int n0, const int lane) {
+        const Panel<GATED, NB> w(p, group, n0, lane);
+#pragma unroll
+        for (int u = 0; u < EARLY; ++u) w.template load<NT>(p, min(u, (p.K >> 5) - 1), f[u]);
+    }
+};
+
 // One unit: rows r0 .. r0 + 16 * XB - 1 of tile d (nrows of the tile are valid), columns n0 .. n0 + 16 * NB - 1.
 // ROUTER: the gate GEMM, K piece d.group of one packed matrix, fp32 partial logits.
 // NT: W loads are non-temporal.  tokens: row r of a routed tile is token tokens[r] (LDS) instead of row_token's.
 template <bool GATED, int NB, int XB, int RING, bool NT, bool ROUTER = false>
 __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, const int r0, const int n0, const int lane,
-                                           const int* tokens = nullptr) {
-    constexpr int WQ = GATED ? 2 * NB : NB;   // W blocks per sub-tile
+                                           const int* tokens = nullptr, const EarlyW<GATED, NB>* early = nullptr) {
+    constexpr int WQ = Panel<GATED, NB>::WQ;
+    static_assert(RING >= EARLY, "early sub-tiles fill the first places of the ring");
     const int rl = lane & 15, g = lane >> 4;
     const bool shared = !ROUTER && d.srow >= 0;
     const int nseg = !GATED && shared ? p.nseg_shared : 1;
@@ -56,8 +97,6 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
             xoff[i] = (uint32_t)(grow >> 4) * (uint32_t)(p.kt_a * 1024) + (uint32_t)(rr * 64 + ((g ^ block_swizzle(rr)) << 4));
         }
     }
-    const uint32_t woff = (uint32_t)(n0 >> 4) * (uint32_t)(p.kt_w * 1024) + (uint32_t)(rl * 64 + ((g ^ block_swizzle(rl)) << 4));
-
     f32x4 acc[WQ][XB];
 #pragma unroll
     for (int j = 0; j < WQ; ++j)
@@ -66,17 +105,15 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
     bf16x8 wf[RING][WQ], xf[RING][XB];
 
     gchar_t xb = (gchar_t)(shared ? p.a_shared : p.a_routed) + (ROUTER ? (size_t)d.group * (size_t)p.K * 2 : 0);
-    gchar_t wa = ROUTER ? (gchar_t)p.w_uniform + (size_t)d.group * (size_t)p.w_uniform_stride : (gchar_t)p.w_a[d.group];
-    gchar_t const wb = GATED ? (gchar_t)p.w_b[d.group] : (gchar_t)nullptr;
-    auto load = [&](const int u, gchar_t x, gchar_t w, const int ks) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < WQ; ++j) {
-            gchar_t base = GATED && j >= NB ? wb : w;
-            const uint32_t off = woff + (uint32_t)((GATED && j >= NB ? j - NB : j) * p.kt_w + ks) * 1024u;
-            wf[u][j] = NT ? __builtin_nontemporal_load((gfrag_t)(base + off)) : *(gfrag_t)(base + off);
-        }
+    const gchar_t w0 = ROUTER ? (gchar_t)p.w_uniform + (size_t)d.group * (size_t)p.w_uniform_stride : (gchar_t)p.w_a[d.group];
+    Panel<GATED, NB> wa(p, w0, GATED ? (gchar_t)p.w_b[d.group] : (gchar_t)nullptr, n0, lane);
+    auto load_x = [&](const int u, gchar_t x, const int ks) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < XB; ++i) xf[u][i] = *(gfrag_t)(x + (xoff[i] + (uint32_t)ks * xstep));
+    };
+    auto load = [&](const int u, gchar_t x, const Panel<GATED, NB>& w, const int ks) __attribute__((always_inline)) {
+        w.template load<NT>(p, ks, wf[u]);
+        load_x(u, x, ks);
     };
     auto multiply = [&](const int u) __attribute__((always_inline)) {
 #pragma unroll
@@ -91,11 +128,20 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
     // wait for all loads behind it): past the end of K the places take the first sub-tiles of the next
     // segment, or re-read the last sub-tile.  (The branch after it, once per segment, only loads where there is a next one.)
 #pragma unroll
-    for (int u = 0; u < RING; ++u) load(u, xb, wa, min(u, KT - 1));
+    for (int u = 0; u < RING; ++u) {
+        if (early && u < EARLY) {
+#pragma unroll
+            for (int j = 0; j < WQ; ++j) wf[u][j] = early->f[u][j];
+            load_x(u, xb, min(u, KT - 1));
+        } else {
+            load(u, xb, wa, min(u, KT - 1));
+        }
+    }
     for (int seg = 0; seg < nseg; ++seg) {
         const bool more = seg + 1 < nseg;
         gchar_t const xn = more ? xb + a_seg_stride : xb;
-        gchar_t const wn = more ? (gchar_t)p.w_a[d.group + seg + 1] : wa;
+        Panel<GATED, NB> wn = wa;
+        if (more) wn.a = (gchar_t)p.w_a[d.group + seg + 1];
         int t = 0;
         for (; t + 2 * RING <= KT; t += RING) {
 #pragma unroll
@@ -166,16 +212,20 @@ __device__ __forceinline__ void small_unit(const GemmArgs& p, const TileDesc d, 
     }
 }
 
-// Part `part` of `parts` of tile d: every parts-th 64 rows, columns n0 ..
+// Up to 64 rows of tile d from row r0 on, columns n0 ..
 template <bool GATED, int NB, bool NT>
-__device__ __forceinline__ void small_rows(const GemmArgs& p, const TileDesc& d, const int part, const int parts, const int n0, const int lane,
-                                           const int* tokens = nullptr) {
-    for (int r0 = part * SMALL_ROWS; r0 < d.nrows; r0 += parts * SMALL_ROWS) {
-        const int blocks = (min(d.nrows - r0, SMALL_ROWS) + 15) >> 4;   // wave-uniform
-        if (blocks > 2) small_unit<GATED, NB, 4, GATED ? 4 : (NB == 2 ? 5 : 6), NT>(p, d, r0, n0, lane, tokens);
-        else if (blocks > 1) small_unit<GATED, NB, 2, GATED ? 6 : (NB == 2 ? 7 : 8), NT>(p, d, r0, n0, lane, tokens);
-        else small_unit<GATED, NB, 1, GATED ? 8 : (NB == 2 ? 8 : 16), NT>(p, d, r0, n0, lane, tokens);
-    }
+__device__ __forceinline__ void small_block(const GemmArgs& p, const TileDesc& d, const int r0, const int n0, const int lane, const int* tokens = nullptr,
+                                            const EarlyW<GATED, NB>* early = nullptr) {
+    const int blocks = (min(d.nrows - r0, SMALL_ROWS) + 15) >> 4;   // wave-uniform
+    if (blocks > 2) small_unit<GATED, NB, 4, GATED ? 4 : (NB == 2 ? 5 : 6), NT>(p, d, r0, n0, lane, tokens, early);
+    else if (blocks > 1) small_unit<GATED, NB, 2, GATED ? 6 : (NB == 2 ? 7 : 8), NT>(p, d, r0, n0, lane, tokens, early);
+    else if (blocks > 0) small_unit<GATED, NB, 1, GATED ? 8 : (NB == 2 ? 8 : 16), NT>(p, d, r0, n0, lane, tokens, early);
+}
+
+// Part `part` of `parts` of tile d: every parts-th 64 rows
+template <bool GATED, int NB, bool NT>
+__device__ __forceinline__ void small_rows(const GemmArgs& p, const TileDesc& d, const int part, const int parts, const int n0, const int lane) {
+    for (int r0 = part * SMALL_ROWS; r0 < d.nrows; r0 += parts * SMALL_ROWS) small_block<GATED, NB, NT>(p, d, r0, n0, lane);
 }
 
 // Units in the order: columns fastest, then the 64-row parts of an m-tile (`halves` of them side by
@@ -219,6 +269,11 @@ __global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
 struct Group {
     int expert, row0, rows;
 };
+// Orders a wave's LDS writes and reads (one wave to a workgroup; a barrier would wait for the loads in flight).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 // The pairs v (of index base + lane) that have expert e: their tokens and number, and the number of those with lower ones.
 template <int MAX>
 __device__ __forceinline__ void count_pairs(const DecodeArgs& a, const int e, const int v, const uint64_t eq, const int base, const int lane, int (&tokens)[MAX],
@@ -233,27 +288,36 @@ __device__ __forceinline__ void count_pairs(const DecodeArgs& a, const int e, co
 // Candidate c of the routed groups: expert c, or with fewer pairs than experts the expert of pair c, of which the first
 // pair that has it is taken.  False: no rows.
 // MAX: tokens at most; the pairs come 64 * CHUNKS at a time, all loads of which are in flight together.
-template <int MAX>
-__device__ __forceinline__ bool candidate_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[MAX]) {
+// ask(expert) comes between the first loads of the pairs and their use (EarlyW).
+template <int MAX, class Ask>
+__device__ __forceinline__ bool candidate_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[MAX], Ask ask) {
     constexpr int CHUNKS = MAX <= 16 ? 1 : 8;   // (few pairs: more code costs more than loads in turn, 1 token 0.8 us)
     const bool by_pair = a.pairs <= a.E;
     const int e = __builtin_amdgcn_readfirstlane(by_pair ? a.topk_idx[c] : c);
-    int n = 0, before = 0;
-    for (int base = 0; base < a.pairs; base += 64 * CHUNKS) {
-        int v[CHUNKS];
+    int n = 0, before = 0, v[CHUNKS];
+    auto get = [&](const int base) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < CHUNKS; ++u) v[u] = a.topk_idx[min(base + u * 64 + lane, a.pairs - 1)];
+    };
+    // false: an earlier pair has the expert
+    auto count = [&](const int base) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < CHUNKS; ++u) {
-            const int p = base + u * 64 + lane;
-            v[u] = p < a.pairs ? a.topk_idx[p] : 0x7fffffff;
-        }
-#pragma unroll
-        for (int u = 0; u < CHUNKS; ++u) {
+            if (base + u * 64 + lane >= a.pairs) v[u] = 0x7fffffff;
             const uint64_t eq = __ballot(v[u] == e);
             if (by_pair && n == 0 && eq && base + u * 64 + __builtin_ctzll(eq) != c) return false;
             count_pairs(a, e, v[u], eq, base + u * 64, lane, tokens, n, before);
         }
+        return true;
+    };
+    get(0);
+    ask(e);
+    if (!count(0)) return false;
+    for (int base = 64 * CHUNKS; base < a.pairs; base += 64 * CHUNKS) {
+        get(base);
+        if (!count(base)) return false;
     }
-    __syncthreads();   // one wave: orders its LDS writes and reads
+    wave_lds_order();
     g.expert = e;
     g.row0 = before;
     g.rows = min(n, MAX);   // a token has an expert once
@@ -265,7 +329,6 @@ __device__ __forceinline__ bool candidate_group(const DecodeArgs& a, const int c
 // top-6, 10 tokens 90 -> 85), and not in a small layer, whose waves take longer to find it (256 tokens 26.8 -> 29.4).
 __device__ __forceinline__ bool active_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[16]) {
     __shared__ uint32_t present[8];   // bit e: expert e has rows
-    if (a.pairs == a.k) return candidate_group(a, c, lane, g, tokens);   // one token: every pair another expert
     int v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) v[u] = u * 64 + lane < a.pairs ? a.topk_idx[u * 64 + lane] : 0x7fffffff;
@@ -290,17 +353,12 @@ __device__ __forceinline__ bool active_group(const DecodeArgs& a, const int c, c
 #pragma unroll
     for (int u = 0; u < 4; ++u)
         if (u * 64 < a.pairs) count_pairs(a, e, v[u], __ballot(v[u] == e), u * 64, lane, tokens, n, before);
-    __syncthreads();
+    wave_lds_order();
     g.expert = e;
     g.row0 = before;
     g.rows = min(n, 16);
     return true;
 }
-template <bool DENSE>
-__device__ __forceinline__ bool decode_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[16]) {
-    return DENSE ? active_group(a, c, lane, g, tokens) : candidate_group(a, c, lane, g, tokens);
-}
-
 // expert_offsets and inv_perm, by one wave (E <= 256, at most 64 * CHUNKS pairs): what the combine and moe_layer_views read.  perm
 // and row_token have no reader in these layers.
 template <int CHUNKS>
@@ -370,8 +428,9 @@ __device__ __forceinline__ TileDesc shared_tile(const DecodeArgs& a, const GemmA
 // the chip, two to a SIMD, about once, so that 16 add half a round (550 layers of 1 to 16 tokens: 16 columns take 1.05 and 1.03 of
 // the time of 32 there, 1.10 and 1.09 at most, elsewhere 0.98).
 template <int UB, bool NT>
-__device__ __forceinline__ void up_unit(const GemmArgs& up, const TileDesc& d, const int unit, const int lane, const int* tokens = nullptr) {
-    small_unit<true, UB, 1, 16 / UB, NT>(up, d, 0, unit * 16 * UB, lane, tokens);
+__device__ __forceinline__ void up_unit(const GemmArgs& up, const TileDesc& d, const int unit, const int lane, const int* tokens = nullptr,
+                                        const EarlyW<true, UB>* early = nullptr) {
+    small_unit<true, UB, 1, 16 / UB, NT>(up, d, 0, unit * 16 * UB, lane, tokens, early);
 }
 // Gate/up unit `unit` of all shared experts'.
 template <int UB, bool NT>
@@ -411,10 +470,15 @@ __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, con
     } else {
         b -= a.Ns * up.n_tiles;
     }
-    const int c = b / up.n_tiles;
+    const int c = b / up.n_tiles, unit = b - c * up.n_tiles;
     Group g;
-    if (!decode_group<NT>(a, c, lane, g, tokens)) return;
-    up_unit<UB, NT>(up, {g.expert, g.row0, g.rows, -1}, b - c * up.n_tiles, lane, tokens);
+    if (NT && a.pairs != a.k) {   // one token: every pair another expert
+        if (active_group(a, c, lane, g, tokens)) up_unit<UB, NT>(up, {g.expert, g.row0, g.rows, -1}, unit, lane, tokens);
+        return;
+    }
+    EarlyW<true, UB> w;
+    if (!candidate_group(a, c, lane, g, tokens, [&](const int e) { w.template ask<NT>(up, e, unit * 16 * UB, lane); })) return;
+    up_unit<UB, NT>(up, {g.expert, g.row0, g.rows, -1}, unit, lane, tokens, &w);
 }
 
 // The shared experts' down units (unless early), then the routed ones.
@@ -430,10 +494,15 @@ __global__ __launch_bounds__(64, 2) void decode_down_kernel(const GemmArgs down,
         }
         b -= down.n_tiles;
     }
-    const int c = b / down.n_tiles;
+    const int c = b / down.n_tiles, n0 = (b - c * down.n_tiles) * 16;
     Group g;
-    if (!decode_group<NT>(a, c, lane, g, tokens)) return;
-    small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, (b - c * down.n_tiles) * 16, lane);
+    if (NT && a.pairs != a.k) {
+        if (active_group(a, c, lane, g, tokens)) small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, n0, lane);
+        return;
+    }
+    EarlyW<false, 1> w;
+    if (!candidate_group(a, c, lane, g, tokens, [&](const int e) { w.template ask<NT>(down, e, n0, lane); })) return;
+    small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, n0, lane, nullptr, &w);
 }
 
 // More than 16 tokens: the same with `parts` waves for every 64 rows of a group.  Workgroup 0: expert_offsets and inv_perm; then all
@@ -450,24 +519,30 @@ __global__ __launch_bounds__(64, 2) void decode_wide_up_kernel(const GemmArgs up
     }
     const int b = blockIdx.x - 1, unit = b % up.n_tiles, q = b / up.n_tiles, part = q / groups, c = q - part * groups - a.Ns;
     if (c < 0) {
-        small_rows<true, 2, NT>(up, shared_tile(a, up, c + a.Ns), part, parts, unit * 32, lane);
+        small_block<true, 2, NT>(up, shared_tile(a, up, c + a.Ns), part * SMALL_ROWS, unit * 32, lane);
         return;
     }
     Group g;
-    if (!candidate_group(a, c, lane, g, tokens)) return;
-    small_rows<true, 2, NT>(up, {g.expert, g.row0, g.rows, -1}, part, parts, unit * 32, lane, tokens);
+    if (candidate_group(a, c, lane, g, tokens, [](int) {}))
+        small_block<true, 2, NT>(up, {g.expert, g.row0, g.rows, -1}, part * SMALL_ROWS, unit * 32, lane, tokens);
 }
 template <int NB, bool NT>
 __global__ __launch_bounds__(64, 2) void decode_wide_down_kernel(const GemmArgs down, const DecodeArgs a, const int parts, const int groups) {
     __shared__ int tokens[WIDE_TOKENS];
     const int lane = threadIdx.x, b = blockIdx.x, unit = b % down.n_tiles, q = b / down.n_tiles, part = q / groups, c = q - part * groups - (a.Ns > 0);
     if (c < 0) {
-        small_rows<false, NB, NT>(down, shared_tile(a, down, 0), part, parts, unit * 16 * NB, lane);
+        small_block<false, NB, NT>(down, shared_tile(a, down, 0), part * SMALL_ROWS, unit * 16 * NB, lane);
         return;
     }
     Group g;
-    if (!candidate_group(a, c, lane, g, tokens)) return;
-    small_rows<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, part, parts, unit * 16 * NB, lane);
+    if (part > 0) {
+        if (candidate_group(a, c, lane, g, tokens, [](int) {}))
+            small_block<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, part * SMALL_ROWS, unit * 16 * NB, lane);
+        return;
+    }
+    EarlyW<false, NB> w;
+    if (!candidate_group(a, c, lane, g, tokens, [&](const int e) { w.template ask<NT>(down, e, unit * 16 * NB, lane); })) return;
+    small_block<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, unit * 16 * NB, lane, nullptr, &w);
 }
 
 }  // namespace
