@@ -131,7 +131,11 @@ RouteGemm route_gemm_config(const moe_shape& s) {
         else below = n;
     }
     r.splits = pick ? pick : below;
-    r.tm = (int64_t)r.splits * ((s.T + 255) / 256) >= 512 ? 256 : 128;
+    // 64 tokens while that leaves no CU more than one tile (64 experts: two), else 128: a tile is bound by what its CU loads, the
+    // gate matrix for every tile and x once (stage time, 64 / 128 / 256 tokens, us: 64 experts, 3001 tokens 13.2 / 15.0 / 17.4, 16384
+    // tokens 29.9 / 28.6 / 27.2, 32768: 53.3 / 51.4 / 54.0; 160 experts, 2000: 24.9 / 28.4 / 38.6, 4000: 26.9 / 30.1 / 40.1, 8000:
+    // 43.0 / 35.5 / 45.1, 32768: 140.7 / 119.6 / 116.0).
+    r.tm = (int64_t)r.splits * ((s.T + 63) / 64) <= (r.ep <= 64 ? 512 : 256) ? 64 : 128;
     return r;
 }
 
@@ -344,10 +348,6 @@ moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     a.N = rg.ep;
     a.T = s.T;
     a.nseg_shared = 1;
-    a.n_tiles = (rg.ep + 255) / 256;
-    a.max_mtiles = rg.splits * ((s.T + rg.tm - 1) / rg.tm);
-    a.group_m = 8;
-    a.small_tiles = 1;
     a.out_fp32 = 3;
     a.lda_bytes = s.H * 2;
     a.kt_w = s.H / 32;
@@ -356,14 +356,12 @@ moe_status run_route(moe_ctx* c, const moe_shape& s, const void* x, const void* 
     a.t_pad = (s.T + 15) & ~15;
     a.kt_a = 0;
     a.tail_splits = 1;
-    GemmConfig cfg = c->gemm;
-    cfg.waves = 4;
-    cfg.wave_rows = 2;
-    // One wave per 16 tokens x 16 experts x K piece up to 1536 of them (stage time with cold weights: 64 experts, 1
-    // token 15.6 -> 11.7 us, 256: 19.4 -> 12.4, 1024 (1024 waves): 21.0 -> 16.6, 2048: 22.8 -> 22.4; 160 experts, 1 token
-    // 29.9 -> 17.4, 512 (1280 waves): 37.7 -> 28.2, 1024: 38.6 -> 39.4); beyond, x is re-read too often.  Same bits.
-    if ((int64_t)((s.T + 15) / 16) * (rg.ep / 16) * rg.splits <= 1536) HIP_TRY(c, launch_route_small(a, st));
-    else HIP_TRY(c, launch_ffn_gemm(false, a, cfg, st));
+    // One wave per 16 tokens x 16 experts x K piece up to 512 of them per 64 experts (stage time with cold x: 64 experts, 256 tokens
+    // 9.7 us against 10.6 by tiles, 512 (512 waves): 10.7, 10.5, 1000: 13.3, 11.1; 160 experts, 512 tokens (1280 waves): 21.2, 23.6,
+    // 700: 28.1, 23.8; 20 experts, 2000 tokens (1000 waves): 13.2, 9.9); beyond, x is re-read too often.  Same bits.
+    const int64_t waves = (int64_t)((s.T + 15) / 16) * (rg.ep / 16) * rg.splits;
+    if (waves <= 1536 && waves <= 512 * ((rg.ep + 63) / 64)) HIP_TRY(c, launch_route_small(a, st));
+    else HIP_TRY(c, launch_route_gemm(a, st));
     if (partial_only) return MOE_OK;
     HIP_TRY(c, launch_route_topk(s, (const float*)(ws + L.rt_logits), rg.splits, rg.ep, bias, idx, w, logits, st));
     return MOE_OK;

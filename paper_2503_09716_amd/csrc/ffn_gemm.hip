@@ -15,7 +15,7 @@
 // unless a tiled copy exists.
 //
 // Tile routine (one workgroup = NW wavefronts in a WM x WN grid):
-//   * macro tile: BM rows of X (32, 64, ... 384) x 256 rows of W (GEMM 1: 128 gate + 128
+//   * macro tile: BM rows of X (32, 64, ... 384) x 256 rows of W (router: its experts; GEMM 1: 128 gate + 128
 //     up rows, so the SiLU-gate product is formed in registers); K advances in sub-tiles of 32.
 //     The tiles above 256 rows (4 waves side by side only) keep the accumulators of their last X blocks in VGPRs, the
 //     256 AGPRs being full: fewer bytes from L2 per FLOP, and other numbers of rounds to choose from (plan.h).
@@ -135,7 +135,7 @@ __device__ __forceinline__ u32x4 swap_rows16(const u32x2 a, const u32x2 b) {
 // the accumulator tied to an AGPR quad: left to itself the register allocator (all 256 AGPRs
 // hold accumulators) routes part of them through temporaries, two to four copies per MFMA.
 // Hazards the compiler would otherwise cover: the operands come from LDS reads it still
-// tracks (s_waitcnt); an accumulator is re-used only a full sub-tile (>= 8 MFMAs) later; the
+// tracks (s_waitcnt); an accumulator is re-used only a full sub-tile (>= 4 MFMAs, 64 cycles) later; the
 // epilogue waits mfma_drain() before it reads accumulators.
 __device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const bf16x8& b) {
 #if defined(__gfx950__)
@@ -174,18 +174,19 @@ __device__ __forceinline__ void ring_sync() {
 // other tiles share): 8x7B, 32 rows per expert gate/up 335 -> 319 us, down 184 -> 168, 100 rows 377 -> 365, 203 -> 193;
 // 160 experts, 2000 tokens gate/up 1105 -> 1050.  Where two tiles share a panel it costs as much (eight experts of
 // 250 rows, down 266 -> 287), and above 128 rows it gains 1-3 %, less than a second copy of the variants costs.
-template <int NW, int WM, int TI, bool GATED, bool UNIFORM = false, bool ONCE = false>
+// WR: rows of W per macro tile.
+template <int NW, int WM, int TI, bool GATED, bool UNIFORM = false, bool ONCE = false, int WR = WROWS>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, const int n_tile, char* lds) {
     constexpr int WN = NW / WM;
-    constexpr int TJ = 8 / WN;               // 32-row W blocks per wave
+    constexpr int TJ = WR / 32 / WN;         // 32-row W blocks per wave
     constexpr int BM = WM * TI * 32;
     constexpr int NLX = (BM / 16 + NW - 1) / NW;   // X wave-loads (16 rows x 64 B) per wave per stage
     constexpr int NQX = NLX * NW;                  // X wave-loads per stage (region padded to a multiple of NW)
     constexpr int XBYTES = NQX * 1024;
-    constexpr int NL = NLX + (WROWS / 16) / NW;    // all wave-loads per wave per stage
+    constexpr int NL = NLX + (WR / 16) / NW;    // all wave-loads per wave per stage
     constexpr int RING_STRIDE = NL * NW * 1024;    // bytes per ring stage
     static_assert(NS * RING_STRIDE <= MAX_LDS, "ring does not fit");
-    constexpr int BN = GATED ? 128 : 256;    // output columns per macro tile
+    constexpr int BN = GATED ? 128 : WR;    // output columns per macro tile
     constexpr int W_AUX = ONCE ? 2 : 0;      // cache policy of the W loads: 2 = non-temporal
     constexpr int TJH = TJ / 2;              // GATED: 32-row gate blocks per wave (= up blocks per wave)
     // The MFMA works on 16-row blocks (v_mfma_f32_16x16x32_bf16: one instruction spans a whole
@@ -543,22 +544,7 @@ __device__ __forceinline__ int tile_order(const int wg, const int total, const i
 // group) and X panels (same m) in L2.  (Runs of a fixed length that cross group boundaries
 // measured 5-12 % faster than runs fitted to each group.)  Entries past n_run are tail tiles
 // of different groups: they are walked along n, which shares the X panel.
-template <bool UNIFORM = false>
 __device__ __forceinline__ bool pick_tile(const GemmArgs& p, const bool gated, TileDesc& d, int& n_tile, bool& once, bool& full) {
-    once = full = false;
-    if (UNIFORM) {
-        // Router GEMM: every K-split s covers all T rows in tiles of uniform_tm rows; nothing to look up.
-        const int L = blockIdx.x;
-        const int mt = L / p.n_tiles;
-        n_tile = L - mt * p.n_tiles;
-        if (mt >= p.uniform_per * p.uniform_splits) return false;
-        const int s = mt / p.uniform_per, m = mt - s * p.uniform_per;
-        d.group = s;
-        d.row0 = m * p.uniform_tm;
-        d.nrows = min(p.uniform_tm, p.T - d.row0);
-        d.srow = -1 - s;
-        return true;
-    }
     const int count = gated ? p.plan->n_gate_up : p.plan->n_down;
     const int n_run = gated ? p.plan->n_run_up : p.plan->n_run_down;
     // Only whole rounds of 256 REAL tiles are dealt to the XCDs in runs of 32, stretches of 64 in runs of 8 (the grid is an upper
@@ -593,19 +579,19 @@ __device__ __forceinline__ bool pick_tile(const GemmArgs& p, const bool gated, T
 }
 
 // 4 wavefronts (one per SIMD, up to 512 registers each), wave grid WM x 4/WM.
-template <int WM, bool GATED, bool UNIFORM = false>
+template <int WM, bool GATED>
 __global__ __launch_bounds__(256, 1) void ffn_gemm_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     TileDesc d;
     int n_tile;
     bool once, full;
-    if (!pick_tile<UNIFORM>(p, GATED, d, n_tile, once, full)) return;
+    if (!pick_tile(p, GATED, d, n_tile, once, full)) return;
     // 32-row blocks that hold real rows; 9 or 10: a tall tile (the plan kernel makes them for this wave grid only)
     const int blocks = d.nrows > 256 ? (d.nrows + 31) >> 5 : (p.small_tiles && !full ? (d.nrows + 31) >> 5 : 8);
     if (WM == 2) {
-        if (blocks > 4) gemm_tile<4, 2, 4, GATED, UNIFORM>(p, d, n_tile, lds);
-        else if (blocks > 2) gemm_tile<4, 2, 2, GATED, UNIFORM>(p, d, n_tile, lds);
-        else gemm_tile<4, 2, 1, GATED, UNIFORM>(p, d, n_tile, lds);
+        if (blocks > 4) gemm_tile<4, 2, 4, GATED>(p, d, n_tile, lds);
+        else if (blocks > 2) gemm_tile<4, 2, 2, GATED>(p, d, n_tile, lds);
+        else gemm_tile<4, 2, 1, GATED>(p, d, n_tile, lds);
     } else {
         if (blocks > 11) gemm_tile<4, 1, 12, GATED>(p, d, n_tile, lds);
         else if (blocks > 10) gemm_tile<4, 1, 11, GATED>(p, d, n_tile, lds);
@@ -626,6 +612,22 @@ __global__ __launch_bounds__(256, 1) void ffn_gemm_kernel(const GemmArgs p) {
         else if (blocks > 1) gemm_tile<4, 1, 2, GATED>(p, d, n_tile, lds);
         else gemm_tile<4, 1, 1, GATED>(p, d, n_tile, lds);
     }
+}
+
+// Router GEMM: every K-split s covers all T rows in tiles of 64 * TI rows and all (64 * TJ) experts; nothing to look up.  What a
+// CU loads bounds it, so the tile has no more rows of the gate matrix than there are experts (in blocks of 64; all
+// 256 rows of the FFN's tile before: 64 experts, 3001 tokens 17.2 -> 13.2 us, 16384 35.5 -> 28.6; 160 experts, 2000 tokens 29.9 -> 24.9).
+template <int TI, int TJ>
+__global__ __launch_bounds__(256, 2) void route_gemm_kernel(const GemmArgs p) {
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int mt = blockIdx.x, s = mt / p.uniform_per, m = mt - s * p.uniform_per;
+    if (s >= p.uniform_splits) return;
+    TileDesc d;
+    d.group = s;
+    d.row0 = m * 64 * TI;
+    d.nrows = min(64 * TI, p.T - d.row0);
+    d.srow = -1 - s;
+    gemm_tile<4, 2, TI, false, true, false, 64 * TJ>(p, d, 0, lds);
 }
 
 // 8 wavefronts (two per SIMD, up to 256 registers each), wave grid WM x 8/WM: while one wave
@@ -697,7 +699,14 @@ hipError_t ffn_gemm_init() {
     if (e != hipSuccess) return e;
     SET_LDS((ffn_gemm_kernel<2, true>))
     SET_LDS((ffn_gemm_kernel<2, false>))
-    SET_LDS((ffn_gemm_kernel<2, false, true>))
+    SET_LDS((route_gemm_kernel<1, 1>))
+    SET_LDS((route_gemm_kernel<1, 2>))
+    SET_LDS((route_gemm_kernel<1, 3>))
+    SET_LDS((route_gemm_kernel<1, 4>))
+    SET_LDS((route_gemm_kernel<2, 1>))
+    SET_LDS((route_gemm_kernel<2, 2>))
+    SET_LDS((route_gemm_kernel<2, 3>))
+    SET_LDS((route_gemm_kernel<2, 4>))
     SET_LDS((ffn_gemm_kernel<1, true>))
     SET_LDS((ffn_gemm_kernel<1, false>))
     SET_LDS((ffn_gemm_kernel8<2, true>))
@@ -713,13 +722,30 @@ hipError_t launch_ffn_plan(const PlanArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+hipError_t launch_route_gemm(const GemmArgs& a, hipStream_t st) {
+    const int cols = (a.N + 63) / 64;   // 64-expert blocks (E <= 256)
+    const dim3 grid((unsigned)(a.uniform_per * a.uniform_splits));
+    const unsigned lds = NS * (a.uniform_tm + 64 * cols) * ROWB;
+#define ROUTE(TI_, TJ_) hipLaunchKernelGGL((route_gemm_kernel<TI_, TJ_>), grid, dim3(256), lds, st, a)
+#define ROUTE_COLS(TI_)                    \
+    switch (cols) {                        \
+        case 1: ROUTE(TI_, 1); break;      \
+        case 2: ROUTE(TI_, 2); break;      \
+        case 3: ROUTE(TI_, 3); break;      \
+        case 4: ROUTE(TI_, 4); break;      \
+        default: return hipErrorInvalidValue; \
+    }
+    if (a.uniform_tm == 128) ROUTE_COLS(2)
+    else if (a.uniform_tm == 64) ROUTE_COLS(1)
+    else return hipErrorInvalidValue;
+#undef ROUTE_COLS
+#undef ROUTE
+    return hipGetLastError();
+}
+
 hipError_t launch_ffn_gemm(bool gated, const GemmArgs& a, const GemmConfig& cfg, hipStream_t st) {
     const dim3 grid((unsigned)(a.max_mtiles * a.n_tiles));
 #define LAUNCH(KERNEL, THREADS) hipLaunchKernelGGL((KERNEL), grid, dim3(THREADS), MAX_LDS, st, a)
-    if (a.w_uniform) {   // router GEMM: 4 waves as 2 x 2, tiles by arithmetic
-        LAUNCH((ffn_gemm_kernel<2, false, true>), 256);
-        return hipGetLastError();
-    }
     if (cfg.waves == 8) {
         if (cfg.wave_rows == 4) {
             if (gated) LAUNCH((ffn_gemm_kernel8<4, true>), 512);

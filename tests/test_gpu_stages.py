@@ -184,6 +184,30 @@ def test_route_small_batch_gives_a_large_batch_s_logits(moe, T, H, E, k):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("T,H,E", [(521, 2048, 64), (577, 1024, 100), (703, 1088, 160), (450, 1024, 256),       # tiles of 64 tokens
+                                   (8253, 1024, 33), (4200, 1024, 100), (4225, 1152, 161), (4161, 1024, 250),   # of 128
+                                   (9001, 64, 17), (9001, 128, 193)])                                        # two sub-tiles of K, four
+def test_route_tiles_hold_a_small_batch_s_logits(moe, T, H, E):
+    """The router's tiles of 64 and 128 tokens and 64 to 256 experts, on both sides of tile edges and at the ragged end:
+    the logits of the same tokens computed alone, bit for bit."""
+    cfg = scaled_config("C4", T=T, H=H, E=E, top_k=4, F=64, num_shared=0)
+    say("route tiles", T, H, E)
+    li = make_layer_inputs(cfg, device="cuda", experts=False)
+
+    def route(x):
+        shape = make_shape(x.shape[0], H, 64, E, 4, 0, False)
+        idx = torch.empty((x.shape[0], 4), dtype=torch.int32, device="cuda")
+        w = torch.empty((x.shape[0], 4), dtype=torch.float32, device="cuda")
+        lg = torch.full((x.shape[0], E), float("nan"), dtype=torch.float32, device="cuda")
+        moe.route(shape, x, li.wg, None, idx, w, lg, moe.new_workspace(shape))
+        return idx, w, lg
+    whole = route(li.x)
+    for t0 in (0, 56, 120, 248, T - 70, T - 16):
+        part = route(li.x[t0:t0 + 16].contiguous())
+        for a, b in zip(whole, part):
+            assert torch.equal(a[t0:t0 + 16], b), t0
+
+
 def random_routing(rng, T, E, k, skew=None):
     """Distinct experts per token.  skew = 'one': expert 0 stays empty, every token goes to expert 1,
     and the top third of the expert ids is hit by a single token each (tiny groups)."""
