@@ -177,7 +177,7 @@ enum DecodeStep { DECODE_TOPK, DECODE_UP, DECODE_DOWN };
 hipError_t launch_decode(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, bool nt, hipStream_t st);
 // The same from topk_idx and topk_w on, for up to 256 tokens; n_tiles: units of 32 and of 16 * col_blocks columns.
 hipError_t launch_decode_wide(DecodeStep step, const GemmArgs& up, const GemmArgs& down, const DecodeArgs& a, int col_blocks, bool nt, hipStream_t st);
-// the router GEMM: tiles of a.uniform_tm (64, 128) tokens and all experts, K piece by K piece
+// the router GEMM: tiles of a.uniform_tm (64, 128) tokens, the experts in a.n_tiles parts, K piece by K piece
 hipError_t launch_route_gemm(const GemmArgs& a, hipStream_t st);
 hipError_t launch_route_small(const GemmArgs& a, hipStream_t st);   // the router GEMM, one wavefront per 16 tokens x 16 experts x K piece
 hipError_t ffn_gemm_init();  // one-time function attributes (dynamic LDS size)

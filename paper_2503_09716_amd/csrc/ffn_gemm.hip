@@ -614,20 +614,21 @@ __global__ __launch_bounds__(256, 1) void ffn_gemm_kernel(const GemmArgs p) {
     }
 }
 
-// Router GEMM: every K-split s covers all T rows in tiles of 64 * TI rows and all (64 * TJ) experts; nothing to look up.  What a
+// Router GEMM: every K-split s covers all T rows in tiles of 64 * TI rows and 64 * TJ experts (all of them, or
+// p.n_tiles tiles side by side); nothing to look up.  What a
 // CU loads bounds it, so the tile has no more rows of the gate matrix than there are experts (in blocks of 64; all
 // 256 rows of the FFN's tile before: 64 experts, 3001 tokens 17.2 -> 13.2 us, 16384 35.5 -> 28.6; 160 experts, 2000 tokens 29.9 -> 24.9).
 template <int TI, int TJ>
 __global__ __launch_bounds__(256, 2) void route_gemm_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const int mt = blockIdx.x, s = mt / p.uniform_per, m = mt - s * p.uniform_per;
+    const int mt = blockIdx.x / p.n_tiles, n = blockIdx.x - mt * p.n_tiles, s = mt / p.uniform_per, m = mt - s * p.uniform_per;
     if (s >= p.uniform_splits) return;
     TileDesc d;
     d.group = s;
     d.row0 = m * 64 * TI;
     d.nrows = min(64 * TI, p.T - d.row0);
     d.srow = -1 - s;
-    gemm_tile<4, 2, TI, false, true, false, 64 * TJ>(p, d, 0, lds);
+    gemm_tile<4, 2, TI, false, true, false, 64 * TJ>(p, d, n, lds);
 }
 
 // 8 wavefronts (two per SIMD, up to 256 registers each), wave grid WM x 8/WM: while one wave
@@ -723,8 +724,8 @@ hipError_t launch_ffn_plan(const PlanArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_route_gemm(const GemmArgs& a, hipStream_t st) {
-    const int cols = (a.N + 63) / 64;   // 64-expert blocks (E <= 256)
-    const dim3 grid((unsigned)(a.uniform_per * a.uniform_splits));
+    const int cols = ((a.N + 63) / 64 + a.n_tiles - 1) / a.n_tiles;   // 64-expert blocks per tile (E <= 256)
+    const dim3 grid((unsigned)(a.uniform_per * a.uniform_splits * a.n_tiles));
     const unsigned lds = NS * (a.uniform_tm + 64 * cols) * ROWB;
 #define ROUTE(TI_, TJ_) hipLaunchKernelGGL((route_gemm_kernel<TI_, TJ_>), grid, dim3(256), lds, st, a)
 #define ROUTE_COLS(TI_)                    \

@@ -185,6 +185,7 @@ def test_route_small_batch_gives_a_large_batch_s_logits(moe, T, H, E, k):
 
 
 @pytest.mark.parametrize("T,H,E", [(521, 2048, 64), (577, 1024, 100), (703, 1088, 160), (450, 1024, 256),       # tiles of 64 tokens
+                                   (4000, 1024, 160), (1025, 1024, 256),                                      # all experts, half of them
                                    (8253, 1024, 33), (4200, 1024, 100), (4225, 1152, 161), (4161, 1024, 250),   # of 128
                                    (9001, 64, 17), (9001, 128, 193)])                                        # two sub-tiles of K, four
 def test_route_tiles_hold_a_small_batch_s_logits(moe, T, H, E):
