@@ -397,7 +397,7 @@ int call_down_splits(const moe_ctx* c, const moe_shape& s) {
     return down_tail_splits(s);
 }
 
-// A down launch of short tails only is cut along K up to this many tiles (plan_lists).
+// A down launch of short tails only is cut along K up to this many tiles (plan_list).
 int split_room_tiles(const moe_shape& s) { return 149 - 79000 / s.F; }
 
 // Which of the two GEMMs of a small batch run one wavefront per 16 or 32 output columns (ffn_small.hip).
@@ -430,7 +430,7 @@ struct SmallRule {
 
 // The down GEMM of few groups of any height (up to 64 tokens a round of tiles, up to 256 tokens tiles for a quarter of
 // the CUs).  The tile routine then takes the longest tile's walk along K, 0.42 us a sub-tile (shared experts: all of
-// theirs; K pieces, where plan_lists cuts: a part, and 10 us), or the time to read W.  In ffn_small.hip every 64 rows of a group read W again and
+// theirs; K pieces, where plan_list cuts: a part, and 10 us), or the time to read W.  In ffn_small.hip every 64 rows of a group read W again and
 // every 16 or 32 columns X, together at about 10.5 TB/s, or a unit's walk along K takes longest, 0.14 to 0.26 us
 // a sub-tile by its height.  15 % covers what the estimates miss by (tile -> small, us: 4 experts of 4,
 // H = 4096, F = 3072: 16 tokens 29 -> 25, 64: 32 -> 32, 96: 33 -> 42, 256: 53 -> 81; 4 experts top-2 + 2 shared,
@@ -526,7 +526,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     if (sm.up) { tm_up = SMALL_TILE_ROWS; choose_up = 0; }
     if (sm.down) tm_down = SMALL_TILE_ROWS;
     // K pieces for short tails of the down GEMM: the device-side plan decides from the real tile
-    // counts whether to cut (plan_lists); here only what the shape alone rules out, which
+    // counts whether to cut (plan_list); here only what the shape alone rules out, which
     // spares the launch of the reduction.
     const int dsp = sm.down ? 1 : call_down_splits(c, s);
     if (s.T <= 256 && dsp == 1 && !c->gemm.tile_rows_down) tm_down = 128;   // the walk along K is long; not where short tails may be cut along K

@@ -653,7 +653,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel8(const GemmArgs p) {
 
 // The lists from expert_offsets in a launch of their own (staged calls, streamed passes, large batches; moe_layer
 // otherwise builds them in the permutation's last launch).
-__global__ __launch_bounds__(256) void ffn_plan_kernel(const PlanArgs p) { plan_lists(p, p.offsets); }
+__global__ __launch_bounds__(256) void ffn_plan_kernel(const PlanArgs p) { plan_list(p, blockIdx.x, p.offsets); }
 
 // y_perm[row0 + r, :] of split tail q = sum over its K pieces of the fp32 partials, added in
 // piece order (one thread per 4 columns, one workgroup per row): deterministic.
@@ -719,7 +719,7 @@ hipError_t ffn_gemm_init() {
 }
 
 hipError_t launch_ffn_plan(const PlanArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(ffn_plan_kernel, dim3(PLAN_LISTS), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

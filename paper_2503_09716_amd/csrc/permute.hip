@@ -138,17 +138,17 @@ __device__ __forceinline__ int block_exclusive(const int v, int (&wave_sum)[4]) 
     return base + incl - v;
 }
 
-// The work of one extra workgroup of the two kernels below: the m-tile lists of the grouped GEMMs,
-// which need nothing but the experts' totals, next to the placement instead of in a launch of their
+// The work of each of the two extra workgroups of the two kernels below: an m-tile list of the grouped GEMMs,
+// which needs nothing but the experts' totals, next to the placement instead of in a launch of their
 // own after it (4 us of every small batch).
-__device__ __forceinline__ void plan_from_totals(const PlanArgs& plan, const int E, const int total, int (&offs)[MAX_E + 1],
+__device__ __forceinline__ void plan_from_totals(const PlanArgs& plan, const int which, const int E, const int total, int (&offs)[MAX_E + 1],
                                                  int (&wave_sum)[4]) {
     const int tid = threadIdx.x;
     const int excl = block_exclusive(total, wave_sum);
     if (tid < E) offs[tid] = excl;
     if (tid == E - 1) offs[E] = excl + total;
     __syncthreads();
-    plan_lists(plan, (const int*)offs);
+    plan_list(plan, which, (const int*)offs);
 }
 
 // Common tail of the two kernels below.  Thread e < E comes in with its expert's pair count over
@@ -230,8 +230,8 @@ __global__ __launch_bounds__(256) void permute_index_fused_kernel(const int32_t*
 #pragma unroll
         for (int w = 0; w < 4; ++w) { total += hist[w][0][tid]; before += hist[w][1][tid]; }
     }
-    if (chunk == nchunks) {   // the extra workgroup
-        plan_from_totals(plan, E, total, cur, wave_sum);
+    if (chunk >= nchunks) {   // the extra workgroups
+        plan_from_totals(plan, chunk - nchunks, E, total, cur, wave_sum);
         return;
     }
     scan_and_place_chunk(idx, T, k, E, total, before, mask, cur, wave_sum, offsets, perm, inv_perm, row_token);
@@ -271,8 +271,8 @@ __global__ __launch_bounds__(256) void permute_place_scan_kernel(const int32_t* 
     }
     __syncthreads();
     const int total = tid < E ? sum[0][tid] : 0, before = tid < E ? sum[1][tid] : 0;
-    if (chunk == nchunks) {   // the extra workgroup
-        plan_from_totals(plan, E, total, cur, wave_sum);
+    if (chunk >= nchunks) {   // the extra workgroups
+        plan_from_totals(plan, chunk - nchunks, E, total, cur, wave_sum);
         return;
     }
     scan_and_place_chunk(idx, T, k, E, total, before, mask, cur, wave_sum, offsets, perm, inv_perm, row_token);
@@ -330,7 +330,7 @@ hipError_t launch_permute_index(const moe_shape& s, const int32_t* idx, int32_t*
                                 hipStream_t st) {
     const int nchunks = permute_chunks(s);
     const PlanArgs pa = plan ? *plan : PlanArgs{};
-    const dim3 grid(nchunks + (plan ? 1 : 0)), block(256);
+    const dim3 grid(nchunks + (plan ? PLAN_LISTS : 0)), block(256);
     if (planned) *planned = plan != nullptr;
     if ((int64_t)s.T * s.top_k <= FUSED_MAX_PAIRS) {
         hipLaunchKernelGGL(permute_index_fused_kernel, grid, block, 0, st, idx, s.T, s.top_k, s.E, offsets, perm, inv_perm,

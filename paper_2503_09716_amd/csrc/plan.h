@@ -153,7 +153,7 @@ __device__ __forceinline__ float list_cost(const ListSum& s, const int choose, c
     return fmaxf(rounds * mean, (float)s.longest);
 }
 
-// Builds the two m-tile lists (gate/up GEMM with tiles of up to tm_up rows, down GEMM with tm_down)
+// Builds an m-tile list (gate/up GEMM with tiles of up to tm_up rows, down GEMM with tm_down)
 // from expert_offsets.  Group order: shared expert 0, routed experts, shared experts 1.. (the down
 // GEMM takes the first two parts only: shared experts are concatenated along K there).
 // cut_group says how a group's rows become tiles.  A tail higher than
@@ -164,13 +164,14 @@ __device__ __forceinline__ float list_cost(const ListSum& s, const int choose, c
 // sorted by falling height, ties in group order, so a launch with few rounds ends on its
 // smallest work items and its other tiles all take the same time (CUs that share operand
 // panels in L2 stay in step).  n_run_* = number of entries listed in group order.
-// One workgroup of 256 threads; `offsets`: E + 1 prefix sums in global memory or LDS.
+// One workgroup of 256 threads to a list (which: 0 gate/up, 1 down), side by side: the lists need nothing of each other, and
+// both in one workgroup held up the launch around them.  `offsets`: E + 1 prefix sums in global memory or LDS.
+constexpr int PLAN_LISTS = 2;
 template <class Offsets>
-__device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offsets) {
+__device__ __forceinline__ void plan_list(const PlanArgs& p, const int which, const Offsets offsets) {
     __shared__ int wsum[4][3];
     __shared__ int group_rows[256];
-    __shared__ float cap_cost[2][PLAN_CAPS];
-    __shared__ ListSum half_sum[2][2][PLAN_CAPS];
+    __shared__ float cap_cost[PLAN_CAPS];
     const int tid = threadIdx.x;
     const int E = p.E, Ns = p.Ns;
     // group order: g = 0 -> shared 0 (if any), then routed 0..E-1, then shared 1..Ns-1
@@ -187,156 +188,146 @@ __device__ __forceinline__ void plan_lists(const PlanArgs& p, const Offsets offs
         // a streamed pass covers routed experts [e_lo, e_hi) and, if shared_on, the shared experts
         if (group < E ? (group < p.e_lo || group >= p.e_hi) : !p.shared_on) rows = 0;
     }
-    int tm_of[2] = {p.tm_up, p.tm_down};
+    int tm = which == 0 ? p.tm_up : p.tm_down;
+    const int choose = which == 0 ? p.choose_up : p.choose_down;
     // Routed groups that are one tile under every candidate cap leave nothing to choose, and the shared experts by themselves are
     // not worth the 5 us that it takes (small launches: p.low_shared; 64 experts + 2 shared, 1500 tokens: the plan 12.8 us
     // with the choice and 9.1 without, the layer 350 and 347; 160 + 2, 3000 tokens: 15.6 and 9.4, 408 and 404).
     const int lowest = p.choose_up % 2 || p.choose_down % 2 ? 128 : 256;   // lowest cap: 2 has none below 256 rows
-    if ((p.choose_up || p.choose_down) && __syncthreads_or(group < E && rows > lowest)) {
+    if (choose && __syncthreads_or(group < E && rows > lowest)) {
         group_rows[tid] = rows;
         __syncthreads();
-        // waves 0 and 1 take half of the groups each for the gate/up list, 2 and 3 for the down list; eight lanes to a cap
-        const int which = tid >> 7, c = (tid & 63) >> 3, choose = which == 0 ? p.choose_up : p.choose_down;
+        const int c = tid >> 5;   // 32 lanes to a cap
         const int groups = which == 0 ? ngroups : (Ns > 0 ? E + 1 : E), nseg0 = which == 1 && Ns > 1 ? Ns : 1;
         ListSum sum = {0, 0, 0, 0, 0.f};
-        if (plan_candidate(c, choose)) sum = list_sum(p, which, group_rows, groups, nseg0, plan_cap(c), choose, (tid >> 6 & 1) * 8 + (tid & 7), 16);
+        if (plan_candidate(c, choose)) sum = list_sum(p, which, group_rows, groups, nseg0, plan_cap(c), choose, tid & 31, 32);
 #pragma unroll
-        for (int d = 1; d < 8; d <<= 1)
+        for (int d = 1; d < 32; d <<= 1)
             sum = add_sums(sum, {__shfl_xor(sum.n, d, 64), __shfl_xor(sum.alone, d, 64), __shfl_xor(sum.beside, d, 64),
                                  __shfl_xor(sum.longest, d, 64), __shfl_xor(sum.sum, d, 64)});
-        if ((tid & 7) == 0) half_sum[which][tid >> 6 & 1][c] = sum;
+        if ((tid & 31) == 0) cap_cost[c] = list_cost(sum, choose, which == 0 ? p.nt_up : p.nt_down);
         __syncthreads();
-        if ((tid & 71) == 0) cap_cost[which][c] = list_cost(add_sums(half_sum[which][0][c], half_sum[which][1][c]), choose, which == 0 ? p.nt_up : p.nt_down);
-        __syncthreads();
-#pragma unroll
-        for (int which = 0; which < 2; ++which) {
-            const int choose = which == 0 ? p.choose_up : p.choose_down;
-            if (!choose) continue;
-            // 256 rows, or 320 where the host says so, unless another height is clearly cheaper
-            const int usual = choose == 2 && tm_of[which] == 320 ? 2 : 3;
-            float best = cap_cost[which][usual] * (usual == 2 ? 0.985f : (choose != 2 ? 0.97f : (which == 0 ? 0.96f : 0.95f)));
-            tm_of[which] = plan_cap(usual);
-            for (int c = 0; c < PLAN_CAPS; ++c)
-                if (plan_candidate(c, choose) && cap_cost[which][c] < best) { best = cap_cost[which][c]; tm_of[which] = plan_cap(c); }
-        }
+        // 256 rows, or 320 where the host says so, unless another height is clearly cheaper
+        const int usual = choose == 2 && tm == 320 ? 2 : 3;
+        float best = cap_cost[usual] * (usual == 2 ? 0.985f : (choose != 2 ? 0.97f : (which == 0 ? 0.96f : 0.95f)));
+        tm = plan_cap(usual);
+        for (int c = 0; c < PLAN_CAPS; ++c)
+            if (plan_candidate(c, choose) && cap_cost[c] < best) { best = cap_cost[c]; tm = plan_cap(c); }
     }
-    for (int which = 0; which < 2; ++which) {
-        const int tm = tm_of[which];
-        TileDesc* descs = which == 0 ? p.descs_up : p.descs_down;
-        const int tall = which == 0 ? p.tall_up : p.tall_down;
-        const int last = which == 0 ? ngroups - 1 : (Ns > 0 ? E : E - 1);  // last group of this list
-        const bool mine = tid <= last;
-        const bool tails_last = (which == 0 ? p.tails_last_up : p.tails_last_down) != 0;
-        const GroupCut cut = list_cut(p, which, group >= E, mine ? rows : 0, tm);
-        const int nfull = cut.nfull, tail = cut.tail, joined = cut.joined, h = cut.h;
-        const int blocks = (tail + 31) >> 5;   // 32-row blocks of the tail tile, 0 = none
-        // A tail higher than half a tile takes nearly as long as a full tile, so it stays with its
-        // group (keeps the group's W panels shared and the CUs in step); only a short tail is moved
-        // to the end of the list.
-        // (A shared expert's tail is not moved in a down list with K pieces: the pieces' partial
-        // sums are reduced into y_perm, while shared rows belong to y_shared.)
-        // (at most 128 rows: the K pieces' partial buffers hold SPLIT_TAIL_ROWS rows)
-        const bool moved = tails_last && blocks > 0 && !cut.even && p.small_tiles && blocks * 64 <= min(cut.cap, 2 * SPLIT_TAIL_ROWS) &&
-                           !(which == 1 && p.down_splits > 1 && group >= E);
-        // tall_* = 2: the tall tile keeps its place in the group (it shares the W panels its
-        // neighbours stream, which is the point when a group is only a few tiles).  tall_* = 1 and
-        // tails_last: a tall tile takes longer than its neighbours and in a long launch puts the
-        // CUs it runs on out of step for the rest of it, so it leaves the group order too: tall
-        // tiles come first after the run region, one entry each, never cut along K.
-        const bool tall_moved = tails_last && joined > 0 && tall == 1;
-        const int nrun = nfull - (tall_moved ? 1 : 0) + (blocks > 0 && !moved);   // tiles listed in group order
-        // Positions by prefix sums over the groups (at most 256, one per thread): tiles listed in
-        // group order; tall tiles moved behind them; moved short tails, counted per height in
-        // 32-row blocks (1..4), three 10-bit counters to a word.
-        int base = nrun;
-        int k2 = (tall_moved ? 1 : 0) | (moved && blocks == 1 ? 1 << 10 : 0) | (moved && blocks == 2 ? 1 << 20 : 0);
-        int k3 = (moved && blocks == 3 ? 1 : 0) | (moved && blocks == 4 ? 1 << 10 : 0);
-        int tot[3];
-        block_scan3(base, k2, k3, tot, wsum, tid);
-        const int n_run_s = tot[0], n_tall_s = tot[1] & 1023;
-        const int cnt[5] = {0, (tot[1] >> 10) & 1023, (tot[1] >> 20) & 1023, tot[2] & 1023, (tot[2] >> 10) & 1023};
-        const int pre[5] = {0, (k2 >> 10) & 1023, (k2 >> 20) & 1023, k3 & 1023, (k3 >> 10) & 1023};
-        const int tails = cnt[1] + cnt[2] + cnt[3] + cnt[4];
-        // Down list with K pieces: only the moved tails of at most p.split_max_blocks 32-row blocks are
-        // cut (p.down_splits list entries each); the higher ones, which come first, stay whole.
-        // Whether to cut at all is decided here, where the tile counts are known.  Pieces make a
-        // launch faster in two cases only (measured on the Mixtral-shaped layer from 64 to 16384
-        // tokens): when EVERY tile of the launch is a short tail (a few tokens per expert) and the
-        // launch is bound by the walk along K, 0.42 us a sub-tile, and not by reading W at 5.8 TB/s and the 7 us of the
-        // second launch: F / 32 * 0.42 > tiles * 512 F / 5.8e6 + 7, that is tiles <= 149 - 79000 / F =
-        // p.split_room_tiles (whole -> cut, us: H = 2240, F = 7808, 63 tiles 97 -> 53; H = 4096, F = 14336, 128 tiles
-        // 190 -> 162; H = 1216, F = 3072, 105 tiles 48 -> 42; but H = 2048, F = 2048, 128 tiles 30 -> 35; H = 6144,
-        // F = 16384, 192 tiles 241 -> 279; H = 2560, F = 1664, 240 tiles 45 -> 72), and when the launch is
-        // many rounds of tiles long (the tails at its end then finish sooner: -2 % on the
-        // 16384-token, skewed workload).  In between, a launch of one to three rounds is as long
-        // as its full tiles whatever happens to the tails, and pieces only add a round and
-        // traffic (+6 ... +50 % measured).  p.split_rule_tiles: that many m-tiles or more count as
-        // "many rounds"; 0: always cut.
-        int n_whole = tails;
-        bool cutting = which == 1 && p.down_splits > 1;
-        if (cutting) {
-            n_whole = 0;
-            for (int b = p.split_max_blocks + 1; b <= 4; ++b) n_whole += cnt[b];
-            const int others = n_run_s + n_tall_s + n_whole;
-            cutting = p.split_rule_tiles == 0 || (others == 0 && tails * p.nt_down <= p.split_room_tiles) || others + tails - n_whole >= p.split_rule_tiles;
-            if (!cutting) n_whole = tails;
+    TileDesc* descs = which == 0 ? p.descs_up : p.descs_down;
+    const int tall = which == 0 ? p.tall_up : p.tall_down;
+    const int last = which == 0 ? ngroups - 1 : (Ns > 0 ? E : E - 1);  // last group of this list
+    const bool mine = tid <= last;
+    const bool tails_last = (which == 0 ? p.tails_last_up : p.tails_last_down) != 0;
+    const GroupCut cut = list_cut(p, which, group >= E, mine ? rows : 0, tm);
+    const int nfull = cut.nfull, tail = cut.tail, joined = cut.joined, h = cut.h;
+    const int blocks = (tail + 31) >> 5;   // 32-row blocks of the tail tile, 0 = none
+    // A tail higher than half a tile takes nearly as long as a full tile, so it stays with its
+    // group (keeps the group's W panels shared and the CUs in step); only a short tail is moved
+    // to the end of the list.
+    // (A shared expert's tail is not moved in a down list with K pieces: the pieces' partial
+    // sums are reduced into y_perm, while shared rows belong to y_shared.)
+    // (at most 128 rows: the K pieces' partial buffers hold SPLIT_TAIL_ROWS rows)
+    const bool moved = tails_last && blocks > 0 && !cut.even && p.small_tiles && blocks * 64 <= min(cut.cap, 2 * SPLIT_TAIL_ROWS) &&
+                       !(which == 1 && p.down_splits > 1 && group >= E);
+    // tall_* = 2: the tall tile keeps its place in the group (it shares the W panels its
+    // neighbours stream, which is the point when a group is only a few tiles).  tall_* = 1 and
+    // tails_last: a tall tile takes longer than its neighbours and in a long launch puts the
+    // CUs it runs on out of step for the rest of it, so it leaves the group order too: tall
+    // tiles come first after the run region, one entry each, never cut along K.
+    const bool tall_moved = tails_last && joined > 0 && tall == 1;
+    const int nrun = nfull - (tall_moved ? 1 : 0) + (blocks > 0 && !moved);   // tiles listed in group order
+    // Positions by prefix sums over the groups (at most 256, one per thread): tiles listed in
+    // group order; tall tiles moved behind them; moved short tails, counted per height in
+    // 32-row blocks (1..4), three 10-bit counters to a word.
+    int base = nrun;
+    int k2 = (tall_moved ? 1 : 0) | (moved && blocks == 1 ? 1 << 10 : 0) | (moved && blocks == 2 ? 1 << 20 : 0);
+    int k3 = (moved && blocks == 3 ? 1 : 0) | (moved && blocks == 4 ? 1 << 10 : 0);
+    int tot[3];
+    block_scan3(base, k2, k3, tot, wsum, tid);
+    const int n_run_s = tot[0], n_tall_s = tot[1] & 1023;
+    const int cnt[5] = {0, (tot[1] >> 10) & 1023, (tot[1] >> 20) & 1023, tot[2] & 1023, (tot[2] >> 10) & 1023};
+    const int pre[5] = {0, (k2 >> 10) & 1023, (k2 >> 20) & 1023, k3 & 1023, (k3 >> 10) & 1023};
+    const int tails = cnt[1] + cnt[2] + cnt[3] + cnt[4];
+    // Down list with K pieces: only the moved tails of at most p.split_max_blocks 32-row blocks are
+    // cut (p.down_splits list entries each); the higher ones, which come first, stay whole.
+    // Whether to cut at all is decided here, where the tile counts are known.  Pieces make a
+    // launch faster in two cases only (measured on the Mixtral-shaped layer from 64 to 16384
+    // tokens): when EVERY tile of the launch is a short tail (a few tokens per expert) and the
+    // launch is bound by the walk along K, 0.42 us a sub-tile, and not by reading W at 5.8 TB/s and the 7 us of the
+    // second launch: F / 32 * 0.42 > tiles * 512 F / 5.8e6 + 7, that is tiles <= 149 - 79000 / F =
+    // p.split_room_tiles (whole -> cut, us: H = 2240, F = 7808, 63 tiles 97 -> 53; H = 4096, F = 14336, 128 tiles
+    // 190 -> 162; H = 1216, F = 3072, 105 tiles 48 -> 42; but H = 2048, F = 2048, 128 tiles 30 -> 35; H = 6144,
+    // F = 16384, 192 tiles 241 -> 279; H = 2560, F = 1664, 240 tiles 45 -> 72), and when the launch is
+    // many rounds of tiles long (the tails at its end then finish sooner: -2 % on the
+    // 16384-token, skewed workload).  In between, a launch of one to three rounds is as long
+    // as its full tiles whatever happens to the tails, and pieces only add a round and
+    // traffic (+6 ... +50 % measured).  p.split_rule_tiles: that many m-tiles or more count as
+    // "many rounds"; 0: always cut.
+    int n_whole = tails;
+    bool cutting = which == 1 && p.down_splits > 1;
+    if (cutting) {
+        n_whole = 0;
+        for (int b = p.split_max_blocks + 1; b <= 4; ++b) n_whole += cnt[b];
+        const int others = n_run_s + n_tall_s + n_whole;
+        cutting = p.split_rule_tiles == 0 || (others == 0 && tails * p.nt_down <= p.split_room_tiles) || others + tails - n_whole >= p.split_rule_tiles;
+        if (!cutting) n_whole = tails;
+    }
+    const int n_cut = tails - n_whole;
+    if (tid == 0) {
+        const int total = n_run_s + n_tall_s + n_whole + n_cut * (cutting ? p.down_splits : 1);
+        // Tiles per XCD run (tile_order): 32, or 8 in a launch of a few rounds next to shared experts.
+        // Theirs are the first and longest tiles of the list; in runs of 32 a few rounds of them
+        // land on two or three XCDs, which then finish last (two shared experts next to 64 routed
+        // ones, down GEMM: 1000 tokens 129 -> 95 us, 3001 tokens 174 -> 149 us).
+        const int run = !p.xcd_remap ? 0 : (Ns > 0 && total * (which == 0 ? p.nt_up : p.nt_down) <= 10 * 256 ? 8 : 32);
+        if (which == 0) { p.plan->n_gate_up = total; p.plan->n_run_up = n_run_s; p.plan->xcd_run_up = run; }
+        else { p.plan->n_down = total; p.plan->n_run_down = n_run_s; p.plan->n_split_tails = n_cut; p.plan->xcd_run_down = run; }
+    }
+    if (mine) {
+        TileDesc d;
+        d.group = group;
+        d.srow = srow;
+        const int once = p.mark_once && nfull + (blocks > 0) == 1 ? TILE_ONCE : 0;
+        const int nlisted = nfull - (tall_moved ? 1 : 0);   // full tiles listed in group order
+        // The rest of a group of four tiles and more keeps the full tiles' pace: a variant of 160 to 224 rows would put
+        // its CUs out of step with those that share its panels (8x7B, 4782 tokens = 4.7 tiles per expert: +0.7 %).
+        const int full = nfull >= 3 && blocks > 4 && blocks < 8 ? TILE_FULL : 0;
+        for (int i = 0; i < nrun; ++i) {
+            // entry nlisted (if any) is a tail that stays with its group; it starts after all full tiles
+            const int at = i < nlisted ? i : nfull;
+            d.row0 = row_begin + at * h;
+            d.nrows = (min(h, rows - at * h) + ((at == nfull - 1 && !tall_moved) ? joined : 0)) | once | (at == nfull ? full : 0);
+            descs[base + i] = d;
         }
-        const int n_cut = tails - n_whole;
-        if (tid == 0) {
-            const int total = n_run_s + n_tall_s + n_whole + n_cut * (cutting ? p.down_splits : 1);
-            // Tiles per XCD run (tile_order): 32, or 8 in a launch of a few rounds next to shared experts.
-            // Theirs are the first and longest tiles of the list; in runs of 32 a few rounds of them
-            // land on two or three XCDs, which then finish last (two shared experts next to 64 routed
-            // ones, down GEMM: 1000 tokens 129 -> 95 us, 3001 tokens 174 -> 149 us).
-            const int run = !p.xcd_remap ? 0 : (Ns > 0 && total * (which == 0 ? p.nt_up : p.nt_down) <= 10 * 256 ? 8 : 32);
-            if (which == 0) { p.plan->n_gate_up = total; p.plan->n_run_up = n_run_s; p.plan->xcd_run_up = run; }
-            else { p.plan->n_down = total; p.plan->n_run_down = n_run_s; p.plan->n_split_tails = n_cut; p.plan->xcd_run_down = run; }
+        if (tall_moved) {
+            const int before = k2 & 1023;   // tall tiles of the groups before this one
+            d.row0 = row_begin + (nfull - 1) * h;
+            d.nrows = (h + joined) | once;
+            descs[n_run_s + before] = d;
         }
-        if (mine) {
-            TileDesc d;
-            d.group = group;
-            d.srow = srow;
-            const int once = p.mark_once && nfull + (blocks > 0) == 1 ? TILE_ONCE : 0;
-            const int nlisted = nfull - (tall_moved ? 1 : 0);   // full tiles listed in group order
-            // The rest of a group of four tiles and more keeps the full tiles' pace: a variant of 160 to 224 rows would put
-            // its CUs out of step with those that share its panels (8x7B, 4782 tokens = 4.7 tiles per expert: +0.7 %).
-            const int full = nfull >= 3 && blocks > 4 && blocks < 8 ? TILE_FULL : 0;
-            for (int i = 0; i < nrun; ++i) {
-                // entry nlisted (if any) is a tail that stays with its group; it starts after all full tiles
-                const int at = i < nlisted ? i : nfull;
-                d.row0 = row_begin + at * h;
-                d.nrows = (min(h, rows - at * h) + ((at == nfull - 1 && !tall_moved) ? joined : 0)) | once | (at == nfull ? full : 0);
-                descs[base + i] = d;
-            }
-            if (tall_moved) {
-                const int before = k2 & 1023;   // tall tiles of the groups before this one
-                d.row0 = row_begin + (nfull - 1) * h;
-                d.nrows = (h + joined) | once;
-                descs[n_run_s + before] = d;
-            }
-            if (moved) {
-                // tails that come before this one: the higher ones, and those as high of earlier groups
-                int rank = pre[blocks];
-                for (int b = blocks + 1; b <= 4; ++b) rank += cnt[b];
-                d.row0 = row_begin + nfull * h;
-                // in more than one round it runs after the group's other tiles, if there are any; within one, next to them, and
-                // the hint then costs as much as elsewhere (9 experts top-1 + 2 shared, H = 4544, F = 1920, 140 tokens:
-                // gate/up 98 us with it, 73 without)
-                const bool later = (n_run_s + n_tall_s) * (which == 0 ? p.nt_up : p.nt_down) > 256;
-                d.nrows = tail | (p.mark_once && (nfull == 0 || later) ? TILE_ONCE : 0);
-                const int tbase = n_run_s + n_tall_s;
-                if (cutting && blocks <= p.split_max_blocks) {
-                    // one entry per K piece; the pieces' partial sums are added up after the launch
-                    const int q = rank - n_whole;   // falling height: the whole ones rank first
-                    for (int sp = 0; sp < p.down_splits; ++sp) {
-                        d.srow = -2 - (q * p.down_splits + sp);
-                        descs[tbase + n_whole + q * p.down_splits + sp] = d;
-                    }
-                    p.split_tails[q].row0 = d.row0;
-                    p.split_tails[q].nrows = tail;
-                } else {
-                    descs[tbase + rank] = d;
+        if (moved) {
+            // tails that come before this one: the higher ones, and those as high of earlier groups
+            int rank = pre[blocks];
+            for (int b = blocks + 1; b <= 4; ++b) rank += cnt[b];
+            d.row0 = row_begin + nfull * h;
+            // in more than one round it runs after the group's other tiles, if there are any; within one, next to them, and
+            // the hint then costs as much as elsewhere (9 experts top-1 + 2 shared, H = 4544, F = 1920, 140 tokens:
+            // gate/up 98 us with it, 73 without)
+            const bool later = (n_run_s + n_tall_s) * (which == 0 ? p.nt_up : p.nt_down) > 256;
+            d.nrows = tail | (p.mark_once && (nfull == 0 || later) ? TILE_ONCE : 0);
+            const int tbase = n_run_s + n_tall_s;
+            if (cutting && blocks <= p.split_max_blocks) {
+                // one entry per K piece; the pieces' partial sums are added up after the launch
+                const int q = rank - n_whole;   // falling height: the whole ones rank first
+                for (int sp = 0; sp < p.down_splits; ++sp) {
+                    d.srow = -2 - (q * p.down_splits + sp);
+                    descs[tbase + n_whole + q * p.down_splits + sp] = d;
                 }
+                p.split_tails[q].row0 = d.row0;
+                p.split_tails[q].nrows = tail;
+            } else {
+                descs[tbase + rank] = d;
             }
         }
     }
