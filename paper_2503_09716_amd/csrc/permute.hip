@@ -22,6 +22,15 @@ namespace {
 
 constexpr int MAX_E = 256;
 
+// These kernels are chains of a few memory latencies, so every loop over global memory has BATCH loads in flight (stage time against
+// one load at a time, us: 64 experts top-6, 300 tokens 9.8 -> 7.5, 3001 tokens 14.1 -> 12.8, 16384: 17.5 -> 14.9).
+constexpr int BATCH = 8;
+// v = p[i0], p[i0 + step], ..., -1 from index n on
+__device__ __forceinline__ void load_batch(int (&v)[BATCH], const int32_t* __restrict__ p, const int i0, const int step, const int n) {
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) v[u] = i0 + u * step < n ? p[i0 + u * step] : -1;
+}
+
 __global__ __launch_bounds__(256) void permute_count_kernel(const int32_t* __restrict__ idx, int T, int k, int E,
                                                             int32_t* __restrict__ chunk_counts) {
     __shared__ int cnt[MAX_E];
@@ -32,9 +41,12 @@ __global__ __launch_bounds__(256) void permute_count_kernel(const int32_t* __res
     const int t1 = min(T, t0 + PERMUTE_CHUNK_TOKENS);
     const int n = (t1 - t0) * k;
     const int32_t* p = idx + (size_t)t0 * k;
-    for (int i = tid; i < n; i += 256) {
-        const int e = p[i];
-        if ((unsigned)e < (unsigned)E) atomicAdd(&cnt[e], 1);  // integer LDS counters: order-independent
+    for (int i = tid; i < n; i += 256 * BATCH) {
+        int v[BATCH];
+        load_batch(v, p, i, 256, n);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+            if ((unsigned)v[u] < (unsigned)E) atomicAdd(&cnt[v[u]], 1);  // integer LDS counters: order-independent
     }
     __syncthreads();
     for (int e = tid; e < E; e += 256) chunk_counts[(size_t)chunk * E + e] = cnt[e];
@@ -151,13 +163,19 @@ __device__ __forceinline__ void plan_from_totals(const PlanArgs& plan, const int
     plan_list(plan, which, (const int*)offs);
 }
 
-// Common tail of the two kernels below.  Thread e < E comes in with its expert's pair count over
+// The first experts of this thread's token of the chunk.
+__device__ __forceinline__ void load_picks(int (&v)[BATCH], const int32_t* __restrict__ idx, const int T, const int k, const int j0) {
+    const int t = blockIdx.x * PERMUTE_CHUNK_TOKENS + threadIdx.x;
+    load_batch(v, idx + (size_t)min(t, T - 1) * k, j0, 1, t < T ? k : 0);
+}
+
+// Common tail of the two kernels below.  v: load_picks from 0 on.  Thread e < E comes in with its expert's pair count over
 // all chunks (total) and over the chunks before this workgroup's (before); mask[][] is zero.
 // Exclusive prefix sum of the totals over the experts (-> expert_offsets, written by chunk 0, and
 // this chunk's cursors), then the placement of the chunk: wavefront w takes tokens 64w .. 64w+63,
 // the lane masks of all four wavefronts give a pair its rank.
 __device__ __forceinline__ void scan_and_place_chunk(const int32_t* __restrict__ idx, const int T, const int k, const int E,
-                                                     const int total, const int before,
+                                                     const int total, const int before, int (&v)[BATCH],
                                                      unsigned long long (&mask)[4][MAX_E], int (&cur)[MAX_E + 1],
                                                      int (&wave_sum)[4], int32_t* __restrict__ offsets,
                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
@@ -171,18 +189,19 @@ __device__ __forceinline__ void scan_and_place_chunk(const int32_t* __restrict__
     if (chunk == 0 && tid == E - 1) offsets[E] = excl + total;
     // placement of this chunk: wave w owns tokens 64w .. 64w+63
     const int t = chunk * PERMUTE_CHUNK_TOKENS + tid;
-    const bool valid = t < T;
-    const int32_t* mine = idx + (size_t)t * k;
     const unsigned long long bit = 1ull << lane, lt = bit - 1ull;
-    if (valid)
-        for (int j = 0; j < k; ++j) {
-            const int e = mine[j];
-            if ((unsigned)e < (unsigned)E) atomicOr(&mask[wave][e], bit);
-        }
+    for (int j0 = 0; j0 < k; j0 += BATCH) {
+        if (j0 > 0) load_picks(v, idx, T, k, j0);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+            if ((unsigned)v[u] < (unsigned)E) atomicOr(&mask[wave][v[u]], bit);
+    }
     __syncthreads();
-    if (valid)
-        for (int j = 0; j < k; ++j) {
-            const int e = mine[j];
+    for (int j0 = 0; j0 < k; j0 += BATCH) {
+        if (k > BATCH) load_picks(v, idx, T, k, j0);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int e = v[u], j = j0 + u;
             if ((unsigned)e >= (unsigned)E) continue;
             int slot = cur[e] + __popcll(mask[wave][e] & lt);
             for (int w = 0; w < wave; ++w) slot += __popcll(mask[w][e]);
@@ -190,17 +209,18 @@ __device__ __forceinline__ void scan_and_place_chunk(const int32_t* __restrict__
             inv_perm[(size_t)t * k + j] = slot;
             if (row_token) row_token[slot] = t;
         }
+    }
 }
 
-// All three steps in ONE launch, for small batches (T*k <= FUSED_MAX_PAIRS), where two extra
-// launches cost more than the work (256 tokens top-2: 6 us against 13; from a few thousand pairs
-// on, the three kernels win: every workgroup here reads the whole index array): every workgroup
+// All three steps in ONE launch, for small batches (T*k <= FUSED_MAX_PAIRS), where more launches cost more than
+// the work (stage time, two launches and one, us: 64 experts top-6, 700 tokens 11.6 and 8.6, 1300: 11.9 and 9.8, 2700
+// (16200 pairs): 13.1 and 14.0, every workgroup here reads the whole index array): every workgroup
 // (one per chunk, 4 wavefronts) histograms ALL pairs into wave-private LDS counters, once counting everything (-> expert_offsets, the same in
 // every workgroup) and once counting only the chunks before its own (-> its cursors), then
 // places its chunk: wavefront w takes tokens 64w .. 64w+63 of the chunk, the lane masks of all
 // four wavefronts give a pair its rank.  Same result as the three kernels above, bit for bit,
 // without their two extra launches.
-constexpr int FUSED_MAX_PAIRS = 1 << 12;
+constexpr int FUSED_MAX_PAIRS = 1 << 13;
 static_assert(PERMUTE_CHUNK_TOKENS == 256, "the fused kernel gives each of its 4 wavefronts 64 tokens of a chunk");
 
 __global__ __launch_bounds__(256) void permute_index_fused_kernel(const int32_t* __restrict__ idx, int T, int k, int E,
@@ -214,15 +234,20 @@ __global__ __launch_bounds__(256) void permute_index_fused_kernel(const int32_t*
     const int tid = threadIdx.x, wave = tid >> 6, chunk = blockIdx.x;
     for (int i = tid; i < 4 * 2 * MAX_E; i += 256) (&hist[0][0][0])[i] = 0;
     for (int i = tid; i < 4 * MAX_E; i += 256) (&mask[0][0])[i] = 0ull;
+    int picks[BATCH];
+    load_picks(picks, idx, T, k, 0);
     __syncthreads();
     const int n = T * k;
     const int mine_begin = chunk * PERMUTE_CHUNK_TOKENS * k;   // pairs of earlier chunks come before this index
-    for (int i = tid; i < n; i += 256) {
-        const int e = idx[i];
-        if ((unsigned)e < (unsigned)E) {
-            atomicAdd(&hist[wave][0][e], 1);                   // integer LDS counters: order-independent
-            if (i < mine_begin) atomicAdd(&hist[wave][1][e], 1);
-        }
+    for (int i = tid; i < n; i += 256 * BATCH) {
+        int v[BATCH];
+        load_batch(v, idx, i, 256, n);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+            if ((unsigned)v[u] < (unsigned)E) {
+                atomicAdd(&hist[wave][0][v[u]], 1);                   // integer LDS counters: order-independent
+                if (i + 256 * u < mine_begin) atomicAdd(&hist[wave][1][v[u]], 1);
+            }
     }
     __syncthreads();
     int total = 0, before = 0;
@@ -234,7 +259,7 @@ __global__ __launch_bounds__(256) void permute_index_fused_kernel(const int32_t*
         plan_from_totals(plan, chunk - nchunks, E, total, cur, wave_sum);
         return;
     }
-    scan_and_place_chunk(idx, T, k, E, total, before, mask, cur, wave_sum, offsets, perm, inv_perm, row_token);
+    scan_and_place_chunk(idx, T, k, E, total, before, picks, mask, cur, wave_sum, offsets, perm, inv_perm, row_token);
 }
 
 // Scan + placement in one launch, from the per-chunk histograms of permute_count_kernel: every
@@ -257,14 +282,22 @@ __global__ __launch_bounds__(256) void permute_place_scan_kernel(const int32_t* 
     const int tid = threadIdx.x, chunk = blockIdx.x;
     for (int i = tid; i < 2 * MAX_E; i += 256) (&sum[0][0])[i] = 0;
     for (int i = tid; i < 4 * MAX_E; i += 256) (&mask[0][0])[i] = 0ull;
+    int picks[BATCH];
+    load_picks(picks, idx, T, k, 0);
     __syncthreads();
     const int e = tid & (ep2 - 1), step = 256 / ep2;
     if (e < E) {
         int all = 0, before = 0;
-        for (int c = tid / ep2; c < nchunks; c += step) {
-            const int v = chunk_counts[(size_t)c * E + e];
-            all += v;
-            if (c < chunk) before += v;
+        constexpr int DEEP = 2 * BATCH;
+        for (int c0 = tid / ep2; c0 < nchunks; c0 += step * DEEP) {
+            int v[DEEP];
+#pragma unroll
+            for (int u = 0; u < DEEP; ++u) v[u] = c0 + u * step < nchunks ? chunk_counts[(size_t)(c0 + u * step) * E + e] : 0;
+#pragma unroll
+            for (int u = 0; u < DEEP; ++u) {
+                all += v[u];
+                if (c0 + u * step < chunk) before += v[u];
+            }
         }
         atomicAdd(&sum[0][e], all);                // integer LDS counters: order-independent
         atomicAdd(&sum[1][e], before);
@@ -275,7 +308,7 @@ __global__ __launch_bounds__(256) void permute_place_scan_kernel(const int32_t* 
         plan_from_totals(plan, chunk - nchunks, E, total, cur, wave_sum);
         return;
     }
-    scan_and_place_chunk(idx, T, k, E, total, before, mask, cur, wave_sum, offsets, perm, inv_perm, row_token);
+    scan_and_place_chunk(idx, T, k, E, total, before, picks, mask, cur, wave_sum, offsets, perm, inv_perm, row_token);
 }
 
 // One wavefront copies one row per pass; 16 bytes per lane, consecutive lanes consecutive addresses.
