@@ -751,7 +751,7 @@ moe_status layer_with_workspace(moe_ctx* c, const moe_shape* s, const void* x, c
         const RouteGemm rg = route_gemm_config(*s);
         const DecodeArgs d{rg.splits && few ? (const float*)(ws + make_layout(*s).rt_logits) : nullptr, bias, rg.splits, rg.ep, s->renormalize,
                            s->routed_scale, f.topk_idx, f.offsets, f.inv_perm, f.topk_w,
-                           s->T * s->top_k, s->top_k, s->E, s->num_shared};
+                           s->T * s->top_k, s->top_k, s->E, s->num_shared, 65536u / (uint32_t)s->top_k + 1};
         const GemmArgs up = gate_up_args(c, *s, fs, b), down = down_args(c, *s, fs, b, ws);
         auto launch = [&](const DecodeStep step) {
             return few ? launch_decode(step, up, down, d, fs.nt, hs) : launch_decode_wide(step, up, down, d, fs.sm.down_cols, fs.nt && fs.sm.once, hs);

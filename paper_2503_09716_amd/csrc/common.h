@@ -107,6 +107,7 @@ struct DecodeArgs {
     int32_t *topk_idx, *offsets, *inv_perm;
     float* topk_w;
     int32_t pairs, k, E, Ns;
+    uint32_t inv_k;            // 65536 / k + 1: p / k = p * inv_k >> 16 for the pairs p < 1024 (k <= 16)
 };
 
 struct GemmConfig {

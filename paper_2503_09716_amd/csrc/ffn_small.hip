@@ -274,13 +274,15 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
-// The pairs v (of index base + lane) that have expert e: their tokens and number, and the number of those with lower ones.
+// The pairs v (of index base + lane) that have expert e: their tokens (unless nullptr) and number, and the number of those with lower ones.
 template <int MAX>
-__device__ __forceinline__ void count_pairs(const DecodeArgs& a, const int e, const int v, const uint64_t eq, const int base, const int lane, int (&tokens)[MAX],
+__device__ __forceinline__ void count_pairs(const DecodeArgs& a, const int e, const int v, const uint64_t eq, const int base, const int lane, int* tokens,
                                             int& n, int& before) {
     if (eq) {
-        const int rank = n + __popcll(eq & ((1ull << lane) - 1));
-        if (v == e && rank < MAX) tokens[rank] = (base + lane) / a.k;
+        if (tokens) {
+            const int rank = n + __popcll(eq & ((1ull << lane) - 1));
+            if (v == e && rank < MAX) tokens[rank] = (int)((uint32_t)(base + lane) * a.inv_k >> 16);
+        }
         n += __popcll(eq);
     }
     before += __popcll(__ballot(v < e));
@@ -290,7 +292,7 @@ __device__ __forceinline__ void count_pairs(const DecodeArgs& a, const int e, co
 // MAX: tokens at most; the pairs come 64 * CHUNKS at a time, all loads of which are in flight together.
 // ask(expert) comes between the first loads of the pairs and their use (EarlyW).
 template <int MAX, class Ask>
-__device__ __forceinline__ bool candidate_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[MAX], Ask ask) {
+__device__ __forceinline__ bool candidate_group(const DecodeArgs& a, const int c, const int lane, Group& g, int* tokens, Ask ask) {
     constexpr int CHUNKS = MAX <= 16 ? 1 : 8;   // (few pairs: more code costs more than loads in turn, 1 token 0.8 us)
     const bool by_pair = a.pairs <= a.E;
     const int e = __builtin_amdgcn_readfirstlane(by_pair ? a.topk_idx[c] : c);
@@ -306,7 +308,7 @@ __device__ __forceinline__ bool candidate_group(const DecodeArgs& a, const int c
             if (base + u * 64 + lane >= a.pairs) v[u] = 0x7fffffff;
             const uint64_t eq = __ballot(v[u] == e);
             if (by_pair && n == 0 && eq && base + u * 64 + __builtin_ctzll(eq) != c) return false;
-            count_pairs(a, e, v[u], eq, base + u * 64, lane, tokens, n, before);
+            count_pairs<MAX>(a, e, v[u], eq, base + u * 64, lane, tokens, n, before);
         }
         return true;
     };
@@ -327,7 +329,7 @@ __device__ __forceinline__ bool candidate_group(const DecodeArgs& a, const int c
 // between the others (candidate_group) they leave some CUs a wave more than others, which counts where a launch fills the chip about once (8
 // experts top-2, H = 6144, F = 16384, 3 tokens that pick 4 experts: gate/up 262 -> 239 us, 4 tokens, 6 experts 374 -> 352, 64 experts
 // top-6, 10 tokens 90 -> 85), and not in a small layer, whose waves take longer to find it (256 tokens 26.8 -> 29.4).
-__device__ __forceinline__ bool active_group(const DecodeArgs& a, const int c, const int lane, Group& g, int (&tokens)[16]) {
+__device__ __forceinline__ bool active_group(const DecodeArgs& a, const int c, const int lane, Group& g, int* tokens) {
     __shared__ uint32_t present[8];   // bit e: expert e has rows
     int v[4];
 #pragma unroll
@@ -352,7 +354,7 @@ __device__ __forceinline__ bool active_group(const DecodeArgs& a, const int c, c
     int n = 0, before = 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-        if (u * 64 < a.pairs) count_pairs(a, e, v[u], __ballot(v[u] == e), u * 64, lane, tokens, n, before);
+        if (u * 64 < a.pairs) count_pairs<16>(a, e, v[u], __ballot(v[u] == e), u * 64, lane, tokens, n, before);
     wave_lds_order();
     g.expert = e;
     g.row0 = before;
@@ -477,14 +479,13 @@ __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, con
         return;
     }
     EarlyW<true, UB> w;
-    if (!candidate_group(a, c, lane, g, tokens, [&](const int e) { w.template ask<NT>(up, e, unit * 16 * UB, lane); })) return;
+    if (!candidate_group<16>(a, c, lane, g, tokens, [&](const int e) { w.template ask<NT>(up, e, unit * 16 * UB, lane); })) return;
     up_unit<UB, NT>(up, {g.expert, g.row0, g.rows, -1}, unit, lane, tokens, &w);
 }
 
 // The shared experts' down units (unless early), then the routed ones.
 template <bool NT>
 __global__ __launch_bounds__(64, 2) void decode_down_kernel(const GemmArgs down, const DecodeArgs a, const bool early) {
-    __shared__ int tokens[16];
     const int lane = threadIdx.x;
     int b = blockIdx.x;
     if (!early && a.Ns > 0) {
@@ -497,11 +498,11 @@ __global__ __launch_bounds__(64, 2) void decode_down_kernel(const GemmArgs down,
     const int c = b / down.n_tiles, n0 = (b - c * down.n_tiles) * 16;
     Group g;
     if (NT && a.pairs != a.k) {
-        if (active_group(a, c, lane, g, tokens)) small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, n0, lane);
+        if (active_group(a, c, lane, g, nullptr)) small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, n0, lane);
         return;
     }
     EarlyW<false, 1> w;
-    if (!candidate_group(a, c, lane, g, tokens, [&](const int e) { w.template ask<NT>(down, e, n0, lane); })) return;
+    if (!candidate_group<16>(a, c, lane, g, nullptr, [&](const int e) { w.template ask<NT>(down, e, n0, lane); })) return;
     small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, n0, lane, nullptr, &w);
 }
 
@@ -523,12 +524,11 @@ __global__ __launch_bounds__(64, 2) void decode_wide_up_kernel(const GemmArgs up
         return;
     }
     Group g;
-    if (candidate_group(a, c, lane, g, tokens, [](int) {}))
+    if (candidate_group<WIDE_TOKENS>(a, c, lane, g, tokens, [](int) {}))
         small_block<true, 2, NT>(up, {g.expert, g.row0, g.rows, -1}, part * SMALL_ROWS, unit * 32, lane, tokens);
 }
 template <int NB, bool NT>
 __global__ __launch_bounds__(64, 2) void decode_wide_down_kernel(const GemmArgs down, const DecodeArgs a, const int parts, const int groups) {
-    __shared__ int tokens[WIDE_TOKENS];
     const int lane = threadIdx.x, b = blockIdx.x, unit = b % down.n_tiles, q = b / down.n_tiles, part = q / groups, c = q - part * groups - (a.Ns > 0);
     if (c < 0) {
         small_block<false, NB, NT>(down, shared_tile(a, down, 0), part * SMALL_ROWS, unit * 16 * NB, lane);
@@ -536,12 +536,12 @@ __global__ __launch_bounds__(64, 2) void decode_wide_down_kernel(const GemmArgs 
     }
     Group g;
     if (part > 0) {
-        if (candidate_group(a, c, lane, g, tokens, [](int) {}))
+        if (candidate_group<WIDE_TOKENS>(a, c, lane, g, nullptr, [](int) {}))
             small_block<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, part * SMALL_ROWS, unit * 16 * NB, lane);
         return;
     }
     EarlyW<false, NB> w;
-    if (!candidate_group(a, c, lane, g, tokens, [&](const int e) { w.template ask<NT>(down, e, unit * 16 * NB, lane); })) return;
+    if (!candidate_group<WIDE_TOKENS>(a, c, lane, g, nullptr, [&](const int e) { w.template ask<NT>(down, e, unit * 16 * NB, lane); })) return;
     small_block<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, unit * 16 * NB, lane, nullptr, &w);
 }
 
