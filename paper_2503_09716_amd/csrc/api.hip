@@ -35,7 +35,7 @@ struct ProfRec {
 struct moe_ctx {
     int device = 0;
     char err[512] = {0};
-    GemmConfig gemm{1, 4, 0, 1, 1, 0, 0, -1, -1, 1, -1};
+    GemmConfig gemm{1, 4, 0, 1, 1, 0, 0, -1, -1, 1, -1, -1};
     bool y_fp32 = true;    // dtype of y_perm / y_shared in the staged calls
     int layer_y = -1;      // moe_layer's y_perm: 1 fp32, 0 bf16, -1 choose (its y_shared is always fp32)
     bool out_fp32 = false; // dtype of the layer output
@@ -489,7 +489,32 @@ struct FfnSetup {
     int mtiles_up, mtiles_down;   // m-tiles each list can have at most
     int group_m_up, group_m_down;
     bool nt;
+    bool combine_behind;   // the shared experts' down GEMM is a launch of its own that finishes the layer (launch_down_combine)
 };
+
+// dtype of moe_layer's y_perm.
+// y_perm in bf16 halves the down projection's stores and the combine's loads.  Its rounding
+// moves out[t] by at most sum_j w_j * 2^-8 * |y_j|.  Chosen when that is small against the
+// output: at least 4 routed terms next to shared experts of weight 1, which then carry most
+// of the output (measured at full size: no change of the error).  Without shared experts the
+// routed terms are the whole output and their rounding would use up most of the error bar
+// whatever their weights: fp32 there (measured on the Mixtral-shaped workloads against the
+// oracle, every token: bf16 y_perm would take 1 % off the step and move the worst element
+// from 1.04e-2 to 1.97e-2 x RMS on the 8x7B shape and to 2.1e-2, past the bar, on the 8x22B shape).
+// y_shared (weight 1) is always fp32.
+bool layer_y_fp32(const moe_ctx* c, const moe_shape& s) { return c->layer_y >= 0 ? c->layer_y != 0 : !(s.top_k >= 4 && s.num_shared > 0); }
+
+// Whether the shared experts' down GEMM is a launch of its own, with the combine behind each tile (launch_down_combine): y_shared is
+// then neither written nor read, and the rows of y_perm are read while other CUs multiply.  It pays where that launch's tiles of
+// 256 tokens come out in whole rounds of 256, or nearly; else the last round costs more than that (layer, us: 160 experts top-6 + 2 shared, F =
+// 1536, 32768 tokens = 10 rounds 10158 -> 9962, 18000 = 5.5 6014 -> 5970, 12000 = 3.7 4334 -> 4294, 6000 = 1.9 2651 -> 2639, but
+// 4000 = 1.25 2134 -> 2144; 64 experts, F = 1408, 16384 = 2 rounds 1960 -> 1933, 9000 = 1.1 1117 -> 1138, 12000 = 1.5 1440 -> 1444).
+bool combine_behind_wins(const moe_ctx* c, const moe_shape& s) {
+    if (s.num_shared == 0 || s.top_k < 4 || s.top_k > 8 || layer_y_fp32(c, s) || c->gemm.combine_behind == 0) return false;
+    if (c->gemm.combine_behind == 1) return true;
+    const int64_t tiles = (int64_t)((s.T + 255) / 256) * ((s.H + 255) / 256), rounds = (tiles + 255) / 256;
+    return tiles > 256 && rounds * 256 * 5 <= tiles * 6;
+}
 
 FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets, char* ws, const FfnPass& ps) {
     const Layout L = make_layout(s);
@@ -530,9 +555,10 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     // spares the launch of the reduction.
     const int dsp = sm.down ? 1 : call_down_splits(c, s);
     if (s.T <= 256 && dsp == 1 && !c->gemm.tile_rows_down) tm_down = 128;   // the walk along K is long; not where short tails may be cut along K
+    const bool combine_behind = ps.layer && tall_kernel && !sm.down && !c->gemm.tile_rows_down && combine_behind_wins(c, s);
     // Forced pieces: which rows are cut must not depend on what else a pass covers, so the heights are fixed.
     int choose_down = tm_down == 256 && !c->gemm.tile_rows_down && !(dsp > 1 && c->gemm.down_tail_splits == 2)
-                          ? may_choose_rows(s, nt_down, s.num_shared ? 1 : 0) : 0;
+                          ? may_choose_rows(s, nt_down, s.num_shared && !combine_behind ? 1 : 0) : 0;
     if (!tall_kernel && choose_down) choose_down = choose_down == 1 ? 3 : 0;
     // "many rounds" for the plan's rule: eight rounds of 256 tiles (at two to three rounds pieces
     // measured +6 %, at four to five +-0, at thirteen -2 %)
@@ -561,8 +587,10 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
                           (s.num_shared > 1 || low_tiles <= 256 || high_tiles > 256);
     FfnSetup f;
     f.nt = nt;
+    f.combine_behind = combine_behind;
     f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
-                      nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, nt, (low_up ? 1 : 0) | (low_down ? 2 : 0), ps.e_lo, ps.e_hi, ps.shared_on,
+                      nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, nt, (low_up ? 1 : 0) | (low_down ? 2 : 0), ps.e_lo, ps.e_hi,
+                      ps.shared_on ? (combine_behind ? 1 : 3) : 0,
                       dsp, 4, split_rule_tiles, split_room_tiles(s), tall, tall, (SplitTail*)(ws + L.split_tails), (PlanHeader*)(ws + L.plan),
                       (TileDesc*)(ws + L.descs_up), (TileDesc*)(ws + L.descs_down)};
     f.sm = sm;
@@ -645,8 +673,9 @@ GemmArgs down_args(const moe_ctx* c, const moe_shape& s, const FfnSetup& f, cons
     return a;
 }
 
-// planned: the m-tile lists are there already.
-moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool planned, const FfnBuffers& b, char* ws, hipStream_t st) {
+// planned: the m-tile lists are there already.  comb: with f.combine_behind, what the layer ends on.
+moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool planned, const FfnBuffers& b, char* ws, hipStream_t st,
+                   const CombineArgs* comb = nullptr) {
     const SmallRule& sm = f.sm;
     const int dsp = f.plan.down_splits;
     if (!planned) {
@@ -666,6 +695,7 @@ moe_status run_ffn(moe_ctx* c, const moe_shape& s, const FfnSetup& f, bool plann
         else HIP_TRY(c, launch_ffn_gemm(false, a, c->gemm, st));
         if (dsp > 1)
             HIP_TRY(c, launch_split_tail_reduce(s, f.plan.plan, f.plan.split_tails, (const float*)a.out_partial, dsp, b.y_perm, b.y_fp32, st));
+        if (f.combine_behind) HIP_TRY(c, launch_down_combine(s, a, *comb, c->out_fp32, st));
     }
     return MOE_OK;
 }
@@ -695,16 +725,7 @@ LayerFront layer_front(const moe_ctx* c, const moe_shape& s, char* w8) {
     f->y_shared = s.num_shared > 0 ? (void*)(w8 + L.y_shared) : nullptr;
     f->x_tiled = nullptr;
     f->planned = false;
-    // y_perm in bf16 halves the down projection's stores and the combine's loads.  Its rounding
-    // moves out[t] by at most sum_j w_j * 2^-8 * |y_j|.  Chosen when that is small against the
-    // output: at least 4 routed terms next to shared experts of weight 1, which then carry most
-    // of the output (measured at full size: no change of the error).  Without shared experts the
-    // routed terms are the whole output and their rounding would use up most of the error bar
-    // whatever their weights: fp32 there (measured on the Mixtral-shaped workloads against the
-    // oracle, every token: bf16 y_perm would take 1 % off the step and move the worst element
-    // from 1.04e-2 to 1.97e-2 x RMS on the 8x7B shape and to 2.1e-2, past the bar, on the 8x22B shape).
-    // y_shared (weight 1) is always fp32.
-    f->y32 = c->layer_y >= 0 ? c->layer_y != 0 : !(s.top_k >= 4 && s.num_shared > 0);
+    f->y32 = layer_y_fp32(c, s);
     return v;
 }
 
@@ -778,8 +799,9 @@ moe_status layer_with_workspace(moe_ctx* c, const moe_shape* s, const void* x, c
     // While stages are timed the lists are built by a launch of their own, so that it can be told from the permutation.
     if (moe_status st = run_front(c, *s, x, wg, bias, ws, hs, c->prof ? nullptr : &fs.plan, &f)) return st;
     const FfnBuffers b{nullptr, f.row_token, x, f.x_tiled, tab, f.h, f.y_perm, f.y_shared, f.y32, true};
-    if (moe_status st = run_ffn(c, *s, fs, f.planned, b, ws, hs)) return st;
-    {
+    const CombineArgs comb{(const char*)f.y_perm, f.inv_perm, f.topk_w, (char*)out};
+    if (moe_status st = run_ffn(c, *s, fs, f.planned, b, ws, hs, &comb)) return st;
+    if (!fs.combine_behind) {
         StageTimer tm(c, hs, MOE_STAGE_COMBINE);
         HIP_TRY(c, launch_combine(*s, f.y_perm, f.inv_perm, f.topk_w, f.y_shared, out, f.y32, true, c->out_fp32, hs));
     }
@@ -863,6 +885,7 @@ moe_status moe_set_option(moe_ctx* c, const char* key, int32_t v) {
     if (!strcmp(key, "down_tail_splits") && v >= 0 && v <= 2) { c->gemm.down_tail_splits = v; return MOE_OK; }
     if (!strcmp(key, "tails_last") && v >= -1 && v <= 1) { c->gemm.tails_last = v; return MOE_OK; }
     if (!strcmp(key, "tall_tiles") && v >= -1 && v <= 2) { c->gemm.tall_tiles = v; return MOE_OK; }
+    if (!strcmp(key, "combine_behind") && v >= -1 && v <= 1) { c->gemm.combine_behind = v; return MOE_OK; }
     if (!strcmp(key, "y_fp32") && (v == 0 || v == 1)) { c->y_fp32 = v != 0; return MOE_OK; }
     if (!strcmp(key, "layer_y_fp32") && v >= -1 && v <= 1) { c->layer_y = v; return MOE_OK; }
     if (!strcmp(key, "out_fp32") && (v == 0 || v == 1)) { c->out_fp32 = v != 0; return MOE_OK; }

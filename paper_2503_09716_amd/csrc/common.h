@@ -80,6 +80,15 @@ struct GemmArgs {
     const char* w_uniform;
     uint32_t w_uniform_stride;
     int32_t uniform_tm, uniform_per, uniform_splits;
+    int32_t shared_group;      // launch_down_combine (uniform_per tiles of 256 tokens): the first shared expert's group
+};
+
+// What the shared experts' down GEMM needs to finish the layer by itself (launch_down_combine).
+struct CombineArgs {
+    const char* y_perm;        // bf16
+    const int32_t* inv_perm;
+    const float* w;
+    char* out;
 };
 
 struct PlanArgs {
@@ -91,7 +100,7 @@ struct PlanArgs {
     int32_t tails_last_up, tails_last_down, small_tiles, xcd_remap;
     int32_t mark_once;                  // 1: TILE_ONCE marks are wanted
     int32_t low_shared;                 // shared experts' tiles are at most 128 rows: bit 0 gate/up, bit 1 down
-    int32_t e_lo, e_hi, shared_on;      // the lists cover routed experts [e_lo, e_hi) and, if shared_on, the shared experts
+    int32_t e_lo, e_hi, shared_on;      // the lists cover routed experts [e_lo, e_hi) and, by shared_on, the shared experts: bit 0 gate/up, bit 1 down
     int32_t down_splits, split_max_blocks, split_rule_tiles, split_room_tiles, tall_up, tall_down;
     SplitTail* split_tails;
     PlanHeader* plan;
@@ -124,6 +133,8 @@ struct GemmConfig {
                            // 1 where it pays (decided on the device from the tile counts), 2 always
     int tall_tiles;        // a tail of <= 64 rows joins its group's last full 256-row tile (4 waves x 1 wave row only):
                            // 0 off, 1 tall tiles after the run region, 2 in place, -1 choose
+    int combine_behind;    // moe_layer: the shared experts' down GEMM in a launch of its own that ends the layer (bf16 y_perm, k = 4 .. 8):
+                           // 0 off, 1 wherever it can be, -1 choose
 };
 
 // Upper bound on the number of m-tiles of `tm` rows for any routing outcome.
@@ -166,6 +177,8 @@ hipError_t launch_permute_gather_tiled(const moe_shape& s, const void* x, const 
 
 hipError_t launch_ffn_plan(const PlanArgs& a, hipStream_t st);
 // y_perm rows of the split tails = sum over pieces of the fp32 partials, in y_perm's dtype
+// the shared experts' down GEMM with the layer's combine behind it: out = sum_j w_j * y_perm rows + its own rows (k = 4 .. 8)
+hipError_t launch_down_combine(const moe_shape& s, const GemmArgs& a, const CombineArgs& c, bool out_fp32, hipStream_t st);
 hipError_t launch_split_tail_reduce(const moe_shape& s, const PlanHeader* plan, const SplitTail* tails, const float* partial,
                                     int splits, void* y_perm, bool y_fp32, hipStream_t st);
 hipError_t launch_ffn_gemm(bool gated, const GemmArgs& a, const GemmConfig& cfg, hipStream_t st);

@@ -66,6 +66,8 @@ constexpr int NS = 4;               // LDS ring depth (deeper rings for the low 
 constexpr int MAX_ROWS = PLAN_MAX_ROWS;   // tallest macro tile
 constexpr int MAX_STAGE = (MAX_ROWS + WROWS) * ROWB;     // 40 KiB
 constexpr int MAX_LDS = NS * MAX_STAGE;
+constexpr int COMBINE_LDS = 2 * 64 * (256 * 4 + 16) + 256 * 64;   // epilogue of launch_down_combine
+static_assert(COMBINE_LDS <= MAX_LDS, "LDS");
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
@@ -108,6 +110,14 @@ __device__ __forceinline__ void buffer_store_bf16(__amdgpu_buffer_rsrc_t rsrc, u
 #if defined(__gfx950__)
     const __bf16 b = (__bf16)v;
     __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, b), rsrc, voff, 0, 0);
+#endif
+}
+
+__device__ __forceinline__ u32x4 buffer_load_b128(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff) {
+#if defined(__gfx950__)
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, 0, 0);
+#else
+    return u32x4{};
 #endif
 }
 
@@ -174,9 +184,9 @@ __device__ __forceinline__ void ring_sync() {
 // other tiles share): 8x7B, 32 rows per expert gate/up 335 -> 319 us, down 184 -> 168, 100 rows 377 -> 365, 203 -> 193;
 // 160 experts, 2000 tokens gate/up 1105 -> 1050.  Where two tiles share a panel it costs as much (eight experts of
 // 250 rows, down 266 -> 287), and above 128 rows it gains 1-3 %, less than a second copy of the variants costs.
-// WR: rows of W per macro tile.
-template <int NW, int WM, int TI, bool GATED, bool UNIFORM = false, bool ONCE = false, int WR = WROWS>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, const int n_tile, char* lds) {
+// WR: rows of W per macro tile.  COMB, OF32: the layer's combine in the epilogue (launch_down_combine), of COMB rows a token.
+template <int NW, int WM, int TI, bool GATED, bool UNIFORM = false, bool ONCE = false, int WR = WROWS, int COMB = 0, bool OF32 = false>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, const int n_tile, char* lds, const CombineArgs* comb = nullptr) {
     constexpr int WN = NW / WM;
     constexpr int TJ = WR / 32 / WN;         // 32-row W blocks per wave
     constexpr int BM = WM * TI * 32;
@@ -292,6 +302,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
     const uint32_t offX = offL + (uint32_t)(bx0 * 32 * ROWB);
     const uint32_t offW = offL + (uint32_t)(XBYTES + bw0 * 32 * ROWB);
 
+    // COMB (k of the combine, 0 = none): this thread's token's rows of y_perm and weights, asked for here and used in the epilogue
+    uint32_t pick[COMB > 0 ? COMB : 1];
+    float weight[COMB > 0 ? COMB : 1];
+    if constexpr (COMB > 0) {
+        const size_t t = (size_t)(d.row0 + min((int)threadIdx.x, d.nrows - 1)) * COMB;
+#pragma unroll
+        for (int j = 0; j < COMB; ++j) {
+            pick[j] = (uint32_t)comb->inv_perm[t + j];
+            weight[j] = comb->w[t + j];
+        }
+    }
+
     f32x4 acc[WB][XB];
 #pragma unroll
     for (int j = 0; j < WB; ++j)
@@ -332,10 +354,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
                 const int j = HF * WBH + jj;
                 const bf16x8 w = HF == 0 ? wA[jj] : wB[jj];
                 if (i < XB_A) {
-                    if (GATED) mfma_16x16x32(acc[j][i], w, xf[i % XD]);
+                    if (GATED || COMB) mfma_16x16x32(acc[j][i], w, xf[i % XD]);
                     else mfma_16x16x32(acc[j][i], xf[i % XD], w);
                 } else {
-                    if (GATED) mfma_16x16x32_v(acc[j][i], w, xf[i % XD]);
+                    if (GATED || COMB) mfma_16x16x32_v(acc[j][i], w, xf[i % XD]);
                     else mfma_16x16x32_v(acc[j][i], xf[i % XD], w);
                 }
             }
@@ -433,6 +455,102 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
     // Accumulator block (j, i) is 16 x 16; a lane holds 4 registers: the block's MFMA-row-operand
     // index 4*(lane/16) + r and column-operand index lane%16.
     mfma_drain();
+    if constexpr (COMB > 0) {
+        static_assert(!GATED && NW == 4 && WM == 1 && BM <= 256 && COMB <= 8, "one row to a thread");
+        // The layer's last step: out[t] = sum_j w[t, j] * y_perm[inv_perm[t, j]] + this GEMM's row t, in combine_kernel's order.
+        // 64 rows of the tile at a time go through LDS, so that a wave reads 512 consecutive bytes of a row of y_perm: with
+        // the accumulators' own columns, 64 bytes of 16 rows to a load, the loads took twice as long (every row is
+        // another page).  W is the row operand as in GEMM 1 (a lane has 4 consecutive columns of a row).  The ring is free: every wave is
+        // past the last barrier.  LDS: two buffers of 64 rows, then the tokens' row offsets and weights.
+        typedef __attribute__((address_space(3))) u32x4* lds4_t;
+        constexpr int ROW = 256 * 4 + 16, BUF = 64 * ROW, META = 2 * BUF;
+        static_assert(META + BM * 64 <= COMBINE_LDS, "LDS");
+        const uint32_t rowbytes = (uint32_t)N * 2u;
+        if ((int)threadIdx.x < BM) {
+            u32x4 v[4] = {};
+#pragma unroll
+            for (int j = 0; j < COMB; ++j) {
+                v[j >> 2][j & 3] = pick[j] * rowbytes;
+                v[2 + (j >> 2)][j & 3] = __float_as_uint(weight[j]);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((q & 1) * 4 < COMB) *((lds4_t)(ring + META + threadIdx.x * 64) + q) = v[q];
+        }
+        ring_sync<63>();   // LDS only: nothing here waits for loads
+        constexpr uint32_t esz = OF32 ? 4 : 2;
+        constexpr int CHUNKS = BM / 64, STEPS = CHUNKS * 8, DEPTH = 3;   // a step: two rows of the wave's 16 (4 and 5 steps on their way: no change)
+        const __amdgpu_buffer_rsrc_t rs_y = uniform_rsrc(comb->y_perm);
+        const __amdgpu_buffer_rsrc_t rs_o = tile_rsrc(comb->out + (size_t)d.row0 * (size_t)N * esz, (uint32_t)d.nrows * (uint32_t)N * esz);
+        const int cols = (lane & 31) * 8, col = n0 + cols;
+        const bool col_ok = col < N;
+        const uint32_t ycol = (uint32_t)min(col, N - 8) * 2u;
+        auto row_of = [&](const int st) __attribute__((always_inline)) { return (st >> 3) * 64 + wave * 16 + (st & 7) * 2 + (lane >> 5); };
+        u32x4 y[DEPTH][COMB];
+        auto gather = [&](const int st) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q * 4 < COMB; ++q) {
+                const u32x4 at = *((lds4_t)(ring + META + row_of(st) * 64) + q);
+#pragma unroll
+                for (int j = q * 4; j < COMB && j < q * 4 + 4; ++j) y[st % DEPTH][j] = buffer_load_b128(rs_y, at[j & 3] + ycol);
+            }
+        };
+#pragma unroll
+        for (int st = 0; st < DEPTH - 1; ++st) gather(st);
+#pragma unroll
+        for (int ch = 0; ch < CHUNKS; ++ch) {
+            const lds_t buf = ring + (ch & 1) * BUF;
+#pragma unroll
+            for (int i = 4 * ch; i < 4 * ch + 4; ++i)
+#pragma unroll
+                for (int j = 0; j < WB; ++j) {
+                    u32x4 v;   // read here, not earlier (as in store_tile below)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        uint32_t a;
+                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(a) : "a"(acc[j][i][q]) : "memory");
+                        v[q] = a;
+                    }
+                    *(lds4_t)(buf + ((i & 3) * 16 + rl) * ROW + (bw0 * 32 + j * 16 + g * 4) * 4) = v;
+                }
+            // one barrier to a buffer: the next write into it comes after the barrier of the other one, and so after every wave's reads
+            ring_sync<63>();
+#pragma unroll
+            for (int st = ch * 8; st < ch * 8 + 8; ++st) {
+                if (st + DEPTH - 1 < STEPS) gather(st + DEPTH - 1);
+                __builtin_amdgcn_sched_barrier(0);
+                const int row = row_of(st);
+                float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int q = 0; q * 4 < COMB; ++q) {
+                    const u32x4 w = *((lds4_t)(ring + META + row * 64) + 2 + q);
+#pragma unroll
+                    for (int j = q * 4; j < COMB && j < q * 4 + 4; ++j)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const uint32_t v = y[st % DEPTH][j][e >> 1];
+                            sum[e] = fmaf(__uint_as_float(w[j & 3]), __uint_as_float(e & 1 ? v & 0xffff0000u : v << 16), sum[e]);
+                        }
+                }
+                const lds4_t own = (lds4_t)(buf + (row & 63) * ROW + cols * 4);
+                const u32x4 lo = own[0], hi = own[1];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { sum[e] += __uint_as_float(lo[e]); sum[4 + e] += __uint_as_float(hi[e]); }
+                const uint32_t at = col_ok ? ((uint32_t)row * (uint32_t)N + (uint32_t)col) * esz : 0xFFFFFFF0u;   // rows past the end are dropped, too
+                if (OF32) {
+                    buffer_store_b128(rs_o, at, u32x4{__float_as_uint(sum[0]), __float_as_uint(sum[1]), __float_as_uint(sum[2]), __float_as_uint(sum[3])});
+                    buffer_store_b128(rs_o, col_ok ? at + 16 : at, u32x4{__float_as_uint(sum[4]), __float_as_uint(sum[5]), __float_as_uint(sum[6]), __float_as_uint(sum[7])});
+                } else {
+                    bf16x8 o;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[e] = (__bf16)sum[e];
+                    buffer_store_b128(rs_o, at, __builtin_bit_cast(u32x4, o));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        return;
+    }
     char* out = shared ? p.out_shared : (tail_split ? p.out_partial : p.out_routed);
     const int orow_base = tail_split ? piece * SPLIT_TAIL_ROWS
                                      : (shared ? (GATED ? d.srow : 0) : split * p.split_rows) + d.row0;
@@ -631,6 +749,26 @@ __global__ __launch_bounds__(256, 2) void route_gemm_kernel(const GemmArgs p) {
     gemm_tile<4, 2, TI, false, true, false, 64 * TJ>(p, d, n, lds);
 }
 
+// The shared experts' down GEMM, all of them along K, with the combine behind it; tiles of 256 tokens by arithmetic, in the order of
+// pick_tile.  Bound by the matrix cores, and in the epilogue by the latency of rows of y_perm from memory.  Against the
+// tiles in the list, fp32 y_shared written and read, and combine_kernel: 160 experts top-6 + 2 shared, H = 5120, F = 1536, 32768 tokens, down
+// and combine 3856 -> 3652 us; 64 experts, H = 2048, F = 1408, 16384 tokens 763 -> 716.
+template <int K, bool OF32>
+__global__ __launch_bounds__(256, 1) void ffn_down_combine_kernel(const GemmArgs p, const CombineArgs c) {
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int L = tile_order(blockIdx.x, p.uniform_per * p.n_tiles, 32);
+    const int per_super = p.group_m * p.n_tiles, sr = L / per_super, rem = L - sr * per_super;
+    const int mt0 = sr * p.group_m, gm = min(p.group_m, p.uniform_per - mt0);
+    const int n_tile = rem / gm, mt = mt0 + (rem - n_tile * gm);
+    TileDesc d;
+    d.group = p.shared_group;
+    d.row0 = mt * 256;
+    d.nrows = min(256, p.T - d.row0);
+    d.srow = 0;
+    if (d.nrows > 128) gemm_tile<4, 1, 8, false, false, false, WROWS, K, OF32>(p, d, n_tile, lds, &c);
+    else gemm_tile<4, 1, 4, false, false, false, WROWS, K, OF32>(p, d, n_tile, lds, &c);
+}
+
 // 8 wavefronts (two per SIMD, up to 256 registers each), wave grid WM x 8/WM: while one wave
 // of a SIMD waits at the ring barrier or on LDS, the other keeps the matrix pipe fed.
 template <int WM, bool GATED>
@@ -710,6 +848,16 @@ hipError_t ffn_gemm_init() {
     SET_LDS((route_gemm_kernel<2, 4>))
     SET_LDS((ffn_gemm_kernel<1, true>))
     SET_LDS((ffn_gemm_kernel<1, false>))
+    SET_LDS((ffn_down_combine_kernel<4, false>))
+    SET_LDS((ffn_down_combine_kernel<4, true>))
+    SET_LDS((ffn_down_combine_kernel<5, false>))
+    SET_LDS((ffn_down_combine_kernel<5, true>))
+    SET_LDS((ffn_down_combine_kernel<6, false>))
+    SET_LDS((ffn_down_combine_kernel<6, true>))
+    SET_LDS((ffn_down_combine_kernel<7, false>))
+    SET_LDS((ffn_down_combine_kernel<7, true>))
+    SET_LDS((ffn_down_combine_kernel<8, false>))
+    SET_LDS((ffn_down_combine_kernel<8, true>))
     SET_LDS((ffn_gemm_kernel8<2, true>))
     SET_LDS((ffn_gemm_kernel8<2, false>))
     SET_LDS((ffn_gemm_kernel8<4, true>))
@@ -720,6 +868,31 @@ hipError_t ffn_gemm_init() {
 
 hipError_t launch_ffn_plan(const PlanArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(ffn_plan_kernel, dim3(PLAN_LISTS), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_down_combine(const moe_shape& s, const GemmArgs& args, const CombineArgs& c, bool out_fp32, hipStream_t st) {
+    GemmArgs a = args;
+    a.uniform_per = (s.T + 255) / 256;
+    a.group_m = 8;
+    a.shared_group = s.E;
+    a.n_tiles = (s.H + 255) / 256;
+    const dim3 grid((unsigned)(a.uniform_per * a.n_tiles));
+    constexpr unsigned lds = COMBINE_LDS > NS * (256 + WROWS) * ROWB ? COMBINE_LDS : NS * (256 + WROWS) * ROWB;
+#define DOWN_COMBINE(K_)                                                                                              \
+    case K_:                                                                                                          \
+        if (out_fp32) hipLaunchKernelGGL((ffn_down_combine_kernel<K_, true>), grid, dim3(256), lds, st, a, c);        \
+        else hipLaunchKernelGGL((ffn_down_combine_kernel<K_, false>), grid, dim3(256), lds, st, a, c);                \
+        break;
+    switch (s.top_k) {
+        DOWN_COMBINE(4)
+        DOWN_COMBINE(5)
+        DOWN_COMBINE(6)
+        DOWN_COMBINE(7)
+        DOWN_COMBINE(8)
+        default: return hipErrorInvalidValue;
+    }
+#undef DOWN_COMBINE
     return hipGetLastError();
 }
 

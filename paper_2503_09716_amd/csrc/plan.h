@@ -185,8 +185,8 @@ __device__ __forceinline__ void plan_list(const PlanArgs& p, const int which, co
             if (pos < E) { group = pos; row_begin = offsets[pos]; rows = offsets[pos + 1] - row_begin; srow = -1; }
             else { const int s = pos - E + 1; group = E + s; rows = p.T; row_begin = 0; srow = s * p.t_pad; }
         }
-        // a streamed pass covers routed experts [e_lo, e_hi) and, if shared_on, the shared experts
-        if (group < E ? (group < p.e_lo || group >= p.e_hi) : !p.shared_on) rows = 0;
+        // a streamed pass covers routed experts [e_lo, e_hi) and, by shared_on, the shared experts
+        if (group < E ? (group < p.e_lo || group >= p.e_hi) : !(p.shared_on >> which & 1)) rows = 0;
     }
     int tm = which == 0 ? p.tm_up : p.tm_down;
     const int choose = which == 0 ? p.choose_up : p.choose_down;
@@ -280,7 +280,7 @@ __device__ __forceinline__ void plan_list(const PlanArgs& p, const int which, co
         // Theirs are the first and longest tiles of the list; in runs of 32 a few rounds of them
         // land on two or three XCDs, which then finish last (two shared experts next to 64 routed
         // ones, down GEMM: 1000 tokens 129 -> 95 us, 3001 tokens 174 -> 149 us).
-        const int run = !p.xcd_remap ? 0 : (Ns > 0 && total * (which == 0 ? p.nt_up : p.nt_down) <= 10 * 256 ? 8 : 32);
+        const int run = !p.xcd_remap ? 0 : (Ns > 0 && (p.shared_on >> which & 1) && total * (which == 0 ? p.nt_up : p.nt_down) <= 10 * 256 ? 8 : 32);
         if (which == 0) { p.plan->n_gate_up = total; p.plan->n_run_up = n_run_s; p.plan->xcd_run_up = run; }
         else { p.plan->n_down = total; p.plan->n_run_down = n_run_s; p.plan->n_split_tails = n_cut; p.plan->xcd_run_down = run; }
     }

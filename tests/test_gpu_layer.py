@@ -302,6 +302,33 @@ def test_layer_at_the_4_gib_limit(moe):
         moe.layer(too_big, gl.x, gl.wg, gl.bias, gl.w1p, gl.w3p, gl.w2p, out, gl.ws, tables=gl.tables)
 
 
+@pytest.mark.parametrize("T,H,F,E,k,shared", [
+    (257, 320, 128, 20, 4, 1),      # a second tile of one token; the last n-tile is one wave's columns
+    (384, 256, 192, 17, 5, 2),      # a tail of exactly 128 rows (the lower variant)
+    (385, 512, 128, 24, 6, 2),      # of 129
+    (1111, 1088, 64, 33, 7, 3),     # two sub-tiles of K, three segments; columns of the last n-tile
+    (2600, 640, 320, 12, 8, 8)])    # more than one run of eight m-tiles
+def test_layer_with_the_combine_behind_the_down_gemm(moe, T, H, F, E, k, shared):
+    """The shared experts' down GEMM that ends the layer adds in the order of the combine launch: the same bits, fp32 and bf16."""
+    cfg = scaled_config("C4", T=T, H=H, F=F, E=E, top_k=k, num_shared=shared)
+    say("combine behind", cfg)
+    gl = P.GpuLayer(moe, make_layer_inputs(cfg, device="cuda"), host_weights=False)
+    got = {}
+    try:
+        for mode in (0, 1):
+            moe.set_option("combine_behind", mode)
+            moe.profile_enable(True)
+            moe.profile_read()
+            got[mode] = [gl.run_layer(fp32).clone() for fp32 in (True, False)]
+            torch.cuda.synchronize()
+            assert moe.profile_read()["combine"][1] == (0 if mode else 2)   # a launch of its own, or none
+    finally:
+        moe.profile_enable(False)
+        moe.set_option("combine_behind", -1)
+    for a, b in zip(got[0], got[1]):
+        assert torch.equal(a, b)
+
+
 STREAMED = [
     # name, overrides, experts per group, slots
     ("C2", dict(T=600, H=256, F=448), 1, 2),                    # one expert at a time, double buffer
