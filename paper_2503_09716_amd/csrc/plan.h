@@ -191,7 +191,7 @@ __device__ __forceinline__ void plan_list(const PlanArgs& p, const int which, co
     int tm = which == 0 ? p.tm_up : p.tm_down;
     const int choose = which == 0 ? p.choose_up : p.choose_down;
     // Routed groups that are one tile under every candidate cap leave nothing to choose, and the shared experts by themselves are
-    // not worth the 5 us that it takes (small launches: p.low_shared; 64 experts + 2 shared, 1500 tokens: the plan 12.8 us
+    // not worth the 3 us that it takes (small launches: p.low_shared; with one workgroup for both lists, 64 experts + 2 shared, 1500 tokens: the plan 12.8 us
     // with the choice and 9.1 without, the layer 350 and 347; 160 + 2, 3000 tokens: 15.6 and 9.4, 408 and 404).
     const int lowest = p.choose_up % 2 || p.choose_down % 2 ? 128 : 256;   // lowest cap: 2 has none below 256 rows
     if (choose && __syncthreads_or(group < E && rows > lowest)) {

@@ -225,7 +225,7 @@ def random_routing(rng, T, E, k, skew=None):
     return idx
 
 
-# One launch up to 4096 pairs, beyond that two (histogram; scan + placement), three when the table of histograms is large
+# One launch up to 8192 pairs, beyond that two (histogram; scan + placement), three when the table of histograms is large
 PERMUTE_CASES = [(256, 8, 2, None), (1000, 64, 6, None), (777, 160, 6, "one"), (1, 4, 1, None), (300, 5, 5, None),
                  (2049, 37, 3, None), (682, 256, 6, None), (683, 256, 6, None), (500, 160, 6, "one"), (12000, 37, 6, "one"),
                  (32768, 8, 2, None), (16384, 16, 4, None), (16385, 16, 4, None), (4099, 13, 3, "one"), (1025, 17, 4, None),
@@ -264,6 +264,15 @@ def test_permute(moe, T, E, k, skew):
     say("permute", T, E, k, skew)
     rng = np.random.default_rng(T * 7 + E)
     check_permute(moe, T, E, k, random_routing(rng, T, E, k, skew))
+
+
+@pytest.mark.parametrize("T,E,k,skew", [(4096, 8, 2, None), (2731, 37, 3, None), (1365, 64, 6, None), (1366, 64, 6, "one"),   # around 8192 pairs
+                                        (600, 40, 12, None), (512, 64, 16, None), (513, 64, 16, None), (900, 64, 9, None),     # k above a batch of 8
+                                        (5000, 33, 17, None), (257, 100, 64, None)])
+def test_permute_batched_loads(moe, T, E, k, skew):
+    """Both sides of the one-launch limit, and picks that take more than one batch of loads per token."""
+    say("permute", T, E, k, skew)
+    check_permute(moe, T, E, k, random_routing(np.random.default_rng(T * 7 + E), T, E, k, skew))
 
 
 @pytest.mark.parametrize("seed", range(FUZZ_SEEDS))
