@@ -536,10 +536,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const TileDesc d, c
                 const u32x4 lo = own[0], hi = own[1];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { sum[e] += __uint_as_float(lo[e]); sum[4 + e] += __uint_as_float(hi[e]); }
-                const uint32_t at = col_ok ? ((uint32_t)row * (uint32_t)N + (uint32_t)col) * esz : 0xFFFFFFF0u;   // rows past the end are dropped, too
+                // offsets of rows past the end (up to 127 * N * 4) may wrap, so the descriptor cannot be left to drop them
+                const bool ok = col_ok && row < d.nrows;
+                const uint32_t at = ok ? ((uint32_t)row * (uint32_t)N + (uint32_t)col) * esz : 0xFFFFFFF0u;
                 if (OF32) {
                     buffer_store_b128(rs_o, at, u32x4{__float_as_uint(sum[0]), __float_as_uint(sum[1]), __float_as_uint(sum[2]), __float_as_uint(sum[3])});
-                    buffer_store_b128(rs_o, col_ok ? at + 16 : at, u32x4{__float_as_uint(sum[4]), __float_as_uint(sum[5]), __float_as_uint(sum[6]), __float_as_uint(sum[7])});
+                    buffer_store_b128(rs_o, ok ? at + 16 : at, u32x4{__float_as_uint(sum[4]), __float_as_uint(sum[5]), __float_as_uint(sum[6]), __float_as_uint(sum[7])});
                 } else {
                     bf16x8 o;
 #pragma unroll

@@ -329,6 +329,43 @@ def test_layer_with_the_combine_behind_the_down_gemm(moe, T, H, F, E, k, shared)
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("H,fp32", [(8454720, True), (16909440, False)])
+def test_combine_behind_where_a_tile_s_padding_rows_pass_4_gib(moe, H, fp32):
+    """Eight tokens in a tile of 128 rows whose last row would lie 30464 bytes past 4 GiB of the output's rows: the rows past the end
+    stay unwritten there, too, by default (this shape takes that launch), and the output has the combine launch's bits."""
+    from paper_2503_09716_amd import make_shape
+    T, F, E, k, shared = 8, 64, 8, 4, 1
+    assert 127 * H * (4 if fp32 else 2) - 2 ** 32 == 30464
+    say("padding rows", H, fp32)
+    gen = torch.Generator(device="cuda").manual_seed(H)
+
+    def normal(n, std):
+        return torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    shape = make_shape(T, H, F, E, k, shared, False)
+    x, wg = normal((T, H), 1.0), normal((H, E), H ** -0.5)
+    w1, w3, w2 = normal(H * F, H ** -0.5), normal(H * F, H ** -0.5), normal(H * F, 0.1)   # one set of packed matrices for all experts
+    tables = moe.tables([w1] * (E + shared), [w3] * (E + shared), [w2] * (E + shared))
+    ws = moe.new_workspace(shape)
+    got = []
+    moe.set_option("out_fp32", int(fp32))
+    try:
+        for mode in (0, -1):
+            moe.set_option("combine_behind", mode)
+            out = torch.full((T, H), float("nan"), dtype=torch.float32 if fp32 else torch.bfloat16, device="cuda")
+            moe.profile_enable(True)
+            moe.profile_read()
+            moe.layer(shape, x, wg, None, None, None, None, out, ws, tables=tables)
+            torch.cuda.synchronize()
+            assert moe.profile_read()["combine"][1] == (0 if mode else 1)
+            got.append(out)
+    finally:
+        moe.profile_enable(False)
+        moe.set_option("combine_behind", -1)
+        moe.set_option("out_fp32", 0)
+    assert not torch.isnan(got[0]).any()
+    assert torch.equal(got[0], got[1])
+
+
 STREAMED = [
     # name, overrides, experts per group, slots
     ("C2", dict(T=600, H=256, F=448), 1, 2),                    # one expert at a time, double buffer
