@@ -29,6 +29,7 @@
  *    refers to the table that was current at capture: it stays valid until 8 further tables
  *    have been uploaded on the context (calls with other weight pointers; every expert group of
  *    moe_layer_streamed is one), so give graphs that are replayed for long a context of their own.
+ *    Of an expert that no token of the batch picks the matrices are not read; its pointer only must not be NULL.
  *  - Weight layout on the hot path is the PACKED one produced by moe_pack_weight from the
  *    logical [H,F] / [F,H] matrices (same number of bytes): the transposed matrix W[n][k]
  *    (k = contraction index) is cut into blocks of 16 rows x 32 k = 1 KiB, blocks ordered

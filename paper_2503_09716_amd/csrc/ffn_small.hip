@@ -53,8 +53,9 @@ struct Panel {
 };
 
 // The first sub-tiles of a unit's W, asked for before the unit's rows are known: their latency passes while the rows are looked up.
-// Down GEMM, us: 8 experts top-2, H = 512, F = 1024, 256 tokens 12.1 -> 11.0, 128 tokens 11.2 -> 9.9, 9 top-3, H = 896, F = 768, 166 tokens
-// 10.9 -> 10.0; layers of one token 35.0 -> 33.9 (64 experts, F = 1408), 116.7 -> 114.9 (8 experts, F = 14336).  Not in the gate/up GEMM
+// Only where the candidate is a pair's expert (no more pairs than experts), which has rows: the matrices of an expert without rows are
+// not touched, they need not be resident.
+// Layers of one token, us: 35.0 -> 33.9 (64 experts, F = 1408), 116.7 -> 114.9 (8 experts, F = 14336).  Not in the gate/up GEMM
 // of more than 16 tokens, whose registers are full (12.7 -> 13.2), nor where the expert has to be searched first (no change).
 constexpr int EARLY = 4;
 template <bool GATED, int NB>
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(64, 2) void route_small_kernel(const GemmArgs p) {
 
 // ---- layers of few pairs: up to 16 tokens, or up to 256 in small layers ---------------------------------------
 // What a wave needs to know of the routing - its expert's tokens and where their rows begin - it reads off topk_idx itself
-// (at most 1024 pairs, a vote per 64).  So no launch stands between the selection and the gate/up GEMM: expert_offsets and
+// (at most 1024 pairs, a vote per 64; in the down GEMM mostly off expert_offsets).  So no launch stands between the selection and the gate/up GEMM: expert_offsets and
 // inv_perm are written by one wave of that GEMM's launch.  Up to 16 tokens every group is one block of 16 rows, and with more
 // than 16 experts the shared ones can run ahead (launch_decode says where): their gate/up GEMM next to the top-k, whose
 // launch leaves the memory idle, and their down GEMM, the longest walk of all, next to the routed gate/up GEMM.  (The first
@@ -360,6 +361,18 @@ __device__ __forceinline__ bool active_group(const DecodeArgs& a, const int c, c
     g.row0 = before;
     g.rows = min(n, 16);
     return true;
+}
+// Down GEMM, more pairs than experts: expert c's rows off the offsets that decode_index wrote in the gate/up GEMM's launch.  They are there
+// after one load, so W is asked for once it is known that the expert has rows.  Layer against counting the pairs again behind an EarlyW of every
+// expert: H = 512, F = 1024, 8 experts, 128 tokens 20.4 -> 20.1 us, 256: 23.9 -> 23.6, 6 experts, H = 1280, F = 896, 48 tokens 20.9 -> 20.5; up to
+// 16 tokens 0.2 us more for the down GEMM (and 0.6 for the gate/up GEMM without EarlyW).
+__device__ __forceinline__ bool indexed_group(const GemmArgs& down, const DecodeArgs& a, const int c, Group& g) {
+    const int row0 = a.offsets[c], end = a.offsets[c + 1];
+    const bool there = down.w_a[c] != nullptr;   // always: puts the load of the matrix's address next to the two above
+    g.expert = c;
+    g.row0 = __builtin_amdgcn_readfirstlane(row0);
+    g.rows = __builtin_amdgcn_readfirstlane(end - row0);
+    return (g.rows > 0) & there;
 }
 // expert_offsets and inv_perm, by one wave (E <= 256, at most 64 * CHUNKS pairs): what the combine and moe_layer_views read.  perm
 // and row_token have no reader in these layers.
@@ -474,8 +487,9 @@ __global__ __launch_bounds__(64, 2) void decode_up_kernel(const GemmArgs up, con
     }
     const int c = b / up.n_tiles, unit = b - c * up.n_tiles;
     Group g;
-    if (NT && a.pairs != a.k) {   // one token: every pair another expert
-        if (active_group(a, c, lane, g, tokens)) up_unit<UB, NT>(up, {g.expert, g.row0, g.rows, -1}, unit, lane, tokens);
+    if (NT ? a.pairs != a.k : a.pairs > a.E) {   // one token: every pair another expert
+        if (NT ? active_group(a, c, lane, g, tokens) : candidate_group<16>(a, c, lane, g, tokens, [](int) {}))
+            up_unit<UB, NT>(up, {g.expert, g.row0, g.rows, -1}, unit, lane, tokens);
         return;
     }
     EarlyW<true, UB> w;
@@ -497,8 +511,8 @@ __global__ __launch_bounds__(64, 2) void decode_down_kernel(const GemmArgs down,
     }
     const int c = b / down.n_tiles, n0 = (b - c * down.n_tiles) * 16;
     Group g;
-    if (NT && a.pairs != a.k) {
-        if (active_group(a, c, lane, g, nullptr)) small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, n0, lane);
+    if (NT ? a.pairs != a.k : a.pairs > a.E) {
+        if (NT ? active_group(a, c, lane, g, nullptr) : indexed_group(down, a, c, g)) small_unit<false, 1, 1, 16, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, n0, lane);
         return;
     }
     EarlyW<false, 1> w;
@@ -535,14 +549,14 @@ __global__ __launch_bounds__(64, 2) void decode_wide_down_kernel(const GemmArgs 
         return;
     }
     Group g;
-    if (part > 0) {
-        if (candidate_group<WIDE_TOKENS>(a, c, lane, g, nullptr, [](int) {}))
+    if (a.pairs > a.E) {
+        if (indexed_group(down, a, c, g))
             small_block<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, part * SMALL_ROWS, unit * 16 * NB, lane);
         return;
     }
     EarlyW<false, NB> w;
     if (!candidate_group<WIDE_TOKENS>(a, c, lane, g, nullptr, [&](const int e) { w.template ask<NT>(down, e, unit * 16 * NB, lane); })) return;
-    small_block<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, 0, unit * 16 * NB, lane, nullptr, &w);
+    small_block<false, NB, NT>(down, {g.expert, g.row0, g.rows, -1}, part * SMALL_ROWS, unit * 16 * NB, lane, nullptr, &w);
 }
 
 }  // namespace

@@ -366,6 +366,49 @@ def test_combine_behind_where_a_tile_s_padding_rows_pass_4_gib(moe, H, fp32):
     assert torch.equal(got[0], got[1])
 
 
+@pytest.mark.parametrize("T,H,F,E,k", [
+    (16, 1024, 2048, 16, 2),      # launch_decode, more pairs than experts: gate/up and down
+    (64, 2048, 256, 32, 2),       # launch_decode_wide
+    (3, 1024, 1024, 24, 2),       # launch_decode by pairs
+    (900, 1024, 256, 16, 2)])     # tile lists
+def test_matrices_of_experts_without_rows_are_not_read(moe, T, H, F, E, k):
+    """Only two experts have rows.  The others' matrices lie in pinned host memory, which kernels can read, but over the host link: the
+    14 MB or more that a look at the first sub-tiles of each takes in the small layers are 250 us there (measured: layers of 33 and 44 us
+    took 350 and 317), so the layer must be nearly as fast as with all matrices in device memory."""
+    import ctypes as C
+    from paper_2503_09716_amd import make_shape
+    say("experts without rows", T, H, F, E, k)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    shape = make_shape(T, H, F, E, k, 0, True)
+    x = torch.empty((T, H), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    wg = torch.empty((H, E), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=gen)
+    picked = (3, E - 2)
+    bias = torch.zeros(E, device="cuda")
+    bias[list(picked)] = 50.0
+    device = torch.empty((3, E, H * F), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=gen)
+    host = torch.full((3, E, H * F), float("nan"), dtype=torch.bfloat16, pin_memory=True)
+    ws = moe.new_workspace(shape)
+    got, us = [], []
+    for rowless in (device, host):
+        tables = [(C.c_void_p * E)(*[(device if e in picked else rowless)[i, e].data_ptr() for e in range(E)]) for i in range(3)]
+        out = torch.empty((T, H), dtype=torch.bfloat16, device="cuda")
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            moe.layer(shape, x, wg, bias, None, None, None, out, ws, tables=tables)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 1e3)
+        got.append(out)
+        us.append(min(times[2:]))
+    say("  us", us)
+    counts = moe.layer_views(shape, ws)["expert_offsets"].diff().tolist()
+    assert [e for e in range(E) if counts[e]] == list(picked)
+    assert torch.equal(got[0], got[1])
+    assert us[1] < 2 * us[0] + 40
+
+
 STREAMED = [
     # name, overrides, experts per group, slots
     ("C2", dict(T=600, H=256, F=448), 1, 2),                    # one expert at a time, double buffer
