@@ -144,6 +144,7 @@ size_t moe_h_scratch_bytes(const moe_shape* shape);
  *   "combine_behind" -1|0|1   moe_layer with shared experts, top_k 4 .. 8 and bf16 y_perm: the shared experts' down GEMM is the last
  *                             launch and adds up the layer's output tile by tile (no combine launch; its time counts as the down
  *                             stage's).  1: also where its rounds of tiles do not come out, -1 (default): where they do.  Same bits
+ *                             (which short tails are cut along K is decided as without it)
  *   "y_fp32"          0 | 1   staged calls: dtype of y_perm / y_shared: 1 (default) fp32, 0 bf16.  bf16 halves the
  *                             traffic of the down projection's store and of the combine's loads, but
  *                             rounds each expert output to 8 mantissa bits before the weighted sum

@@ -556,9 +556,11 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     const int dsp = sm.down ? 1 : call_down_splits(c, s);
     if (s.T <= 256 && dsp == 1 && !c->gemm.tile_rows_down) tm_down = 128;   // the walk along K is long; not where short tails may be cut along K
     const bool combine_behind = ps.layer && tall_kernel && !sm.down && !c->gemm.tile_rows_down && combine_behind_wins(c, s);
+    // Their tiles are then no part of the plan, unless short tails may be cut along K: that is decided with them in view (plan_list).
+    const bool shared_apart = combine_behind && dsp == 1;
     // Forced pieces: which rows are cut must not depend on what else a pass covers, so the heights are fixed.
     int choose_down = tm_down == 256 && !c->gemm.tile_rows_down && !(dsp > 1 && c->gemm.down_tail_splits == 2)
-                          ? may_choose_rows(s, nt_down, s.num_shared && !combine_behind ? 1 : 0) : 0;
+                          ? may_choose_rows(s, nt_down, s.num_shared && !shared_apart ? 1 : 0) : 0;
     if (!tall_kernel && choose_down) choose_down = choose_down == 1 ? 3 : 0;
     // "many rounds" for the plan's rule: eight rounds of 256 tiles (at two to three rounds pieces
     // measured +6 %, at four to five +-0, at thirteen -2 %)
@@ -590,7 +592,7 @@ FfnSetup ffn_setup(const moe_ctx* c, const moe_shape& s, const int32_t* offsets,
     f.combine_behind = combine_behind;
     f.plan = PlanArgs{offsets, s.T, (s.T + 15) & ~15, s.E, s.num_shared, tm_up, tm_down, choose_up, choose_down, nt_up,
                       nt_down, tl_up, tl_down, c->gemm.small_tiles != 0, c->gemm.xcd_remap, nt, (low_up ? 1 : 0) | (low_down ? 2 : 0), ps.e_lo, ps.e_hi,
-                      ps.shared_on ? (combine_behind ? 1 : 3) : 0,
+                      ps.shared_on ? (!combine_behind ? 3 : (shared_apart ? 1 : 1 | 4)) : 0,
                       dsp, 4, split_rule_tiles, split_room_tiles(s), tall, tall, (SplitTail*)(ws + L.split_tails), (PlanHeader*)(ws + L.plan),
                       (TileDesc*)(ws + L.descs_up), (TileDesc*)(ws + L.descs_down)};
     f.sm = sm;

@@ -100,7 +100,7 @@ struct PlanArgs {
     int32_t tails_last_up, tails_last_down, small_tiles, xcd_remap;
     int32_t mark_once;                  // 1: TILE_ONCE marks are wanted
     int32_t low_shared;                 // shared experts' tiles are at most 128 rows: bit 0 gate/up, bit 1 down
-    int32_t e_lo, e_hi, shared_on;      // the lists cover routed experts [e_lo, e_hi) and, by shared_on, the shared experts: bit 0 gate/up, bit 1 down
+    int32_t e_lo, e_hi, shared_on;      // the lists cover routed experts [e_lo, e_hi) and, by shared_on, the shared experts: bit 0 gate/up, bit 1 down, bit 2 down without listing them
     int32_t down_splits, split_max_blocks, split_rule_tiles, split_room_tiles, tall_up, tall_down;
     SplitTail* split_tails;
     PlanHeader* plan;

@@ -186,7 +186,7 @@ __device__ __forceinline__ void plan_list(const PlanArgs& p, const int which, co
             else { const int s = pos - E + 1; group = E + s; rows = p.T; row_begin = 0; srow = s * p.t_pad; }
         }
         // a streamed pass covers routed experts [e_lo, e_hi) and, by shared_on, the shared experts
-        if (group < E ? (group < p.e_lo || group >= p.e_hi) : !(p.shared_on >> which & 1)) rows = 0;
+        if (group < E ? (group < p.e_lo || group >= p.e_hi) : !(p.shared_on >> which & (which == 0 ? 1 : 3))) rows = 0;
     }
     int tm = which == 0 ? p.tm_up : p.tm_down;
     const int choose = which == 0 ? p.choose_up : p.choose_down;
@@ -213,6 +213,14 @@ __device__ __forceinline__ void plan_list(const PlanArgs& p, const int which, co
         tm = plan_cap(usual);
         for (int c = 0; c < PLAN_CAPS; ++c)
             if (plan_candidate(c, choose) && cap_cost[c] < best) { best = cap_cost[c]; tm = plan_cap(c); }
+    }
+    // Shared experts that only count: their tiles belong to another launch (launch_down_combine), and what is cut along K is decided as if they
+    // were listed, so that the layer has the same bits either way.
+    int apart = 0;
+    if (which == 1 && (p.shared_on & 4)) {
+        const GroupCut c = list_cut(p, 1, true, p.T, tm);
+        apart = c.nfull + (c.tail > 0);
+        if (group >= E) rows = 0;
     }
     TileDesc* descs = which == 0 ? p.descs_up : p.descs_down;
     const int tall = which == 0 ? p.tall_up : p.tall_down;
@@ -269,7 +277,7 @@ __device__ __forceinline__ void plan_list(const PlanArgs& p, const int which, co
     if (cutting) {
         n_whole = 0;
         for (int b = p.split_max_blocks + 1; b <= 4; ++b) n_whole += cnt[b];
-        const int others = n_run_s + n_tall_s + n_whole;
+        const int others = n_run_s + n_tall_s + n_whole + apart;
         cutting = p.split_rule_tiles == 0 || (others == 0 && tails * p.nt_down <= p.split_room_tiles) || others + tails - n_whole >= p.split_rule_tiles;
         if (!cutting) n_whole = tails;
     }

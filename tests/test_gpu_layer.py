@@ -307,13 +307,20 @@ def test_layer_at_the_4_gib_limit(moe):
     (384, 256, 192, 17, 5, 2),      # a tail of exactly 128 rows (the lower variant)
     (385, 512, 128, 24, 6, 2),      # of 129
     (1111, 1088, 64, 33, 7, 3),     # two sub-tiles of K, three segments; columns of the last n-tile
-    (2600, 640, 320, 12, 8, 8)])    # more than one run of eight m-tiles
-def test_layer_with_the_combine_behind_the_down_gemm(moe, T, H, F, E, k, shared):
-    """The shared experts' down GEMM that ends the layer adds in the order of the combine launch: the same bits, fp32 and bf16."""
+    (2600, 640, 320, 12, 8, 8),     # more than one run of eight m-tiles
+    (1111, 1088, 512, 12, 4, 2),    # short tails of the routed experts in two pieces along K (option 2)
+    (700, 512, 1024, 30, 6, 1),     # in four
+    (8000, 4096, 512, 16, 6, 1),    # few experts, around the number of tiles from which short tails are cut (option 1)
+    (9000, 2048, 1024, 9, 8, 2)])
+@pytest.mark.parametrize("splits", [1, 0, 2])
+def test_layer_with_the_combine_behind_the_down_gemm(moe, T, H, F, E, k, shared, splits):
+    """The shared experts' down GEMM that ends the layer adds in the order of the combine launch, and which rows of the routed experts are cut
+    along K does not depend on where the shared experts' tiles are: the same bits, fp32 and bf16."""
     cfg = scaled_config("C4", T=T, H=H, F=F, E=E, top_k=k, num_shared=shared)
     say("combine behind", cfg)
     gl = P.GpuLayer(moe, make_layer_inputs(cfg, device="cuda"), host_weights=False)
     got = {}
+    moe.set_option("down_tail_splits", splits)
     try:
         for mode in (0, 1):
             moe.set_option("combine_behind", mode)
@@ -325,6 +332,7 @@ def test_layer_with_the_combine_behind_the_down_gemm(moe, T, H, F, E, k, shared)
     finally:
         moe.profile_enable(False)
         moe.set_option("combine_behind", -1)
+        moe.set_option("down_tail_splits", 1)
     for a, b in zip(got[0], got[1]):
         assert torch.equal(a, b)
 
