@@ -156,6 +156,8 @@ class Layer:
             "down": {"flops_per_launch": f2, "TFLOP/s": tf(f2, g2), "frac_of_bf16_peak": tf(f2, g2) / PEAK_BF16_TFLOPS,
                      "TFLOP/s_at_min": tf(f2, stage_ms["ffn_down"]["min"])},
             "grouped_ffn_tflops": ffn, "grouped_ffn_frac_of_bf16_peak": ffn / PEAK_BF16_TFLOPS,
+            # the shared experts' down GEMM ends the layer: "down" and "grouped_ffn" are then rates of GEMM and combine together
+            "down_includes_combine": stage_ms["combine"]["n"] == 0,
         }
 
 
@@ -259,8 +261,8 @@ def hbm_stages(moe, L: Layer, copy_gbs: float, reps: int = 5):
                                       "is_moe_layer_choice": y32 == layer_y32})
         del ys, ysh, outs
     res["note"] = ("moe_layer on this workload keeps y_perm in %s (y_shared always fp32); the in-layer stage_ms of combine "
-                   "reads y_perm that the down projection has just written (partly cache-resident), these figures do not"
-                   % ("fp32" if layer_y32 else "bf16"))
+                   "(none where down_includes_combine) reads y_perm that the down projection has just written (partly cache-resident), "
+                   "these figures do not" % ("fp32" if layer_y32 else "bf16"))
     torch.cuda.empty_cache()
     return res
 
@@ -472,7 +474,7 @@ def main():
         "step_ms": head["step_ms"],
         "grouped_ffn_tflops": head["grouped_ffn_tflops"],
         "grouped_ffn_frac_of_bf16_peak": head["grouped_ffn_frac_of_bf16_peak"],
-        "gate_up": head["gate_up"], "down": head["down"],
+        "gate_up": head["gate_up"], "down": head["down"], "down_includes_combine": head["down_includes_combine"],
         "stage_ms": head["stage_ms"],
         "timing": "ms_per_step / value: %d steps between two synchronisations, no events on the stream; step_ms and stage_ms: "
                   "a second loop of %d steps with HIP events (median, min); while stages are timed the m-tile lists are "

@@ -333,7 +333,9 @@ moe_status moe_layer_views(const moe_shape* shape, void* workspace, int32_t** to
  * moe_layer on a small batch (up to 256 tokens and 1024 pairs, where both GEMMs run without m-tile lists) launches no
  * permutation and no list: those stages then have no intervals, the gate/up launch writes the index arrays, and with up to 16 tokens and
  * more than 16 experts the shared experts' gate/up tiles run in the route stage's last launch and their down tiles in the gate/up
- * stage's.  Larger layers build the lists in a launch of their own while profiling is on, else next to the permutation. */
+ * stage's.  Larger layers build the lists in a launch of their own while profiling is on, else next to the permutation.  A moe_layer that
+ * ends on the shared experts' down GEMM with the combine behind it (option "combine_behind") has no combine interval: the down stage's
+ * time contains it, and that GEMM's FLOPs over it are no rate of the GEMM alone. */
 moe_status moe_profile_enable(moe_ctx* ctx, int32_t on);
 moe_status moe_profile_read(moe_ctx* ctx, double* ms_sum, int32_t* launches);
 /* The same record interval by interval, in the order the calls enqueued them: stage[i] is a

@@ -43,3 +43,4 @@ def test_one_json_line_with_the_agreed_fields():
     for key in ("value", "unit", "cores", "kind", "sample"):
         assert key in cb, key
     assert cb["kind"] == "oracle" and cb["value"] > 0 and cb["cores"] >= 1
+    assert j["down_includes_combine"] is False   # no shared experts
