@@ -59,7 +59,8 @@ SMALL = [
     ("C4", dict(T=96, H=64, F=64, E=254, top_k=32, num_shared=2)),   # E + shared = 256 groups, wide top-k
     ("C4", dict(T=70, H=128, F=64, E=8, top_k=8, num_shared=8)),     # k = E, 8 shared experts
     ("C2", dict(T=2500, H=256, F=256)),                      # few experts, 5000 pairs, token count not a multiple of 16
-    ("C3", dict(T=4100, H=128, F=128, E=16, top_k=4)),       # the same with 16 experts, a gate bias and a last router workgroup of 4 tokens
+    ("C3", dict(T=4100, H=128, F=128, E=16, top_k=4)),       # 16400 pairs (two-launch permutation), a gate bias and a last router workgroup of 4 tokens
+    ("C2", dict(T=4501, H=128, F=192)),                      # few experts, 9002 pairs: the lists are built in the second of the two launches
 ]
 
 
@@ -335,6 +336,33 @@ def test_layer_with_the_combine_behind_the_down_gemm(moe, T, H, F, E, k, shared,
         moe.set_option("down_tail_splits", 1)
     for a, b in zip(got[0], got[1]):
         assert torch.equal(a, b)
+
+
+def test_combine_behind_with_infinities_and_nan(moe):
+    """Infinite and NaN weights of routed and shared experts, a token of zeros, one of NaN, one that overflows: each
+    element is what the combine launch makes of it, and only the columns and tokens concerned are not finite."""
+    cfg = scaled_config("C4", T=700, H=576, F=128, E=20, top_k=6, num_shared=2)
+    say("combine behind, not finite", cfg)
+    li = make_layer_inputs(cfg, device="cuda")
+    li.x[7], li.x[300], li.x[699] = 0.0, float("nan"), 1e37
+    # single infinite weights: a column of them is inf - inf in every row
+    li.w2[3][4, 5], li.w2[11][9, 300], li.w2[3][:, 575] = float("inf"), float("-inf"), float("nan")
+    li.w2[cfg.E][2, 300], li.w2[cfg.E + 1][17, 64] = float("inf"), float("nan")
+    gl = P.GpuLayer(moe, li, host_weights=False)
+    got = []
+    try:
+        for mode in (0, 1):
+            moe.set_option("combine_behind", mode)
+            got.append([gl.run_layer(fp32).clone() for fp32 in (True, False)])
+    finally:
+        moe.set_option("combine_behind", -1)
+    for a, b in zip(*got):
+        assert torch.equal(a.isnan(), b.isnan())
+        assert torch.equal(a.nan_to_num(nan=0.0, posinf=3e38, neginf=-3e38), b.nan_to_num(nan=0.0, posinf=3e38, neginf=-3e38))
+        assert a.isinf().any() and a[:, 64].isnan().all()
+        keep_t, keep_c = torch.ones(cfg.T, dtype=torch.bool), torch.ones(cfg.H, dtype=torch.bool)
+        keep_t[[300, 699]], keep_c[[5, 300, 575, 64]] = False, False
+        assert torch.isfinite(b[keep_t.cuda()][:, keep_c.cuda()]).all()
 
 
 @pytest.mark.parametrize("H,fp32", [(8454720, True), (16909440, False)])
