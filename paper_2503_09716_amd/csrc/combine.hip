@@ -5,7 +5,8 @@
 // combine: one thread per token and 4 or 8 consecutive hidden elements (combine_elements), which gathers the k expert
 // rows of its token through inv_perm, all of them in flight at once.  Sums are fp32 in the fixed order j = 0..k-1 then
 // shared, every output element is written exactly once: no atomics, and the result is bit-identical from run to run.
-// HBM-bound: reads k+1 rows, writes 1 row per token.  Against one workgroup per token that walked its row 8 elements per
+// HBM-bound: reads k+1 rows, writes 1 row per token.  (moe_layer has this launch unless its shared experts' down GEMM does the work,
+// launch_down_combine; the two larger layers below then make it in staged, streamed and fp32-y_perm calls only.)  Against one workgroup per token that walked its row 8 elements per
 // thread and waited for each expert's row before it asked for the next: 160 experts top-6 + 2 shared, H = 5120, 32768
 // tokens 614 -> 500 to 545 us by box (3.0 GB = 5.5 to 6.0 TB/s), 64 experts, H = 2048, 16384 tokens 120 -> 94 us, 1 token
 // 2 us less of the layer's 47.

@@ -163,7 +163,7 @@ __host__ __device__ constexpr int block_swizzle(const int r) { return (0 - (r >>
 
 constexpr int PERMUTE_CHUNK_TOKENS = 256;
 inline int permute_chunks(const moe_shape& s) { return (s.T + PERMUTE_CHUNK_TOKENS - 1) / PERMUTE_CHUNK_TOKENS; }
-// plan: when non-null, the m-tile lists are built by one more workgroup of the last launch, and *planned
+// plan: when non-null, the m-tile lists are built by two more workgroups of the last launch, one each, and *planned
 // says whether they were (not in the form with three launches)
 hipError_t launch_permute_index(const moe_shape& s, const int32_t* idx, int32_t* chunk_counts, int32_t* offsets,
                                 int32_t* perm, int32_t* inv_perm, int32_t* row_token, const PlanArgs* plan, bool* planned,
@@ -176,9 +176,9 @@ hipError_t launch_permute_gather_tiled(const moe_shape& s, const void* x, const 
                                        hipStream_t st);
 
 hipError_t launch_ffn_plan(const PlanArgs& a, hipStream_t st);
-// y_perm rows of the split tails = sum over pieces of the fp32 partials, in y_perm's dtype
 // the shared experts' down GEMM with the layer's combine behind it: out = sum_j w_j * y_perm rows + its own rows (k = 4 .. 8)
 hipError_t launch_down_combine(const moe_shape& s, const GemmArgs& a, const CombineArgs& c, bool out_fp32, hipStream_t st);
+// y_perm rows of the split tails = sum over pieces of the fp32 partials, in y_perm's dtype
 hipError_t launch_split_tail_reduce(const moe_shape& s, const PlanHeader* plan, const SplitTail* tails, const float* partial,
                                     int splits, void* y_perm, bool y_fp32, hipStream_t st);
 hipError_t launch_ffn_gemm(bool gated, const GemmArgs& a, const GemmConfig& cfg, hipStream_t st);

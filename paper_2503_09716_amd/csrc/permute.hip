@@ -22,8 +22,9 @@ namespace {
 
 constexpr int MAX_E = 256;
 
-// These kernels are chains of a few memory latencies, so every loop over global memory has BATCH loads in flight (stage time against
-// one load at a time, us: 64 experts top-6, 300 tokens 9.8 -> 7.5, 3001 tokens 14.1 -> 12.8, 16384: 17.5 -> 14.9).
+// These kernels are chains of a few memory latencies, so the loops over global memory of the one- and two-launch forms have BATCH loads in
+// flight (stage time against one load at a time, us: 64 experts top-6, 300 tokens 9.8 -> 7.5, 3001 tokens 14.1 -> 12.8, 16384: 17.5 ->
+// 14.9).  permute_place_kernel, of the form with three launches, loads its picks one after the other.
 constexpr int BATCH = 8;
 // v = p[i0], p[i0 + step], ..., -1 from index n on
 __device__ __forceinline__ void load_batch(int (&v)[BATCH], const int32_t* __restrict__ p, const int i0, const int step, const int n) {
@@ -218,8 +219,7 @@ __device__ __forceinline__ void scan_and_place_chunk(const int32_t* __restrict__
 // (one per chunk, 4 wavefronts) histograms ALL pairs into wave-private LDS counters, once counting everything (-> expert_offsets, the same in
 // every workgroup) and once counting only the chunks before its own (-> its cursors), then
 // places its chunk: wavefront w takes tokens 64w .. 64w+63 of the chunk, the lane masks of all
-// four wavefronts give a pair its rank.  Same result as the three kernels above, bit for bit,
-// without their two extra launches.
+// four wavefronts give a pair its rank.  Same result as the forms with two and three launches, bit for bit.
 constexpr int FUSED_MAX_PAIRS = 1 << 13;
 static_assert(PERMUTE_CHUNK_TOKENS == 256, "the fused kernel gives each of its 4 wavefronts 64 tokens of a chunk");
 
